@@ -58,8 +58,8 @@ def listed():
         # an observer's poll period in the streaming network
         _case("tick 10000", "tick", 128, 128256, 128, 512, (1024, 1024), (64, 256), 1000, 16384, 1.2, 0.05,
               refreshed=4, inserts=10000),
-        # a node that serves requests one by one within its KV budget
-        _case("serve 1", "serve", 4, 32000, 0, 57, (380, 520), (40, 140), 120, 1, 0.8, 0.0, steps=8, budget=20000),
+        # a node that serves requests one by one within its KV budget, which does not hold a period's requests
+        _case("serve 1", "serve", 4, 32000, 0, 57, (380, 520), (40, 140), 60, 1, 0.8, 0.0, steps=24, budget=6000),
         # sendTrie of a large tree and its arrival
         _case("broadcast 4000", "broadcast", 16, 128256, 256, 512, (512, 2048), (64, 1792), 4000, 0, 1.2),
         # a node's cold start
@@ -98,9 +98,11 @@ def draw(rng):
         return _case("", do, peers, vocab, sys, topics, head, suffix, prompts, _log_int(rng, 64, 20000), zipf, unseen,
                      refreshed=rng.randint(1, 4), inserts=_log_int(rng, 50, 12000))
     if do == "serve":
-        batch = _log_int(rng, 1, 128)
+        batch, steps = _log_int(rng, 1, 128), rng.randint(3, 12)
+        # tokens a period's requests add to an empty tree, roughly: the budget is less, so every period evicts
+        period = steps * batch * sum(suffix) / 2 + min(topics / 2, steps * batch / 2) * sum(head) / 2
         return _case("", do, rng.randint(2, 70), vocab, sys, topics, head, suffix, rng.randint(20, 150), batch, zipf,
-                     unseen, steps=rng.randint(3, 8), budget=int(mean * batch * rng.uniform(8, 30)))
+                     unseen, steps=steps, budget=int(period * rng.uniform(0.3, 0.7)))
     if do == "broadcast":
         return _case("", do, rng.randint(2, 64), vocab, sys, topics, head, suffix, _log_int(rng, 30, 1500), 0, zipf)
     return _case("", do, _log_int(rng, 2, 64), vocab, sys, topics, head, suffix, _log_int(rng, 20, 600),
@@ -237,6 +239,8 @@ def prepare(case, seed):
         s["forest"] = _forest(case, snaps, local=0)
         s["batches"] = [w.sequences(w.requests(case["queries"])) for _ in range(case["steps"])]
         s["own"] = torch.zeros(case["queries"], dtype=torch.int32, device=DEVICE)
+        s["out"] = [torch.empty((case["steps"], case["queries"]) + more, dtype=torch.int32, device=DEVICE)
+                    for more in ((case["peers"],), (), ())]
         s["other"], s["q"] = _forest(case, snaps), w.sequences(w.requests(case["queries"]))
         s["now"] = 0
     elif do == "broadcast":
@@ -263,19 +267,19 @@ def run(s):
         f.merge(s["to"], *s["new"])
         return f.route(*s["q"], *s["out"])
     if do == "serve":
-        f, got = s["forest"], []
-        for t, o in s["batches"]:
+        f, evicted = s["forest"], []
+        for (t, o), m, best, second in zip(s["batches"], *s["out"]):
             s["now"] += 1
             f.set_time(s["now"])
-            m, best, second = f.route_select(t, o, None, 0, True)
+            f.route_select(t, o, None, 0, True, m, best, second)
             f.touch(t, o)
             fresh = t.numel() - int(m[:, 0].sum())  # tokens whose KV entries this batch adds
             over = f.tree_tokens(0) + fresh - s["case"]["budget"]
-            got.append((m, best, second, f.evict_lru(over) if over > 0 else 0))
+            evicted.append(f.evict_lru(over) if over > 0 else 0)
             f.merge(s["own"], t, o)
         f.compact()
         s["other"].load_snapshot_device(0, *f.export_snapshot(0))
-        return got, s["other"].route(*s["q"])
+        return s["out"], evicted, s["other"].route(*s["q"])
     if do == "broadcast":
         t, o = s["forest"].export_snapshot(s["peer"])
         s["other"].load_snapshot_device(s["peer"], t, o)
