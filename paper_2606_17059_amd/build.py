@@ -4,6 +4,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -18,6 +19,7 @@ ARCH = "gfx950"
 HIP_FLAGS = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC",
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
              "-Wall", "-Wno-unused-result"]
+HIP_SOURCES = ["route", "router"]
 HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-Wall"]
 
 
@@ -37,11 +39,17 @@ def build(verbose: bool = False, defines=(), out_path: str = LIB_PATH) -> str:
     os.makedirs(BUILD_DIR, exist_ok=True)
     host_obj = os.path.join(BUILD_DIR, "forest_host.o")
     out = _run(["g++", *HOST_FLAGS, "-I", CSRC, "-c", os.path.join(CSRC, "forest_host.cpp"), "-o", host_obj])
-    dev_obj = os.path.join(BUILD_DIR, "router.o")
-    out += _run([HIPCC, *HIP_FLAGS, *["-D" + d for d in defines], "-I", INCLUDE, "-I", CSRC, "-c",
-                 os.path.join(CSRC, "router.hip"), "-o", dev_obj])
+    names = HIP_SOURCES
+    objs = [os.path.join(BUILD_DIR, n + ".o") for n in names]
+
+    def compile_one(n):
+        return _run([HIPCC, *HIP_FLAGS, *["-D" + d for d in defines], "-I", INCLUDE, "-I", CSRC, "-c",
+                     os.path.join(CSRC, n + ".hip"), "-o", os.path.join(BUILD_DIR, n + ".o")])
+
+    with ThreadPoolExecutor(len(names)) as pool:
+        out += "".join(pool.map(compile_one, names))
     tmp = out_path + ".tmp"
-    out += _run([HIPCC, "--offload-arch=" + ARCH, "-shared", "-fPIC", dev_obj, host_obj, "-o", tmp])
+    out += _run([HIPCC, "--offload-arch=" + ARCH, "-shared", "-fPIC", *objs, host_obj, "-o", tmp])
     os.replace(tmp, out_path)
     if verbose and out.strip():
         print(out)

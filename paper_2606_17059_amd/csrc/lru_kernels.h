@@ -52,29 +52,6 @@ __global__ void lru_init_kernel(DevForest F, int64_t n_nodes, unsigned long long
     F.ltime[x] = lru_holds(F, x, F.local) ? t : 0ull;
 }
 
-// Touch: the matched prefix of query i in the local tree has match_len[i][L]
-// tokens (-1 for a query with invalid offsets: nothing).  len1[i + 1] gets
-// that length, len1[0] = 0, so an inclusive scan gives CSR offsets.
-__global__ void touch_lengths_kernel(const int32_t *__restrict__ match_len, int32_t P, int32_t L, int64_t n,
-                                     int64_t *__restrict__ len1) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == 0) len1[0] = 0;
-    if (i < n) len1[i + 1] = max(0, match_len[i * (int64_t)P + L]);
-}
-
-// One wave per query: copy its matched prefix to out[toff[i] .. toff[i + 1]).
-__global__ __launch_bounds__(256) void touch_gather_kernel(const int32_t *__restrict__ qtok,
-                                                           const int64_t *__restrict__ qoff,
-                                                           const int64_t *__restrict__ toff, int64_t n,
-                                                           int32_t *__restrict__ out) {
-    const int lane = (int)(threadIdx.x & 63);
-    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (i >= n) return;
-    const int64_t len = toff[i + 1] - toff[i];
-    const int32_t *src = qtok + qoff[i];
-    for (int64_t k = lane; k < len; k += 64) out[toff[i] + k] = src[k];
-}
-
 // ---- eviction ---------------------------------------------------------------
 
 struct EvictPlan {

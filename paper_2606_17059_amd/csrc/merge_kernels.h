@@ -99,14 +99,18 @@ struct DevForest {
 };
 
 struct Batch {
-    const int32_t *peer_of;
+    const int32_t *peer_of;  // nullptr: every sequence is for `peer`
     const int32_t *tokens;
     const int64_t *offsets;
     int64_t num_tokens;
     int64_t n;
     int32_t P;
     int32_t stamp;  // 1: inserts into the local peer stamp their path with F.now
+    int32_t peer;
+    int32_t touch;  // 1: not inserts but touches of `peer`: a walk ends where its tree does, nothing is added
 };
+
+__device__ __forceinline__ int32_t batch_peer(const Batch &B, int64_t i) { return B.peer_of ? B.peer_of[i] : B.peer; }
 
 constexpr int kMergeWavesPerBlock = 4;
 constexpr int kMoveBlocks = 1024;  // workgroups of the grid-stride move kernel
@@ -216,26 +220,21 @@ __global__ void merge_validate_kernel(Batch B, InsState *st, MergeCounters *ctr)
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= B.n) return;
     const int64_t b = B.offsets[i], e = B.offsets[i + 1];
-    const int32_t p = B.peer_of[i];
+    const int32_t p = batch_peer(B, i);
     const bool ok = p >= 0 && p < B.P && b >= 0 && e >= b && e <= B.num_tokens && e - b <= (int64_t)INT32_MAX;
     st[i].kind = ok ? kInsActive : kInsSkip;
-    if (!ok) atomicAdd(&ctr->skipped, 1ull);
+    if (!ok && !B.touch) atomicAdd(&ctr->skipped, 1ull);  // touches ignore bad queries
 }
 
-// Walk every active insert; classify it as DONE, ADD or SPLIT.
-__global__ __launch_bounds__(64 *kMergeWavesPerBlock) void merge_walk_kernel(DevForest F, Batch B, InsState *st,
-                                                                            MergeCounters *ctr) {
-    const int lane = (int)(threadIdx.x & 63);
-    const int64_t i = m_wave_index();
-    if (i >= B.n) return;
-    const int32_t kind = st[i].kind;
-    if (kind == kInsSkip || kind == kInsDone) return;
-    const int32_t *s = B.tokens + B.offsets[i];
-    const int64_t len = B.offsets[i + 1] - B.offsets[i];
-    const int32_t p = B.peer_of[i];
+// Walk one insert (tokens s[0, len) for peer p) from the root and classify it
+// as DONE, ADD or SPLIT, setting the peer's bit in every node it passes through
+// whole.  A touch walks p's tree only: it is DONE where no child holds p, and
+// SPLIT where p's tree goes on but the query leaves (or ends inside) the label.
+// Wave-cooperative; every lane returns the same state.
+__device__ __forceinline__ InsState m_walk(const DevForest &F, const int32_t *s, int64_t len, int32_t p, bool touch,
+                                           bool stamp, int lane) {
     const int32_t w = p >> 6;
     const unsigned long long bit = 1ull << (p & 63);
-    const bool stamp = F.ltime && B.stamp && p == F.local;
     int32_t x = 0;
     int64_t d = 0;
     InsState r;
@@ -252,11 +251,18 @@ __global__ __launch_bounds__(64 *kMergeWavesPerBlock) void merge_walk_kernel(Dev
         const int32_t t = s[d];
         const int32_t c = m_find_child(F, nx, t, lane);
         if (c < 0) {
-            r.kind = kInsAdd;
+            r.kind = touch ? kInsDone : kInsAdd;
             r.t = t;
             break;
         }
         const Node nc = F.nodes[c];
+        if (touch) {
+            const uint64_t held = w == 0 ? nc.mask0 : F.mext[(int64_t)c * (F.W - 1) + (w - 1)];
+            if (!(held & bit)) {
+                r.kind = kInsDone;
+                break;
+            }
+        }
         const int64_t n = min((int64_t)nc.lab_len, len - d);
         const int64_t l = m_lcp(F.pool + nc.lab_off, s + d, n, lane);
         if (l == nc.lab_len && nc.lab_len > 0) {
@@ -273,7 +279,26 @@ __global__ __launch_bounds__(64 *kMergeWavesPerBlock) void merge_walk_kernel(Dev
     }
     r.x = x;
     r.d = (int32_t)d;
+    return r;
+}
+
+// Walk every active insert.
+__global__ __launch_bounds__(64 *kMergeWavesPerBlock) void merge_walk_kernel(DevForest F, Batch B, InsState *st) {
+    const int lane = (int)(threadIdx.x & 63);
+    const int64_t i = m_wave_index();
+    if (i >= B.n) return;
+    const int32_t kind = st[i].kind;
+    if (kind == kInsSkip || kind == kInsDone) return;
+    const int64_t b = B.offsets[i];
+    const int32_t p = batch_peer(B, i);
+    const InsState r = m_walk(F, B.tokens + b, B.offsets[i + 1] - b, p, B.touch, F.ltime && B.stamp && p == F.local,
+                              lane);
     if (lane == 0) st[i] = r;  // merge_tally_kernel counts the kinds
+}
+
+// Tokens insert i adds past the depth where its walk ended (l: SPLIT).
+__device__ __forceinline__ int64_t ins_rest(const Batch &B, int64_t i, const InsState &r, int32_t l) {
+    return B.touch ? 0 : B.offsets[i + 1] - B.offsets[i] - (int64_t)r.d - l;
 }
 
 // Counts of the walk's ADD and SPLIT inserts and the pool tokens they may
@@ -292,7 +317,7 @@ __global__ __launch_bounds__(kTallyThreads) void merge_tally_kernel(Batch B, con
         if (kind == kInsAdd || kind == kInsSplit) {
             n_add += kind == kInsAdd;
             n_split += kind == kInsSplit;
-            const int64_t rest = B.offsets[i + 1] - B.offsets[i] - st[i].d;
+            const int64_t rest = ins_rest(B, i, st[i], 0);
             pool += (unsigned long long)rest;
             if (kind == kInsAdd) ar = (int32_t)rest;
         }
@@ -339,12 +364,28 @@ __global__ void split_claim_kernel(DevForest F, Batch B, const InsState *st, lon
     atomicMax(&F.nodes[current_pos(F, st[i].c, stamp)].aux, (int32_t)(INT32_MAX - i));
 }
 
+// Reads past the CU's first-level cache, whose lines atomics of the same launch
+// do not update.
+__device__ __forceinline__ uint64_t fresh_u64(const void *p) {
+    return __hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ Node fresh_node(const Node *p) {
+    union {
+        uint64_t w[4];
+        Node n;
+    } u;
+#pragma unroll
+    for (int k = 0; k < 4; k++) u.w[k] = fresh_u64(reinterpret_cast<const uint64_t *>(p) + k);
+    return u.n;
+}
+
 // Mask words past the first of a cut edge: the lower part (dst) keeps the
 // edge's peers, the upper part (src, in place) adds peer p.  Each word is read
 // and written by one lane.
 __device__ __forceinline__ void cut_mext(const DevForest &F, int64_t dst, int64_t src, int32_t p, int lane) {
     for (int w = lane; w < F.W - 1; w += 64) {
-        const uint64_t v = F.mext[src * (F.W - 1) + w];
+        const uint64_t v = fresh_u64(&F.mext[src * (F.W - 1) + w]);
         F.mext[dst * (F.W - 1) + w] = v;
         if ((p >> 6) == w + 1) F.mext[src * (F.W - 1) + w] = v | (1ull << (p & 63));
     }
@@ -359,6 +400,97 @@ __device__ __forceinline__ void leaf_mext(const DevForest &F, int64_t dst, int32
 // Copy n tokens into freshly allocated pool space (wave-cooperative).
 __device__ __forceinline__ void copy_tokens(int32_t *dst, const int32_t *src, int64_t n, int lane) {
     for (int64_t k = lane; k < n; k += 64) dst[k] = src[k];
+}
+
+// Where appended labels' narrow copy goes (p16 nullptr: the forest has none).
+struct NarrowDst {
+    uint16_t *p16;
+    uint32_t *hib;
+};
+
+// Copy n tokens to pool[pb ..) and their narrow copy (wave-cooperative), in
+// pool-aligned chunks of 64, eight loaded before the first is stored (a chunk
+// at a time waits out one round trip to memory for every 256 bytes).  A chunk's
+// bits of bit 16 are a ballot; whole words are stored and words shared with
+// other spans ORed (the plane is zero past the used pool).  seen: bit 0 a
+// 17-bit token, bit 1 a wider one.
+__device__ __forceinline__ void copy_tokens_narrow(const DevForest &F, const NarrowDst &N, int64_t pb,
+                                                   const int32_t *src, int64_t n, int lane, uint32_t &seen) {
+    constexpr int kChunks = 8;
+    for (int64_t k0 = pb & ~63ll; k0 < pb + n; k0 += 64 * kChunks) {
+        uint32_t t[kChunks];
+#pragma unroll
+        for (int u = 0; u < kChunks; u++) {
+            const int64_t k = k0 + 64 * u + lane;
+            t[u] = k >= pb && k < pb + n ? (uint32_t)src[k - pb] : 0u;
+        }
+#pragma unroll
+        for (int u = 0; u < kChunks; u++) {
+            const int64_t k = k0 + 64 * u + lane;
+            const bool in = k >= pb && k < pb + n;
+            if (in) F.pool[k] = (int32_t)t[u];
+            if (!N.p16) continue;
+            if (in) N.p16[k] = (uint16_t)t[u];
+            const uint64_t bits = __ballot((t[u] >> 16) & 1u);
+            const int64_t w = k0 + 64 * u + 32 * lane;  // lane 0 and 1's word covers tokens [w, w + 32)
+            if (lane < 2 && w + 32 > pb && w < pb + n) {
+                const uint32_t word = (uint32_t)(bits >> (32 * lane));
+                if (w >= pb && w + 32 <= pb + n)
+                    N.hib[w >> 5] = word;
+                else if (word)
+                    atomicOr(&N.hib[w >> 5], word);
+            }
+            seen |= t[u] > 0x1FFFFu ? 2u : (t[u] > 0xFFFFu ? 1u : 0u);
+        }
+    }
+}
+
+// Cut the edge of the node at c (its record: old) after l tokens.  The lower
+// part takes the edge's children and peers; tokens [0, rest) of s, what the
+// cutting sequence has past the cut, become a leaf of peer p (none if rest is
+// 0).  The new child block starts at nb, the leaf's label at pb.  stamped: the
+// sequence stamps its path.  Wave-cooperative.
+__device__ __forceinline__ void cut_edge(const DevForest &F, const NarrowDst &N, const Node &old, int32_t c,
+                                         int32_t l, const int32_t *s, int64_t rest, int32_t p, bool stamped,
+                                         int64_t nb, int64_t pb, int lane, uint32_t &seen) {
+    Node lower = old;
+    lower.tok = F.pool[old.lab_off + l];
+    lower.lab_off = old.lab_off + (uint32_t)l;
+    lower.lab_len = old.lab_len - l;
+    lower.aux = 0;
+    int64_t pos_lower = nb, pos_leaf = nb + 1;
+    if (rest > 0 && s[0] < lower.tok) {
+        pos_leaf = nb;
+        pos_lower = nb + 1;
+    }
+    if (rest > 0) copy_tokens_narrow(F, N, pb, s, rest, lane, seen);
+    // the cutting peer holds the upper part and its leaf; the lower part keeps
+    // the edge's peers
+    const unsigned long long bit0 = (p >> 6) == 0 ? 1ull << (p & 63) : 0ull;
+    cut_mext(F, pos_lower, c, p, lane);
+    if (rest > 0) leaf_mext(F, pos_leaf, p, lane);
+    if (lane == 0) {
+        F.nodes[pos_lower] = lower;
+        F.ntok[pos_lower] = lower.tok;
+        if (F.ltime) {
+            const unsigned long long tc = fresh_u64(&F.ltime[c]);
+            F.ltime[pos_lower] = tc;  // both parts of the edge keep its time
+            if (stamped && tc < F.now) F.ltime[c] = F.now;
+            if (rest > 0) F.ltime[pos_leaf] = stamped ? F.now : 0ull;
+        }
+        if (rest > 0) {
+            const Node leaf{s[0], (uint32_t)pb, (int32_t)rest, 0, 0, 0, bit0};
+            F.nodes[pos_leaf] = leaf;
+            F.ntok[pos_leaf] = leaf.tok;
+        }
+        Node upper = old;  // keeps tok, label start, peers and c's slot in its parent
+        upper.mask0 |= bit0;
+        upper.lab_len = l;
+        upper.ct_beg = (int32_t)nb;
+        upper.ct_cnt = rest > 0 ? 2 : 1;
+        upper.aux = 0;
+        F.nodes[c] = upper;
+    }
 }
 
 // Cut child c's edge after l tokens; the winning insert's rest becomes a leaf,
@@ -402,7 +534,7 @@ __global__ __launch_bounds__(64 *kSplitWaves) void split_apply_kernel(DevForest 
         r.c = current_pos(F, r.c, stamp);
         if (F.nodes[r.c].aux == (int32_t)(INT32_MAX - i)) {  // else another insert cuts c this round
             s = B.tokens + B.offsets[i];
-            rest = B.offsets[i + 1] - B.offsets[i] - (int64_t)r.d - r.l;
+            rest = ins_rest(B, i, r, r.l);
             k = rest > 0 ? 2 : 1;
             if (r.l > 0)
                 win = true;
@@ -441,55 +573,11 @@ __global__ __launch_bounds__(64 *kSplitWaves) void split_apply_kernel(DevForest 
         }
         return;
     }
-    const Node old = F.nodes[r.c];
-    Node lower = old;
-    lower.tok = F.pool[old.lab_off + r.l];
-    lower.lab_off = old.lab_off + (uint32_t)r.l;
-    lower.lab_len = old.lab_len - r.l;
-    lower.aux = 0;
-    int64_t pos_lower = nb, pos_leaf = nb + 1;
-    if (rest > 0 && s[r.d + r.l] < lower.tok) {
-        pos_leaf = nb;
-        pos_lower = nb + 1;
-    }
-    if (rest > 0) copy_tokens(F.pool + pb, s + r.d + r.l, rest, lane);
-    // the winner's peer holds the upper part and its leaf; the lower part
-    // keeps the edge's peers
-    const int32_t p = B.peer_of[i];
-    const unsigned long long bit0 = (p >> 6) == 0 ? 1ull << (p & 63) : 0ull;
-    const bool local = F.ltime && B.stamp && p == F.local;
-    cut_mext(F, pos_lower, r.c, p, lane);
-    if (rest > 0) leaf_mext(F, pos_leaf, p, lane);
-    if (lane == 0) {
-        F.nodes[pos_lower] = lower;
-        F.ntok[pos_lower] = lower.tok;
-        if (F.ltime) {
-            const unsigned long long tc = F.ltime[r.c];
-            F.ltime[pos_lower] = tc;  // both parts of the edge keep its time
-            if (local && tc < F.now) F.ltime[r.c] = F.now;
-            if (rest > 0) F.ltime[pos_leaf] = local ? F.now : 0ull;
-        }
-        if (rest > 0) {
-            Node leaf;
-            leaf.tok = s[r.d + r.l];
-            leaf.lab_off = (uint32_t)pb;
-            leaf.lab_len = (int32_t)rest;
-            leaf.ct_beg = 0;
-            leaf.ct_cnt = 0;
-            leaf.aux = 0;
-            leaf.mask0 = bit0;
-            F.nodes[pos_leaf] = leaf;
-            F.ntok[pos_leaf] = leaf.tok;
-        }
-        Node upper = old;  // keeps tok, label start, peers and c's slot in its parent
-        upper.mask0 |= bit0;
-        upper.lab_len = r.l;
-        upper.ct_beg = (int32_t)nb;
-        upper.ct_cnt = k;
-        upper.aux = 0;
-        F.nodes[r.c] = upper;
-        st[i].kind = kInsDone;  // the sequence ends at the leaf, or at upper (rest 0)
-    }
+    const int32_t p = batch_peer(B, i);
+    uint32_t seen = 0;
+    cut_edge(F, NarrowDst{nullptr, nullptr}, F.nodes[r.c], r.c, r.l, s + r.d + r.l, rest, p,
+             F.ltime && B.stamp && p == F.local, nb, pb, lane, seen);
+    if (lane == 0) st[i].kind = kInsDone;  // the sequence ends at the leaf, or at the upper part (rest 0)
 }
 
 // Sort keys of ADD inserts: (parent, next token) in (unsigned, signed) order;
@@ -1187,7 +1275,7 @@ __global__ __launch_bounds__(64 *kMergeWavesPerBlock) void add_leaf_kernel(
         const int64_t rest = len - d;  // >= 1: an ADD insert has a next token
         const int64_t dst = nb + (widx[e] - widx[k]) + lower_count(F.ntok + nx.ct_beg, nx.ct_cnt, s[d]);
         const int64_t pb = pofs ? (int64_t)ctr->add_pool_base + pofs[i] : grp_pb[k] + (poff[e] - poff[k]);
-        const int32_t p = B.peer_of[i];
+        const int32_t p = batch_peer(B, i);
         copy_tokens(F.pool + pb, s + d, rest, lane);
         leaf_mext(F, dst, p, lane);
         if (lane == 0) {
@@ -1256,12 +1344,6 @@ __global__ void clear_peer_kernel(DevForest F, int64_t n_nodes, int32_t p) {
         F.nodes[x].mask0 &= keep;
     else
         F.mext[x * (F.W - 1) + (w - 1)] &= keep;
-}
-
-// Fill a peer id array (snapshot loads insert every sequence into one peer).
-__global__ void fill_peer_kernel(int32_t *peer_of, int64_t n, int32_t p) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) peer_of[i] = p;
 }
 
 }  // namespace pr

@@ -45,11 +45,9 @@
 #include <type_traits>
 
 #include "forest_layout.h"
+#include "route_launch.h"
 #include "wave_ops.h"
 
-#ifndef PR_ROUTE_WAVES_PER_BLOCK
-#define PR_ROUTE_WAVES_PER_BLOCK 1
-#endif
 #ifndef PR_LCP_VECTORS
 #define PR_LCP_VECTORS 16
 #endif
@@ -65,9 +63,6 @@
 #ifndef PR_FIRST_WINDOW
 #define PR_FIRST_WINDOW 1
 #endif
-#ifndef PR_WIN_VECTORS
-#define PR_WIN_VECTORS 2
-#endif
 #ifndef PR_ROUTE_WAVES_PER_EU
 #define PR_ROUTE_WAVES_PER_EU 8
 #endif
@@ -80,8 +75,6 @@
 
 namespace pr {
 
-constexpr int kWave = 64;
-constexpr int kRouteWavesPerBlock = PR_ROUTE_WAVES_PER_BLOCK;
 constexpr int kLcpVectors = PR_LCP_VECTORS;               // 64-token vectors per compare step
 constexpr int kLcpFirstVectors = PR_LCP_FIRST_VECTORS;    // ... in a label's first step
 
@@ -272,10 +265,6 @@ __device__ __forceinline__ int64_t wave_lcp(const LabelSrc<LT, HB> &lab, const i
     return n;
 }
 
-constexpr int kWinVectors = PR_WIN_VECTORS;
-constexpr int kWideWinVectors = 4;
-static_assert(kWinVectors >= 2 && kWinVectors <= 16, "window of 2 to 16 vectors");
-
 #if PR_FIRST_WINDOW
 // First-level window: the query's first 64 * WV tokens are loaded into
 // registers together with its first token, whose HBM round trip the walk
@@ -417,19 +406,6 @@ __device__ __forceinline__ bool locate(const ChildBlock &cb, int32_t t, const No
     return true;
 }
 
-// Peer selection (the argmax of Algorithm 1, with the push-back and failover
-// rules of Sections "Hot specialist push-back" and "In-flight forwarded
-// request failure").  Candidates are ordered by larger match, then, when
-// prefer_local is set, the local peer, then the lower id; best is the first
-// eligible candidate and second the next (-1 when there is none).  The local
-// peer is always eligible.  Plain routing is the case "every peer eligible,
-// no local peer, no second".
-struct Select {
-    const uint64_t *eligible;  // ceil(P / 64) words, bit p % 64 of word p / 64; nullptr: every peer
-    int32_t local;             // -1: none
-    int32_t prefer_local;
-    int32_t *second;           // nullptr: not wanted
-};
 
 // Order key of a candidate: larger is earlier; 0 for peers that are not
 // candidates (every real key is above 2^32 - 1026).
@@ -638,13 +614,6 @@ __attribute__((amdgpu_waves_per_eu(PR_ROUTE_WAVES_PER_EU))) void route_kernel(
 // first.  Within a bucket the order is fixed by the layout below, so it is
 // deterministic.  Offsets are not checked here (a bad pair lands in some
 // bucket); the route kernel checks every query's offsets itself.
-constexpr int kOrderThreads = 1024;
-constexpr int kOrderWaves = kOrderThreads / kWave;
-constexpr int kOrderPerThread = 4;
-constexpr int kOrderChunk = kOrderThreads * kOrderPerThread;  // queries per workgroup
-constexpr int kOrderBuckets = 16;
-constexpr int kOrderMaxBlocks = 16;
-constexpr int32_t kOrderMaxQueries = kOrderChunk * kOrderMaxBlocks;  // 65,536
 
 // Query i of thread t in workgroup b: base + i * kOrderThreads + t.
 __device__ __forceinline__ int32_t order_query(int b, int i, int t) {

@@ -3,7 +3,7 @@
 //
 // Host side: per-peer snapshot copies, the union-forest build, device memory
 // with spare capacity for merges, argument checks, the merge round loop and
-// launches.  Device side: route_kernels.h, merge_kernels.h.
+// launches.  Device side: route_kernels.h (compiled in route.hip), merge_kernels.h.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -24,7 +24,8 @@
 #include "merge_kernels.h"
 #include "narrow_kernels.h"
 #include "prefix_router.h"
-#include "route_kernels.h"
+#include "route_launch.h"
+#include "small_merge.h"
 
 using pr::Node;
 
@@ -57,7 +58,8 @@ struct DevImage {
     unsigned long long *ltime = nullptr;  // local peer's access times (allocated while a local peer is set)
     uint16_t *pool16 = nullptr;  // low 16 bits of pool, which routes read while every label token fits 17 bits
     int64_t cap_pool16 = 0;
-    uint32_t *hib = nullptr;     // bit 16 of pool token i: bit i % 32 of hib[i / 32] (hib_words(cap_pool16) words)
+    uint32_t *hib = nullptr;     // bit 16 of pool token i: bit i % 32 of hib[i / 32] (hib_words(cap_pool16) words),
+                                 // zero past the used pool
     int64_t cap_nodes = 0, cap_pool = 0;
     int64_t n_nodes = 0, n_pool = 0;  // host mirror of the device counters
 };
@@ -76,7 +78,7 @@ struct MergeScratch {
     void *sort_tmp = nullptr;
     size_t sort_tmp_bytes = 0;
     // snapshot loads on the device path stage their host batch here
-    int32_t *load_tok = nullptr, *load_peer = nullptr;
+    int32_t *load_tok = nullptr;
     int64_t *load_off = nullptr;
     int64_t load_tok_cap = 0, load_seq_cap = 0;
 };
@@ -325,7 +327,6 @@ void free_scratch(pr_forest *f) {
     if (m.sort_tmp) (void)hipFree(m.sort_tmp);
     f->device_bytes -= (int64_t)m.sort_tmp_bytes;
     dfree(f, &m.load_tok, m.load_tok_cap);
-    dfree(f, &m.load_peer, m.load_seq_cap);
     dfree(f, &m.load_off, m.load_seq_cap + 1);
     m = MergeScratch();
     free_export_scratch(f);
@@ -426,6 +427,7 @@ pr_status ensure_capacity(pr_forest *f, int64_t need_nodes, int64_t need_pool, h
             hipMemsetAsync(np + d.n_pool, 0, (cap - d.n_pool) * sizeof(int32_t), s) != hipSuccess ||
             (keep16 &&
              (hipMemcpyAsync(n16, d.pool16, d.n_pool * sizeof(uint16_t), hipMemcpyDeviceToDevice, s) != hipSuccess ||
+              hipMemsetAsync(nhb, 0, hib_words(cap) * sizeof(uint32_t), s) != hipSuccess ||
               hipMemcpyAsync(nhb, d.hib, hib_words(d.n_pool) * sizeof(uint32_t), hipMemcpyDeviceToDevice, s) !=
                   hipSuccess)) ||
             hipStreamSynchronize(s) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
@@ -505,6 +507,8 @@ pr_status pool16_extend(pr_forest *f, int64_t from, hipStream_t s, bool device_e
         d.pool16 = np;
         d.hib = nh;
         d.cap_pool16 = d.cap_pool;
+        if (hipMemsetAsync(d.hib, 0, hib_words(d.cap_pool) * sizeof(uint32_t), s) != hipSuccess)
+            return fail(PR_EDEVICE, "clearing the bit plane failed");
         from = 0;
         f->layout_epoch++;
     }
@@ -605,6 +609,7 @@ pr_status commit(pr_forest *f) {
         if (f->narrow && dalloc(f, &d.pool16, d.cap_pool) && dalloc(f, &d.hib, hib_words(d.cap_pool))) {
             d.cap_pool16 = d.cap_pool;
             if ((np > 0 && hipMemcpy(d.pool16, p16.data(), np * sizeof(uint16_t), hipMemcpyHostToDevice) != hipSuccess) ||
+                hipMemset(d.hib, 0, hib_words(d.cap_pool) * sizeof(uint32_t)) != hipSuccess ||
                 hipMemcpy(d.hib, hb.data(), hb.size() * sizeof(uint32_t), hipMemcpyHostToDevice) != hipSuccess) {
                 d.cap_pool16 = d.cap_pool;
                 free_image(f);
@@ -644,23 +649,6 @@ bool use_longest_first(int64_t nq, int64_t ntok) {
            ntok >= 4096 * nq;
 }
 
-// The two order launches (at most 16 workgroups each) on stream s: bkt gets
-// every query's length bucket (a quarter of the mean query wide), blockcnt
-// the per-workgroup bucket counts, order the queries longest first.  Every
-// entry read is written earlier in the same two launches, so the buffers need
-// no clearing.  nq <= pr::kOrderMaxQueries.
-pr_status launch_order(const int64_t *q_offsets, int64_t nq, int64_t ntok, hipStream_t s, uint8_t *bkt,
-                       int32_t *blockcnt, int32_t *order) {
-    const uint32_t unit = (uint32_t)std::min<int64_t>(std::max<int64_t>(1, ntok / nq / 4), INT32_MAX);
-    const unsigned blocks = (unsigned)((nq + pr::kOrderChunk - 1) / pr::kOrderChunk);
-    hipLaunchKernelGGL(pr::route_order_count_kernel, dim3(blocks), dim3(pr::kOrderThreads), 0, s, q_offsets,
-                       (int32_t)nq, unit, bkt, blockcnt);
-    hipLaunchKernelGGL(pr::route_order_scatter_kernel, dim3(blocks), dim3(pr::kOrderThreads), 0, s, bkt,
-                       (int32_t)nq, blockcnt, order);
-    if (hipGetLastError() != hipSuccess) return fail(PR_EDEVICE, "route order launch failed");
-    return PR_OK;
-}
-
 // Fill f->rs.order with the queries longest first (two launches of at most 16
 // workgroups) on stream s; length buckets are a quarter of the mean query wide.
 pr_status route_order(pr_forest *f, const int64_t *q_offsets, int64_t nq, int64_t ntok, hipStream_t s,
@@ -686,62 +674,18 @@ pr_status route_order(pr_forest *f, const int64_t *q_offsets, int64_t nq, int64_
     }
     if (R.pending && hipStreamWaitEvent(s, R.done, 0) != hipSuccess)
         return fail(PR_EDEVICE, "hipStreamWaitEvent failed");
-    pr_status r = launch_order(q_offsets, nq, ntok, s, R.bkt, R.blockcnt, R.order);
-    if (r) return r;
+    if (pr::launch_route_order(q_offsets, nq, ntok, s, R.bkt, R.blockcnt, R.order) != hipSuccess)
+        return fail(PR_EDEVICE, "route order launch failed");
     *order = R.order;
     return PR_OK;
 }
 
-template <int W, bool SEL, typename LT, bool HB>
-void launch_route_t(const pr_forest *f, const LT *pool, const int32_t *qt, int64_t ntok, const int64_t *qo,
-                    int64_t nq, const pr::Select &sel, int32_t *ml, int32_t *ch, const int32_t *order,
-                    hipStream_t s) {
-    const int64_t blocks = (nq + pr::kRouteWavesPerBlock - 1) / pr::kRouteWavesPerBlock;
-    const uint32_t *hib = HB ? f->dev.hib : nullptr;
-    if (f->wide_window)
-        hipLaunchKernelGGL((pr::route_kernel<W, SEL, LT, HB, pr::kWideWinVectors>), dim3((unsigned)blocks),
-                           dim3(pr::kWave * pr::kRouteWavesPerBlock), 0, s, f->dev.nodes, f->dev.ntok, f->dev.nsep,
-                           f->dev.mext, pool, hib, qt, ntok, qo, nq, f->P, sel, ml, ch, order);
-    else
-        hipLaunchKernelGGL((pr::route_kernel<W, SEL, LT, HB>), dim3((unsigned)blocks),
-                           dim3(pr::kWave * pr::kRouteWavesPerBlock), 0, s, f->dev.nodes, f->dev.ntok, f->dev.nsep,
-                           f->dev.mext, pool, hib, qt, ntok, qo, nq, f->P, sel, ml, ch, order);
-}
-
-template <int W, bool SEL>
-void launch_route_l(const pr_forest *f, const int32_t *qt, int64_t ntok, const int64_t *qo, int64_t nq,
-                    const pr::Select &sel, int32_t *ml, int32_t *ch, const int32_t *order, hipStream_t s) {
-    const bool narrow = f->narrow && f->dev.pool16 && f->dev.hib;
-    if (narrow && f->hi17)
-        launch_route_t<W, SEL, uint16_t, true>(f, f->dev.pool16, qt, ntok, qo, nq, sel, ml, ch, order, s);
-    else if (narrow)
-        launch_route_t<W, SEL, uint16_t, false>(f, f->dev.pool16, qt, ntok, qo, nq, sel, ml, ch, order, s);
-    else
-        launch_route_t<W, SEL, int32_t, false>(f, f->dev.pool, qt, ntok, qo, nq, sel, ml, ch, order, s);
-}
-
-// Plain routing or selection, over the narrow labels when they are current.
-template <int W>
-hipError_t launch_route(const pr_forest *f, const int32_t *qt, int64_t ntok, const int64_t *qo, int64_t nq,
-                        const pr::Select &sel, int32_t *ml, int32_t *ch, const int32_t *order, hipStream_t s) {
-    const bool plain = !sel.eligible && !sel.prefer_local && !sel.second;
-    if (plain)
-        launch_route_l<W, false>(f, qt, ntok, qo, nq, sel, ml, ch, order, s);
-    else
-        launch_route_l<W, true>(f, qt, ntok, qo, nq, sel, ml, ch, order, s);
-    return hipGetLastError();
-}
-
-// The route kernel for the forest's mask-word count.
-hipError_t launch_route_w(const pr_forest *f, const int32_t *qt, int64_t ntok, const int64_t *qo, int64_t nq,
-                          const pr::Select &sel, int32_t *ml, int32_t *ch, const int32_t *order, hipStream_t s) {
-    switch (f->W) {
-        case 1: return launch_route<1>(f, qt, ntok, qo, nq, sel, ml, ch, order, s);
-        case 2: return launch_route<2>(f, qt, ntok, qo, nq, sel, ml, ch, order, s);
-        case 4: return launch_route<4>(f, qt, ntok, qo, nq, sel, ml, ch, order, s);
-        case 8: return launch_route<8>(f, qt, ntok, qo, nq, sel, ml, ch, order, s);
-        default: return launch_route<16>(f, qt, ntok, qo, nq, sel, ml, ch, order, s);
-    }
+// The forest as a route reads it: over the narrow labels when they are current.
+pr::RouteForest route_view(const pr_forest *f) {
+    const DevImage &d = f->dev;
+    const bool narrow = f->narrow && d.pool16 && d.hib;
+    return pr::RouteForest{d.nodes, d.ntok, d.nsep, d.mext, d.pool, narrow ? d.pool16 : nullptr,
+                           narrow && f->hi17 ? d.hib : nullptr, f->P, f->W, f->wide_window};
 }
 
 // ---- routes without allocation ----------------------------------------------
@@ -912,7 +856,7 @@ bool read_small(pr_forest *f, void *out, const void *dsrc, size_t bytes, hipStre
     return true;
 }
 
-static_assert(sizeof(pr::MergeCounters) <= kStageBytes && sizeof(pr::EvictPlan) <= kStageBytes,
+static_assert(sizeof(pr::MergeCounters) <= kStageBytes && sizeof(pr::SmallStatus) <= kStageBytes && sizeof(pr::EvictPlan) <= kStageBytes,
               "readbacks fit the staging buffer");
 
 // Read the device counters and refresh the host mirror of the used sizes
@@ -948,15 +892,62 @@ pr::DevForest dev_view(const pr_forest *f) {
 }
 
 
-// Insert a device batch into the device forest (see merge_kernels.h).
-pr_status run_merge(pr_forest *f, const int32_t *peer_of, const int32_t *tokens, int64_t num_tokens,
-                    const int64_t *offsets, int64_t n, hipStream_t s, int32_t stamp = 1) {
-    pr_status r = ensure_merge_scratch(f, n, s);
-    if (r) return r;
+// A batch of device sequences for run_merge: inserts into peer_of[i]'s trees,
+// or into one peer's (peer_of nullptr), or touches of one peer's.
+pr::Batch batch_of(const pr_forest *f, const int32_t *peer_of, int32_t peer, const int32_t *tokens,
+                   int64_t num_tokens, const int64_t *offsets, int64_t n) {
+    return pr::Batch{peer_of, tokens, offsets, num_tokens, n, f->P, 1, peer, 0};
+}
+
+// What a merge's appended labels mean for the narrow copy: hi, wide count (or
+// flag) tokens in [65536, 131071] and outside [0, 131071].
+void narrow_seen(pr_forest *f, bool hi, bool wide) {
+    if (wide)
+        drop_pool16(f);
+    else if (hi && f->narrow && !f->hi17) {
+        f->hi17 = true;  // routes now read the bit plane too (a new kernel: the arrays stay)
+        f->layout_epoch++;
+    }
+}
+
+// Batches of at most pr::kSmallMax sequences: one launch (small_merge.h) and
+// one wait.  *done: false if part of the batch is left for the rounds below.
+pr_status run_small_merge(pr_forest *f, const pr::Batch &B, hipStream_t s, bool *done) {
+    DevImage &d = f->dev;
+    pr::SmallStatus *out = reinterpret_cast<pr::SmallStatus *>(f->d_stage);
+    const pr::NarrowDst N{f->narrow ? d.pool16 : nullptr, d.hib};
+    hipLaunchKernelGGL(pr::small_merge_kernel, dim3(1), dim3(64 * pr::kSmallWaves), 0, s, dev_view(f), B, N,
+                       f->d_ctr, f->d_skipped, f->stamp + 1, out);
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
+        return fail(PR_EDEVICE, "small merge failed");
+    pr::SmallStatus st;
+    std::memcpy(&st, f->h_stage, sizeof(st));
+    f->stamp += st.stamps;
+    d.n_nodes = (int64_t)st.n_nodes;
+    d.n_pool = (int64_t)st.n_pool;
+    narrow_seen(f, st.hi != 0, st.wide != 0);
+    f->merged = true;
+    *done = st.done != 0;
+    return PR_OK;
+}
+
+// Insert a device batch into the device forest (see merge_kernels.h), or touch
+// the local peer's tree with it.
+pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
     const int64_t pool0 = f->dev.n_pool;  // labels appended from here on
     const int64_t nodes0 = f->dev.n_nodes;
+    pr_status r;
+    // one workgroup serves a batch up to a lane per sequence in about the time
+    // of five launches (65 and more take the rounds below, about 22 launches);
+    // it writes the narrow copy itself, which must be as long as the pool
+    if (B.n <= pr::kSmallMax && f->d_stage && (!f->narrow || f->dev.cap_pool16 >= f->dev.cap_pool)) {
+        bool small_done = false;
+        if ((r = run_small_merge(f, B, s, &small_done))) return r;
+        if (small_done) return PR_OK;
+    }
+    if ((r = ensure_merge_scratch(f, B.n, s))) return r;
     MergeScratch &m = f->ms;
-    pr::Batch B{peer_of, tokens, offsets, num_tokens, n, f->P, stamp};
+    const int64_t n = B.n;
     const int bs = 256, wb = 64 * pr::kMergeWavesPerBlock;
     hipLaunchKernelGGL(reset_call_kernel, dim3(1), dim3(1), 0, s, f->d_ctr);
     hipLaunchKernelGGL(pr::merge_validate_kernel, dim3(grid_threads(n, bs)), dim3(bs), 0, s, B, m.st, f->d_ctr);
@@ -982,7 +973,7 @@ pr_status run_merge(pr_forest *f, const int32_t *peer_of, const int32_t *tokens,
         // the round counters start cleared (reset_call_kernel above), and each
         // round's split kernel clears them for the next walk
         for (int k = 0; k < kDeviceRounds; k++) {
-            hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_waves(n)), dim3(wb), 0, s, F, B, m.st, f->d_ctr);
+            hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_waves(n)), dim3(wb), 0, s, F, B, m.st);
             hipLaunchKernelGGL(pr::merge_tally_kernel,
                                dim3((unsigned)std::min<int64_t>(256, (n + pr::kTallyThreads - 1) / pr::kTallyThreads)),
                                dim3(pr::kTallyThreads), 0, s, B, m.st, f->d_ctr, m.arest);
@@ -1003,7 +994,7 @@ pr_status run_merge(pr_forest *f, const int32_t *peer_of, const int32_t *tokens,
             hipLaunchKernelGGL(pr::split_apply_kernel, dim3(grid_split(n)), dim3(64 * pr::kSplitWaves), 0, s, F, B,
                                m.st, f->d_ctr, stamp, 1);
         }
-        hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_waves(n)), dim3(wb), 0, s, F, B, m.st, f->d_ctr);
+        hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_waves(n)), dim3(wb), 0, s, F, B, m.st);
         hipLaunchKernelGGL(pr::merge_tally_kernel,
                            dim3((unsigned)std::min<int64_t>(256, (n + pr::kTallyThreads - 1) / pr::kTallyThreads)),
                            dim3(pr::kTallyThreads), 0, s, B, m.st, f->d_ctr, m.arest);
@@ -1018,8 +1009,7 @@ pr_status run_merge(pr_forest *f, const int32_t *peer_of, const int32_t *tokens,
     }
     for (; !done && round < max_rounds; round++) {
         hipLaunchKernelGGL(reset_round_kernel, dim3(1), dim3(1), 0, s, f->d_ctr);
-        hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_waves(n)), dim3(wb), 0, s, dev_view(f), B, m.st,
-                           f->d_ctr);
+        hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_waves(n)), dim3(wb), 0, s, dev_view(f), B, m.st);
         hipLaunchKernelGGL(pr::merge_tally_kernel,
                            dim3((unsigned)std::min<int64_t>(256, (n + pr::kTallyThreads - 1) / pr::kTallyThreads)),
                            dim3(pr::kTallyThreads), 0, s, B, m.st, f->d_ctr, m.arest);
@@ -1138,12 +1128,7 @@ pr_status run_merge(pr_forest *f, const int32_t *peer_of, const int32_t *tokens,
     if (c.overflow || c.bad_path)
         return fail(PR_EDEVICE, "merge invariant broken (overflow " + std::to_string(c.overflow) + ", bad paths " +
                                     std::to_string(c.bad_path) + "); destroy the forest");
-    if (c.wide_tokens)
-        drop_pool16(f);  // a label token outside [0, 131071] arrived
-    else if (c.hi_tokens && f->narrow && !f->hi17) {
-        f->hi17 = true;  // routes now read the bit plane too (a new kernel: the arrays stay)
-        f->layout_epoch++;
-    }
+    narrow_seen(f, c.hi_tokens != 0, c.wide_tokens != 0);
     f->merged = true;
     return PR_OK;
 }
@@ -1166,19 +1151,15 @@ pr_status device_load(pr_forest *f, int32_t peer, const pr::PeerSeqs &S) {
         m.load_tok_cap = nt;
     }
     if (ns > m.load_seq_cap) {
-        dfree(f, &m.load_peer, m.load_seq_cap);
         dfree(f, &m.load_off, m.load_seq_cap + 1);
         m.load_seq_cap = 0;
-        if (!dalloc(f, &m.load_peer, ns) || !dalloc(f, &m.load_off, ns + 1))
-            return fail(PR_ENOMEM, "hipMalloc failed for the snapshot");
+        if (!dalloc(f, &m.load_off, ns + 1)) return fail(PR_ENOMEM, "hipMalloc failed for the snapshot");
         m.load_seq_cap = ns;
     }
     if ((nt > 0 && hipMemcpy(m.load_tok, S.tokens.data(), nt * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess) ||
         hipMemcpy(m.load_off, S.offsets.data(), (ns + 1) * sizeof(int64_t), hipMemcpyHostToDevice) != hipSuccess)
         return fail(PR_EDEVICE, "snapshot upload failed");
-    hipLaunchKernelGGL(pr::fill_peer_kernel, dim3(grid_threads(ns, 256)), dim3(256), 0, s, m.load_peer, ns, peer);
-    if (hipGetLastError() != hipSuccess) return fail(PR_EDEVICE, "snapshot kernels failed to launch");
-    return run_merge(f, m.load_peer, m.load_tok, nt, m.load_off, ns, s);
+    return run_merge(f, batch_of(f, nullptr, peer, m.load_tok, nt, m.load_off, ns), s);
 }
 
 pr_status ensure_export_scratch(pr_forest *f, int64_t nn) {
@@ -1408,7 +1389,7 @@ pr_status pr_merge(pr_forest *f, const int32_t *peer_of, const int32_t *tokens, 
     if (!ds.ok()) return fail(PR_EDEVICE, "cannot select the forest's device");
     pr_status s = commit(f);
     if (s) return s;
-    s = run_merge(f, peer_of, tokens, num_tokens, offsets, num_seqs, (hipStream_t)hip_stream);
+    s = run_merge(f, batch_of(f, peer_of, 0, tokens, num_tokens, offsets, num_seqs), (hipStream_t)hip_stream);
     if (s) {
         f->broken = true;
         return s;
@@ -1430,7 +1411,6 @@ pr_status pr_load_snapshot_device(pr_forest *f, int32_t peer, const int32_t *tok
     pr_status r = commit(f);
     if (r) return r;
     hipStream_t s = (hipStream_t)hip_stream;
-    MergeScratch &m = f->ms;
     hipLaunchKernelGGL(pr::clear_peer_kernel, dim3(grid_threads(f->dev.n_nodes, 256)), dim3(256), 0, s,
                        dev_view(f), f->dev.n_nodes, peer);
     if (hipGetLastError() != hipSuccess) {
@@ -1438,19 +1418,7 @@ pr_status pr_load_snapshot_device(pr_forest *f, int32_t peer, const int32_t *tok
         return fail(PR_EDEVICE, "snapshot kernels failed to launch");
     }
     if (num_seqs > 0) {
-        if (num_seqs > m.load_seq_cap) {
-            dfree(f, &m.load_peer, m.load_seq_cap);
-            dfree(f, &m.load_off, m.load_seq_cap + 1);
-            m.load_seq_cap = 0;
-            if (!dalloc(f, &m.load_peer, num_seqs) || !dalloc(f, &m.load_off, num_seqs + 1)) {
-                f->broken = true;
-                return fail(PR_ENOMEM, "hipMalloc failed for the snapshot");
-            }
-            m.load_seq_cap = num_seqs;
-        }
-        hipLaunchKernelGGL(pr::fill_peer_kernel, dim3(grid_threads(num_seqs, 256)), dim3(256), 0, s, m.load_peer,
-                           num_seqs, peer);
-        r = run_merge(f, m.load_peer, tokens, num_tokens, offsets, num_seqs, s);
+        r = run_merge(f, batch_of(f, nullptr, peer, tokens, num_tokens, offsets, num_seqs), s);
     } else {
         r = hipStreamSynchronize(s) == hipSuccess ? PR_OK : fail(PR_EDEVICE, "sync failed");
         f->merged = true;
@@ -1691,10 +1659,6 @@ pr_status pr_set_time(pr_forest *f, int64_t t) {
     return ok();
 }
 
-static pr_status route_impl(pr_forest *f, const int32_t *q_tokens, int64_t num_tokens, const int64_t *q_offsets,
-                            int64_t num_queries, const pr::Select &sel, int32_t *match_len, int32_t *chosen,
-                            void *hip_stream);
-
 pr_status pr_touch(pr_forest *f, const int32_t *q_tokens, int64_t num_tokens, const int64_t *q_offsets,
                    int64_t num_queries, void *hip_stream) {
     if (!f) return fail(PR_EINVAL, "forest is NULL");
@@ -1707,41 +1671,13 @@ pr_status pr_touch(pr_forest *f, const int32_t *q_tokens, int64_t num_tokens, co
     if (f->broken) return fail(PR_ESTATE, "an earlier device update failed; destroy the forest");
     DeviceScope ds(f);
     if (!ds.ok()) return fail(PR_EDEVICE, "cannot select the forest's device");
-    hipStream_t s = (hipStream_t)hip_stream;
-    CallScratch X;
-    int32_t *ml = nullptr, *ch = nullptr, *peer_of = nullptr, *ttok = nullptr;
-    int64_t *len1 = nullptr, *toff = nullptr;
-    if (!X.get(&ml, num_queries * (int64_t)f->P) || !X.get(&ch, num_queries) || !X.get(&len1, num_queries + 1) ||
-        !X.get(&toff, num_queries + 1) || !X.get(&peer_of, num_queries))
-        return fail(PR_ENOMEM, "hipMalloc failed for the touch");
-    // 1. the matched prefix of every query in the local tree
-    const pr::Select sel{nullptr, -1, 0, nullptr};
-    pr_status r = route_impl(f, q_tokens, num_tokens, q_offsets, num_queries, sel, ml, ch, hip_stream);
+    pr_status r = commit(f);
     if (r) return r;
-    // 2. gather the prefixes into one batch
-    hipLaunchKernelGGL(pr::touch_lengths_kernel, dim3(grid_threads(num_queries, 256)), dim3(256), 0, s, ml, f->P,
-                       f->local, num_queries, len1);
-    size_t need = 0;
-    if (rocprim::inclusive_scan(nullptr, need, len1, toff, (size_t)num_queries + 1, rocprim::plus<int64_t>(), s) !=
-        hipSuccess)
-        return fail(PR_EDEVICE, "touch scan sizing failed");
-    void *tmp = nullptr;
-    if (!X.get((char **)&tmp, (int64_t)need)) return fail(PR_ENOMEM, "hipMalloc failed for the touch");
-    if (rocprim::inclusive_scan(tmp, need, len1, toff, (size_t)num_queries + 1, rocprim::plus<int64_t>(), s) !=
-        hipSuccess)
-        return fail(PR_EDEVICE, "touch scan failed");
-    int64_t total = 0;
-    if (!read_small(f, &total, toff + num_queries, sizeof(total), s))
-        return fail(PR_EDEVICE, "touch readback failed");
-    if (!X.get(&ttok, total)) return fail(PR_ENOMEM, "hipMalloc failed for the touch");
-    hipLaunchKernelGGL(pr::touch_gather_kernel, dim3((unsigned)((num_queries + 3) / 4)), dim3(256), 0, s, q_tokens,
-                       q_offsets, toff, num_queries, ttok);
-    hipLaunchKernelGGL(pr::fill_peer_kernel, dim3(grid_threads(num_queries, 256)), dim3(256), 0, s, peer_of,
-                       num_queries, f->local);
-    if (hipGetLastError() != hipSuccess) return fail(PR_EDEVICE, "touch launch failed");
-    // 3. inserting the prefixes into the local peer adds nothing but node
-    //    boundaries where a prefix ends inside a label, and stamps the paths
-    r = run_merge(f, peer_of, ttok, total, toff, num_queries, s, 1);
+    // the walk of a touch ends where the local tree does: it adds nothing but
+    // node boundaries where a prefix ends inside a label, and stamps the paths
+    pr::Batch B = batch_of(f, nullptr, f->local, q_tokens, num_tokens, q_offsets, num_queries);
+    B.touch = 1;
+    r = run_merge(f, B, (hipStream_t)hip_stream);
     if (r) {
         f->broken = true;
         return r;
@@ -1866,8 +1802,8 @@ pr_status pr_evict_lru(pr_forest *f, int64_t max_tokens, int64_t *evicted, void 
             return fail_dev("eviction failed");
         if (h_cut > 0) {
             int64_t *offs = nullptr, *old_len = nullptr;
-            int32_t *peer_of = nullptr, *ctok = nullptr;
-            if (!X.get(&offs, h_cut + 1) || !X.get(&old_len, h_cut) || !X.get(&peer_of, h_cut))
+            int32_t *ctok = nullptr;
+            if (!X.get(&offs, h_cut + 1) || !X.get(&old_len, h_cut))
                 return fail_nomem("hipMalloc failed for the eviction");
             size_t n5 = 0;
             if (rocprim::inclusive_scan(nullptr, n5, cut_len1, offs, (size_t)h_cut + 1, rocprim::plus<int64_t>(),
@@ -1886,11 +1822,11 @@ pr_status pr_evict_lru(pr_forest *f, int64_t max_tokens, int64_t *evicted, void 
                                cut_node, h_cut, offs, W.parent, W.depth, ctok);
             hipLaunchKernelGGL(pr::lru_old_len_kernel, dim3(grid_threads(h_cut, 256)), dim3(256), 0, s, F, cut_node,
                                h_cut, old_len);
-            hipLaunchKernelGGL(pr::fill_peer_kernel, dim3(grid_threads(h_cut, 256)), dim3(256), 0, s, peer_of,
-                               (int64_t)h_cut, f->local);
             if (hipGetLastError() != hipSuccess) return fail_dev("eviction launch failed");
             // the kept paths are held already: inserting them only splits the cut nodes
-            if ((r = run_merge(f, peer_of, ctok, total_cut, offs, h_cut, s, 0))) {
+            pr::Batch cuts = batch_of(f, nullptr, f->local, ctok, total_cut, offs, h_cut);
+            cuts.stamp = 0;
+            if ((r = run_merge(f, cuts, s))) {
                 f->broken = true;
                 return r;
             }
@@ -1931,8 +1867,8 @@ static pr_status route_impl(pr_forest *f, const int32_t *q_tokens, int64_t num_t
     if (!capturing && use_longest_first(num_queries, num_tokens) &&
         (s = route_order(f, q_offsets, num_queries, num_tokens, st, &order)))
         return s;
-    const hipError_t e = launch_route_w(f, q_tokens, num_tokens, q_offsets, num_queries, sel, match_len, chosen,
-                                        order, st);
+    const pr::RouteBatch batch{q_tokens, num_tokens, q_offsets, num_queries, match_len, chosen, order};
+    const hipError_t e = pr::launch_route(route_view(f), batch, sel, st);
     if (e != hipSuccess) return fail(PR_EDEVICE, std::string("route launch failed: ") + hipGetErrorString(e));
     if (order) {
         // the order buffers are in use until the stream passes this launch
@@ -1975,14 +1911,14 @@ pr_status pr_route_noalloc(pr_forest *f, const int32_t *q_tokens, int64_t num_to
     const int32_t *order = nullptr;
     if (use_longest_first(num_queries, num_tokens)) {
         int32_t *ord = reinterpret_cast<int32_t *>(sp + kNoAllocOrder);
-        if ((r = launch_order(q_offsets, num_queries, num_tokens, st, sp + kNoAllocBkt,
-                              reinterpret_cast<int32_t *>(sp + kNoAllocBlockcnt), ord)))
-            return r;
+        if (pr::launch_route_order(q_offsets, num_queries, num_tokens, st, sp + kNoAllocBkt,
+                                   reinterpret_cast<int32_t *>(sp + kNoAllocBlockcnt), ord) != hipSuccess)
+            return fail(PR_EDEVICE, "route order launch failed");
         order = ord;
     }
     const pr::Select sel{nullptr, -1, 0, nullptr};
-    const hipError_t e = launch_route_w(f, q_tokens, num_tokens, q_offsets, num_queries, sel, match_len, chosen,
-                                        order, st);
+    const pr::RouteBatch batch{q_tokens, num_tokens, q_offsets, num_queries, match_len, chosen, order};
+    const hipError_t e = pr::launch_route(route_view(f), batch, sel, st);
     if (e != hipSuccess) return fail(PR_EDEVICE, std::string("route launch failed: ") + hipGetErrorString(e));
     return ok();
 }

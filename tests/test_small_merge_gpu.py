@@ -1,0 +1,169 @@
+"""Merges and touches of at most 64 sequences (one launch) and just above
+(rounds of launches), against the CPU oracles: conflicts on slots and edges
+inside a batch, wide parents past the one launch's limit, growth, token widths,
+mask words past the first."""
+import numpy as np
+import pytest
+
+import pins
+import workloads as W
+from gpu_util import announce, assert_rows_equal, device, gpu_route, oracle_for
+
+pytestmark = pytest.mark.gpu
+
+
+def _dev(peers, seqs):
+    import torch
+    t, o = pins._csr(seqs)
+    return [torch.from_numpy(x).to(device()) for x in (np.asarray(peers, np.int32), t, o)]
+
+
+def _check(f, o, queries, what):
+    t, off = pins._csr(queries)
+    m, c = gpu_route(f, W.SeqSet(t, off, None), what)
+    m_or, c_or = o.route(t, off, 4)
+    assert_rows_equal(m, c, m_or, c_or, what=what)
+
+
+def _seqs(rng, vocab, k, lo=0, hi=14, known=()):
+    """Random sequences, many of them grown from the start of a known one."""
+    out = []
+    for _ in range(k):
+        s = list(known[int(rng.integers(0, len(known)))]) if len(known) and rng.random() < 0.6 else []
+        s = s[:int(rng.integers(0, len(s) + 1))]
+        out.append(s + rng.integers(0, vocab, int(rng.integers(lo, hi))).tolist())
+    return out
+
+
+@pytest.mark.parametrize("n", [1, 2, 17, 63, 64, 65])
+@pytest.mark.parametrize("P", [3, 130])
+def test_batches_around_one_lane_each(n, P):
+    """Batches of n conflicting inserts (shared slots, shared edges, chains of
+    cuts, duplicates, empty sequences, bad peers), then every stored sequence
+    and random ones routed."""
+    import oracle
+    from paper_2606_17059_amd import Forest, RouterError
+    rng = np.random.default_rng(100 * n + P)
+    f, o = Forest(P), oracle.Oracle(P)
+    known = [[]]
+    for step in range(6):
+        vocab = [2, 3, 8, 2, 100, 3][step]
+        seqs = _seqs(rng, vocab, n, known=known)
+        peers = rng.integers(0, P, n)
+        if step == 2 and n > 2:
+            seqs[1:] = [seqs[0][:i % (len(seqs[0]) + 1)] for i in range(1, n)]  # every cut of one path
+        bad = np.array(peers)
+        bad[0] = P if step == 4 else bad[0]
+        announce(f"small merge n={n} P={P} step={step}")
+        f.merge(*_dev(bad, seqs))
+        keep = [i for i in range(n) if 0 <= bad[i] < P]
+        t, off = pins._csr([seqs[i] for i in keep])
+        o.merge(np.asarray([bad[i] for i in keep], np.int32), t, off)
+        if step == 4:
+            with pytest.raises(RouterError, match="1 device inputs were skipped"):
+                f.check()
+        known += [seqs[i] for i in keep if seqs[i]]
+        _check(f, o, known[-200:] + _seqs(rng, vocab, 60, known=known), f"n={n} P={P} step={step}")
+    f.check()
+    f.close()
+    o.close()
+
+
+def test_wide_parent_and_growth():
+    """A root of 17,000 children has more chunks than the one launch moves; an
+    insert there and one elsewhere in the same batch, then a leaf of 200,000
+    tokens, which outgrows the pool."""
+    import oracle
+    from paper_2606_17059_amd import Forest
+    f, o = Forest(2), oracle.RadixOracle(2)
+    wide = [[2 * i, 5] for i in range(17000)]
+    t, off = pins._csr(wide)
+    f.load_snapshot(0, t, off)
+    o.load(0, t, off)
+    rng = np.random.default_rng(4)
+    for step, seqs in enumerate([[[6, 5, 1], [7, 1]], [[6, 5, 2, 9]], [[3, 3], [6, 5, 2, 8], [4, 4]],
+                                 [[8] + rng.integers(0, 60000, 200000).tolist()], [[8, 8], [9], [10, 5, 7]]]):
+        announce(f"wide parent, step {step}")
+        f.merge(*_dev([1] * len(seqs), seqs))
+        t, off = pins._csr(seqs)
+        o.merge(np.full(len(seqs), 1, np.int32), t, off)
+        queries = [s[:500] for s in seqs] + [s[:-1] for s in seqs] + wide[::170] + [[2 * i + 1, 5] for i in range(20)]
+        _check(f, o, queries, f"wide parent, step {step}")
+    f.close()
+    o.close()
+
+
+def test_narrow_copy_of_every_alignment():
+    """One-launch merges write the narrow labels as they go: 17-bit sequences
+    of 1 to 200 tokens end to end in the pool, queried with bit 16 flipped at
+    each kind of place; then a token past 17 bits."""
+    import oracle
+    from paper_2606_17059_amd import Forest
+    rng = np.random.default_rng(8)
+    f, o = Forest(3), oracle.Oracle(3)
+    f.merge(*_dev([0], [[1, 2, 3]]))
+    o.merge(np.zeros(1, np.int32), *pins._csr([[1, 2, 3]]))
+    assert f.info()["label_bits"] == 16
+    stored = []
+    for step in range(6):
+        seqs = [[100 * step + L] + (rng.integers(0, 2, L) * 65536 + rng.integers(0, 3, L)).tolist()
+                for L in range(step + 1, 200, 11)]
+        peers = rng.integers(0, 3, len(seqs))
+        announce(f"17-bit one-launch merge {step}")
+        f.merge(*_dev(peers, seqs))
+        o.merge(peers.astype(np.int32), *pins._csr(seqs))
+        stored += seqs
+        flips = []
+        for s in stored[-18:]:
+            for at in {1, len(s) // 2, len(s) - 1}:
+                flips.append(s[:at] + [s[at] ^ 65536] + s[at + 1:])
+        _check(f, o, stored + flips, f"17-bit merge {step}")
+    assert f.info()["label_bits"] == 17
+    f.merge(*_dev([1], [[1, 2, 200000]]))
+    o.merge(np.ones(1, np.int32), *pins._csr([[1, 2, 200000]]))
+    assert f.info()["label_bits"] == 32
+    _check(f, o, stored + [[1, 2, 200000, 4], [1, 2, 200000 - 131072]], "after a wide token")
+    f.close()
+    o.close()
+
+
+@pytest.mark.parametrize("n", [1, 5, 64, 65, 300])
+def test_touches_then_evictions(n):
+    """Touches of n queries (empty, past the tree, ending inside labels, with
+    bad offsets) at rising times; evictions then take paths in the oracle's
+    order, and other peers keep theirs."""
+    import oracle
+    import torch
+    from paper_2606_17059_amd import Forest
+    rng = np.random.default_rng(n)
+    P, L = 70, 66
+    f, o = Forest(P), oracle.Oracle(P)
+    f.set_local_peer(L)
+    o.set_local(L)
+    base = _seqs(rng, 3, 60, 1, 12)
+    peers = np.where(np.arange(60) % 3 == 0, L, rng.integers(0, P, 60)).astype(np.int32)
+    f.merge(*_dev(peers, base))
+    o.merge(peers, *pins._csr(base))
+    for step in range(4):
+        f.set_time(step + 1)
+        o.set_time(step + 1)
+        qs = _seqs(rng, 3, n, 0, 6, known=base)
+        t, off = pins._csr(qs)
+        dt, do = torch.from_numpy(t).to(device()), torch.from_numpy(off).to(device())
+        if step == 1:
+            # the last query's end lies past the batch: ignored, and not counted as skipped
+            do[-1] += 1000
+            qs = qs[:-1]
+        announce(f"touch n={n} step={step}")
+        f.touch(dt, do)
+        if qs:
+            o.touch(*pins._csr(qs))
+        f.check()
+        k = int(rng.integers(1, 9))
+        assert f.evict_lru(k) == o.evict(k), (n, step)
+        et, eo = f.export_snapshot(L)
+        got = sorted(map(tuple, pins.csr_to_list(et.cpu().numpy(), eo.cpu().numpy())))
+        assert got == sorted(map(tuple, pins.csr_to_list(*o.export(L)))), (n, step)
+        _check(f, o, base + qs, f"touch n={n} step={step}")
+    f.close()
+    o.close()
