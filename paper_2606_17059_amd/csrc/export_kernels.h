@@ -24,6 +24,7 @@
 
 #include "forest_layout.h"
 #include "merge_kernels.h"
+#include "tree_walk.h"
 
 namespace pr {
 
@@ -101,24 +102,30 @@ __global__ void export_lengths_kernel(const int32_t *__restrict__ leaves, int32_
     if (i < n) len1[i + 1] = depth[leaves[i]];
 }
 
-// One wave per leaf: climb to the root, writing each label at its depth.
+// One wave per leaf (grid-stride): climb to the root, writing each label at
+// its depth.  walk (not nullptr): the leaf count is the one-launch walk's, none
+// if it did not finish or the buffers are too small.
 __global__ __launch_bounds__(64 * kExportWavesPerBlock) void export_write_kernel(
-    DevForest F, const int32_t *__restrict__ leaves, int32_t n, const int64_t *__restrict__ depth,
-    const int32_t *__restrict__ parent, const int64_t *__restrict__ offsets, int32_t *__restrict__ out) {
+    DevForest F, const int32_t *__restrict__ leaves, int32_t n, const WalkStatus *__restrict__ walk,
+    const int64_t *__restrict__ depth, const int32_t *__restrict__ parent, const int64_t *__restrict__ offsets,
+    int32_t *__restrict__ out) {
     const int lane = (int)(threadIdx.x & 63);
-    const int64_t i = (int64_t)blockIdx.x * kExportWavesPerBlock + (threadIdx.x >> 6);
-    if (i >= n) return;
-    const int64_t base = offsets[i];
-    int32_t c = leaves[i];
-    // depth falls by at least one token per step, so the climb ends at the root
-    while (c != 0) {
-        const Node r = F.nodes[c];
-        const int64_t d = depth[c];
-        if (r.lab_len <= 0 || d < r.lab_len) break;  // not a well-formed path: stop
-        const int64_t start = base + d - r.lab_len;
-        const int32_t *lab = F.pool + r.lab_off;
-        for (int32_t k = lane; k < r.lab_len; k += 64) out[start + k] = lab[k];
-        c = parent[c];
+    const int64_t waves = (int64_t)gridDim.x * kExportWavesPerBlock;
+    if (walk) n = walk->done && walk->fits ? (int32_t)walk->leaves : 0;
+    for (int64_t i = (int64_t)blockIdx.x * kExportWavesPerBlock + uniform((int32_t)(threadIdx.x >> 6)); i < n;
+         i += waves) {
+        const int64_t base = offsets[i];
+        int32_t c = leaves[i];
+        // depth falls by at least one token per step, so the climb ends at the root
+        while (c != 0) {
+            const Node r = F.nodes[c];
+            const int64_t d = depth[c];
+            if (r.lab_len <= 0 || d < r.lab_len) break;  // not a well-formed path: stop
+            const int64_t start = base + d - r.lab_len;
+            const int32_t *lab = F.pool + r.lab_off;
+            for (int32_t k = lane; k < r.lab_len; k += 64) out[start + k] = lab[k];
+            c = parent[c];
+        }
     }
 }
 

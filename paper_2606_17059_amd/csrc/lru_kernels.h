@@ -17,8 +17,7 @@
 //      where it runs out, tokens deeper than a depth D go entirely and at depth
 //      D the lexicographically smallest paths go, as many as remain;
 //   3. nodes evicted entirely lose the local peer's bit; a node cut inside its
-//      label is first split there (by inserting the kept path through the
-//      merge kernels, without stamping times) and the lower part loses the bit.
+//      label is split there and the lower part loses the bit.
 #ifndef PR_LRU_KERNELS_H
 #define PR_LRU_KERNELS_H
 
@@ -61,7 +60,7 @@ struct EvictPlan {
     int64_t depth;  // cut depth D inside the class
     int64_t r_at;   // tokens to evict at depth D (lexicographically smallest paths)
     int32_t maxd;   // deepest token of the class
-    int32_t bad;    // a split did not leave the expected structure
+    int32_t pad;
 };
 
 // Time and id of every node the walk visited (sorted by time next).
@@ -208,26 +207,30 @@ __device__ __forceinline__ bool lru_path_before(const int32_t *__restrict__ ntok
     return ntok[u] < ntok[v];
 }
 
-// rank_of[v] = number of level nodes whose path comes before v's.
-__global__ void lru_rank_kernel(DevForest F, const int32_t *__restrict__ level, int32_t n_level,
-                                const int32_t *__restrict__ parent, const int64_t *__restrict__ depth,
-                                int32_t *__restrict__ rank_of) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// rank_of[v] = number of level nodes whose path comes before v's (a wave per
+// level node, its lanes over the others).
+__global__ __launch_bounds__(256) void lru_rank_kernel(DevForest F, const int32_t *__restrict__ level,
+                                                       int32_t n_level, const int32_t *__restrict__ parent,
+                                                       const int64_t *__restrict__ depth,
+                                                       int32_t *__restrict__ rank_of) {
+    const int lane = (int)(threadIdx.x & 63);
+    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (i >= n_level) return;
     const int32_t v = level[i];
     int32_t r = 0;
-    for (int32_t j = 0; j < n_level; j++)
+    for (int32_t j = lane; j < n_level; j += 64)
         if (j != i && lru_path_before(F.ntok, parent, depth, level[j], v)) r++;
-    rank_of[v] = r;
+    for (int off = 32; off >= 1; off >>= 1) r += __shfl_xor(r, off);
+    if (lane == 0) rank_of[v] = r;
 }
 
 // Class nodes: keep the tokens up to keep_end.  Nodes evicted entirely lose
-// the local peer's bit; a node cut inside its label is listed with its kept
-// path length for the split.
+// the local peer's bit; a node cut inside its label is listed with the
+// label tokens it keeps.
 __global__ void lru_apply_kernel(DevForest F, const int32_t *__restrict__ vals, int64_t a, int64_t b,
                                  const int64_t *__restrict__ depth, const int32_t *__restrict__ rank_of,
                                  const EvictPlan *plan, int32_t *__restrict__ cut_node,
-                                 int64_t *__restrict__ cut_len1, int32_t *__restrict__ n_cut) {
+                                 int32_t *__restrict__ cut_len, int32_t *__restrict__ n_cut) {
     const int64_t i = a + (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= b) return;
     const int32_t v = vals[i];
@@ -241,57 +244,38 @@ __global__ void lru_apply_kernel(DevForest F, const int32_t *__restrict__ vals, 
     const int32_t k = lru_wave_slot(n_cut, keep >= s && keep < e);
     if (k >= 0) {
         cut_node[k] = v;
-        cut_len1[k + 1] = keep;
+        cut_len[k] = (int32_t)(keep - s + 1);
     }
 }
 
-// One wave per cut node: write the root path up to its kept length.
-__global__ __launch_bounds__(256) void lru_cut_paths_kernel(DevForest F, const int32_t *__restrict__ cut_node,
-                                                            int32_t n_cut, const int64_t *__restrict__ offs,
-                                                            const int32_t *__restrict__ parent,
-                                                            const int64_t *__restrict__ depth,
-                                                            int32_t *__restrict__ out) {
-    const int lane = (int)(threadIdx.x & 63);
-    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (i >= n_cut) return;
-    const int64_t base = offs[i], keep = offs[i + 1] - offs[i];
-    int32_t c = cut_node[i];
-    {
-        const Node r = F.nodes[c];
-        const int64_t s = depth[c] - r.lab_len;  // tokens above the node
-        for (int64_t k = lane; k < keep - s; k += 64) out[base + s + k] = F.pool[r.lab_off + k];
-        c = parent[c];
-    }
-    while (c != 0) {
-        const Node r = F.nodes[c];
-        const int64_t d = depth[c];
-        if (r.lab_len <= 0 || d < r.lab_len) break;
-        for (int32_t k = lane; k < r.lab_len; k += 64) out[base + d - r.lab_len + k] = F.pool[r.lab_off + k];
-        c = parent[c];
-    }
+// Cut node v's label after l tokens: the lower part becomes record pos, its
+// only child, which peer p does not hold.
+__device__ __forceinline__ void lru_cut(const DevForest &F, int32_t v, int32_t l, int32_t pos, int32_t p) {
+    const Node old = F.nodes[v];
+    Node lower = old;
+    lower.lab_off = old.lab_off + (uint32_t)l;
+    lower.lab_len = old.lab_len - l;
+    lower.tok = F.pool[lower.lab_off];
+    lower.aux = 0;
+    F.ntok[pos] = lower.tok;
+    F.ltime[pos] = F.ltime[v];
+    for (int w = 0; w < F.W - 1; w++) F.mext[(int64_t)pos * (F.W - 1) + w] = F.mext[(int64_t)v * (F.W - 1) + w];
+    F.nodes[pos] = lower;
+    lru_clear(F, pos, p);
+    Node upper = old;
+    upper.lab_len = l;
+    upper.ct_beg = pos;
+    upper.ct_cnt = 1;
+    upper.aux = 0;
+    F.nodes[v] = upper;
 }
 
-// After the split, each cut node holds the kept part and has the rest as its
-// only child: the local peer leaves that child.
-__global__ void lru_clear_lower_kernel(DevForest F, const int32_t *__restrict__ cut_node, int32_t n_cut,
-                                       const int64_t *__restrict__ offs, const int64_t *__restrict__ depth,
-                                       const int64_t *__restrict__ old_len, EvictPlan *plan) {
+// One thread per cut: its lower part goes to record base + i.
+__global__ void lru_cut_kernel(DevForest F, const int32_t *__restrict__ cut_node, const int32_t *__restrict__ cut_len,
+                               int32_t n_cut, int64_t base, MergeCounters *ctr) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_cut) return;
-    const int32_t v = cut_node[i];
-    const Node r = F.nodes[v];
-    const int64_t kept = (offs[i + 1] - offs[i]) - (depth[v] - old_len[i]);
-    if (r.ct_cnt != 1 || r.lab_len != kept) {
-        atomicAdd(&plan->bad, 1);
-        return;
-    }
-    lru_clear(F, r.ct_beg, F.local);
-}
-
-__global__ void lru_old_len_kernel(DevForest F, const int32_t *__restrict__ cut_node, int32_t n_cut,
-                                   int64_t *__restrict__ old_len) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n_cut) old_len[i] = F.nodes[cut_node[i]].lab_len;
+    if (i == 0) ctr->n_nodes = (unsigned long long)(base + n_cut);
+    if (i < n_cut) lru_cut(F, cut_node[i], cut_len[i], (int32_t)(base + i), F.local);
 }
 
 }  // namespace pr

@@ -26,6 +26,7 @@
 #include "prefix_router.h"
 #include "route_launch.h"
 #include "small_merge.h"
+#include "tree_walk.h"
 
 using pr::Node;
 
@@ -124,6 +125,7 @@ struct pr_forest {
     void *h_stage = nullptr;      // pinned host staging for the small readbacks between device rounds
     uint32_t *d_stage = nullptr;  // h_stage as the device addresses it (nullptr: readbacks by DMA)
     unsigned long long *d_skipped = nullptr;  // inputs skipped by device calls
+    pr::WalkStatus *d_walk = nullptr;         // what the last one-launch tree walk found
     MergeScratch ms;
     ExportScratch xs;
     RouteScratch rs;
@@ -191,6 +193,8 @@ class DeviceScope {
 };
 
 constexpr size_t kStageBytes = 256;  // pinned readback staging per forest
+constexpr size_t kEvictStage = 128;  // where in it an eviction's status goes (a walk's is at its start)
+constexpr unsigned kExportBlocks = 2048;  // workgroups of an export's write when only the device knows its size
 constexpr int kDeviceRounds = 2;     // merge rounds queued before the first readback
 
 unsigned grid_threads(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
@@ -543,7 +547,11 @@ pr_status commit(pr_forest *f) {
     pr_status s = ensure_host_image(f);
     if (s) return s;
     if (!f->d_skipped) {
-        if (!dalloc(f, &f->d_skipped, 1) || !dalloc(f, &f->d_ctr, 1)) return fail(PR_ENOMEM, "hipMalloc failed");
+        if (!dalloc(f, &f->d_walk, 1) || !dalloc(f, &f->d_ctr, 1) || !dalloc(f, &f->d_skipped, 1)) {
+            dfree(f, &f->d_walk, 1);
+            dfree(f, &f->d_ctr, 1);
+            return fail(PR_ENOMEM, "hipMalloc failed");
+        }
         if (!f->h_stage && hipHostMalloc(&f->h_stage, kStageBytes, hipHostMallocDefault) != hipSuccess) {
             f->h_stage = nullptr;
             return fail(PR_ENOMEM, "hipHostMalloc failed for the readback staging");
@@ -1208,6 +1216,19 @@ pr_status walk_peer(pr_forest *f, int32_t peer, bool want_all, hipStream_t s, in
     return PR_OK;
 }
 
+// One-launch walk of peer's tree (tree_walk.h) with the outputs O asks for,
+// enqueued; its status goes to f->d_walk and to the start of the pinned buffer.
+bool enqueue_walk(pr_forest *f, int32_t peer, const pr::WalkOut &O, hipStream_t s) {
+    hipLaunchKernelGGL(pr::tree_walk_kernel, dim3(1), dim3(pr::kWalkThreads), 0, s, dev_view(f), f->dev.n_nodes, peer,
+                       O, f->d_walk, reinterpret_cast<pr::WalkStatus *>(f->d_stage));
+    return hipGetLastError() == hipSuccess;
+}
+
+pr_status export_too_small(int64_t seqs, int64_t tokens) {
+    return fail(PR_EINVAL, "export buffers too small: need " + std::to_string(seqs + 1) + " offsets and " +
+                               std::to_string(tokens) + " tokens");
+}
+
 // sendTrie for one peer (see export_kernels.h).  Host-synchronous.  Writes the
 // sizes always; the data only if both buffers are given and large enough.
 pr_status export_impl(pr_forest *f, int32_t peer, int32_t *tokens, int64_t tokens_cap, int64_t *offsets,
@@ -1218,6 +1239,27 @@ pr_status export_impl(pr_forest *f, int32_t peer, int32_t *tokens, int64_t token
     ExportScratch &X = f->xs;
     const pr::DevForest F = dev_view(f);
     const int wb = 64 * pr::kExportWavesPerBlock;
+    if (f->d_stage) {
+        // a tree that one workgroup walks: sizes, or sizes, order and offsets, in
+        // one launch, the tokens in a second, and one wait
+        const bool fill = offsets != nullptr;
+        const pr::WalkOut O{X.depth, X.parent, nullptr, X.leaves, X.sorted, offsets, seqs_cap,
+                            tokens ? tokens_cap : 0};
+        if (!enqueue_walk(f, peer, O, s)) return fail(PR_EDEVICE, "tree walk launch failed");
+        if (fill)
+            hipLaunchKernelGGL(pr::export_write_kernel, dim3(kExportBlocks), dim3(wb), 0, s, F, X.sorted, 0, f->d_walk,
+                               X.depth, X.parent, offsets, tokens);
+        if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
+            return fail(PR_EDEVICE, "export failed");
+        pr::WalkStatus st;
+        std::memcpy(&st, f->h_stage, sizeof(st));
+        if (st.done) {
+            *num_seqs = st.leaves;
+            *num_tokens = (int64_t)st.leaf_tokens;
+            if ((!tokens && !offsets) || (fill && st.fits)) return ok();
+            return export_too_small(*num_seqs, *num_tokens);
+        }
+    }
     int32_t counts[3] = {0, 0, 0};
     r = walk_peer(f, peer, false, s, counts);
     if (r) return r;
@@ -1258,8 +1300,7 @@ pr_status export_impl(pr_forest *f, int32_t peer, int32_t *tokens, int64_t token
     *num_tokens = total;
     if (!tokens && !offsets) return ok();
     if (!offsets || (total > 0 && !tokens) || tokens_cap < total || seqs_cap < (int64_t)n_leaves + 1)
-        return fail(PR_EINVAL, "export buffers too small: need " + std::to_string(n_leaves + 1) + " offsets and " +
-                                   std::to_string(total) + " tokens");
+        return export_too_small(n_leaves, total);
     const int64_t zero = 0;
     if (hipMemcpyAsync(offsets, &zero, sizeof(zero), hipMemcpyHostToDevice, s) != hipSuccess)
         return fail(PR_EDEVICE, "export copy failed");
@@ -1269,7 +1310,8 @@ pr_status export_impl(pr_forest *f, int32_t peer, int32_t *tokens, int64_t token
             return fail(PR_EDEVICE, "export copy failed");
         hipLaunchKernelGGL(pr::export_write_kernel,
                            dim3((unsigned)((n_leaves + pr::kExportWavesPerBlock - 1) / pr::kExportWavesPerBlock)),
-                           dim3(wb), 0, s, F, X.sorted, n_leaves, X.depth, X.parent, offsets, tokens);
+                           dim3(wb), 0, s, F, X.sorted, n_leaves, (const pr::WalkStatus *)nullptr, X.depth, X.parent,
+                           offsets, tokens);
         if (hipGetLastError() != hipSuccess) return fail(PR_EDEVICE, "export launch failed");
     }
     if (hipStreamSynchronize(s) != hipSuccess) return fail(PR_EDEVICE, "export failed");
@@ -1331,6 +1373,7 @@ void pr_forest_destroy(pr_forest *f) {
         free_scratch(f);
         dfree(f, &f->d_skipped, 1);
         dfree(f, &f->d_ctr, 1);
+        dfree(f, &f->d_walk, 1);
         if (f->h_stage) (void)hipHostFree(f->h_stage);
         free_route_buffers(f);
         if (f->rs.done) (void)hipEventDestroy(f->rs.done);
@@ -1613,6 +1656,16 @@ pr_status pr_tree_tokens(pr_forest *f, int32_t peer, int64_t *tokens, void *hip_
     pr_status r = commit(f);
     if (r) return r;
     hipStream_t s = (hipStream_t)hip_stream;
+    if (f->d_stage) {
+        if (!enqueue_walk(f, peer, pr::WalkOut{}, s) || hipStreamSynchronize(s) != hipSuccess)
+            return fail(PR_EDEVICE, "tree walk failed");
+        pr::WalkStatus st;
+        std::memcpy(&st, f->h_stage, sizeof(st));
+        if (st.done) {
+            *tokens = (int64_t)st.tokens;
+            return ok();
+        }
+    }
     int32_t counts[3];
     if ((r = walk_peer(f, peer, true, s, counts))) return r;
     if (counts[2] == 0) return ok();
@@ -1699,11 +1752,38 @@ pr_status pr_evict_lru(pr_forest *f, int64_t max_tokens, int64_t *evicted, void 
     if (r) return r;
     if (!f->dev.ltime && (r = init_local_times(f, f->local_load_time))) return r;
     hipStream_t s = (hipStream_t)hip_stream;
+    ExportScratch &W = f->xs;
+    if (f->d_stage) {
+        // a tree of at most pr::kEvictNodes nodes: walk and eviction in two
+        // launches and one wait
+        if ((r = ensure_export_scratch(f, f->dev.n_nodes))) return r;
+        pr::WalkOut O{};
+        O.depth = W.depth;
+        O.parent = W.parent;
+        O.all = W.all;
+        pr::EvictStatus *out = reinterpret_cast<pr::EvictStatus *>(f->d_stage + kEvictStage / 4);
+        if (!enqueue_walk(f, f->local, O, s)) return fail(PR_EDEVICE, "tree walk launch failed");
+        hipLaunchKernelGGL(pr::evict_kernel, dim3(1), dim3(pr::kWalkThreads), 0, s, dev_view(f), f->d_walk, W.all,
+                           W.depth, W.parent, max_tokens, f->d_ctr, out);
+        if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
+            f->broken = true;
+            return fail(PR_EDEVICE, "eviction failed");
+        }
+        pr::EvictStatus st;
+        std::memcpy(&st, static_cast<const char *>(f->h_stage) + kEvictStage, sizeof(st));
+        if (st.done) {
+            f->dev.n_nodes = (int64_t)st.n_nodes;
+            if (st.evicted == 0) return ok();
+            f->merged = true;
+            f->sets[(size_t)f->local] = pr::PeerSeqs();  // the host copy no longer describes the local peer
+            *evicted = (int64_t)st.evicted;
+            return ok();
+        }
+    }
     int32_t counts[3];
     if ((r = walk_peer(f, f->local, true, s, counts))) return r;
     const int64_t V = counts[2];
     if (V == 0) return ok();
-    ExportScratch &W = f->xs;
     CallScratch X;
     unsigned long long *keys = nullptr, *keys_s = nullptr;
     int32_t *vals = nullptr, *vals_s = nullptr;
@@ -1758,15 +1838,14 @@ pr_status pr_evict_lru(pr_forest *f, int64_t max_tokens, int64_t *evicted, void 
         const int32_t maxd = plan.maxd;
         long long *hist = nullptr, *cnt = nullptr, *rev = nullptr, *S = nullptr;
         int32_t *level = nullptr, *n_level = nullptr, *rank_of = nullptr, *cut_node = nullptr, *n_cut = nullptr;
-        int64_t *cut_len1 = nullptr;
+        int32_t *cut_len = nullptr;
         if (!X.get(&hist, maxd + 2) || !X.get(&cnt, maxd + 2) || !X.get(&rev, maxd) || !X.get(&S, maxd) ||
             !X.get(&level, nc) || !X.get(&n_level, 1) || !X.get(&rank_of, f->dev.n_nodes) ||
-            !X.get(&cut_node, nc) || !X.get(&n_cut, 1) || !X.get(&cut_len1, nc + 1))
+            !X.get(&cut_node, nc) || !X.get(&n_cut, 1) || !X.get(&cut_len, nc))
             return fail_nomem("hipMalloc failed for the eviction");
         if (hipMemsetAsync(hist, 0, (maxd + 2) * sizeof(long long), s) != hipSuccess ||
             hipMemsetAsync(n_level, 0, sizeof(int32_t), s) != hipSuccess ||
-            hipMemsetAsync(n_cut, 0, sizeof(int32_t), s) != hipSuccess ||
-            hipMemsetAsync(cut_len1, 0, (nc + 1) * sizeof(int64_t), s) != hipSuccess)
+            hipMemsetAsync(n_cut, 0, sizeof(int32_t), s) != hipSuccess)
             return fail_dev("eviction memset failed");
         hipLaunchKernelGGL(pr::lru_hist_kernel, dim3(grid_threads(nc, 256)), dim3(256), 0, s, F, vals_s, a, b,
                            W.depth, hist);
@@ -1792,49 +1871,23 @@ pr_status pr_evict_lru(pr_forest *f, int64_t max_tokens, int64_t *evicted, void 
         if (!read_small(f, &h_level, n_level, sizeof(h_level), s))
             return fail_dev("eviction readback failed");
         if (h_level > nc) return fail_dev("eviction level list overflow");
-        hipLaunchKernelGGL(pr::lru_rank_kernel, dim3(grid_threads(h_level, 256)), dim3(256), 0, s, F, level, h_level,
+        hipLaunchKernelGGL(pr::lru_rank_kernel, dim3(grid_threads(h_level, 4)), dim3(256), 0, s, F, level, h_level,
                            W.parent, W.depth, rank_of);
         hipLaunchKernelGGL(pr::lru_apply_kernel, dim3(grid_threads(nc, 256)), dim3(256), 0, s, F, vals_s, a, b,
-                           W.depth, rank_of, d_plan, cut_node, cut_len1, n_cut);
+                           W.depth, rank_of, d_plan, cut_node, cut_len, n_cut);
         int32_t h_cut = 0;
         if (hipGetLastError() != hipSuccess ||
             !read_small(f, &h_cut, n_cut, sizeof(h_cut), s))
             return fail_dev("eviction failed");
         if (h_cut > 0) {
-            int64_t *offs = nullptr, *old_len = nullptr;
-            int32_t *ctok = nullptr;
-            if (!X.get(&offs, h_cut + 1) || !X.get(&old_len, h_cut))
-                return fail_nomem("hipMalloc failed for the eviction");
-            size_t n5 = 0;
-            if (rocprim::inclusive_scan(nullptr, n5, cut_len1, offs, (size_t)h_cut + 1, rocprim::plus<int64_t>(),
-                                        s) != hipSuccess)
-                return fail_dev("eviction scan sizing failed");
-            char *tmp3 = nullptr;
-            if (!X.get(&tmp3, (int64_t)n5)) return fail_nomem("hipMalloc failed for the eviction");
-            if (rocprim::inclusive_scan(tmp3, n5, cut_len1, offs, (size_t)h_cut + 1, rocprim::plus<int64_t>(), s) !=
-                hipSuccess)
-                return fail_dev("eviction scan failed");
-            int64_t total_cut = 0;
-            if (!read_small(f, &total_cut, offs + h_cut, sizeof(total_cut), s))
-                return fail_dev("eviction readback failed");
-            if (!X.get(&ctok, total_cut)) return fail_nomem("hipMalloc failed for the eviction");
-            hipLaunchKernelGGL(pr::lru_cut_paths_kernel, dim3((unsigned)((h_cut + 3) / 4)), dim3(256), 0, s, F,
-                               cut_node, h_cut, offs, W.parent, W.depth, ctok);
-            hipLaunchKernelGGL(pr::lru_old_len_kernel, dim3(grid_threads(h_cut, 256)), dim3(256), 0, s, F, cut_node,
-                               h_cut, old_len);
-            if (hipGetLastError() != hipSuccess) return fail_dev("eviction launch failed");
-            // the kept paths are held already: inserting them only splits the cut nodes
-            pr::Batch cuts = batch_of(f, nullptr, f->local, ctok, total_cut, offs, h_cut);
-            cuts.stamp = 0;
-            if ((r = run_merge(f, cuts, s))) {
+            const int64_t base = f->dev.n_nodes;
+            if ((r = ensure_capacity(f, base + h_cut, f->dev.n_pool, s))) {
                 f->broken = true;
                 return r;
             }
-            hipLaunchKernelGGL(pr::lru_clear_lower_kernel, dim3(grid_threads(h_cut, 256)), dim3(256), 0, s,
-                               dev_view(f), cut_node, h_cut, offs, W.depth, old_len, d_plan);
-            if (!read_small(f, &plan, d_plan, sizeof(plan), s))
-                return fail_dev("eviction readback failed");
-            if (plan.bad) return fail_dev("eviction split left an unexpected structure; destroy the forest");
+            hipLaunchKernelGGL(pr::lru_cut_kernel, dim3(grid_threads(h_cut, 256)), dim3(256), 0, s, dev_view(f),
+                               cut_node, cut_len, h_cut, base, f->d_ctr);
+            f->dev.n_nodes = base + h_cut;
         }
     }
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return fail_dev("eviction failed");
