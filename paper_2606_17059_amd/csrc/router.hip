@@ -126,12 +126,14 @@ struct pr_forest {
     uint32_t *d_stage = nullptr;  // h_stage as the device addresses it (nullptr: readbacks by DMA)
     unsigned long long *d_skipped = nullptr;  // inputs skipped by device calls
     pr::WalkStatus *d_walk = nullptr;         // what the last one-launch tree walk found
+    pr::CompactState *d_compact = nullptr;    // a compaction's ranges and totals
+    DevImage spare;               // the arrays the last compaction replaced, for the next one (see retire_image)
     MergeScratch ms;
     ExportScratch xs;
     RouteScratch rs;
     long long stamp = 0;          // add-round counter (stamps of moved records)
-    int64_t round_nodes = 0;      // records the last merge added (spare capacity kept for the next)
-    int64_t round_pool = 0;       // pool tokens the last merge added (0: no merge yet)
+    int64_t round_nodes = 0;      // records recent merges added at most (spare capacity kept for the next)
+    int64_t round_pool = 0;       // pool tokens, likewise (0: no merge yet)
     int64_t refusals = 0;         // merge rounds repeated after running out of capacity
     int32_t local = -1;           // peer whose tree keeps access times (-1: none)
     int64_t now = 0;              // current time, set by the caller, never decreasing
@@ -195,22 +197,33 @@ class DeviceScope {
 constexpr size_t kStageBytes = 256;  // pinned readback staging per forest
 constexpr size_t kEvictStage = 128;  // where in it an eviction's status goes (a walk's is at its start)
 constexpr unsigned kExportBlocks = 2048;  // workgroups of an export's write when only the device knows its size
+constexpr int kCompactLevels = 6;    // levels a compaction enqueues before it reads anything back
 constexpr int kDeviceRounds = 2;     // merge rounds queued before the first readback
 
 unsigned grid_threads(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 unsigned grid_waves(int64_t n) { return (unsigned)((n + pr::kMergeWavesPerBlock - 1) / pr::kMergeWavesPerBlock); }
 unsigned grid_split(int64_t n) { return (unsigned)((n + pr::kSplitWaves - 1) / pr::kSplitWaves); }
 
-template <typename T>
-bool dalloc(pr_forest *f, T **p, int64_t count) {
-    const size_t n = (size_t)std::max<int64_t>(count, 1) * sizeof(T);
-    if (hipMalloc((void **)p, n) != hipSuccess) {
+bool drop_spare(pr_forest *f);
+
+// Device memory for the forest; when there is none left, what the forest keeps
+// for its next compaction is given back first.
+bool dev_malloc(pr_forest *f, void **p, size_t n) {
+    if (hipMalloc(p, n) != hipSuccess) {
         (void)hipGetLastError();
-        *p = nullptr;
-        return false;
+        if (!drop_spare(f) || hipMalloc(p, n) != hipSuccess) {
+            (void)hipGetLastError();
+            *p = nullptr;
+            return false;
+        }
     }
     f->device_bytes += (int64_t)n;
     return true;
+}
+
+template <typename T>
+bool dalloc(pr_forest *f, T **p, int64_t count) {
+    return dev_malloc(f, (void **)p, (size_t)std::max<int64_t>(count, 1) * sizeof(T));
 }
 
 template <typename T>
@@ -240,11 +253,7 @@ bool alloc_node_arrays(pr_forest *f, DevImage &d, int64_t cap) {
     const size_t o_moved = o_mext + align256(std::max<size_t>(c * (size_t)(f->W - 1), 1) * sizeof(uint64_t));
     const size_t bytes = o_moved + c * sizeof(long long);
     void *b = nullptr;
-    if (hipMalloc(&b, bytes) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    f->device_bytes += (int64_t)bytes;
+    if (!dev_malloc(f, &b, bytes)) return false;
     char *p = static_cast<char *>(b);
     d.node_block = b;
     d.node_block_bytes = bytes;
@@ -270,17 +279,113 @@ void free_node_arrays(pr_forest *f, DevImage &d) {
     d.moved = nullptr;
 }
 
-void free_image(pr_forest *f) {
-    DevImage &d = f->dev;
+void free_arrays(pr_forest *f, DevImage &d) {
     free_node_arrays(f, d);
     dfree(f, &d.pool, d.cap_pool);
     dfree(f, &d.ltime, d.cap_nodes);
     dfree(f, &d.pool16, d.cap_pool16);
     dfree(f, &d.hib, hib_words(d.cap_pool16));
     d = DevImage();
+}
+
+void free_image(pr_forest *f) {
+    free_arrays(f, f->dev);
+    free_arrays(f, f->spare);
     f->has_dev = false;
     f->narrow = false;
     f->hi17 = false;
+}
+
+bool drop_spare(pr_forest *f) {
+    const bool any = f->spare.node_block || f->spare.pool;
+    free_arrays(f, f->spare);
+    return any;
+}
+
+int64_t image_bytes(const DevImage &d) {
+    return (int64_t)d.node_block_bytes + d.cap_pool * 4 + (d.ltime ? d.cap_nodes * 8 : 0) +
+           (d.pool16 ? d.cap_pool16 * 2 + hib_words(d.cap_pool16) * 4 : 0);
+}
+
+// The image a compaction replaced.  Its arrays are kept for the next
+// compaction, which then allocates nothing (hipMalloc and hipFree of arrays of
+// tens of MB take 0.3 to 0.6 ms each, more than the rebuild itself), as long as
+// they are small beside the GPU's memory; at most one such set per forest.
+constexpr int64_t kSpareBytes = 1ll << 30;
+void retire_image(pr_forest *f) {
+    free_arrays(f, f->spare);
+    if (image_bytes(f->dev) <= kSpareBytes)
+        f->spare = f->dev;
+    else
+        free_arrays(f, f->dev);
+    f->dev = DevImage();
+}
+
+// A capacity of at least n with 1/16 to 1/8 slack, so that needs that vary a
+// little from one compaction to the next fit the same arrays.
+int64_t slack_cap(int64_t n) {
+    int64_t g = 1;
+    while (g * 16 <= n) g *= 2;
+    return (n + g - 1) / g * g;
+}
+
+// Node arrays (and access times, if wanted) for at least need records in nw:
+// the spare's, unless they are too small or far too large.
+bool new_node_arrays(pr_forest *f, DevImage &nw, int64_t need, bool times) {
+    DevImage &sp = f->spare;
+    if (sp.node_block && sp.cap_nodes >= need && sp.cap_nodes <= 4 * need + (1 << 16)) {
+        nw.node_block = sp.node_block;
+        nw.node_block_bytes = sp.node_block_bytes;
+        nw.nodes = sp.nodes;
+        nw.ntok = sp.ntok;
+        nw.nsep = sp.nsep;
+        nw.mext = sp.mext;
+        nw.moved = sp.moved;
+        nw.cap_nodes = sp.cap_nodes;
+        nw.ltime = sp.ltime;
+        sp.node_block = nullptr;
+        sp.node_block_bytes = 0;
+        sp.ltime = nullptr;
+    } else {
+        free_node_arrays(f, sp);
+        dfree(f, &sp.ltime, sp.cap_nodes);
+        if (!alloc_node_arrays(f, nw, slack_cap(need))) return false;
+    }
+    if (times) return nw.ltime || dalloc(f, &nw.ltime, nw.cap_nodes);
+    dfree(f, &nw.ltime, nw.cap_nodes);
+    return true;
+}
+
+// The label pool (and its narrow copy, if wanted and there is memory for it)
+// for at least need tokens in nw, in the same way.
+bool new_pool(pr_forest *f, DevImage &nw, int64_t need, bool narrow) {
+    DevImage &sp = f->spare;
+    if (sp.pool && sp.cap_pool >= need && sp.cap_pool <= 4 * need + (1 << 18)) {
+        nw.pool = sp.pool;
+        nw.cap_pool = sp.cap_pool;
+        sp.pool = nullptr;
+        sp.cap_pool = 0;
+        if (narrow && sp.pool16 && sp.hib && sp.cap_pool16 == nw.cap_pool) {
+            nw.pool16 = sp.pool16;
+            nw.hib = sp.hib;
+            nw.cap_pool16 = sp.cap_pool16;
+            sp.pool16 = nullptr;
+            sp.hib = nullptr;
+            sp.cap_pool16 = 0;
+        }
+    } else {
+        free_arrays(f, sp);
+        nw.cap_pool = std::min<int64_t>(slack_cap(need), (int64_t)UINT32_MAX);
+        if (!dalloc(f, &nw.pool, nw.cap_pool)) return false;
+    }
+    if (narrow && !nw.pool16) {
+        nw.cap_pool16 = nw.cap_pool;
+        if (!dalloc(f, &nw.pool16, nw.cap_pool) || !dalloc(f, &nw.hib, hib_words(nw.cap_pool))) {
+            dfree(f, &nw.pool16, nw.cap_pool);
+            nw.cap_pool16 = 0;
+        }
+    }
+    return true;
 }
 
 void free_export_scratch(pr_forest *f) {
@@ -414,8 +519,9 @@ pr_status ensure_capacity(pr_forest *f, int64_t need_nodes, int64_t need_pool, h
         f->layout_epoch++;
     }
     if (need_pool > d.cap_pool) {
-        const int64_t cap = std::min<int64_t>(std::max<int64_t>(need_pool, d.cap_pool + d.cap_pool / 2),
-                                              (int64_t)UINT32_MAX);
+        // like the node arrays, a pool that is still small grows fourfold
+        const int64_t more = d.cap_pool < (16 << 20) ? 4 * d.cap_pool : d.cap_pool + d.cap_pool / 2;
+        const int64_t cap = std::min<int64_t>(std::max<int64_t>(need_pool, more), (int64_t)UINT32_MAX);
         int32_t *np = nullptr;
         if (!dalloc(f, &np, cap)) return fail(PR_ENOMEM, "hipMalloc failed while growing the label pool");
         // the narrow copy grows with the pool, under the same wait (without
@@ -547,8 +653,10 @@ pr_status commit(pr_forest *f) {
     pr_status s = ensure_host_image(f);
     if (s) return s;
     if (!f->d_skipped) {
-        if (!dalloc(f, &f->d_walk, 1) || !dalloc(f, &f->d_ctr, 1) || !dalloc(f, &f->d_skipped, 1)) {
+        if (!dalloc(f, &f->d_walk, 1) || !dalloc(f, &f->d_compact, 1) || !dalloc(f, &f->d_ctr, 1) ||
+            !dalloc(f, &f->d_skipped, 1)) {
             dfree(f, &f->d_walk, 1);
+            dfree(f, &f->d_compact, 1);
             dfree(f, &f->d_ctr, 1);
             return fail(PR_ENOMEM, "hipMalloc failed");
         }
@@ -572,9 +680,12 @@ pr_status commit(pr_forest *f) {
     const int64_t n = (int64_t)h.nodes.size(), np = (int64_t)h.pool.size();
     // merges append records (rebuilt blocks move), so node capacity starts at
     // four times the image (a few merge batches before the first growth);
-    // labels grow only by new leaves
-    d.cap_pool = std::max<int64_t>(np + np / 4, 4096);
-    if (!alloc_node_arrays(f, d, std::max<int64_t>(4 * n, 1024)) || !dalloc(f, &d.pool, d.cap_pool)) {
+    // labels grow only by new leaves.  At least 1 MiB each: allocations up to
+    // there cost a microsecond, each growth of a forest that starts empty and
+    // takes its snapshots on the device some hundred
+    const int64_t least = 1 << 20, node_bytes = sizeof(Node) + 2 * sizeof(int32_t) + 8 * (int64_t)f->W;
+    d.cap_pool = std::max<int64_t>(np + np / 4, least / 4);
+    if (!alloc_node_arrays(f, d, std::max<int64_t>(4 * n, least / node_bytes)) || !dalloc(f, &d.pool, d.cap_pool)) {
         free_image(f);
         return fail(PR_ENOMEM, "hipMalloc failed for the forest image");
     }
@@ -829,6 +940,14 @@ __global__ void reset_call_kernel(pr::MergeCounters *c) {
     c->plan_fallback = 0;
 }
 
+// The counters of a forest that was just compacted.
+__global__ void compact_counters_kernel(pr::MergeCounters *c, const pr::CompactState *S) {
+    if (S->bad) return;
+    *c = pr::MergeCounters{};
+    c->n_nodes = (unsigned long long)S->hi;
+    c->n_pool = (unsigned long long)S->n_pool;
+}
+
 __global__ void add_skipped_kernel(unsigned long long *acc, const pr::MergeCounters *c) { *acc += c->skipped; }
 
 // Counters after refused allocations: the used sizes the host clipped to the
@@ -864,7 +983,8 @@ bool read_small(pr_forest *f, void *out, const void *dsrc, size_t bytes, hipStre
     return true;
 }
 
-static_assert(sizeof(pr::MergeCounters) <= kStageBytes && sizeof(pr::SmallStatus) <= kStageBytes && sizeof(pr::EvictPlan) <= kStageBytes,
+static_assert(sizeof(pr::MergeCounters) <= kStageBytes && sizeof(pr::SmallStatus) <= kStageBytes && sizeof(pr::EvictPlan) <= kStageBytes &&
+                  sizeof(pr::CompactState) <= kStageBytes,
               "readbacks fit the staging buffer");
 
 // Read the device counters and refresh the host mirror of the used sizes
@@ -1123,10 +1243,11 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
         if (hipGetLastError() != hipSuccess) return fail(PR_EDEVICE, "merge launch failed");
     }
     if (round == max_rounds) return fail(PR_EDEVICE, "merge did not converge");
-    // records and pool tokens this merge added: the spare capacity the next
-    // one keeps free
-    f->round_nodes = std::max<int64_t>(f->dev.n_nodes - nodes0, 0);
-    f->round_pool = std::max<int64_t>(f->dev.n_pool - pool0, 1);
+    // records and pool tokens the largest recent merge added: the spare
+    // capacity the next one keeps free (a snapshot load between two merge
+    // batches, which adds little, does not shrink it at once)
+    f->round_nodes = std::max<int64_t>(f->dev.n_nodes - nodes0, f->round_nodes - f->round_nodes / 8);
+    f->round_pool = std::max<int64_t>({f->dev.n_pool - pool0, f->round_pool - f->round_pool / 8, 1});
     hipLaunchKernelGGL(add_skipped_kernel, dim3(1), dim3(1), 0, s, f->d_skipped, f->d_ctr);
     if (hipGetLastError() != hipSuccess) return fail(PR_EDEVICE, "merge launch failed");
     if (!done) {  // the device-driven rounds read everything back with the narrow copy done
@@ -1374,6 +1495,7 @@ void pr_forest_destroy(pr_forest *f) {
         dfree(f, &f->d_skipped, 1);
         dfree(f, &f->d_ctr, 1);
         dfree(f, &f->d_walk, 1);
+        dfree(f, &f->d_compact, 1);
         if (f->h_stage) (void)hipHostFree(f->h_stage);
         free_route_buffers(f);
         if (f->rs.done) (void)hipEventDestroy(f->rs.done);
@@ -1499,28 +1621,18 @@ pr_status pr_forest_compact(pr_forest *f, int64_t *nodes_before, int64_t *nodes_
     hipStream_t s = (hipStream_t)hip_stream;
     DevImage &d = f->dev;
     const int64_t n_old = d.n_nodes;
-    const bool narrow_before = f->narrow;
     if (nodes_before) *nodes_before = n_old;
-    // the new image (capacity: the old node count plus spare; labels sized below)
+    if ((r = ensure_export_scratch(f, n_old))) return r;
+    ExportScratch &X = f->xs;
+    // the new image: the old node count, 1/8 spare and what recent merges added;
+    // labels sized once the live ones are known
     DevImage nw;
-    nw.cap_nodes = std::max<int64_t>(n_old + n_old / 8, 1024);
-    auto free_new = [&]() {
-        dfree(f, &nw.ltime, nw.cap_nodes);
-        dfree(f, &nw.pool, nw.cap_pool);
-        free_node_arrays(f, nw);
+    auto fail_new = [&](pr_status st, const char *m) {
+        free_arrays(f, nw);
+        return fail(st, m);
     };
-    if (!alloc_node_arrays(f, nw, nw.cap_nodes) || (d.ltime && !dalloc(f, &nw.ltime, nw.cap_nodes))) {
-        free_new();
-        return fail(PR_ENOMEM, "hipMalloc failed for the compacted forest");
-    }
-    CallScratch X;
-    int32_t *fo = nullptr, *fn = nullptr, *go = nullptr, *gn = nullptr;
-    int64_t *kept1 = nullptr, *start1 = nullptr;
-    if (!X.get(&fo, n_old) || !X.get(&fn, n_old) || !X.get(&go, n_old) || !X.get(&gn, n_old) ||
-        !X.get(&kept1, n_old + 1) || !X.get(&start1, n_old + 1)) {
-        free_new();
-        return fail(PR_ENOMEM, "hipMalloc failed for the compaction");
-    }
+    if (!new_node_arrays(f, nw, std::max<int64_t>(n_old + n_old / 8, 1024) + 2 * f->round_nodes, d.ltime != nullptr))
+        return fail_new(PR_ENOMEM, "hipMalloc failed for the compacted forest");
     const pr::DevForest O = dev_view(f);
     pr::DevForest N = O;
     N.nodes = nw.nodes;
@@ -1528,120 +1640,80 @@ pr_status pr_forest_compact(pr_forest *f, int64_t *nodes_before, int64_t *nodes_
     N.nsep = nw.nsep;
     N.mext = nw.mext;
     N.moved = nw.moved;
-    N.ltime = nw.ltime;
+    N.ltime = d.ltime ? nw.ltime : nullptr;
     N.pool = nullptr;
     N.cap_nodes = nw.cap_nodes;
-    auto fail_dev = [&](const char *m) {
-        free_new();
-        return fail(PR_EDEVICE, m);
-    };
-    hipLaunchKernelGGL(pr::compact_init_kernel, dim3(1), dim3(1), 0, s, O, N, fo, fn);
-    size_t need = 0;
-    if (rocprim::inclusive_scan(nullptr, need, kept1, start1, (size_t)n_old + 1, rocprim::plus<int64_t>(), s) !=
-        hipSuccess)
-        return fail_dev("compaction scan sizing failed");
-    char *tmp = nullptr;
-    if (!X.get(&tmp, (int64_t)need)) {
-        free_new();
-        return fail(PR_ENOMEM, "hipMalloc failed for the compaction");
+    const bool narrow = f->narrow && d.pool16 && d.hib;
+    auto pool_need = [&](int64_t n) { return std::max<int64_t>(n + n / 8, 4096) + 2 * f->round_pool; };
+    int32_t *old_of = X.front, *start = X.next;
+    int64_t *off = X.len1, *blk = X.offs;
+    pr::CompactState S;
+    // a small forest's labels are bounded by the old pool's, so that it takes
+    // one wait
+    const bool small = n_old <= pr::kCompactSmall;
+    const bool one_wait = small && d.n_pool <= (4 << 20);
+    if (small) {
+        hipLaunchKernelGGL(pr::compact_small_kernel, dim3(1), dim3(pr::kCompactThreads), 0, s, O, N, old_of, off,
+                           n_old, f->d_compact);
+    } else {
+        hipLaunchKernelGGL(pr::compact_init_kernel, dim3(1), dim3(1), 0, s, O, N, old_of, f->d_compact);
+        const unsigned g = (unsigned)std::min<int64_t>(2048, (n_old + pr::kCompactWaves - 1) / pr::kCompactWaves);
+        do {
+            for (int level = 0; level < kCompactLevels; level++) {
+                hipLaunchKernelGGL(pr::compact_count_kernel, dim3(g), dim3(pr::kCompactThreads), 0, s, O, old_of,
+                                   f->d_compact, start, blk);
+                hipLaunchKernelGGL(pr::compact_scan_kernel, dim3(1), dim3(pr::kCompactThreads), 0, s, f->d_compact,
+                                   blk, n_old);
+                hipLaunchKernelGGL(pr::compact_copy_kernel, dim3(g), dim3(pr::kCompactThreads), 0, s, O, N, old_of,
+                                   f->d_compact, start, blk);
+            }
+            hipLaunchKernelGGL(pr::compact_lab_kernel, dim3(g), dim3(pr::kCompactThreads), 0, s, N, f->d_compact, off,
+                               blk);
+            hipLaunchKernelGGL(pr::compact_lab_scan_kernel, dim3(1), dim3(pr::kCompactThreads), 0, s, f->d_compact,
+                               blk);
+            if (hipGetLastError() != hipSuccess || !read_small(f, &S, f->d_compact, sizeof(S), s))
+                return fail_new(PR_EDEVICE, "compaction failed");
+        } while (S.lo < S.hi && !S.bad);
     }
-    const int wb = 64 * pr::kCompactWavesPerBlock;
-    int64_t n_front = 1, first_new = 1;
-    while (n_front > 0) {
-        const unsigned g = (unsigned)((n_front + pr::kCompactWavesPerBlock - 1) / pr::kCompactWavesPerBlock);
-        if (hipMemsetAsync(kept1, 0, sizeof(int64_t), s) != hipSuccess) return fail_dev("compaction memset failed");
-        hipLaunchKernelGGL(pr::compact_count_kernel, dim3(g), dim3(wb), 0, s, O, fo, (int32_t)n_front, kept1 + 1);
-        size_t t = need;
-        if (rocprim::inclusive_scan(tmp, t, kept1, start1, (size_t)n_front + 1, rocprim::plus<int64_t>(), s) !=
-            hipSuccess)
-            return fail_dev("compaction scan failed");
-        int64_t total = 0;
-        if (!read_small(f, &total, start1 + n_front, sizeof(total), s))
-            return fail_dev("compaction readback failed");
-        // live nodes are distinct old records: more than n_old means a malformed forest
-        if (total < 0 || first_new + total > n_old) return fail_dev("compaction found more live nodes than exist");
-        hipLaunchKernelGGL(pr::compact_copy_kernel, dim3(g), dim3(wb), 0, s, O, N, fo, fn, (int32_t)n_front, start1,
-                           first_new, go, gn, (int64_t)0);
-        if (hipGetLastError() != hipSuccess) return fail_dev("compaction launch failed");
-        first_new += total;
-        n_front = total;
-        std::swap(fo, go);
-        std::swap(fn, gn);
+    if (small && !one_wait && !read_small(f, &S, f->d_compact, sizeof(S), s))
+        return fail_new(PR_EDEVICE, "compaction failed");
+    if (!one_wait) {
+        if (S.bad) return fail_new(PR_EDEVICE, "compaction found more live nodes than exist");
+        if (S.n_pool > (int64_t)UINT32_MAX) return fail_new(PR_EDEVICE, "compacted label pool exceeds 2^32 tokens");
     }
-    const int64_t n_new = first_new;
-    // labels into a fresh pool, then separators
-    int64_t *len1 = nullptr, *off = nullptr;
-    if (!X.get(&len1, n_new + 1) || !X.get(&off, n_new + 1)) {
-        free_new();
-        return fail(PR_ENOMEM, "hipMalloc failed for the compaction");
-    }
-    hipLaunchKernelGGL(pr::compact_lab_len_kernel, dim3(grid_threads(n_new, 256)), dim3(256), 0, s, N, n_new, len1);
-    size_t need2 = 0;
-    if (rocprim::inclusive_scan(nullptr, need2, len1, off, (size_t)n_new + 1, rocprim::plus<int64_t>(), s) !=
-        hipSuccess)
-        return fail_dev("compaction scan sizing failed");
-    char *tmp2 = nullptr;
-    if (!X.get(&tmp2, (int64_t)need2)) {
-        free_new();
-        return fail(PR_ENOMEM, "hipMalloc failed for the compaction");
-    }
-    if (rocprim::inclusive_scan(tmp2, need2, len1, off, (size_t)n_new + 1, rocprim::plus<int64_t>(), s) != hipSuccess)
-        return fail_dev("compaction scan failed");
-    int64_t n_pool = 0;
-    if (!read_small(f, &n_pool, off + n_new, sizeof(n_pool), s))
-        return fail_dev("compaction readback failed");
-    if (n_pool > (int64_t)UINT32_MAX) return fail_dev("compacted label pool exceeds 2^32 tokens");
-    nw.cap_pool = std::min<int64_t>(std::max<int64_t>(n_pool + n_pool / 8, 4096), (int64_t)UINT32_MAX);
-    if (!dalloc(f, &nw.pool, nw.cap_pool)) {
-        free_new();
-        return fail(PR_ENOMEM, "hipMalloc failed for the compacted label pool");
-    }
+    const int64_t pool_from = one_wait ? 0 : S.n_pool;  // tokens past the used ones are zero
+    if (!new_pool(f, nw, pool_need(one_wait ? d.n_pool : S.n_pool), narrow))
+        return fail_new(PR_ENOMEM, "hipMalloc failed for the compacted label pool");
     N.pool = nw.pool;
     N.cap_pool = nw.cap_pool;
-    const unsigned gn_all = (unsigned)((n_new + pr::kCompactWavesPerBlock - 1) / pr::kCompactWavesPerBlock);
-    if (hipMemsetAsync(nw.pool + n_pool, 0, (nw.cap_pool - n_pool) * sizeof(int32_t), s) != hipSuccess)
-        return fail_dev("compaction memset failed");
-    hipLaunchKernelGGL(pr::compact_labels_kernel, dim3(gn_all), dim3(wb), 0, s, d.pool, N, n_new, off);
-    hipLaunchKernelGGL(pr::compact_sep_kernel, dim3(gn_all), dim3(wb), 0, s, N, n_new);
-    if (hipGetLastError() != hipSuccess ||
-        hipMemsetAsync(nw.moved, 0, nw.cap_nodes * sizeof(long long), s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-        return fail_dev("compaction failed");
+    const unsigned gl = (unsigned)std::min<int64_t>(16384, ((one_wait ? n_old : S.hi) + 3) / 4);
+    if (hipMemsetAsync(nw.pool + pool_from, 0, (nw.cap_pool - pool_from) * sizeof(int32_t), s) != hipSuccess ||
+        (nw.pool16 && hipMemsetAsync(nw.hib, 0, hib_words(nw.cap_pool16) * sizeof(uint32_t), s) != hipSuccess) ||
+        hipMemsetAsync(nw.moved, 0, nw.cap_nodes * sizeof(long long), s) != hipSuccess)
+        return fail_new(PR_EDEVICE, "compaction memset failed");
+    hipLaunchKernelGGL(pr::compact_labels_kernel, dim3(gl), dim3(256), 0, s, d.pool, N,
+                       pr::NarrowDst{nw.pool16, nw.hib}, f->d_compact, off, small ? nullptr : blk);
+    hipLaunchKernelGGL(compact_counters_kernel, dim3(1), dim3(1), 0, s, f->d_ctr, f->d_compact);
+    if (hipGetLastError() != hipSuccess || !read_small(f, &S, f->d_compact, sizeof(S), s)) {
+        f->broken = true;  // the counters may be the new image's already
+        return fail_new(PR_EDEVICE, "compaction failed");
+    }
+    if (S.bad) return fail_new(PR_EDEVICE, "compaction found more live nodes than exist");
     // install the new image once no launch on another stream still reads the old one
-    if (hipDeviceSynchronize() != hipSuccess) return fail_dev("hipDeviceSynchronize failed");
-    free_image(f);
-    nw.n_nodes = n_new;
-    nw.n_pool = n_pool;
+    if (hipDeviceSynchronize() != hipSuccess) return fail_new(PR_EDEVICE, "hipDeviceSynchronize failed");
+    retire_image(f);
+    nw.n_nodes = S.hi;
+    nw.n_pool = S.n_pool;
     f->dev = nw;
-    f->has_dev = true;
     f->layout_epoch++;
-    pr::MergeCounters c;
-    std::memset(&c, 0, sizeof(c));
-    c.n_nodes = (unsigned long long)n_new;
-    c.n_pool = (unsigned long long)n_pool;
-    if (hipMemcpy(f->d_ctr, &c, sizeof(c), hipMemcpyHostToDevice) != hipSuccess) {
-        f->broken = true;
-        return fail(PR_EDEVICE, "counter upload failed");
-    }
-    // the 16-bit copy of the new pool (its labels are a subset of the old ones)
-    f->narrow = narrow_before;
-    if ((r = pool16_extend(f, 0, s))) {
-        f->broken = true;
-        return r;
-    }
-    pr::MergeCounters cc;
-    if (f->narrow && !read_small(f, &cc, f->d_ctr, sizeof(cc), s)) {
-        f->broken = true;
-        return fail(PR_EDEVICE, "reading the narrow label check failed");
-    }
-    if (f->narrow) {
-        if (cc.wide_tokens)
-            drop_pool16(f);
-        else
-            f->hi17 = cc.hi_tokens > 0;  // the rebuilt pool holds only live labels
-    }
+    f->stamp = 0;  // no record carries a move stamp
+    f->narrow = narrow && nw.pool16;
+    f->hi17 = f->narrow && S.hi_tokens;  // the rebuilt pool holds only live labels
+    if (f->narrow && S.wide_tokens) drop_pool16(f);
     f->host_img_valid = false;  // the host image no longer mirrors the device layout
-    if (nodes_after) *nodes_after = n_new;
+    // scratch sized for far more records than are left goes back
+    if (X.cap > 4 * nw.n_nodes + (1 << 16)) free_export_scratch(f);
+    if (nodes_after) *nodes_after = nw.n_nodes;
     return ok();
 }
 
