@@ -72,7 +72,7 @@ struct MergeCounters {
     unsigned long long hi_tokens;    // nonzero: an appended label token lies in [65536, 131071] (17-bit labels)
     unsigned long long add_pool_base;  // add round planned in one workgroup: first pool token of its labels
     unsigned long long plan_n;         // ADD entries the one-workgroup plan took this round (0: none)
-    unsigned long long plan_fallback;  // nonzero: this round's ADD entries do not fit the one-workgroup plan
+    unsigned long long plan_fallback;  // nonzero: a round's ADD entries did not fit the one-workgroup plan
 };
 
 // Entry count of an add step: the host's, or (n_add < 0, rounds the host does
@@ -216,16 +216,6 @@ __device__ __forceinline__ int32_t m_find_child(const DevForest &F, const Node &
     return be ? beg + lo + (int32_t)(__ffsll((unsigned long long)be) - 1) : -1;
 }
 
-__global__ void merge_validate_kernel(Batch B, InsState *st, MergeCounters *ctr) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= B.n) return;
-    const int64_t b = B.offsets[i], e = B.offsets[i + 1];
-    const int32_t p = batch_peer(B, i);
-    const bool ok = p >= 0 && p < B.P && b >= 0 && e >= b && e <= B.num_tokens && e - b <= (int64_t)INT32_MAX;
-    st[i].kind = ok ? kInsActive : kInsSkip;
-    if (!ok && !B.touch) atomicAdd(&ctr->skipped, 1ull);  // touches ignore bad queries
-}
-
 // Walk one insert (tokens s[0, len) for peer p) from the root and classify it
 // as DONE, ADD or SPLIT, setting the peer's bit in every node it passes through
 // whole.  A touch walks p's tree only: it is DONE where no child holds p, and
@@ -282,18 +272,37 @@ __device__ __forceinline__ InsState m_walk(const DevForest &F, const int32_t *s,
     return r;
 }
 
-// Walk every active insert.
-__global__ __launch_bounds__(64 *kMergeWavesPerBlock) void merge_walk_kernel(DevForest F, Batch B, InsState *st) {
+// Walk every unfinished insert.  first: nothing has looked at the batch yet;
+// invalid entries are skipped and counted (touches ignore them).  arest[i]
+// (nullptr: not wanted) gets the label tokens an ADD insert needs, else -1.
+__global__ __launch_bounds__(64 *kMergeWavesPerBlock) void merge_walk_kernel(DevForest F, Batch B, InsState *st,
+                                                                            int32_t *arest, MergeCounters *ctr,
+                                                                            int first) {
     const int lane = (int)(threadIdx.x & 63);
     const int64_t i = m_wave_index();
     if (i >= B.n) return;
-    const int32_t kind = st[i].kind;
-    if (kind == kInsSkip || kind == kInsDone) return;
-    const int64_t b = B.offsets[i];
+    const int64_t b = B.offsets[i], e = B.offsets[i + 1];
     const int32_t p = batch_peer(B, i);
-    const InsState r = m_walk(F, B.tokens + b, B.offsets[i + 1] - b, p, B.touch, F.ltime && B.stamp && p == F.local,
-                              lane);
-    if (lane == 0) st[i] = r;  // merge_tally_kernel counts the kinds
+    bool walk;
+    if (first) {
+        walk = p >= 0 && p < B.P && b >= 0 && e >= b && e <= B.num_tokens && e - b <= (int64_t)INT32_MAX;
+        if (!walk && lane == 0) {
+            st[i].kind = kInsSkip;
+            if (!B.touch) atomicAdd(&ctr->skipped, 1ull);
+        }
+    } else {
+        const int32_t kind = st[i].kind;
+        walk = kind != kInsSkip && kind != kInsDone;
+    }
+    if (!walk) {
+        if (arest && lane == 0) arest[i] = -1;
+        return;
+    }
+    const InsState r = m_walk(F, B.tokens + b, e - b, p, B.touch, F.ltime && B.stamp && p == F.local, lane);
+    if (lane == 0) {
+        st[i] = r;
+        if (arest) arest[i] = r.kind == kInsAdd ? (int32_t)(e - b - r.d) : -1;
+    }
 }
 
 // Tokens insert i adds past the depth where its walk ended (l: SPLIT).
@@ -305,23 +314,18 @@ __device__ __forceinline__ int64_t ins_rest(const Batch &B, int64_t i, const Ins
 // need, reduced per block before one atomic each: per-insert atomics on the
 // same counters would serialise.
 constexpr int kTallyThreads = 256;
-// arest[i] (if not nullptr): the label tokens ADD insert i needs, else -1 (the
-// one-workgroup add plan reads it).
 __global__ __launch_bounds__(kTallyThreads) void merge_tally_kernel(Batch B, const InsState *st,
-                                                                    MergeCounters *ctr, int32_t *arest) {
+                                                                    MergeCounters *ctr) {
     __shared__ unsigned long long part[3][kTallyThreads / 64];
     unsigned long long n_add = 0, n_split = 0, pool = 0;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < B.n; i += (int64_t)gridDim.x * blockDim.x) {
         const int32_t kind = st[i].kind;
-        int32_t ar = -1;
         if (kind == kInsAdd || kind == kInsSplit) {
             n_add += kind == kInsAdd;
             n_split += kind == kInsSplit;
             const int64_t rest = ins_rest(B, i, st[i], 0);
             pool += (unsigned long long)rest;
-            if (kind == kInsAdd) ar = (int32_t)rest;
         }
-        if (arest) arest[i] = ar;
     }
     for (int off = 32; off >= 1; off >>= 1) {
         n_add += __shfl_xor(n_add, off);
@@ -354,14 +358,6 @@ __device__ __forceinline__ int32_t current_pos(const DevForest &F, int32_t c, lo
     if (stamp <= 0) return c;
     const long long mv = F.moved[c];
     return (mv >> 32) == stamp ? (int32_t)(uint32_t)mv : c;
-}
-
-// SPLIT phase, step 1: per child c, the lowest batch index wins the claim.
-// stamp: that of the add phase that ran earlier in this round, or 0.
-__global__ void split_claim_kernel(DevForest F, Batch B, const InsState *st, long long stamp) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= B.n || st[i].kind != kInsSplit) return;
-    atomicMax(&F.nodes[current_pos(F, st[i].c, stamp)].aux, (int32_t)(INT32_MAX - i));
 }
 
 // Reads past the CU's first-level cache, whose lines atomics of the same launch
@@ -397,11 +393,6 @@ __device__ __forceinline__ void leaf_mext(const DevForest &F, int64_t dst, int32
         F.mext[dst * (F.W - 1) + w] = (p >> 6) == w + 1 ? 1ull << (p & 63) : 0ull;
 }
 
-// Copy n tokens into freshly allocated pool space (wave-cooperative).
-__device__ __forceinline__ void copy_tokens(int32_t *dst, const int32_t *src, int64_t n, int lane) {
-    for (int64_t k = lane; k < n; k += 64) dst[k] = src[k];
-}
-
 // Where appended labels' narrow copy goes (p16 nullptr: the forest has none).
 struct NarrowDst {
     uint16_t *p16;
@@ -409,40 +400,58 @@ struct NarrowDst {
 };
 
 // Copy n tokens to pool[pb ..) and their narrow copy (wave-cooperative), in
-// pool-aligned chunks of 64, eight loaded before the first is stored (a chunk
+// pool-aligned chunks of 64, four loaded before the first is stored (a chunk
 // at a time waits out one round trip to memory for every 256 bytes).  A chunk's
 // bits of bit 16 are a ballot; whole words are stored and words shared with
 // other spans ORed (the plane is zero past the used pool).  seen: bit 0 a
 // 17-bit token, bit 1 a wider one.
 __device__ __forceinline__ void copy_tokens_narrow(const DevForest &F, const NarrowDst &N, int64_t pb,
                                                    const int32_t *src, int64_t n, int lane, uint32_t &seen) {
-    constexpr int kChunks = 8;
-    for (int64_t k0 = pb & ~63ll; k0 < pb + n; k0 += 64 * kChunks) {
+    constexpr int kChunks = 4;
+    const int32_t len = (int32_t)n;
+    int32_t *dst = F.pool + pb;
+    uint16_t *d16 = N.p16 + pb;
+    uint32_t all = 0;
+    // k: place in the span of the chunk's first token (below 0 in the first chunk)
+    for (int32_t k = -(int32_t)(pb & 63); k < len; k += 64 * kChunks) {
         uint32_t t[kChunks];
 #pragma unroll
         for (int u = 0; u < kChunks; u++) {
-            const int64_t k = k0 + 64 * u + lane;
-            t[u] = k >= pb && k < pb + n ? (uint32_t)src[k - pb] : 0u;
+            const int32_t j = k + 64 * u + lane;
+            t[u] = (uint32_t)j < (uint32_t)len ? (uint32_t)src[j] : 0u;
         }
 #pragma unroll
         for (int u = 0; u < kChunks; u++) {
-            const int64_t k = k0 + 64 * u + lane;
-            const bool in = k >= pb && k < pb + n;
-            if (in) F.pool[k] = (int32_t)t[u];
+            const int32_t c = k + 64 * u, j = c + lane;
+            if (c >= len) break;
+            const bool in = (uint32_t)j < (uint32_t)len;
+            if (in) dst[j] = (int32_t)t[u];
+            all |= t[u];
             if (!N.p16) continue;
-            if (in) N.p16[k] = (uint16_t)t[u];
+            if (in) d16[j] = (uint16_t)t[u];
             const uint64_t bits = __ballot((t[u] >> 16) & 1u);
-            const int64_t w = k0 + 64 * u + 32 * lane;  // lane 0 and 1's word covers tokens [w, w + 32)
-            if (lane < 2 && w + 32 > pb && w < pb + n) {
+            const int32_t w = c + 32 * lane;  // lane 0 and 1's word covers tokens [w, w + 32) of the span
+            if (lane < 2 && w + 32 > 0 && w < len) {
                 const uint32_t word = (uint32_t)(bits >> (32 * lane));
-                if (w >= pb && w + 32 <= pb + n)
-                    N.hib[w >> 5] = word;
+                uint32_t *at = &N.hib[(pb + w) >> 5];
+                if (w >= 0 && w + 32 <= len)
+                    *at = word;
                 else if (word)
-                    atomicOr(&N.hib[w >> 5], word);
+                    atomicOr(at, word);
             }
-            seen |= t[u] > 0x1FFFFu ? 2u : (t[u] > 0xFFFFu ? 1u : 0u);
         }
     }
+    seen |= all > 0x1FFFFu ? 2u : 0u;
+    seen |= (all >> 16) & 1u;
+}
+
+// The merge counters' flags for what a wave has seen: written once (a flag per
+// wave on one address would serialise).  The 17-bit flag may also be raised by
+// wider tokens, which drop the narrow copy anyway.
+__device__ __forceinline__ void narrow_flags(MergeCounters *ctr, uint32_t seen, int lane) {
+    const bool h = __ballot(seen & 1u) != 0, w = __ballot(seen & 2u) != 0;
+    if (lane == 0 && h && !fresh_u64(&ctr->hi_tokens)) atomicOr(&ctr->hi_tokens, 1ull);
+    if (lane == 0 && w && !fresh_u64(&ctr->wide_tokens)) atomicOr(&ctr->wide_tokens, 1ull);
 }
 
 // Cut the edge of the node at c (its record: old) after l tokens.  The lower
@@ -496,32 +505,21 @@ __device__ __forceinline__ void cut_edge(const DevForest &F, const NarrowDst &N,
 // Cut child c's edge after l tokens; the winning insert's rest becomes a leaf,
 // and the winner is done.  An add phase earlier in the round may have moved
 // c's record (stamp, as for the claim); it also may have given c a new child
-// block, which the lower part of the edge takes along.  reset_round: also
-// clear the round's counters for the next walk (every kernel that reads them
-// has finished; this one only allocates), which saves a launch per round.
+// block, which the lower part of the edge takes along.
 // Waves per workgroup of split_apply_kernel: a workgroup takes one allocation
 // of records and one of pool tokens for all its winners (two atomics on the
 // merge's counters instead of two per winner, which serialise on their two
 // addresses when a batch cuts thousands of edges).
 constexpr int kSplitWaves = 16;
 
-__global__ __launch_bounds__(64 *kSplitWaves) void split_apply_kernel(DevForest F, Batch B, InsState *st,
-                                                                     MergeCounters *ctr, long long stamp,
-                                                                     int reset_round) {
+__global__ __launch_bounds__(64 *kSplitWaves) void split_apply_kernel(DevForest F, Batch B, NarrowDst N,
+                                                                     InsState *st, MergeCounters *ctr,
+                                                                     long long stamp) {
     __shared__ unsigned long long s_need[2][kSplitWaves];  // records, pool tokens per wave
     __shared__ unsigned long long s_base[2];
     const int lane = (int)(threadIdx.x & 63);
     const int wv = uniform((int32_t)(threadIdx.x / 64));
     const int64_t i = (int64_t)blockIdx.x * kSplitWaves + wv;
-    if (reset_round && blockIdx.x == 0 && threadIdx.x == 0) {
-        ctr->n_add = 0;
-        ctr->n_split = 0;
-        ctr->pool_need = 0;
-        ctr->node_need = 0;
-        ctr->move_chunks = 0;
-        ctr->plan_n = 0;
-        ctr->plan_fallback = 0;
-    }
     // every wave reaches the workgroup's allocation below; only the winner of
     // its edge's claim takes a share
     bool win = false;
@@ -575,8 +573,9 @@ __global__ __launch_bounds__(64 *kSplitWaves) void split_apply_kernel(DevForest 
     }
     const int32_t p = batch_peer(B, i);
     uint32_t seen = 0;
-    cut_edge(F, NarrowDst{nullptr, nullptr}, F.nodes[r.c], r.c, r.l, s + r.d + r.l, rest, p,
-             F.ltime && B.stamp && p == F.local, nb, pb, lane, seen);
+    cut_edge(F, N, F.nodes[r.c], r.c, r.l, s + r.d + r.l, rest, p, F.ltime && B.stamp && p == F.local, nb, pb, lane,
+             seen);
+    narrow_flags(ctr, seen, lane);
     if (lane == 0) st[i].kind = kInsDone;  // the sequence ends at the leaf, or at the upper part (rest 0)
 }
 
@@ -604,6 +603,23 @@ __device__ __forceinline__ int32_t lower_count(const int32_t *a, int32_t n, int3
             hi = mid;
     }
     return lo;
+}
+
+// Number of entries of the sorted array a[0..n) that are < v (wave-cooperative:
+// 64 probes a step, so 10,000 entries take three dependent loads instead of
+// fourteen).  Every lane passes and gets the same values.
+__device__ __forceinline__ int32_t wave_lower_count(const int32_t *a, int32_t n, int32_t v, int lane) {
+    int32_t lo = 0, hi = n;
+    while (hi - lo > 64) {
+        const int32_t stride = (hi - lo + 63) / 64;
+        const int32_t j = lo + lane * stride;
+        const int32_t c = (int32_t)__popcll(__ballot(j < hi && a[j] < v));
+        if (c == 0) return lo;
+        hi = min(lo + c * stride, hi);
+        lo += (c - 1) * stride;
+    }
+    const int32_t j = lo + lane;
+    return lo + (int32_t)__popcll(__ballot(j < hi && a[j] < v));
 }
 
 __device__ __forceinline__ bool add_is_head(const unsigned long long *keys, int64_t e) {
@@ -661,9 +677,7 @@ __global__ void add_group_kernel(DevForest F, const unsigned long long *keys, co
 // steps 0-3 (sort keys, radix sort, marks, the four scans, groups and their
 // allocation):
 //  1. the batch is read in coalesced chunks; ADD entries are gathered in batch
-//     order, and each gets its label span in one pool allocation for the whole
-//     round, in batch order (`pofs`, indexed by insert; a slot loser's span
-//     stays unused, zero-filled);
+//     order;
 //  2. parents are numbered through a hash table in LDS, so that the sort key
 //     (parent slot, token) needs about 11 + 17 bits instead of 31 + 32; with
 //     more distinct parents than the table takes, the key keeps the node id;
@@ -672,7 +686,8 @@ __global__ void add_group_kernel(DevForest F, const unsigned long long *keys, co
 //     each thread's own counters, which also give the entry's rank among the
 //     thread's entries of that digit;
 //  4. marks and scans in registers; one node allocation for every rebuilt
-//     block of the round, refused as a whole when the capacity runs out.
+//     block of the round and one label allocation for its winners (`pofs`,
+//     indexed by insert), refused as a whole when the capacity runs out.
 // The outputs keep the multi-launch path's layout (keys hold the parent's node
 // id), so the move, leaf, separator and fix steps serve both paths.
 constexpr int kPlanThreads = 1024;
@@ -709,13 +724,6 @@ __device__ __forceinline__ uint32_t wave_incl_add_u32(uint32_t v) {
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);  // row_bcast:15 -> rows 1, 3
     v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);  // row_bcast:31 -> rows 2, 3
     return v;
-}
-
-// Inclusive sum over the wave of values below 2^25 each (so no sum
-// overflows 32 bits), else of any values.
-__device__ __forceinline__ long long wave_incl_add_i64(long long v) {
-    if (__ballot(v >= (1ll << 25)) == 0) return (long long)wave_incl_add_u32((uint32_t)v);
-    return plan_wave_incl(v, [](long long a, long long b) { return a + b; });
 }
 
 // Exclusive scan over the workgroup in thread order (id: the identity of op);
@@ -775,13 +783,13 @@ __device__ __forceinline__ int plan_pad(int p) { return p + (p >> 5); }
 constexpr int kPlanPadded = kPlanMax + kPlanMax / 32;
 
 // One workgroup of kPlanThreads, for batches of at most kPlanMaxBatch inserts
-// whose round has at most kPlanMax ADD entries.  n_add is the walk's tally of
-// ADD inserts (< 0: take the tally from ctr, for rounds the host does not read
-// back; a round that does not fit then raises plan_fallback and plans
-// nothing), and arest the tally's per-insert label tokens (-1: not ADD); a
-// count that differs from the host's raises bad_path and plans nothing (the
-// merge then fails).  pofs[i]: the label span of ADD insert i from the round's
-// pool base (ctr->add_pool_base); ctr->plan_n: the entries planned.
+// whose round has at most kPlanMax ADD entries.  arest: the walk's label tokens
+// per insert (-1: not ADD).  n_add: the host's tally of ADD inserts (a count
+// that differs raises bad_path and plans nothing; the merge then fails), or -1
+// for rounds the host does not read back (a round that does not fit then
+// raises plan_fallback and plans nothing).  pofs[i]: the label span of ADD
+// winner i from the round's pool base (ctr->add_pool_base); ctr->plan_n: the
+// entries planned.
 __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Batch B, const InsState *st,
                                                                 const int32_t *arest, int64_t n_add,
                                                                 unsigned long long *keys, int32_t *vals,
@@ -794,7 +802,6 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
     __shared__ uint32_t s_cnt[8 * kPlanThreads];             // digits d, d + 8 of thread t: word d * T + t
     __shared__ int32_t s_tab[kPlanSlots];                    // parent node id per slot, or -1
     __shared__ int s_cw[kPlanBatchItems * kPlanWaves];       // ADD entries per (chunk, wave), then their scan
-    __shared__ long long s_rw[kPlanBatchItems * kPlanWaves]; // their label tokens, then the scan
     __shared__ uint32_t s_wt[kPlanWaves * 8];                // per wave: packed digit totals, then prefixes
     __shared__ uint32_t s_dt[8];                             // packed digit totals of the workgroup
     __shared__ long long s_tmp[kPlanWaves];
@@ -807,23 +814,11 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
     const auto plus = [](int a, int b) { return a + b; };
     const auto plus64 = [](long long a, long long b) { return a + b; };
 
-    if (n_add < 0) {
-        const unsigned long long na = ctr->n_add;  // the tally's, complete before this launch
-        if (na == 0 || na > (unsigned long long)kPlanMax || B.n > kPlanMaxBatch) {
-            if (t == 0) {
-                ctr->plan_n = 0;
-                ctr->move_chunks = 0;
-                if (na) ctr->plan_fallback = 1;
-            }
-            return;
-        }
-        n_add = (int64_t)na;
-    }
     for (int q = t; q < kPlanSlots; q += T) s_tab[q] = -1;
     if (t < 4) s_misc[t] = 0;
 
-    // 1. chunk j holds inserts [j*T, (j+1)*T): count the ADD entries and their
-    // label tokens per (chunk, wave), in batch order
+    // 1. chunk j holds inserts [j*T, (j+1)*T): count the ADD entries per
+    // (chunk, wave), in batch order
     const int n = (int)min<int64_t>(B.n, kPlanMaxBatch);
     const int R = (n + T - 1) / T;
     int32_t ar[kPlanBatchItems];
@@ -836,60 +831,42 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
             const bool a = ar[j] >= 0;
             addbits |= (uint32_t)a << j;
             const uint64_t bal = __ballot(a);
-            const long long rs = wave_incl_add_i64((long long)(a ? ar[j] : 0));
-            if (lane == 63) {
-                s_cw[j * kPlanWaves + wv] = (int)__popcll(bal);
-                s_rw[j * kPlanWaves + wv] = rs;
-            }
+            if (lane == 63) s_cw[j * kPlanWaves + wv] = (int)__popcll(bal);
         }
     }
     __syncthreads();
     if (wv == 0) {
-        // exclusive scans of the (chunk, wave) tables in their order, 4 entries a lane
-        int c[4];
-        long long r[4];
-        int cs = 0;
-        long long rsum = 0;
+        // exclusive scan of the (chunk, wave) table in its order, 4 entries a lane
+        int c[4], cs = 0;
 #pragma unroll
         for (int q = 0; q < 4; q++) {
             const int idx = lane * 4 + q;
             c[q] = idx < R * kPlanWaves ? s_cw[idx] : 0;
-            r[q] = idx < R * kPlanWaves ? s_rw[idx] : 0;
             cs += c[q];
-            rsum += r[q];
         }
         const int ci = plan_wave_incl(cs, plus);
-        const long long ri = plan_wave_incl(rsum, plus64);
         int cp = ci - cs;
-        long long rp = ri - rsum;
 #pragma unroll
         for (int q = 0; q < 4; q++) {
             const int idx = lane * 4 + q;
-            if (idx < R * kPlanWaves) {
-                s_cw[idx] = cp;
-                s_rw[idx] = rp;
-            }
+            if (idx < R * kPlanWaves) s_cw[idx] = cp;
             cp += c[q];
-            rp += r[q];
         }
-        if (lane == 63) {
-            s_misc[3] = ci;  // ADD entries
-            s_tmp[0] = ri;   // their label tokens
-        }
+        if (lane == 63) s_misc[3] = ci;  // ADD entries
     }
     __syncthreads();
     const int m = s_misc[3];
-    const long long pool_total = s_tmp[0];
-    if ((int64_t)m != n_add || m > kPlanMax || B.n > kPlanMaxBatch) {
+    const bool bad = B.n > kPlanMaxBatch || (n_add >= 0 && (int64_t)m != n_add);
+    if (m == 0 || m > kPlanMax || bad) {
         if (t == 0) {
-            atomicAdd(&ctr->bad_path, 1ull);
+            if (bad || (m > kPlanMax && n_add >= 0)) atomicAdd(&ctr->bad_path, 1ull);
+            if (m > kPlanMax && n_add < 0) ctr->plan_fallback = 1;
             ctr->plan_n = 0;
             ctr->move_chunks = 0;
         }
         return;  // the same in every thread
     }
-    __syncthreads();  // s_tmp is reused by the scans below
-    // second sweep: place each ADD entry, record its span, hash its parent
+    // second sweep: place each ADD entry, hash its parent
     // (parents are looked up until the table holds kPlanMaxParents of them;
     // small rounds are ranked by counting and keep node ids)
     const bool small = m <= kPlanSmall;
@@ -911,12 +888,9 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
             if (j < R) {
                 const int i = j * T + t;
                 const bool a = (addbits >> j) & 1u;
-                const long long rest = a ? ar[j] : 0;
                 const uint64_t bal = __ballot(a);
-                const long long rs = wave_incl_add_i64(rest) - rest;
                 if (a) {
                     const int pos = s_cw[j * kPlanWaves + wv] + (int)__popcll(bal & lt_mask);
-                    pofs[i] = s_rw[j * kPlanWaves + wv] + rs;
                     if (s_misc[1] == 0) {
                         if (s_misc[0] > kPlanMaxParents || plan_slot_insert(s_tab, &s_misc[0], xs[j]) < 0)
                             s_misc[1] = 1;
@@ -1102,6 +1076,21 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
             }
         }
     }
+    // winners' label spans, in sorted order
+    long long srest = 0, pool_total;
+    int32_t rest[kPlanItems];
+#pragma unroll
+    for (int j = 0; j < kPlanItems; j++) {
+        rest[j] = j < nv && ((wbits >> j) & 1u) ? arest[v[j]] : 0;
+        srest += rest[j];
+    }
+    long long prest = plan_block_excl<long long>(srest, 0, plus64, s_tmp, &pool_total);
+#pragma unroll
+    for (int j = 0; j < kPlanItems; j++)
+        if (j < nv && ((wbits >> j) & 1u)) {
+            pofs[v[j]] = prest;
+            prest += rest[j];
+        }
     int tw, tc, th;
     int pw = plan_block_excl<int>(sw, 0, plus, s_tmp32, &tw);
     int pc = plan_block_excl<int>(sc, 0, plus, s_tmp32, &tc);
@@ -1210,126 +1199,103 @@ __global__ void add_alloc_kernel(DevForest F, const unsigned long long *keys, in
     grp_pb[k] = pb;
 }
 
-// Step 4 (64-child chunks of every rebuilt parent's old block, a wave per
-// chunk, grid-stride over the chunk count step 2 recorded): old children keep
-// their order, each moving up by the winners below it, and are stamped with
-// their new position.  The grid is small and fixed, so its size does not
-// follow the forest's record count.
-__global__ __launch_bounds__(64 *kMergeWavesPerBlock) void add_move_kernel(
-    DevForest F, const unsigned long long *keys, int64_t n_add, const int32_t *cstart,
-    const MergeCounters *__restrict__ ctr, const int32_t *grp_nw, const int32_t *grp_nb, const int32_t *win_tok,
-    long long stamp) {
-    const int lane = (int)(threadIdx.x & 63);
-    const int64_t nchunks = (int64_t)ctr->move_chunks;
-    const int64_t waves = (int64_t)gridDim.x * kMergeWavesPerBlock;
-    n_add = add_count(n_add, ctr);
-    for (int64_t c = m_wave_index(); c < nchunks; c += waves) {
-        // the group whose chunks hold c: cstart[k] <= c < cstart[k + 1]
-        int64_t lo = 0, hi = n_add;
-        while (lo < hi) {
-            const int64_t mid = (lo + hi) >> 1;
-            if (cstart[mid] <= c)
-                lo = mid + 1;
-            else
-                hi = mid;
-        }
-        const int64_t k = lo - 1;
-        const int32_t nb = grp_nb[k];
-        if (nb < 0) continue;
-        const Node nx = F.nodes[key_parent(keys[k])];
-        const int32_t j = (int32_t)(c - cstart[k]) * 64 + lane;
-        if (j >= nx.ct_cnt) continue;
-        const int32_t src = nx.ct_beg + j;
-        const int64_t dst = nb + j + lower_count(win_tok + k, grp_nw[k], F.ntok[src]);
-        F.nodes[dst] = F.nodes[src];
-        F.ntok[dst] = F.ntok[src];
-        if (F.ltime) F.ltime[dst] = F.ltime[src];
-        for (int w = 0; w < F.W - 1; w++) F.mext[dst * (F.W - 1) + w] = F.mext[(int64_t)src * (F.W - 1) + w];
-        F.moved[src] = (stamp << 32) | (long long)(uint32_t)dst;
-    }
-}
-
-// Step 5 (one wave per winning entry): the leaf holding the rest of the
-// winner's sequence, in its token's slot among the parent's children.
+// Step 4, waves striding over two kinds of work.  First the 64-child chunks of
+// every rebuilt parent's old block: old children keep their order, each moving
+// up by the winners below it, and are stamped with their new position.  Then
+// the entries: a winner's leaf, holding the rest of its sequence, goes to its
+// token's slot among the parent's children.
 // pofs: nullptr after the multi-launch steps (spans from poff and grp_pb),
 // else the one-workgroup plan's spans per insert from ctr->add_pool_base.
-// Steps 5-7 stride over their entries, so a grid sized without the count
-// (rounds the host does not read back) serves as well.
-__global__ __launch_bounds__(64 *kMergeWavesPerBlock) void add_leaf_kernel(
-    DevForest F, Batch B, const unsigned long long *keys, const int32_t *vals, int64_t n_add, InsState *st,
-    const int32_t *win, const int32_t *widx, const int64_t *poff, const int32_t *hd, const int32_t *grp_nb,
-    const int64_t *grp_pb, const int64_t *pofs, const MergeCounters *ctr) {
+// The grid is fixed, so it follows neither the forest's records nor a count
+// that only the device knows.
+__global__ __launch_bounds__(64 *kMergeWavesPerBlock) void add_build_kernel(
+    DevForest F, Batch B, NarrowDst N, const unsigned long long *keys, const int32_t *vals, int64_t n_add,
+    InsState *st, const int32_t *win, const int32_t *widx, const int64_t *poff, const int32_t *hd,
+    const int32_t *cstart, const int32_t *grp_nw, const int32_t *grp_nb, const int64_t *grp_pb, const int64_t *pofs,
+    const int32_t *win_tok, MergeCounters *ctr, long long stamp) {
     const int lane = (int)(threadIdx.x & 63);
-    const int64_t cnt = add_count(n_add, ctr);
     const int64_t waves = (int64_t)gridDim.x * kMergeWavesPerBlock;
-    for (int64_t e = m_wave_index(); e < cnt; e += waves) {
+    const int32_t cnt = (int32_t)add_count(n_add, ctr);
+    const int64_t nchunks = cnt > 0 ? (int64_t)ctr->move_chunks : 0;
+    const int64_t pool_base = (int64_t)ctr->add_pool_base;
+    uint32_t seen = 0;
+    for (int64_t q = m_wave_index(); q < nchunks + cnt; q += waves) {
+        if (q < nchunks) {
+            // the group whose chunks hold q: cstart[k] <= q < cstart[k + 1]
+            const int32_t k = wave_lower_count(cstart, cnt, (int32_t)q + 1, lane) - 1;
+            const int32_t nb = grp_nb[k];
+            if (nb < 0) continue;
+            const Node nx = F.nodes[key_parent(keys[k])];
+            const int32_t j = (int32_t)(q - cstart[k]) * 64 + lane;
+            if (j >= nx.ct_cnt) continue;
+            const int32_t src = nx.ct_beg + j;
+            const Node r = F.nodes[src];
+            const int64_t dst = nb + j + lower_count(win_tok + k, grp_nw[k], r.tok);
+            F.nodes[dst] = r;
+            F.ntok[dst] = r.tok;
+            if (F.ltime) F.ltime[dst] = F.ltime[src];
+            for (int w = 0; w < F.W - 1; w++) F.mext[dst * (F.W - 1) + w] = F.mext[(int64_t)src * (F.W - 1) + w];
+            F.moved[src] = (stamp << 32) | (long long)(uint32_t)dst;
+            continue;
+        }
+        const int32_t e = (int32_t)(q - nchunks);
         if (!win[e]) continue;
-        const int32_t k = hd[e];
+        const int32_t k = hd[e], i = vals[e];
         const int32_t nb = grp_nb[k];
         if (nb < 0) continue;
-        const int32_t i = vals[e];
         const Node nx = F.nodes[key_parent(keys[e])];
         const int32_t *s = B.tokens + B.offsets[i];
         const int64_t len = B.offsets[i + 1] - B.offsets[i];
-        const int32_t d = st[i].d;
+        const int32_t d = st[i].d, t = st[i].t;
         const int64_t rest = len - d;  // >= 1: an ADD insert has a next token
-        const int64_t dst = nb + (widx[e] - widx[k]) + lower_count(F.ntok + nx.ct_beg, nx.ct_cnt, s[d]);
-        const int64_t pb = pofs ? (int64_t)ctr->add_pool_base + pofs[i] : grp_pb[k] + (poff[e] - poff[k]);
+        const int64_t dst = nb + (widx[e] - widx[k]) + wave_lower_count(F.ntok + nx.ct_beg, nx.ct_cnt, t, lane);
+        const int64_t pb = pofs ? pool_base + pofs[i] : grp_pb[k] + (poff[e] - poff[k]);
         const int32_t p = batch_peer(B, i);
-        copy_tokens(F.pool + pb, s + d, rest, lane);
+        copy_tokens_narrow(F, N, pb, s + d, rest, lane, seen);
         leaf_mext(F, dst, p, lane);
         if (lane == 0) {
-            Node leaf;
-            leaf.tok = s[d];
-            leaf.lab_off = (uint32_t)pb;
-            leaf.lab_len = (int32_t)rest;
-            leaf.ct_beg = 0;
-            leaf.ct_cnt = 0;
-            leaf.aux = 0;
-            leaf.mask0 = (p >> 6) == 0 ? 1ull << (p & 63) : 0ull;  // the winner's peer holds its leaf
+            // the winner's peer holds its leaf
+            const Node leaf{t, (uint32_t)pb, (int32_t)rest, 0, 0, 0, (p >> 6) == 0 ? 1ull << (p & 63) : 0ull};
             F.nodes[dst] = leaf;
-            F.ntok[dst] = leaf.tok;
+            F.ntok[dst] = t;
             if (F.ltime) F.ltime[dst] = (B.stamp && p == F.local) ? F.now : 0ull;
             st[i].kind = kInsDone;  // the winner's sequence ends at its new leaf
         }
     }
+    narrow_flags(ctr, seen, lane);
 }
 
-// Separators of every rebuilt wide block (runs after the build, before the
-// parents are pointed at their new blocks; the old record of x still holds the
-// old child count).
-__global__ __launch_bounds__(64 *kMergeWavesPerBlock) void add_sep_kernel(DevForest F,
-                                                                         const unsigned long long *keys,
-                                                                         int64_t n_add, const int32_t *grp_nw,
-                                                                         const int32_t *grp_nb,
-                                                                         const MergeCounters *ctr) {
+// Step 5 (a thread per insert, which is also entry e of the sorted ones): the
+// separators of every rebuilt wide block, and its parent, wherever the parent's
+// record lives now, pointed at it; and the first step of the split phase, which
+// depends on neither: per child c, the lowest batch index wins the claim.
+// stamp: that of the round's build, or 0 if nothing was added.
+__global__ __launch_bounds__(256) void add_finish_kernel(DevForest F, Batch B, const InsState *st,
+                                                        const unsigned long long *keys, int64_t n_add,
+                                                        const int32_t *grp_nw, const int32_t *grp_nb, long long stamp,
+                                                        const MergeCounters *ctr) {
     const int lane = (int)(threadIdx.x & 63);
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < B.n && st[i].kind == kInsSplit)
+        atomicMax(&F.nodes[current_pos(F, st[i].c, stamp)].aux, (int32_t)(INT32_MAX - i));
     const int64_t cnt = add_count(n_add, ctr);
-    const int64_t waves = (int64_t)gridDim.x * kMergeWavesPerBlock;
-    for (int64_t k = m_wave_index(); k < cnt; k += waves) {
-        if (k > 0 && key_parent(keys[k - 1]) == key_parent(keys[k])) continue;
-        const int32_t nb = grp_nb[k];
-        if (nb < 0) continue;
-        const int32_t c = F.nodes[key_parent(keys[k])].ct_cnt + grp_nw[k];
-        if (c <= kSepCount) continue;
-        F.nsep[nb + lane] = F.ntok[nb + PR_SEP_INDEX(lane, c)];
-        if (c < kSep2Min) continue;
-        sep2_write(F.nsep + nb, F.ntok + nb, c, lane);
+    int32_t nb = -1, nw = 0, x = 0, c = 0;
+    if (i < cnt && add_is_head(keys, i)) {
+        nb = grp_nb[i];  // -1: the build of this group was refused
+        nw = grp_nw[i];
+        x = key_parent(keys[i]);
+        if (nb >= 0) c = F.nodes[x].ct_cnt + nw;
     }
-}
-
-// Point every rebuilt parent at its new block, wherever its record lives now.
-__global__ void add_fix_kernel(DevForest F, const unsigned long long *keys, int64_t n_add, const int32_t *grp_nw,
-                               const int32_t *grp_nb, long long stamp, const MergeCounters *ctr) {
-    const int64_t cnt = add_count(n_add, ctr);
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < cnt; k += (int64_t)gridDim.x * blockDim.x) {
-        if (k > 0 && key_parent(keys[k - 1]) == key_parent(keys[k])) continue;
-        if (grp_nb[k] < 0) continue;  // the build of this group was refused
-        const int32_t x = key_parent(keys[k]);
-        const long long mv = F.moved[x];
-        const int64_t pos = (mv >> 32) == stamp ? (int64_t)(uint32_t)mv : (int64_t)x;
-        F.nodes[pos].ct_cnt = F.nodes[pos].ct_cnt + grp_nw[k];
-        F.nodes[pos].ct_beg = grp_nb[k];
+    for (uint64_t wide = __ballot(c > kSepCount); wide; wide &= wide - 1) {
+        const int l = __ffsll((unsigned long long)wide) - 1;
+        const int32_t b = __builtin_amdgcn_readlane(nb, l), n = __builtin_amdgcn_readlane(c, l);
+        F.nsep[b + lane] = F.ntok[b + PR_SEP_INDEX(lane, n)];
+        if (n >= kSep2Min) sep2_write(F.nsep + b, F.ntok + b, n, lane);
+    }
+    if (nb >= 0) {
+        const int32_t pos = current_pos(F, x, stamp);
+        F.nodes[pos].ct_cnt = c;
+        F.nodes[pos].ct_beg = nb;
     }
 }
 

@@ -22,7 +22,6 @@
 #include "export_kernels.h"
 #include "lru_kernels.h"
 #include "merge_kernels.h"
-#include "narrow_kernels.h"
 #include "prefix_router.h"
 #include "route_launch.h"
 #include "small_merge.h"
@@ -570,8 +569,8 @@ pr::DevForest dev_view(const pr_forest *f);
 // read labels from pool16 (the low 16 bits: half the label bytes) and, once
 // some token is 65536 or more, from hib (bit 16, one bit per token) as well;
 // otherwise from the int32 pool.  Labels are only ever appended to the pool
-// (a split reuses a span of its label), so the copy follows merges by
-// converting the appended range.
+// (a split reuses a span of its label), and the kernels that append them write
+// the copy too (copy_tokens_narrow).
 void drop_pool16(pr_forest *f) {
     DevImage &d = f->dev;
     if (d.pool16 || d.hib) {
@@ -584,56 +583,6 @@ void drop_pool16(pr_forest *f) {
     d.cap_pool16 = 0;
     f->narrow = false;
     f->hi17 = false;
-}
-
-// Enqueue the copy of pool[from, n_pool) on s, first growing the copy to the
-// pool's capacity (then it is rebuilt from 0).  Tokens in [65536, 131071] are
-// counted in the merge counters' hi_tokens, tokens outside [0, 131071] in
-// wide_tokens; the caller reads them with its next counter readback, turns
-// the bit plane on for the former and drops the copy for the latter.  Without
-// memory for a larger copy, routes fall back to the int32 pool.
-// device_end: the range ends at the device counters' n_pool (a merge whose
-// rounds the host has not read back), on a grid sized without it.
-pr_status pool16_extend(pr_forest *f, int64_t from, hipStream_t s, bool device_end = false) {
-    DevImage &d = f->dev;
-    if (!f->narrow) return PR_OK;
-    if (d.cap_pool16 < d.cap_pool) {
-        uint16_t *np = nullptr;
-        uint32_t *nh = nullptr;
-        if (!dalloc(f, &np, d.cap_pool) || !dalloc(f, &nh, hib_words(d.cap_pool))) {
-            dfree(f, &np, d.cap_pool);
-            drop_pool16(f);
-            return PR_OK;
-        }
-        if (d.pool16) {
-            if (hipDeviceSynchronize() != hipSuccess) {
-                dfree(f, &np, d.cap_pool);
-                dfree(f, &nh, hib_words(d.cap_pool));
-                return fail(PR_EDEVICE, "hipDeviceSynchronize failed while growing the narrow labels");
-            }
-            dfree(f, &d.pool16, d.cap_pool16);
-            dfree(f, &d.hib, hib_words(d.cap_pool16));
-        }
-        d.pool16 = np;
-        d.hib = nh;
-        d.cap_pool16 = d.cap_pool;
-        if (hipMemsetAsync(d.hib, 0, hib_words(d.cap_pool) * sizeof(uint32_t), s) != hipSuccess)
-            return fail(PR_EDEVICE, "clearing the bit plane failed");
-        from = 0;
-        f->layout_epoch++;
-    }
-    const int64_t to = device_end ? d.cap_pool : d.n_pool;
-    if (to > from) {
-        const int64_t chunks = (to + pr::kWave - 1) / pr::kWave - from / pr::kWave;
-        // a wave per chunk: each wave's load waits on memory, so waves, not
-        // iterations, carry the chunks
-        const int64_t blocks = device_end && from > 0 ? 2048 : std::min<int64_t>((chunks + 3) / 4, 16384);
-        hipLaunchKernelGGL(pr::pool_narrow_kernel, dim3((unsigned)blocks), dim3(pr::kNarrowThreads), 0, s, d.pool,
-                           d.pool16, d.hib, from, to, &f->d_ctr->hi_tokens, &f->d_ctr->wide_tokens,
-                           device_end ? (const unsigned long long *)&f->d_ctr->n_pool : nullptr);
-        if (hipGetLastError() != hipSuccess) return fail(PR_EDEVICE, "narrow label copy failed to launch");
-    }
-    return PR_OK;
 }
 
 // Access times of the local peer: every node it holds gets time t, others 0.
@@ -925,21 +874,6 @@ __global__ void reset_round_kernel(pr::MergeCounters *c) {
     c->plan_fallback = 0;
 }
 
-__global__ void reset_call_kernel(pr::MergeCounters *c) {
-    c->wide_tokens = 0;
-    c->hi_tokens = 0;
-    c->n_add = 0;
-    c->n_split = 0;
-    c->pool_need = 0;
-    c->node_need = 0;
-    c->overflow = 0;
-    c->skipped = 0;
-    c->bad_path = 0;
-    c->move_chunks = 0;
-    c->plan_n = 0;
-    c->plan_fallback = 0;
-}
-
 // The counters of a forest that was just compacted.
 __global__ void compact_counters_kernel(pr::MergeCounters *c, const pr::CompactState *S) {
     if (S->bad) return;
@@ -948,7 +882,15 @@ __global__ void compact_counters_kernel(pr::MergeCounters *c, const pr::CompactS
     c->n_pool = (unsigned long long)S->n_pool;
 }
 
-__global__ void add_skipped_kernel(unsigned long long *acc, const pr::MergeCounters *c) { *acc += c->skipped; }
+// The end of a merge: its skipped inputs are added up, and every counter but
+// the used sizes is cleared for the next one.
+__global__ void add_skipped_kernel(unsigned long long *acc, pr::MergeCounters *c) {
+    *acc += c->skipped;
+    pr::MergeCounters z{};
+    z.n_nodes = c->n_nodes;
+    z.n_pool = c->n_pool;
+    *c = z;
+}
 
 // Counters after refused allocations: the used sizes the host clipped to the
 // capacities, and no refusal pending.
@@ -986,15 +928,6 @@ bool read_small(pr_forest *f, void *out, const void *dsrc, size_t bytes, hipStre
 static_assert(sizeof(pr::MergeCounters) <= kStageBytes && sizeof(pr::SmallStatus) <= kStageBytes && sizeof(pr::EvictPlan) <= kStageBytes &&
                   sizeof(pr::CompactState) <= kStageBytes,
               "readbacks fit the staging buffer");
-
-// Read the device counters and refresh the host mirror of the used sizes
-// (growing the arrays copies exactly the used part).
-pr_status read_counters(pr_forest *f, pr::MergeCounters *c, hipStream_t s) {
-    if (!read_small(f, c, f->d_ctr, sizeof(*c), s)) return fail(PR_EDEVICE, "reading merge counters failed");
-    f->dev.n_nodes = (int64_t)c->n_nodes;
-    f->dev.n_pool = (int64_t)c->n_pool;
-    return PR_OK;
-}
 
 // The counters only (the caller decides what the used sizes are).
 pr_status read_counters_raw(pr_forest *f, pr::MergeCounters *c, hipStream_t s) {
@@ -1038,25 +971,46 @@ void narrow_seen(pr_forest *f, bool hi, bool wide) {
     }
 }
 
-// Batches of at most pr::kSmallMax sequences: one launch (small_merge.h) and
-// one wait.  *done: false if part of the batch is left for the rounds below.
-pr_status run_small_merge(pr_forest *f, const pr::Batch &B, hipStream_t s, bool *done) {
+pr::NarrowDst narrow_dst(const pr_forest *f) {
+    return pr::NarrowDst{f->narrow ? f->dev.pool16 : nullptr, f->dev.hib};
+}
+
+// One launch of the one-workgroup merge (small_merge.h) and one wait: a batch
+// of at most pr::kSmallMax sequences (states nullptr), or what rounds left of a
+// larger one (its states).
+pr_status run_small_merge(pr_forest *f, const pr::Batch &B, const pr::InsState *states, hipStream_t s,
+                          pr::SmallStatus *st) {
     DevImage &d = f->dev;
-    pr::SmallStatus *out = reinterpret_cast<pr::SmallStatus *>(f->d_stage);
-    const pr::NarrowDst N{f->narrow ? d.pool16 : nullptr, d.hib};
-    hipLaunchKernelGGL(pr::small_merge_kernel, dim3(1), dim3(64 * pr::kSmallWaves), 0, s, dev_view(f), B, N,
-                       f->d_ctr, f->d_skipped, f->stamp + 1, out);
+    hipLaunchKernelGGL(pr::small_merge_kernel, dim3(1), dim3(64 * pr::kSmallWaves), 0, s, dev_view(f), B,
+                       narrow_dst(f), f->d_ctr, f->d_skipped, states, f->stamp + 1,
+                       reinterpret_cast<pr::SmallStatus *>(f->d_stage));
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
-        return fail(PR_EDEVICE, "small merge failed");
-    pr::SmallStatus st;
-    std::memcpy(&st, f->h_stage, sizeof(st));
-    f->stamp += st.stamps;
-    d.n_nodes = (int64_t)st.n_nodes;
-    d.n_pool = (int64_t)st.n_pool;
-    narrow_seen(f, st.hi != 0, st.wide != 0);
+        return fail(PR_EDEVICE, "merge failed");
+    std::memcpy(st, f->h_stage, sizeof(*st));
+    f->stamp += st->stamps;
+    if (!st->overflow) {  // else refused requests advanced the counters (refused_round)
+        d.n_nodes = (int64_t)st->n_nodes;
+        d.n_pool = (int64_t)st->n_pool;
+    }
+    narrow_seen(f, st->hi != 0, st->wide != 0);
     f->merged = true;
-    *done = st.done != 0;
     return PR_OK;
+}
+
+// A round ran out of capacity.  Every refused allocation wrote nothing and left
+// its inserts to walk again, but the refused requests still advanced the
+// counters: records and tokens past the last allocation that fit were never
+// written, so the counters are clipped to the capacities, and the forest grows
+// to what the round asked for before the round is repeated.
+pr_status refused_round(pr_forest *f, int64_t want_nodes, int64_t want_pool, int64_t pool_need, hipStream_t s) {
+    f->refusals++;
+    f->dev.n_nodes = std::min<int64_t>(want_nodes, f->dev.cap_nodes);
+    f->dev.n_pool = std::min<int64_t>(want_pool, f->dev.cap_pool);
+    hipLaunchKernelGGL(set_used_kernel, dim3(1), dim3(1), 0, s, f->d_ctr, (unsigned long long)f->dev.n_nodes,
+                       (unsigned long long)f->dev.n_pool);
+    if (hipGetLastError() != hipSuccess) return fail(PR_EDEVICE, "merge launch failed");
+    return ensure_capacity(f, std::max<int64_t>(want_nodes, f->dev.n_nodes + 1),
+                           std::max<int64_t>(want_pool, f->dev.n_pool + pool_need), s);
 }
 
 // Insert a device batch into the device forest (see merge_kernels.h), or touch
@@ -1064,102 +1018,80 @@ pr_status run_small_merge(pr_forest *f, const pr::Batch &B, hipStream_t s, bool 
 pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
     const int64_t pool0 = f->dev.n_pool;  // labels appended from here on
     const int64_t nodes0 = f->dev.n_nodes;
-    pr_status r;
-    // one workgroup serves a batch up to a lane per sequence in about the time
-    // of five launches (65 and more take the rounds below, about 22 launches);
-    // it writes the narrow copy itself, which must be as long as the pool
-    if (B.n <= pr::kSmallMax && f->d_stage && (!f->narrow || f->dev.cap_pool16 >= f->dev.cap_pool)) {
-        bool small_done = false;
-        if ((r = run_small_merge(f, B, s, &small_done))) return r;
-        if (small_done) return PR_OK;
-    }
-    if ((r = ensure_merge_scratch(f, B.n, s))) return r;
-    MergeScratch &m = f->ms;
     const int64_t n = B.n;
+    pr_status r;
+    pr::SmallStatus ss;
+    // one workgroup serves a batch up to a lane per sequence in about the time
+    // of five launches (65 and more take the rounds below, eleven launches)
+    if (n <= pr::kSmallMax && f->d_stage) {
+        if ((r = run_small_merge(f, B, nullptr, s, &ss))) return r;
+        if (ss.done) return PR_OK;
+    }
+    if ((r = ensure_merge_scratch(f, n, s))) return r;
+    MergeScratch &m = f->ms;
     const int bs = 256, wb = 64 * pr::kMergeWavesPerBlock;
-    hipLaunchKernelGGL(reset_call_kernel, dim3(1), dim3(1), 0, s, f->d_ctr);
-    hipLaunchKernelGGL(pr::merge_validate_kernel, dim3(grid_threads(n, bs)), dim3(bs), 0, s, B, m.st, f->d_ctr);
-    pr::MergeCounters c;
-    const int max_rounds = 100000;
-    int round = 0;
-    int refusals = 0;
+    const unsigned build_blocks = (unsigned)std::min<int64_t>(pr::kMoveBlocks, std::max<int64_t>(256, n / 4));
+    int first = 1;  // the next walk is the first to look at the batch
     bool done = false;
     // Rounds the device drives: kDeviceRounds full rounds, each sized on the
-    // device (the add phase planned in one workgroup, the later add steps
-    // striding over what it planned), then a checking walk, the narrow copy
-    // and one readback.  Most batches end there: the first round places every
-    // insert but the losers of a slot or an edge, the second places those.
-    // Anything else (work left, a round too large for the one-workgroup plan,
-    // a refused allocation) continues in the host-driven rounds below, which
-    // read the counters back after every walk.  A forest's first merge takes
-    // the host-driven rounds, which size its spare capacity.
-    if (PR_MERGE_PLAN && n <= pr::kPlanMaxBatch && f->round_pool > 0) {
+    // device (the add phase planned in one workgroup, the later steps striding
+    // over what it planned), then one workgroup, which finishes up to
+    // pr::kSmallMax inserts that are left, and one readback.  Most batches end
+    // there: the first round places every insert but the losers of a slot or an
+    // edge, the second those, but for the losers among them.  With more left, as
+    // when many sequences share a prefix the forest does not have (a slot, then
+    // an edge, then the slots below it), two more rounds run.  Anything else (a
+    // round too large for the one-workgroup plan, a refused allocation)
+    // continues in the host-driven rounds below, which read the counters back
+    // after every walk.
+    for (int k = 0; PR_MERGE_PLAN && !done && f->d_stage && n <= pr::kPlanMaxBatch && k < 4; k++) {
         if ((r = ensure_capacity(f, f->dev.n_nodes + 2 * std::max<int64_t>(f->round_nodes, n),
                                  f->dev.n_pool + 2 * f->round_pool, s)))
             return r;
         const pr::DevForest F = dev_view(f);
-        // the round counters start cleared (reset_call_kernel above), and each
-        // round's split kernel clears them for the next walk
-        for (int k = 0; k < kDeviceRounds; k++) {
-            hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_waves(n)), dim3(wb), 0, s, F, B, m.st);
-            hipLaunchKernelGGL(pr::merge_tally_kernel,
-                               dim3((unsigned)std::min<int64_t>(256, (n + pr::kTallyThreads - 1) / pr::kTallyThreads)),
-                               dim3(pr::kTallyThreads), 0, s, B, m.st, f->d_ctr, m.arest);
-            hipLaunchKernelGGL(pr::add_plan_kernel, dim3(1), dim3(pr::kPlanThreads), 0, s, F, B, m.st, m.arest,
-                               (int64_t)-1, m.keys_out, m.vals_out, m.win, m.widx, m.hd, m.cstart, m.grp_nw, m.grp_nb,
-                               m.win_tok, m.rest, f->d_ctr);
+        const pr::NarrowDst N = narrow_dst(f);
+        for (int round = 0; round < kDeviceRounds; round++, first = 0) {
             const long long stamp = ++f->stamp;
-            hipLaunchKernelGGL(pr::add_move_kernel, dim3(pr::kMoveBlocks), dim3(wb), 0, s, F, m.keys_out, (int64_t)-1,
-                               m.cstart, f->d_ctr, m.grp_nw, m.grp_nb, m.win_tok, stamp);
-            hipLaunchKernelGGL(pr::add_leaf_kernel, dim3(grid_waves(std::min<int64_t>(n, pr::kPlanMax))), dim3(wb), 0,
-                               s, F, B, m.keys_out, m.vals_out, (int64_t)-1, m.st, m.win, m.widx, m.poff, m.hd,
-                               m.grp_nb, m.grp_pb, m.rest, f->d_ctr);
-            hipLaunchKernelGGL(pr::add_sep_kernel, dim3(grid_waves(std::min<int64_t>(n, pr::kPlanMax))), dim3(wb), 0,
-                               s, F, m.keys_out, (int64_t)-1, m.grp_nw, m.grp_nb, f->d_ctr);
-            hipLaunchKernelGGL(pr::add_fix_kernel, dim3(grid_threads(std::min<int64_t>(n, pr::kPlanMax), bs)),
-                               dim3(bs), 0, s, F, m.keys_out, (int64_t)-1, m.grp_nw, m.grp_nb, stamp, f->d_ctr);
-            hipLaunchKernelGGL(pr::split_claim_kernel, dim3(grid_threads(n, bs)), dim3(bs), 0, s, F, B, m.st, stamp);
-            hipLaunchKernelGGL(pr::split_apply_kernel, dim3(grid_split(n)), dim3(64 * pr::kSplitWaves), 0, s, F, B,
-                               m.st, f->d_ctr, stamp, 1);
+            hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_waves(n)), dim3(wb), 0, s, F, B, m.st, m.arest,
+                               f->d_ctr, first);
+            if (!B.touch) {  // touches add nothing
+                hipLaunchKernelGGL(pr::add_plan_kernel, dim3(1), dim3(pr::kPlanThreads), 0, s, F, B, m.st, m.arest,
+                                   (int64_t)-1, m.keys_out, m.vals_out, m.win, m.widx, m.hd, m.cstart, m.grp_nw,
+                                   m.grp_nb, m.win_tok, m.rest, f->d_ctr);
+                hipLaunchKernelGGL(pr::add_build_kernel, dim3(build_blocks), dim3(wb), 0, s, F, B, N, m.keys_out,
+                                   m.vals_out, (int64_t)-1, m.st, m.win, m.widx, m.poff, m.hd, m.cstart, m.grp_nw,
+                                   m.grp_nb, m.grp_pb, m.rest, m.win_tok, f->d_ctr, stamp);
+            }
+            hipLaunchKernelGGL(pr::add_finish_kernel, dim3(grid_threads(n, bs)), dim3(bs), 0, s, F, B, m.st,
+                               m.keys_out, (int64_t)(B.touch ? 0 : -1), m.grp_nw, m.grp_nb, stamp, f->d_ctr);
+            hipLaunchKernelGGL(pr::split_apply_kernel, dim3(grid_split(n)), dim3(64 * pr::kSplitWaves), 0, s, F, B, N,
+                               m.st, f->d_ctr, stamp);
         }
-        hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_waves(n)), dim3(wb), 0, s, F, B, m.st);
-        hipLaunchKernelGGL(pr::merge_tally_kernel,
-                           dim3((unsigned)std::min<int64_t>(256, (n + pr::kTallyThreads - 1) / pr::kTallyThreads)),
-                           dim3(pr::kTallyThreads), 0, s, B, m.st, f->d_ctr, m.arest);
         if (hipGetLastError() != hipSuccess) return fail(PR_EDEVICE, "merge launch failed");
-        if ((r = pool16_extend(f, pool0, s, true))) return r;
-        if ((r = read_counters_raw(f, &c, s))) return r;
-        done = !c.overflow && !c.plan_fallback && !c.bad_path && c.n_add == 0 && c.n_split == 0;
-        if (!c.overflow) {
-            f->dev.n_nodes = (int64_t)c.n_nodes;
-            f->dev.n_pool = (int64_t)c.n_pool;
-        }  // else the first host-driven readback sees the refusal and clips the counters
+        if ((r = run_small_merge(f, B, m.st, s, &ss))) return r;
+        done = ss.done != 0;
+        if (ss.bad)
+            return fail(PR_EDEVICE, "merge invariant broken; destroy the forest");
+        if (ss.overflow && (r = refused_round(f, (int64_t)ss.n_nodes, (int64_t)ss.n_pool, 1, s))) return r;
+        if (ss.overflow || ss.fallback) break;
     }
-    for (; !done && round < max_rounds; round++) {
+    pr::MergeCounters c;
+    std::memset(&c, 0, sizeof(c));
+    const int max_rounds = 100000;
+    int round = 0;
+    int refusals = 0;
+    const bool host_rounds = !done;
+    for (; !done && round < max_rounds; round++, first = 0) {
         hipLaunchKernelGGL(reset_round_kernel, dim3(1), dim3(1), 0, s, f->d_ctr);
-        hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_waves(n)), dim3(wb), 0, s, dev_view(f), B, m.st);
+        hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_waves(n)), dim3(wb), 0, s, dev_view(f), B, m.st, m.arest,
+                           f->d_ctr, first);
         hipLaunchKernelGGL(pr::merge_tally_kernel,
                            dim3((unsigned)std::min<int64_t>(256, (n + pr::kTallyThreads - 1) / pr::kTallyThreads)),
-                           dim3(pr::kTallyThreads), 0, s, B, m.st, f->d_ctr, m.arest);
+                           dim3(pr::kTallyThreads), 0, s, B, m.st, f->d_ctr);
         if ((r = read_counters_raw(f, &c, s))) return r;
         if (c.overflow) {
-            // The last round ran out of capacity.  Every refused allocation
-            // wrote nothing and left its inserts to walk again (above), but
-            // the refused requests still advanced the counters: records and
-            // tokens past the last allocation that fit were never written, so
-            // the counters are clipped to the capacities, and the forest grows
-            // to what the round asked for before the round is repeated.
             if (++refusals > 4) break;  // reported below
-            f->refusals++;
-            const int64_t want_nodes = (int64_t)c.n_nodes, want_pool = (int64_t)c.n_pool;
-            f->dev.n_nodes = std::min<int64_t>(want_nodes, f->dev.cap_nodes);
-            f->dev.n_pool = std::min<int64_t>(want_pool, f->dev.cap_pool);
-            hipLaunchKernelGGL(set_used_kernel, dim3(1), dim3(1), 0, s, f->d_ctr,
-                               (unsigned long long)f->dev.n_nodes, (unsigned long long)f->dev.n_pool);
-            if (hipGetLastError() != hipSuccess) return fail(PR_EDEVICE, "merge launch failed");
-            if ((r = ensure_capacity(f, std::max<int64_t>(want_nodes, f->dev.n_nodes + 1),
-                                     std::max<int64_t>(want_pool, f->dev.n_pool + (int64_t)c.pool_need), s)))
-                return r;
+            if ((r = refused_round(f, (int64_t)c.n_nodes, (int64_t)c.n_pool, (int64_t)c.pool_need, s))) return r;
             continue;
         }
         f->dev.n_nodes = (int64_t)c.n_nodes;
@@ -1170,22 +1102,23 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
         // their move stamps), then the split phase.  The winners of either are
         // done; the losers (the same slot or the same edge as a winner) walk
         // again.  Allocations come from the device counters; one that does not
-        // fit the capacity is refused (see above), so no readback sits between
-        // the phases.  A forest whose spare capacity is short of what the last
-        // merges added grows first (the walk's tally bounds the pool tokens).
-        const int64_t n_split = (int64_t)c.n_split;
+        // fit the capacity is refused (see refused_round), so no readback sits
+        // between the phases.  A forest whose spare capacity is short of what the
+        // last merges added grows first (the walk's tally bounds the pool tokens).
+        const int64_t n_split = (int64_t)c.n_split, n_add = (int64_t)c.n_add;
         if ((r = ensure_capacity(f, f->dev.n_nodes + 2 * std::max<int64_t>(f->round_nodes, n),
                                  f->dev.n_pool + (int64_t)c.pool_need, s)))
             return r;
+        const pr::DevForest F = dev_view(f);
+        const pr::NarrowDst N = narrow_dst(f);
         long long add_stamp = 0;
-        if (c.n_add > 0) {
-            const int64_t n_add = (int64_t)c.n_add;
+        if (n_add > 0) {
             const bool plan = PR_MERGE_PLAN && n_add <= pr::kPlanMax && n <= pr::kPlanMaxBatch;
             if (plan) {
                 // sort, marks, scans and groups in one workgroup
-                hipLaunchKernelGGL(pr::add_plan_kernel, dim3(1), dim3(pr::kPlanThreads), 0, s, dev_view(f), B, m.st,
-                                   m.arest, n_add, m.keys_out, m.vals_out, m.win, m.widx, m.hd, m.cstart, m.grp_nw,
-                                   m.grp_nb, m.win_tok, m.rest, f->d_ctr);
+                hipLaunchKernelGGL(pr::add_plan_kernel, dim3(1), dim3(pr::kPlanThreads), 0, s, F, B, m.st, m.arest,
+                                   n_add, m.keys_out, m.vals_out, m.win, m.widx, m.hd, m.cstart, m.grp_nw, m.grp_nb,
+                                   m.win_tok, m.rest, f->d_ctr);
             } else {
                 hipLaunchKernelGGL(pr::add_keys_kernel, dim3(grid_threads(n, bs)), dim3(bs), 0, s, B, m.st, m.keys_in,
                                    m.vals_in);
@@ -1194,8 +1127,8 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
                                               s) != hipSuccess)
                     return fail(PR_EDEVICE, "radix sort failed");
                 // winners, group heads and chunks; their scans; per-group totals
-                hipLaunchKernelGGL(pr::add_mark_kernel, dim3(grid_threads(n_add + 1, bs)), dim3(bs), 0, s, dev_view(f),
-                                   B, m.keys_out, m.vals_out, n_add, m.st, m.win, m.rest, m.headv, m.nch);
+                hipLaunchKernelGGL(pr::add_mark_kernel, dim3(grid_threads(n_add + 1, bs)), dim3(bs), 0, s, F, B,
+                                   m.keys_out, m.vals_out, n_add, m.st, m.win, m.rest, m.headv, m.nch);
                 size_t t1 = m.sort_tmp_bytes;
                 if (rocprim::exclusive_scan(m.sort_tmp, t1, m.win, m.widx, 0, (size_t)n_add, rocprim::plus<int32_t>(),
                                             s) != hipSuccess)
@@ -1213,33 +1146,22 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
                                             rocprim::plus<int32_t>(), s) != hipSuccess)
                     return fail(PR_EDEVICE, "add scan failed");
                 hipLaunchKernelGGL(reset_round_kernel, dim3(1), dim3(1), 0, s, f->d_ctr);
-                hipLaunchKernelGGL(pr::add_group_kernel, dim3(grid_threads(n_add, bs)), dim3(bs), 0, s, dev_view(f),
+                hipLaunchKernelGGL(pr::add_group_kernel, dim3(grid_threads(n_add, bs)), dim3(bs), 0, s, F,
                                    m.keys_out, m.vals_out, n_add, m.st, m.win, m.rest, m.widx, m.poff, m.hd, m.cstart,
                                    m.grp_nw, m.grp_pool, m.win_tok, m.win_ins, f->d_ctr);
-            }
-            const long long stamp = ++f->stamp;
-            add_stamp = stamp;
-            const pr::DevForest F = dev_view(f);
-            if (!plan)
                 hipLaunchKernelGGL(pr::add_alloc_kernel, dim3(grid_threads(n_add, bs)), dim3(bs), 0, s, F, m.keys_out,
                                    n_add, m.grp_nw, m.grp_pool, m.grp_nb, m.grp_pb, f->d_ctr);
-            hipLaunchKernelGGL(pr::add_move_kernel, dim3(pr::kMoveBlocks), dim3(wb), 0, s, F, m.keys_out, n_add,
-                               m.cstart, f->d_ctr, m.grp_nw, m.grp_nb, m.win_tok, stamp);
-            hipLaunchKernelGGL(pr::add_leaf_kernel, dim3(grid_waves(n_add)), dim3(wb), 0, s, F, B, m.keys_out,
-                               m.vals_out, n_add, m.st, m.win, m.widx, m.poff, m.hd, m.grp_nb, m.grp_pb,
-                               plan ? m.rest : nullptr, f->d_ctr);
-            hipLaunchKernelGGL(pr::add_sep_kernel, dim3(grid_waves(n_add)), dim3(wb), 0, s, F, m.keys_out, n_add,
-                               m.grp_nw, m.grp_nb, f->d_ctr);
-            hipLaunchKernelGGL(pr::add_fix_kernel, dim3(grid_threads(n_add, bs)), dim3(bs), 0, s, F, m.keys_out,
-                               n_add, m.grp_nw, m.grp_nb, stamp, f->d_ctr);
+            }
+            add_stamp = ++f->stamp;
+            hipLaunchKernelGGL(pr::add_build_kernel, dim3(std::max<unsigned>(pr::kMoveBlocks, grid_waves(n_add))), dim3(wb), 0, s,
+                               F, B, N, m.keys_out, m.vals_out, n_add, m.st, m.win, m.widx, m.poff, m.hd, m.cstart,
+                               m.grp_nw, m.grp_nb, m.grp_pb, plan ? m.rest : nullptr, m.win_tok, f->d_ctr, add_stamp);
         }
-        if (n_split > 0) {
-            const pr::DevForest F = dev_view(f);
-            hipLaunchKernelGGL(pr::split_claim_kernel, dim3(grid_threads(n, bs)), dim3(bs), 0, s, F, B, m.st,
-                               add_stamp);
-            hipLaunchKernelGGL(pr::split_apply_kernel, dim3(grid_split(n)), dim3(64 * pr::kSplitWaves), 0, s, F, B,
-                               m.st, f->d_ctr, add_stamp, 0);
-        }
+        hipLaunchKernelGGL(pr::add_finish_kernel, dim3(grid_threads(n, bs)), dim3(bs), 0, s, F, B, m.st, m.keys_out,
+                           n_add, m.grp_nw, m.grp_nb, add_stamp, f->d_ctr);
+        if (n_split > 0)
+            hipLaunchKernelGGL(pr::split_apply_kernel, dim3(grid_split(n)), dim3(64 * pr::kSplitWaves), 0, s, F, B, N,
+                               m.st, f->d_ctr, add_stamp);
         if (hipGetLastError() != hipSuccess) return fail(PR_EDEVICE, "merge launch failed");
     }
     if (round == max_rounds) return fail(PR_EDEVICE, "merge did not converge");
@@ -1248,12 +1170,12 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
     // batches, which adds little, does not shrink it at once)
     f->round_nodes = std::max<int64_t>(f->dev.n_nodes - nodes0, f->round_nodes - f->round_nodes / 8);
     f->round_pool = std::max<int64_t>({f->dev.n_pool - pool0, f->round_pool - f->round_pool / 8, 1});
+    if (!host_rounds) return PR_OK;
+    // the last readback saw the last round's work; the counters are cleared for
+    // the next call
     hipLaunchKernelGGL(add_skipped_kernel, dim3(1), dim3(1), 0, s, f->d_skipped, f->d_ctr);
-    if (hipGetLastError() != hipSuccess) return fail(PR_EDEVICE, "merge launch failed");
-    if (!done) {  // the device-driven rounds read everything back with the narrow copy done
-        if ((r = pool16_extend(f, pool0, s))) return r;
-        if ((r = read_counters(f, &c, s))) return r;
-    }
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
+        return fail(PR_EDEVICE, "merge failed");
     if (c.overflow || c.bad_path)
         return fail(PR_EDEVICE, "merge invariant broken (overflow " + std::to_string(c.overflow) + ", bad paths " +
                                     std::to_string(c.bad_path) + "); destroy the forest");

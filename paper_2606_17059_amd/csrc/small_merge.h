@@ -1,4 +1,5 @@
-// small_merge.h -- a merge (or touch) of at most 64 sequences in one launch.
+// small_merge.h -- a merge (or touch) of at most 64 sequences in one launch,
+// and the last unfinished ones of a larger batch.
 //
 // A node that serves requests one at a time merges and touches batches of one
 // or a few sequences.  The rounds of merge_kernels.h take two dozen dependent
@@ -41,12 +42,16 @@ namespace pr {
 constexpr int kSmallWaves = 16;
 constexpr int kSmallMax = 64;      // inserts: one lane each
 constexpr int kSmallChunks = 256;  // chunks of 64 old children one round moves
+constexpr int kSmallGather = 16;   // inserts a thread looks at for the unfinished ones of a larger batch
+constexpr int64_t kSmallBatch = 64 * kSmallWaves * kSmallGather;
 
 // Written to pinned host memory when the launch ends.
 struct SmallStatus {
     uint32_t done;  // 1: every insert is in; 0: the other kernels go on
     uint32_t hi, wide;  // an appended token is in [65536, 131071], past 131071 (or negative)
     uint32_t stamps;    // stamps taken
+    uint32_t left;      // unfinished inserts found at the start
+    uint32_t overflow, fallback, bad;  // the counters' of the rounds before
     unsigned long long n_nodes, n_pool;
 };
 
@@ -69,10 +74,14 @@ __device__ __forceinline__ int64_t lane_excl(int64_t v, int lane, int64_t *total
 }
 
 // One workgroup.  stamp0: the first stamp not used yet; a round that moves
-// records takes one.
+// records takes one.  st: nullptr for a batch of at most kSmallMax sequences,
+// else the states that rounds of launches left of one of at most kSmallBatch:
+// at most kSmallMax unfinished ones are done here, more are left to further
+// rounds.  Either way the round counters are cleared for the next call.
 __global__ __launch_bounds__(64 *kSmallWaves) void small_merge_kernel(DevForest F, Batch B, NarrowDst N,
                                                                      MergeCounters *ctr,
-                                                                     unsigned long long *skipped_acc, long long stamp0,
+                                                                     unsigned long long *skipped_acc,
+                                                                     const InsState *st, long long stamp0,
                                                                      SmallStatus *out) {
     __shared__ InsState s_st[kSmallMax];
     __shared__ int64_t s_off[kSmallMax], s_len[kSmallMax], s_pb[kSmallMax];
@@ -82,20 +91,42 @@ __global__ __launch_bounds__(64 *kSmallWaves) void small_merge_kernel(DevForest 
     __shared__ int32_t s_win[kSmallMax], s_ord[kSmallMax], s_head[kSmallMax], s_nb[kSmallMax];
     // per group head: the parent's old block, its chunks' prefix, new leaves
     __shared__ int32_t s_beg[kSmallMax], s_cnt[kSmallMax], s_c0[kSmallMax], s_nw[kSmallMax];
+    __shared__ int32_t s_idx[kSmallMax];
+    __shared__ int s_tmp[kSmallWaves];
     __shared__ int s_state, s_chunks;  // s_state: 0 go on, 1 done, 2 leave the rest
     __shared__ uint32_t s_seen, s_skip;
     const int lane = (int)(threadIdx.x & 63);
     const int wv = uniform((int32_t)(threadIdx.x / 64));
-    const int n = (int)B.n;
+    int n = (int)B.n, left = n;
     unsigned long long n_nodes = ctr->n_nodes, n_pool = ctr->n_pool;  // wave 0 keeps them
     uint32_t seen = 0;
     long long stamp = stamp0;
 
+    const bool broken = st && (ctr->overflow || ctr->plan_fallback || ctr->bad_path);
+    if (st) {
+        // the unfinished inserts, in batch order
+        int c = 0, at[kSmallGather];
+#pragma unroll
+        for (int k = 0; k < kSmallGather; k++) {
+            const int i = (int)threadIdx.x * kSmallGather + k;
+            const int32_t kind = i < n ? st[i].kind : kInsSkip;
+            at[k] = kind == kInsSkip || kind == kInsDone ? -1 : c++;
+        }
+        const int before = plan_block_excl<int>(c, 0, [](int a, int b) { return a + b; }, s_tmp, &left);
+#pragma unroll
+        for (int k = 0; k < kSmallGather; k++)
+            if (at[k] >= 0 && before + at[k] < kSmallMax) s_idx[before + at[k]] = (int)threadIdx.x * kSmallGather + k;
+        n = min(left, kSmallMax);
+    } else if (wv == 0) {
+        s_idx[lane] = lane;
+    }
+    __syncthreads();
     if (wv == 0) {
         bool ok = false, bad = false;
         if (lane < n) {
-            const int64_t b = B.offsets[lane], e = B.offsets[lane + 1];
-            const int32_t p = batch_peer(B, lane);
+            const int32_t i = s_idx[lane];
+            const int64_t b = B.offsets[i], e = B.offsets[i + 1];
+            const int32_t p = batch_peer(B, i);
             ok = p >= 0 && p < B.P && b >= 0 && e >= b && e <= B.num_tokens && e - b <= (int64_t)INT32_MAX;
             bad = !ok && !B.touch;
             s_off[lane] = ok ? b : 0;
@@ -105,15 +136,15 @@ __global__ __launch_bounds__(64 *kSmallWaves) void small_merge_kernel(DevForest 
         }
         const uint32_t skip = (uint32_t)__popcll(__ballot(bad));
         if (lane == 0) {
-            s_state = 0;
+            s_state = left > kSmallMax || broken ? 2 : 0;
             s_seen = 0;
-            s_skip = skip;
+            s_skip = st ? (uint32_t)ctr->skipped : skip;
         }
     }
     small_sync();
 
     // every round finishes at least the lowest unfinished insert
-    for (int round = 0; round < 2 * kSmallMax; round++) {
+    for (int round = 0; round < 2 * kSmallMax && s_state == 0; round++) {
         // walk
         for (int i = wv; i < n; i += kSmallWaves) {
             const int32_t kind = s_st[i].kind;
@@ -266,12 +297,24 @@ __global__ __launch_bounds__(64 *kSmallWaves) void small_merge_kernel(DevForest 
     if (lane == 0 && f) atomicOr(&s_seen, f);
     small_sync();
     if (threadIdx.x == 0) {
+        const bool done = s_state == 1;
+        SmallStatus r{};
+        r.done = done;
+        r.hi = (s_seen & 1u) || ctr->hi_tokens;
+        r.wide = (s_seen & 2u) || ctr->wide_tokens;
+        r.stamps = (uint32_t)(stamp - stamp0);
+        r.left = (uint32_t)left;
+        r.overflow = ctr->overflow != 0;
+        r.fallback = ctr->plan_fallback != 0;
+        r.bad = ctr->bad_path != 0;
+        r.n_nodes = n_nodes;
+        r.n_pool = n_pool;
+        // the rounds after these do not look at the entries they skip again
+        if (done || st) *skipped_acc += s_skip;
+        *ctr = MergeCounters{};
         ctr->n_nodes = n_nodes;
         ctr->n_pool = n_pool;
-        const bool done = s_state == 1;
-        if (done) *skipped_acc += s_skip;
         // system scope: straight to the pinned buffer
-        const SmallStatus r{done ? 1u : 0u, s_seen & 1u, s_seen >> 1, (uint32_t)(stamp - stamp0), n_nodes, n_pool};
         const uint64_t *w = reinterpret_cast<const uint64_t *>(&r);
         for (int k = 0; k < (int)(sizeof(r) / 8); k++)
             __hip_atomic_store(reinterpret_cast<uint64_t *>(out) + k, w[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
