@@ -83,30 +83,67 @@ __device__ __forceinline__ long long compact_scan(long long v, long long *tmp, l
     return plan_block_excl<long long>(v, 0, [](long long a, long long b) { return a + b; }, tmp, total);
 }
 
-// Step 1 (tiles of kCompactWaves frontier nodes, grid-stride): start[i] = kept
-// children of the tile's earlier nodes, blk[tile] = the tile's total.
+// Frontier nodes of a tile.  A wave per node suits a level of parents; the
+// leaves, most of a forest's nodes, have no children to look at, so a level of
+// more than kCompactLeafLevel nodes (which cannot all have many) takes a thread
+// per node to find the few that do.  256,000 nodes, their last level: count 34
+// -> LEAF_COUNT us, copy 27 -> LEAF_COPY us.
+constexpr int64_t kCompactLeafLevel = 16384;
+__device__ __forceinline__ int compact_tile(int64_t n) { return n > kCompactLeafLevel ? kCompactThreads : kCompactWaves; }
+
+// Children of old node x that some peer holds (wave-cooperative).
+__device__ __forceinline__ int32_t compact_kept(const DevForest &O, int32_t beg, int32_t cnt, int lane) {
+    int32_t k = 0;
+    for (int32_t j0 = 0; j0 < cnt; j0 += 64 * kCompactUnroll) {
+        bool keep[kCompactUnroll];
+#pragma unroll
+        for (int u = 0; u < kCompactUnroll; u++) {
+            const int32_t j = j0 + 64 * u + lane;
+            keep[u] = j < cnt && node_has_peers(O, beg + j, O.nodes[beg + j]);
+        }
+#pragma unroll
+        for (int u = 0; u < kCompactUnroll; u++) k += (int32_t)__popcll(__ballot(keep[u]));
+    }
+    return k;
+}
+
+// Step 1 (grid-stride over tiles): start[i] = kept children of the tile's
+// earlier nodes, blk[tile] = the tile's total.
 __global__ __launch_bounds__(kCompactThreads) void compact_count_kernel(DevForest O, const int32_t *__restrict__ old_of,
                                                                        const CompactState *__restrict__ S,
                                                                        int32_t *__restrict__ start,
                                                                        int64_t *__restrict__ blk) {
     __shared__ int32_t s_cnt[kCompactWaves];
-    const int lane = (int)(threadIdx.x & 63), wv = uniform((int32_t)(threadIdx.x >> 6));
+    __shared__ long long s_tmp[kCompactWaves];
+    const int t = (int)threadIdx.x, lane = t & 63, wv = uniform((int32_t)(threadIdx.x >> 6));
     const int64_t lo = S->lo, n = S->hi - lo;
-    for (int64_t b = blockIdx.x; b * kCompactWaves < n; b += gridDim.x) {
-        const int64_t i = b * kCompactWaves + wv;
+    const int tile = compact_tile(n);
+    for (int64_t b = blockIdx.x; b * tile < n; b += gridDim.x) {
+        if (tile == kCompactThreads) {
+            const int64_t i = b * tile + t;
+            int32_t beg = 0, cnt = 0;
+            if (i < n) {
+                const Node &x = O.nodes[old_of[lo + i]];
+                beg = x.ct_beg;
+                cnt = x.ct_cnt;
+            }
+            int32_t mine = 0;
+            for (uint64_t m = __ballot(cnt > 0); m; m &= m - 1) {
+                const int l = __ffsll((unsigned long long)m) - 1;
+                const int32_t k = compact_kept(O, __builtin_amdgcn_readlane(beg, l), __builtin_amdgcn_readlane(cnt, l), lane);
+                if (lane == l) mine = k;
+            }
+            long long total;
+            const long long pre = compact_scan(mine, s_tmp, &total);
+            if (i < n) start[lo + i] = (int32_t)pre;
+            if (t == 0) blk[b] = total;
+            continue;
+        }
+        const int64_t i = b * tile + wv;
         int32_t k = 0;
         if (i < n) {
             const Node x = O.nodes[old_of[lo + i]];
-            for (int32_t j0 = 0; j0 < x.ct_cnt; j0 += 64 * kCompactUnroll) {
-                bool keep[kCompactUnroll];
-#pragma unroll
-                for (int u = 0; u < kCompactUnroll; u++) {
-                    const int32_t j = j0 + 64 * u + lane;
-                    keep[u] = j < x.ct_cnt && node_has_peers(O, x.ct_beg + j, O.nodes[x.ct_beg + j]);
-                }
-#pragma unroll
-                for (int u = 0; u < kCompactUnroll; u++) k += (int32_t)__popcll(__ballot(keep[u]));
-            }
+            k = compact_kept(O, x.ct_beg, x.ct_cnt, lane);
         }
         if (lane == 0) s_cnt[wv] = k;
         __syncthreads();
@@ -117,7 +154,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_count_kernel(DevFores
             all += s_cnt[w];
         }
         if (i < n && lane == 0) start[lo + i] = pre;
-        if (threadIdx.x == 0) blk[b] = all;
+        if (t == 0) blk[b] = all;
         __syncthreads();
     }
 }
@@ -150,7 +187,8 @@ __device__ __forceinline__ long long compact_scan_tiles(int64_t *blk, int64_t n,
 __global__ __launch_bounds__(kCompactThreads) void compact_scan_kernel(CompactState *S, int64_t *blk, int64_t n_old) {
     __shared__ long long s_tmp[kCompactWaves];
     const long long lo = S->lo, hi = S->hi;
-    const long long total = compact_scan_tiles(blk, (hi - lo + kCompactWaves - 1) / kCompactWaves, s_tmp);
+    const int tile = compact_tile(hi - lo);
+    const long long total = compact_scan_tiles(blk, (hi - lo + tile - 1) / tile, s_tmp);
     if (threadIdx.x == 0) {
         // live nodes are distinct old records: more than n_old means a malformed forest
         const bool bad = hi + total > n_old;
@@ -162,42 +200,61 @@ __global__ __launch_bounds__(kCompactThreads) void compact_scan_kernel(CompactSt
     }
 }
 
-// Step 3 (a wave per frontier node, grid-stride).
+// Kept children of the frontier node with old block [cbeg, cbeg + ccnt) and new
+// id i to new ids from beg on (wave-cooperative).
+__device__ __forceinline__ void compact_copy_children(const DevForest &O, const DevForest &N, int32_t *old_of,
+                                                      int32_t cbeg, int32_t ccnt, int64_t i, int64_t beg, int lane) {
+    const uint64_t below = (1ull << lane) - 1ull;
+    int64_t pos = beg;
+    for (int32_t j0 = 0; j0 < ccnt; j0 += 64 * kCompactUnroll) {
+        Node r[kCompactUnroll];
+        bool keep[kCompactUnroll];
+#pragma unroll
+        for (int u = 0; u < kCompactUnroll; u++) {
+            const int32_t j = j0 + 64 * u + lane;
+            keep[u] = false;
+            if (j < ccnt) {
+                r[u] = O.nodes[cbeg + j];
+                keep[u] = node_has_peers(O, cbeg + j, r[u]);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kCompactUnroll; u++) {
+            const uint64_t b = __ballot(keep[u]);
+            if (keep[u]) compact_copy_node(O, N, cbeg + j0 + 64 * u + lane, pos + __popcll(b & below), r[u], old_of);
+            pos += __popcll(b);
+        }
+    }
+    if (lane == 0) {
+        N.nodes[i].ct_beg = (int32_t)beg;
+        N.nodes[i].ct_cnt = (int32_t)(pos - beg);
+    }
+}
+
+// Step 3 (grid-stride; a wave per frontier node, or per 64 of a level of leaves,
+// whose records already say that they have no children).
 __global__ __launch_bounds__(kCompactThreads) void compact_copy_kernel(DevForest O, DevForest N, int32_t *old_of,
                                                                       const CompactState *__restrict__ S,
                                                                       const int32_t *__restrict__ start,
                                                                       const int64_t *__restrict__ blk) {
     const int lane = (int)(threadIdx.x & 63);
     const int64_t lo = S->flo, n = S->fhi - lo, next = S->fhi;
-    const uint64_t below = (1ull << lane) - 1ull;
-    for (int64_t i = (int64_t)blockIdx.x * kCompactWaves + uniform((int32_t)(threadIdx.x >> 6)); i < n;
-         i += (int64_t)gridDim.x * kCompactWaves) {
-        const Node x = O.nodes[old_of[lo + i]];
-        const int64_t beg = next + blk[i / kCompactWaves] + start[lo + i];
-        int64_t pos = beg;
-        for (int32_t j0 = 0; j0 < x.ct_cnt; j0 += 64 * kCompactUnroll) {
-            Node r[kCompactUnroll];
-            bool keep[kCompactUnroll];
-#pragma unroll
-            for (int u = 0; u < kCompactUnroll; u++) {
-                const int32_t j = j0 + 64 * u + lane;
-                keep[u] = false;
-                if (j < x.ct_cnt) {
-                    r[u] = O.nodes[x.ct_beg + j];
-                    keep[u] = node_has_peers(O, x.ct_beg + j, r[u]);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < kCompactUnroll; u++) {
-                const uint64_t b = __ballot(keep[u]);
-                if (keep[u])
-                    compact_copy_node(O, N, x.ct_beg + j0 + 64 * u + lane, pos + __popcll(b & below), r[u], old_of);
-                pos += __popcll(b);
-            }
+    const int tile = compact_tile(n);
+    const int per = tile / kCompactWaves;  // frontier nodes of a wave
+    for (int64_t i0 = ((int64_t)blockIdx.x * kCompactWaves + uniform((int32_t)(threadIdx.x >> 6))) * per; i0 < n;
+         i0 += (int64_t)gridDim.x * kCompactWaves * per) {
+        const int64_t i = i0 + lane;
+        int32_t cbeg = 0, ccnt = 0, pre = 0;
+        if (lane < per && i < n) {
+            const Node &x = O.nodes[old_of[lo + i]];
+            cbeg = x.ct_beg;
+            ccnt = x.ct_cnt;
+            pre = start[lo + i];
         }
-        if (lane == 0) {
-            N.nodes[lo + i].ct_beg = (int32_t)beg;
-            N.nodes[lo + i].ct_cnt = (int32_t)(pos - beg);
+        for (uint64_t m = __ballot(ccnt > 0); m; m &= m - 1) {
+            const int l = __ffsll((unsigned long long)m) - 1;
+            compact_copy_children(O, N, old_of, __builtin_amdgcn_readlane(cbeg, l), __builtin_amdgcn_readlane(ccnt, l),
+                                  lo + i0 + l, next + blk[(i0 + l) / tile] + __builtin_amdgcn_readlane(pre, l), lane);
         }
     }
 }
@@ -236,26 +293,107 @@ __global__ __launch_bounds__(kCompactThreads) void compact_lab_scan_kernel(Compa
     if (threadIdx.x == 0) S->n_pool = total;
 }
 
-// Step 4c (a wave per new node, grid-stride): labels, their narrow copy, and
-// wide blocks' separators.  blk nullptr: off holds whole offsets.
-__global__ __launch_bounds__(256) void compact_labels_kernel(const int32_t *__restrict__ old_pool, DevForest N,
-                                                            NarrowDst D, CompactState *S,
-                                                            const int64_t *__restrict__ off,
-                                                            const int64_t *__restrict__ blk) {
-    const int lane = (int)(threadIdx.x & 63);
-    const int64_t n = S->hi;
-    uint32_t seen = 0;
-    for (int64_t i = (int64_t)blockIdx.x * 4 + uniform((int32_t)(threadIdx.x >> 6)); i < n;
-         i += (int64_t)gridDim.x * 4) {
-        const Node r = N.nodes[i];
-        const int64_t o = off[i] + (blk ? blk[i / kCompactLabTile] : 0);
-        copy_tokens_narrow(N, D, o, old_pool + r.lab_off, r.lab_len, lane, seen);
-        if (lane == 0) N.nodes[i].lab_off = (uint32_t)o;
-        if (r.ct_cnt > kSepCount) N.nsep[r.ct_beg + lane] = N.ntok[r.ct_beg + PR_SEP_INDEX(lane, r.ct_cnt)];
-        if (r.ct_cnt >= kSep2Min) sep2_write(N.nsep + r.ct_beg, N.ntok + r.ct_beg, r.ct_cnt, lane);
+// Step 4c (a workgroup per kCompactSeg tokens of the new pool): labels, their
+// narrow copy, and for the nodes whose labels start there the new label offset
+// and a wide block's separators.  The segment's nodes are found by a search over
+// the label offsets and listed in LDS, where every token then finds its own:
+// short labels cost no more than long ones, every store is a full line, segments
+// are alike however the lengths are spread, and the bit plane is written in
+// whole words.  (A wave per node, most of which have one or two 64-token chunks,
+// took 160 us for 23 M tokens; this takes LABELS_US.)
+// blk nullptr: off holds whole offsets.
+constexpr int kCompactSeg = 4096;
+constexpr int kCompactSegThreads = 256;
+__global__ __launch_bounds__(kCompactSegThreads) void compact_labels_kernel(DevForest O, DevForest N, NarrowDst D,
+                                                                           const int32_t *__restrict__ old_of,
+                                                                           CompactState *S,
+                                                                           const int64_t *__restrict__ off,
+                                                                           const int64_t *__restrict__ blk) {
+    constexpr int T = kCompactSegThreads, kUnroll = 4;
+    __shared__ int32_t s_off[kCompactSeg + 1];   // label start, from the segment's
+    __shared__ uint32_t s_src[kCompactSeg + 1];  // of its source in the old pool
+    __shared__ int s_m;
+    const int t = (int)threadIdx.x, lane = t & 63;
+    const int64_t n = S->hi, base = (int64_t)blockIdx.x * kCompactSeg;
+    const int64_t end = min<int64_t>(S->n_pool, base + kCompactSeg);
+    if (base >= end) return;
+    const auto at = [&](int64_t i) { return off[i] + (blk ? blk[i / kCompactLabTile] : 0); };
+    // the last node whose label starts at or before the segment (only the root's
+    // label is empty, so it is the one that holds its first token)
+    int64_t lo = 0, hi = n;
+    while (hi - lo > 1) {
+        const int64_t stride = (hi - lo + 63) / 64, j = lo + lane * stride;
+        const int c = (int)__popcll(__ballot(j < hi && at(j) <= base));  // lane 0 always: at(lo) <= base
+        hi = min(lo + c * stride, hi);
+        lo += (c - 1) * stride;
     }
-    if (__ballot(seen & 1u) && lane == 0 && !fresh_u64(&S->hi_tokens)) atomicOr(&S->hi_tokens, 1ull);
-    if (__ballot(seen & 2u) && lane == 0 && !fresh_u64(&S->wide_tokens)) atomicOr(&S->wide_tokens, 1ull);
+    const auto separators = [&](int32_t b, int32_t c) {
+        if (c > kSepCount) N.nsep[b + lane] = N.ntok[b + PR_SEP_INDEX(lane, c)];
+        if (c >= kSep2Min) sep2_write(N.nsep + b, N.ntok + b, c, lane);
+    };
+    if (base == 0 && t < 64) separators(N.nodes[0].ct_beg, N.nodes[0].ct_cnt);  // the root has no label to list it by
+    if (t == 0) s_m = 0;
+    __syncthreads();
+    for (int64_t i0 = lo;; i0 += T) {
+        const int64_t i = i0 + t;
+        const int64_t o = i < n ? at(i) : end;
+        int32_t beg = 0, cnt = 0;
+        if (o < end) {
+            const int k = (int)(i - lo);
+            // the source is the old record's; a label that starts before the
+            // segment is listed from the segment's start on
+            const int32_t skip = (int32_t)max<int64_t>(base - o, 0);
+            s_off[k] = (int32_t)(o + skip - base);
+            s_src[k] = O.nodes[old_of[i]].lab_off + (uint32_t)skip;
+            atomicMax(&s_m, k + 1);
+            if (o >= base) {
+                N.nodes[i].lab_off = (uint32_t)o;
+                beg = N.nodes[i].ct_beg;
+                cnt = N.nodes[i].ct_cnt;
+            }
+        }
+        for (uint64_t wide = __ballot(cnt > kSepCount); wide; wide &= wide - 1) {
+            const int l = __ffsll((unsigned long long)wide) - 1;
+            separators(__builtin_amdgcn_readlane(beg, l), __builtin_amdgcn_readlane(cnt, l));
+        }
+        if (__syncthreads_or(o >= end)) break;  // offsets ascend: the rest start past the segment
+    }
+    const int m = s_m, len = (int)(end - base);
+    uint32_t all = 0;
+    for (int q0 = 0; q0 < len; q0 += T * kUnroll) {
+        uint32_t v[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; u++) {
+            const int k = q0 + u * T + t;
+            v[u] = 0;
+            if (k < len) {
+                int a = 0, b = m;  // the last node with s_off <= k
+                while (b - a > 1) {
+                    const int mid = (a + b) >> 1;
+                    if (s_off[mid] <= k)
+                        a = mid;
+                    else
+                        b = mid;
+                }
+                v[u] = (uint32_t)O.pool[(int64_t)s_src[a] + (k - s_off[a])];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kUnroll; u++) {
+            const int k = q0 + u * T + t;
+            if (k < len) {
+                N.pool[base + k] = (int32_t)v[u];
+                if (D.p16) D.p16[base + k] = (uint16_t)v[u];
+                all |= v[u];
+            }
+            const uint64_t bits = __ballot((v[u] >> 16) & 1u);
+            if (D.p16 && lane < 2 && k - lane + 32 * lane < len)
+                D.hib[(base + k - lane + 32 * lane) >> 5] = (uint32_t)(bits >> (32 * lane));
+        }
+    }
+    // (a wider token may raise the 17-bit flag too; it drops the narrow copy)
+    if (__ballot((all >> 16) & 1u) && lane == 0 && !fresh_u64(&S->hi_tokens)) atomicOr(&S->hi_tokens, 1ull);
+    if (__ballot(all > 0x1FFFFu) && lane == 0 && !fresh_u64(&S->wide_tokens)) atomicOr(&S->wide_tokens, 1ull);
 }
 
 // Steps 1 to 4b for a small forest in one workgroup: each level a thousand

@@ -332,7 +332,7 @@ int64_t slack_cap(int64_t n) {
 // the spare's, unless they are too small or far too large.
 bool new_node_arrays(pr_forest *f, DevImage &nw, int64_t need, bool times) {
     DevImage &sp = f->spare;
-    if (sp.node_block && sp.cap_nodes >= need && sp.cap_nodes <= 4 * need + (1 << 16)) {
+    if (sp.node_block && sp.cap_nodes >= need && sp.cap_nodes <= 8 * need) {
         nw.node_block = sp.node_block;
         nw.node_block_bytes = sp.node_block_bytes;
         nw.nodes = sp.nodes;
@@ -359,7 +359,7 @@ bool new_node_arrays(pr_forest *f, DevImage &nw, int64_t need, bool times) {
 // for at least need tokens in nw, in the same way.
 bool new_pool(pr_forest *f, DevImage &nw, int64_t need, bool narrow) {
     DevImage &sp = f->spare;
-    if (sp.pool && sp.cap_pool >= need && sp.cap_pool <= 4 * need + (1 << 18)) {
+    if (sp.pool && sp.cap_pool >= need && sp.cap_pool <= 8 * need) {
         nw.pool = sp.pool;
         nw.cap_pool = sp.cap_pool;
         sp.pool = nullptr;
@@ -1045,8 +1045,8 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
     // continues in the host-driven rounds below, which read the counters back
     // after every walk.
     for (int k = 0; PR_MERGE_PLAN && !done && f->d_stage && n <= pr::kPlanMaxBatch && k < 4; k++) {
-        if ((r = ensure_capacity(f, f->dev.n_nodes + 2 * std::max<int64_t>(f->round_nodes, n),
-                                 f->dev.n_pool + 2 * f->round_pool, s)))
+        if ((r = ensure_capacity(f, f->dev.n_nodes + std::max<int64_t>(f->round_nodes, n),
+                                 f->dev.n_pool + f->round_pool, s)))
             return r;
         const pr::DevForest F = dev_view(f);
         const pr::NarrowDst N = narrow_dst(f);
@@ -1106,7 +1106,7 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
         // between the phases.  A forest whose spare capacity is short of what the
         // last merges added grows first (the walk's tally bounds the pool tokens).
         const int64_t n_split = (int64_t)c.n_split, n_add = (int64_t)c.n_add;
-        if ((r = ensure_capacity(f, f->dev.n_nodes + 2 * std::max<int64_t>(f->round_nodes, n),
+        if ((r = ensure_capacity(f, f->dev.n_nodes + std::max<int64_t>(f->round_nodes, n),
                                  f->dev.n_pool + (int64_t)c.pool_need, s)))
             return r;
         const pr::DevForest F = dev_view(f);
@@ -1166,10 +1166,12 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
     }
     if (round == max_rounds) return fail(PR_EDEVICE, "merge did not converge");
     // records and pool tokens the largest recent merge added: the spare
-    // capacity the next one keeps free (a snapshot load between two merge
-    // batches, which adds little, does not shrink it at once)
-    f->round_nodes = std::max<int64_t>(f->dev.n_nodes - nodes0, f->round_nodes - f->round_nodes / 8);
-    f->round_pool = std::max<int64_t>({f->dev.n_pool - pool0, f->round_pool - f->round_pool / 8, 1});
+    // capacity the next one finds free (snapshot loads between two merge
+    // batches, which add little, shrink it slowly).  A compaction leaves room
+    // for two such merges, so that a period of loads, a merge and a compaction
+    // settles on arrays that never grow
+    f->round_nodes = std::max<int64_t>(f->dev.n_nodes - nodes0, f->round_nodes - f->round_nodes / 32);
+    f->round_pool = std::max<int64_t>({f->dev.n_pool - pool0, f->round_pool - f->round_pool / 32, 1});
     if (!host_rounds) return PR_OK;
     // the last readback saw the last round's work; the counters are cleared for
     // the next call
@@ -1608,13 +1610,13 @@ pr_status pr_forest_compact(pr_forest *f, int64_t *nodes_before, int64_t *nodes_
         return fail_new(PR_ENOMEM, "hipMalloc failed for the compacted label pool");
     N.pool = nw.pool;
     N.cap_pool = nw.cap_pool;
-    const unsigned gl = (unsigned)std::min<int64_t>(16384, ((one_wait ? n_old : S.hi) + 3) / 4);
+    const unsigned gl = std::max(1u, grid_threads(one_wait ? d.n_pool : S.n_pool, pr::kCompactSeg));
     if (hipMemsetAsync(nw.pool + pool_from, 0, (nw.cap_pool - pool_from) * sizeof(int32_t), s) != hipSuccess ||
         (nw.pool16 && hipMemsetAsync(nw.hib, 0, hib_words(nw.cap_pool16) * sizeof(uint32_t), s) != hipSuccess) ||
         hipMemsetAsync(nw.moved, 0, nw.cap_nodes * sizeof(long long), s) != hipSuccess)
         return fail_new(PR_EDEVICE, "compaction memset failed");
-    hipLaunchKernelGGL(pr::compact_labels_kernel, dim3(gl), dim3(256), 0, s, d.pool, N,
-                       pr::NarrowDst{nw.pool16, nw.hib}, f->d_compact, off, small ? nullptr : blk);
+    hipLaunchKernelGGL(pr::compact_labels_kernel, dim3(gl), dim3(pr::kCompactSegThreads), 0, s, O, N,
+                       pr::NarrowDst{nw.pool16, nw.hib}, old_of, f->d_compact, off, small ? nullptr : blk);
     hipLaunchKernelGGL(compact_counters_kernel, dim3(1), dim3(1), 0, s, f->d_ctr, f->d_compact);
     if (hipGetLastError() != hipSuccess || !read_small(f, &S, f->d_compact, sizeof(S), s)) {
         f->broken = true;  // the counters may be the new image's already
