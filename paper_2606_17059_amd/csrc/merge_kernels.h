@@ -41,6 +41,7 @@
 #include <stdint.h>
 
 #include "forest_layout.h"
+#include "lcp.h"
 #include "wave_ops.h"
 
 namespace pr {
@@ -70,15 +71,13 @@ struct MergeCounters {
     unsigned long long move_chunks;  // add round: 64-child chunks of the old blocks that move
     unsigned long long wide_tokens;  // nonzero: an appended label token lies outside [0, 131071] (no narrow copy)
     unsigned long long hi_tokens;    // nonzero: an appended label token lies in [65536, 131071] (17-bit labels)
-    unsigned long long add_pool_base;  // add round planned in one workgroup: first pool token of its labels
-    unsigned long long plan_n;         // ADD entries the one-workgroup plan took this round (0: none)
-    unsigned long long plan_fallback;  // nonzero: a round's ADD entries did not fit the one-workgroup plan
+    unsigned long long plan_alloc;     // the round's planned ADD entries << 32 | chunks that move for them
+    unsigned long long plan_fallback;  // nonzero: a round had a plan bucket too large for its workgroup
 };
 
-// Entry count of an add step: the host's, or (n_add < 0, rounds the host does
-// not read back) the one-workgroup plan's.
+// Entry count of an add step: the host's, or (n_add < 0) the plan kernel's.
 __device__ __forceinline__ int64_t add_count(int64_t n_add, const MergeCounters *ctr) {
-    return n_add >= 0 ? n_add : (int64_t)ctr->plan_n;
+    return n_add >= 0 ? n_add : (int64_t)(ctr->plan_alloc >> 32);
 }
 
 struct DevForest {
@@ -126,27 +125,6 @@ __device__ __forceinline__ unsigned long long wave_atomic_add(unsigned long long
     return (unsigned long long)readlane64((uint64_t)r, 0);
 }
 
-// First i < n with a[i] != b[i], or n (wave-cooperative).  Steps of 1024
-// tokens: a step's loads are all issued before its first wait, so a 1024-token
-// label costs one round trip.
-constexpr int kMergeLcpVectors = 16;
-__device__ __forceinline__ int64_t m_lcp(const int32_t *a, const int32_t *b, int64_t n, int lane) {
-    for (int64_t base = 0; base < n; base += 64 * kMergeLcpVectors) {
-        uint64_t bal[kMergeLcpVectors];
-#pragma unroll
-        for (int j = 0; j < kMergeLcpVectors; j++) {
-            const int64_t i = base + j * 64 + lane;
-            bool mis = false;
-            if (i < n) mis = a[i] != b[i];
-            bal[j] = __ballot(mis);
-        }
-#pragma unroll
-        for (int j = 0; j < kMergeLcpVectors; j++)
-            if (bal[j]) return base + j * 64 + (__ffsll((unsigned long long)bal[j]) - 1);
-    }
-    return n;
-}
-
 // The insert's peer bit in node x's mask, set only where it is missing (the
 // nodes near the root lie on almost every path, and atomics on one address
 // serialise); inserts into the local peer also stamp x with the current time.
@@ -179,18 +157,33 @@ __device__ __forceinline__ void sep2_write(int32_t *sep, const int32_t *tok, int
     }
 }
 
-// Child of node x whose first token is t, or -1 (wave-cooperative).  Blocks
-// of up to 64 children take one ballot over their first tokens; wider blocks
-// first pick their sub-range through the block's 64 separators (and, from
-// kSep2Min children on, through the sub-range's own 64).
-__device__ __forceinline__ int32_t m_find_child(const DevForest &F, const Node &x, int32_t t, int lane) {
-    const int32_t beg = x.ct_beg, cnt = x.ct_cnt;
+// A node's child block as a wave holds it: lane j the first token of child j
+// (up to 64 children) or separator j.
+struct MergeBlock {
+    int32_t beg, cnt, tok;
+};
+
+__device__ __forceinline__ MergeBlock m_load_block(const DevForest &F, int32_t beg, int32_t cnt, int lane) {
+    MergeBlock b{beg, cnt, 0};
+    if (cnt > kSepCount)
+        b.tok = F.nsep[beg + lane];
+    else if (lane < cnt)
+        b.tok = F.ntok[beg + lane];
+    return b;
+}
+
+// Child whose first token is t, or -1 (wave-cooperative).  Blocks of up to 64
+// children take one ballot over their first tokens; wider blocks first pick
+// their sub-range through the block's 64 separators (and, from kSep2Min
+// children on, through the sub-range's own 64).
+__device__ __forceinline__ int32_t m_find_child(const DevForest &F, const MergeBlock &x, int32_t t, int lane) {
+    const int32_t beg = x.beg, cnt = x.cnt;
     if (cnt <= kSepCount) {
-        const uint64_t b = __ballot(lane < cnt && F.ntok[beg + lane] == t);
+        const uint64_t b = __ballot(lane < cnt && x.tok == t);
         return b ? beg + (int32_t)(__ffsll((unsigned long long)b) - 1) : -1;
     }
     // separators ascend, so the lanes with sep <= t form a prefix
-    const uint64_t b = __ballot(F.nsep[beg + lane] <= t);
+    const uint64_t b = __ballot(x.tok <= t);
     if (!b) return -1;  // t is below every first token
     const int32_t k = (int32_t)__popcll(b) - 1;
     int32_t lo = PR_SEP_INDEX(k, cnt);
@@ -220,66 +213,67 @@ __device__ __forceinline__ int32_t m_find_child(const DevForest &F, const Node &
 // as DONE, ADD or SPLIT, setting the peer's bit in every node it passes through
 // whole.  A touch walks p's tree only: it is DONE where no child holds p, and
 // SPLIT where p's tree goes on but the query leaves (or ends inside) the label.
-// Wave-cooperative; every lane returns the same state.
+// Wave-cooperative; every lane returns the same state.  As in the route kernel,
+// a level's loads go out together: the child's record first, then the token
+// after its label, its own child block and the label compare (two round trips
+// a level; one after the other they took four).
 __device__ __forceinline__ InsState m_walk(const DevForest &F, const int32_t *s, int64_t len, int32_t p, bool touch,
                                            bool stamp, int lane) {
     const int32_t w = p >> 6;
     const unsigned long long bit = 1ull << (p & 63);
-    int32_t x = 0;
-    int64_t d = 0;
     InsState r;
+    r.kind = kInsDone;
+    r.x = 0;
     r.c = -1;
     r.l = 0;
     r.t = 0;
-    if (lane == 0) m_mark(F, 0, F.nodes[0].mask0, w, bit, stamp);
-    while (true) {
-        if (d == len) {
-            r.kind = kInsDone;
-            break;
-        }
-        const Node nx = F.nodes[x];
-        const int32_t t = s[d];
-        const int32_t c = m_find_child(F, nx, t, lane);
+    int64_t d = 0;
+    const Node root = F.nodes[0];
+    int32_t t = len > 0 ? s[0] : 0;
+    MergeBlock cb = m_load_block(F, root.ct_beg, root.ct_cnt, lane);
+    if (lane == 0) m_mark(F, 0, root.mask0, w, bit, stamp);
+    while (d < len) {
+        const int32_t c = m_find_child(F, cb, t, lane);
         if (c < 0) {
             r.kind = touch ? kInsDone : kInsAdd;
             r.t = t;
             break;
         }
         const Node nc = F.nodes[c];
-        if (touch) {
-            const uint64_t held = w == 0 ? nc.mask0 : F.mext[(int64_t)c * (F.W - 1) + (w - 1)];
-            if (!(held & bit)) {
-                r.kind = kInsDone;
-                break;
-            }
+        const int64_t end = d + nc.lab_len;
+        const int32_t tnext = end < len ? s[end] : 0;
+        uint64_t held = bit;
+        if (touch) held = w == 0 ? nc.mask0 : F.mext[(int64_t)c * (F.W - 1) + (w - 1)];
+        cb = m_load_block(F, nc.ct_beg, nc.ct_cnt, lane);
+        const LabelSrc<int32_t, false> lab{F.pool + nc.lab_off, nullptr, nc.lab_off};
+        const int64_t l = wave_lcp<int32_t, false>(lab, s + d, min((int64_t)nc.lab_len, len - d), 0,
+                                                   (int64_t)kWave * kLcpVectors, lane);
+        if (!(held & bit)) break;  // a touch: the peer's tree ends at the parent
+        if (l < nc.lab_len || nc.lab_len <= 0) {
+            r.kind = kInsSplit;
+            r.c = c;
+            r.l = (int32_t)l;
+            r.t = t;
+            break;
         }
-        const int64_t n = min((int64_t)nc.lab_len, len - d);
-        const int64_t l = m_lcp(F.pool + nc.lab_off, s + d, n, lane);
-        if (l == nc.lab_len && nc.lab_len > 0) {
-            x = c;
-            d += l;
-            if (lane == 0) m_mark(F, c, nc.mask0, w, bit, stamp);
-            continue;
-        }
-        r.kind = kInsSplit;
-        r.c = c;
-        r.l = (int32_t)l;
-        r.t = t;
-        break;
+        r.x = c;
+        d = end;
+        t = tnext;
+        if (lane == 0) m_mark(F, c, nc.mask0, w, bit, stamp);
     }
-    r.x = x;
     r.d = (int32_t)d;
     return r;
 }
 
 // Walk every unfinished insert.  first: nothing has looked at the batch yet;
-// invalid entries are skipped and counted (touches ignore them).  arest[i]
-// (nullptr: not wanted) gets the label tokens an ADD insert needs, else -1.
+// invalid entries are skipped and counted (touches ignore them).  addx[i] gets
+// the parent of an ADD insert, else -1, arest[i] the label tokens it needs.
 __global__ __launch_bounds__(64 *kMergeWavesPerBlock) void merge_walk_kernel(DevForest F, Batch B, InsState *st,
-                                                                            int32_t *arest, MergeCounters *ctr,
-                                                                            int first) {
+                                                                            int32_t *addx, int32_t *arest,
+                                                                            MergeCounters *ctr, int first) {
     const int lane = (int)(threadIdx.x & 63);
     const int64_t i = m_wave_index();
+    if (blockIdx.x == 0 && threadIdx.x == 0) ctr->plan_alloc = 0;  // the round's plan starts from nothing
     if (i >= B.n) return;
     const int64_t b = B.offsets[i], e = B.offsets[i + 1];
     const int32_t p = batch_peer(B, i);
@@ -295,13 +289,14 @@ __global__ __launch_bounds__(64 *kMergeWavesPerBlock) void merge_walk_kernel(Dev
         walk = kind != kInsSkip && kind != kInsDone;
     }
     if (!walk) {
-        if (arest && lane == 0) arest[i] = -1;
+        if (lane == 0) addx[i] = -1;
         return;
     }
     const InsState r = m_walk(F, B.tokens + b, e - b, p, B.touch, F.ltime && B.stamp && p == F.local, lane);
     if (lane == 0) {
         st[i] = r;
-        if (arest) arest[i] = r.kind == kInsAdd ? (int32_t)(e - b - r.d) : -1;
+        addx[i] = r.kind == kInsAdd ? r.x : -1;
+        arest[i] = (int32_t)(e - b - r.d);
     }
 }
 
@@ -672,33 +667,47 @@ __global__ void add_group_kernel(DevForest F, const unsigned long long *keys, co
     if (e == n_add - 1) ctr->move_chunks = (unsigned long long)cstart[n_add];
 }
 
-// ---- the add plan in one workgroup -------------------------------------------
-// For a round whose ADD entries fit one workgroup's LDS, one launch replaces
-// steps 0-3 (sort keys, radix sort, marks, the four scans, groups and their
-// allocation):
-//  1. the batch is read in coalesced chunks; ADD entries are gathered in batch
-//     order;
-//  2. parents are numbered through a hash table in LDS, so that the sort key
-//     (parent slot, token) needs about 11 + 17 bits instead of 31 + 32; with
-//     more distinct parents than the table takes, the key keeps the node id;
+// ---- the add plan in one launch ---------------------------------------------
+// For batches of up to kPlanMaxBatch inserts one launch replaces steps 0-3 (sort
+// keys, radix sort, marks, the four scans, groups and their allocation).  The
+// parents are spread over the workgroups by a hash, and each plans its own:
+//  1. the batch is read in coalesced chunks; the workgroup's ADD entries are
+//     gathered in batch order;
+//  2. up to kPlanSmall of them are ranked by counting.  More (a hot parent)
+//     are sorted: parents are numbered through a hash table in LDS, so that
+//     the sort key (parent slot, token) needs about 11 + 17 bits instead of
+//     31 + 32; with more distinct parents than the table takes, the key keeps
+//     the node id;
 //  3. a stable least-significant-digit radix sort in LDS, 4-bit digits, a pass
 //     only for digits that differ between keys; digit counts are LDS atomics on
 //     each thread's own counters, which also give the entry's rank among the
 //     thread's entries of that digit;
-//  4. marks and scans in registers; one node allocation for every rebuilt
-//     block of the round and one label allocation for its winners (`pofs`,
-//     indexed by insert), refused as a whole when the capacity runs out.
+//  4. marks and scans in registers; one allocation of entry places and moving
+//     chunks, one of records for the workgroup's rebuilt blocks and one of
+//     label tokens for its winners (`pofs`, indexed by insert), the last two
+//     refused as a whole when the capacity runs out.
 // The outputs keep the multi-launch path's layout (keys hold the parent's node
-// id), so the move, leaf, separator and fix steps serve both paths.
+// id), so the build and finish steps serve both paths.  10,000 entries in 512
+// parents, a fifth of them in the hottest: 82-107 us in one workgroup, PLAN_US
+// in 64.
 constexpr int kPlanThreads = 1024;
 constexpr int kPlanItems = 10;                              // sorted entries per thread
-constexpr int kPlanMax = kPlanThreads * kPlanItems;         // ADD entries per round
+constexpr int kPlanMax = kPlanThreads * kPlanItems;         // ADD entries per workgroup
 constexpr int kPlanBatchItems = 16;                         // batch chunks of kPlanThreads
 constexpr int64_t kPlanMaxBatch = (int64_t)kPlanThreads * kPlanBatchItems;  // insert ids fit 16 bits
 constexpr int kPlanWaves = kPlanThreads / 64;
 constexpr int kPlanSlots = 2048;                            // parent hash table
 constexpr int kPlanMaxParents = kPlanSlots / 2;
-constexpr int kPlanSmall = 256;                             // rounds ranked by counting instead
+constexpr int kPlanSmall = 256;                             // entries ranked by counting instead
+constexpr int kPlanMaxBlocks = 64;
+
+// Workgroups of a plan for n inserts: about 128 each, so that most rank by
+// counting and none waits on many.
+inline int plan_blocks(int64_t n) {
+    int g = 1;
+    while (g < kPlanMaxBlocks && g * 128 < n) g *= 2;
+    return g;
+}
 
 // Inclusive scan over the wave.
 template <typename T, typename Op>
@@ -752,6 +761,11 @@ __device__ __forceinline__ uint32_t plan_hash(int32_t x) {
     return ((uint32_t)x * 2654435761u) >> 21;  // 11 bits: kPlanSlots
 }
 
+// The workgroup (of a power of two of them) that plans parent x.
+__device__ __forceinline__ uint32_t plan_bucket(int32_t x, uint32_t blocks) {
+    return (((uint32_t)x * 0x9E3779B1u) >> 24) & (blocks - 1);
+}
+
 // Slot of parent x in the table (x >= 0), inserting it; -1 when the table is full.
 __device__ __forceinline__ int plan_slot_insert(int32_t *tab, int *n_new, int32_t x) {
     uint32_t h = plan_hash(x);
@@ -782,16 +796,11 @@ __device__ __forceinline__ int plan_slot_find(const int32_t *tab, int32_t x) {
 __device__ __forceinline__ int plan_pad(int p) { return p + (p >> 5); }
 constexpr int kPlanPadded = kPlanMax + kPlanMax / 32;
 
-// One workgroup of kPlanThreads, for batches of at most kPlanMaxBatch inserts
-// whose round has at most kPlanMax ADD entries.  arest: the walk's label tokens
-// per insert (-1: not ADD).  n_add: the host's tally of ADD inserts (a count
-// that differs raises bad_path and plans nothing; the merge then fails), or -1
-// for rounds the host does not read back (a round that does not fit then
-// raises plan_fallback and plans nothing).  pofs[i]: the label span of ADD
-// winner i from the round's pool base (ctr->add_pool_base); ctr->plan_n: the
-// entries planned.
+// plan_blocks(B.n) workgroups of kPlanThreads, B.n <= kPlanMaxBatch.  addx,
+// arest: the walk's parents (-1: not ADD) and label tokens.  A workgroup with
+// more than kPlanMax entries plans none and raises plan_fallback.
 __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Batch B, const InsState *st,
-                                                                const int32_t *arest, int64_t n_add,
+                                                                const int32_t *addx, const int32_t *arest,
                                                                 unsigned long long *keys, int32_t *vals,
                                                                 int32_t *win, int32_t *widx, int32_t *hd,
                                                                 int32_t *cstart, int32_t *grp_nw, int32_t *grp_nb,
@@ -807,6 +816,7 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
     __shared__ long long s_tmp[kPlanWaves];
     __shared__ int s_tmp32[kPlanWaves];
     __shared__ int s_misc[4];                                // distinct parents, table full, ADD entries
+    __shared__ unsigned long long s_place;                   // first entry << 32 | first chunk
     constexpr int T = kPlanThreads;
     const int t = (int)threadIdx.x;
     const int lane = t & 63, wv = t >> 6;
@@ -821,14 +831,14 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
     // (chunk, wave), in batch order
     const int n = (int)min<int64_t>(B.n, kPlanMaxBatch);
     const int R = (n + T - 1) / T;
-    int32_t ar[kPlanBatchItems];
+    int32_t ax[kPlanBatchItems];
 #pragma unroll
-    for (int j = 0; j < kPlanBatchItems; j++) ar[j] = (j < R && j * T + t < n) ? arest[j * T + t] : -1;
+    for (int j = 0; j < kPlanBatchItems; j++) ax[j] = (j < R && j * T + t < n) ? addx[j * T + t] : -1;
     uint32_t addbits = 0;
 #pragma unroll
     for (int j = 0; j < kPlanBatchItems; j++) {
         if (j < R) {
-            const bool a = ar[j] >= 0;
+            const bool a = ax[j] >= 0 && plan_bucket(ax[j], gridDim.x) == blockIdx.x;
             addbits |= (uint32_t)a << j;
             const uint64_t bal = __ballot(a);
             if (lane == 63) s_cw[j * kPlanWaves + wv] = (int)__popcll(bal);
@@ -856,14 +866,8 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
     }
     __syncthreads();
     const int m = s_misc[3];
-    const bool bad = B.n > kPlanMaxBatch || (n_add >= 0 && (int64_t)m != n_add);
-    if (m == 0 || m > kPlanMax || bad) {
-        if (t == 0) {
-            if (bad || (m > kPlanMax && n_add >= 0)) atomicAdd(&ctr->bad_path, 1ull);
-            if (m > kPlanMax && n_add < 0) ctr->plan_fallback = 1;
-            ctr->plan_n = 0;
-            ctr->move_chunks = 0;
-        }
+    if (m == 0 || m > kPlanMax) {
+        if (t == 0 && m) ctr->plan_fallback = 1;
         return;  // the same in every thread
     }
     // second sweep: place each ADD entry, hash its parent
@@ -873,16 +877,9 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
     if (small && t == 0) s_misc[1] = 1;
     __syncthreads();
     {
-        int32_t xs[kPlanBatchItems], ts[kPlanBatchItems];
+        int32_t ts[kPlanBatchItems];
 #pragma unroll
-        for (int j = 0; j < kPlanBatchItems; j++) {
-            xs[j] = 0;
-            ts[j] = 0;
-            if ((addbits >> j) & 1u) {
-                xs[j] = st[j * T + t].x;
-                ts[j] = st[j * T + t].t;
-            }
-        }
+        for (int j = 0; j < kPlanBatchItems; j++) ts[j] = (addbits >> j) & 1u ? st[j * T + t].t : 0;
 #pragma unroll
         for (int j = 0; j < kPlanBatchItems; j++) {
             if (j < R) {
@@ -892,11 +889,11 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
                 if (a) {
                     const int pos = s_cw[j * kPlanWaves + wv] + (int)__popcll(bal & lt_mask);
                     if (s_misc[1] == 0) {
-                        if (s_misc[0] > kPlanMaxParents || plan_slot_insert(s_tab, &s_misc[0], xs[j]) < 0)
+                        if (s_misc[0] > kPlanMaxParents || plan_slot_insert(s_tab, &s_misc[0], ax[j]) < 0)
                             s_misc[1] = 1;
                     }
                     s_key[plan_pad(pos)] =
-                        ((unsigned long long)(uint32_t)xs[j] << 32) | (uint32_t)(ts[j] ^ (int32_t)0x80000000);
+                        ((unsigned long long)(uint32_t)ax[j] << 32) | (uint32_t)(ts[j] ^ (int32_t)0x80000000);
                     s_val[plan_pad(pos)] = (uint16_t)i;
                 }
             }
@@ -1048,12 +1045,6 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
     // 3. marks: slot winners, group heads and ends; per-thread totals
     const unsigned long long before = (nv > 0 && e0 > 0) ? s_key[plan_pad(e0 - 1)] : 0ull;
     const unsigned long long after = (nv > 0 && e0 + nv < m) ? s_key[plan_pad(e0 + nv)] : 0ull;
-    for (int p = t; p < m; p += T) {
-        const unsigned long long kk = s_key[plan_pad(p)];
-        const uint32_t x = slotted ? (uint32_t)s_tab[(int)(kk >> 32)] : (uint32_t)(kk >> 32);
-        keys[p] = ((unsigned long long)x << 32) | (kk & 0xFFFFFFFFull);
-        vals[p] = (int32_t)s_val[plan_pad(p)];
-    }
     uint32_t wbits = 0, hbits = 0, lbits = 0;
     int sw = 0, sc = 0, lh = -1;
 #pragma unroll
@@ -1076,7 +1067,7 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
             }
         }
     }
-    // winners' label spans, in sorted order
+    // label tokens of the winners
     long long srest = 0, pool_total;
     int32_t rest[kPlanItems];
 #pragma unroll
@@ -1085,19 +1076,23 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
         srest += rest[j];
     }
     long long prest = plan_block_excl<long long>(srest, 0, plus64, s_tmp, &pool_total);
-#pragma unroll
-    for (int j = 0; j < kPlanItems; j++)
-        if (j < nv && ((wbits >> j) & 1u)) {
-            pofs[v[j]] = prest;
-            prest += rest[j];
-        }
     int tw, tc, th;
     int pw = plan_block_excl<int>(sw, 0, plus, s_tmp32, &tw);
     int pc = plan_block_excl<int>(sc, 0, plus, s_tmp32, &tc);
     int ph = plan_block_excl<int>(lh, -1, [](int x, int y) { return x > y ? x : y; }, s_tmp32, &th);
-    // 4. per entry: widx, hd and cstart, staged in LDS (s_key's entries and
-    // s_val's ids were read before the scans' barriers) and written out
-    // coalesced; widx stays in s_val for the group ends
+    // places of the workgroup's entries and of its chunks: both from one atomic,
+    // so that cstart ascends over all workgroups' entries
+    if (t == 0) s_place = atomicAdd(&ctr->plan_alloc, ((unsigned long long)m << 32) | (unsigned)tc);
+    __syncthreads();
+    const int eb = (int)(s_place >> 32), cb = (int)(uint32_t)s_place;
+    for (int p = t; p < m; p += T) {
+        const unsigned long long kk = s_key[plan_pad(p)];
+        const uint32_t x = slotted ? (uint32_t)s_tab[(int)(kk >> 32)] : (uint32_t)(kk >> 32);
+        keys[eb + p] = ((unsigned long long)x << 32) | (kk & 0xFFFFFFFFull);
+        vals[eb + p] = (int32_t)s_val[plan_pad(p)];
+    }
+    __syncthreads();  // s_key and s_val are staged over below
+    // 4. per entry: widx, hd and cstart, staged in LDS and written out coalesced; widx stays in s_val for the group ends
     const int ph0 = ph;
 #pragma unroll
     for (int j = 0; j < kPlanItems; j++) {
@@ -1119,10 +1114,10 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
         const unsigned long long sk = s_key[plan_pad(p)];
         const int wi = (int)s_val[plan_pad(p)];
         const int wn = p + 1 < m ? (int)s_val[plan_pad(p + 1)] : tw;
-        win[p] = wn - wi;
-        widx[p] = wi;
-        hd[p] = (int32_t)(uint32_t)sk;
-        cstart[p] = (int32_t)(sk >> 32);
+        win[eb + p] = wn - wi;
+        widx[eb + p] = wi;
+        hd[eb + p] = eb + (int32_t)(uint32_t)sk;
+        cstart[eb + p] = cb + (int32_t)(sk >> 32);
     }
     // 5. records per rebuilt block (old children + winners), scanned over the
     // groups in order; one allocation for all of them and one for the pool
@@ -1147,13 +1142,17 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
         const long long pb = (long long)atomicAdd(&ctr->n_pool, (unsigned long long)pool_total);
         const bool ok = nb + need_all <= F.cap_nodes && pb + pool_total <= F.cap_pool;
         if (!ok) atomicAdd(&ctr->overflow, 1ull);
-        ctr->add_pool_base = (unsigned long long)pb;
-        ctr->move_chunks = (unsigned long long)tc;
-        ctr->plan_n = (unsigned long long)m;
-        cstart[m] = tc;
         s_tmp[0] = ok ? nb : -1;
+        s_tmp[1] = pb;
     }
     __syncthreads();
+    prest += s_tmp[1];
+#pragma unroll
+    for (int j = 0; j < kPlanItems; j++)
+        if (j < nv && ((wbits >> j) & 1u)) {
+            pofs[v[j]] = prest;
+            prest += rest[j];
+        }
     // winners' tokens go to LDS at their place in win_tok (head + ordinal) and
     // out coalesced; entries past a group's winners hold no token
     const long long nb0 = s_tmp[0];
@@ -1170,14 +1169,14 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
             if ((lbits >> j) & 1u) {
                 const int32_t x = slotted ? s_tab[(int)(k[j] >> 32)] : (int32_t)(k[j] >> 32);
                 const int nw = (int)s_val[plan_pad(e)] + (int)w - wk;
-                grp_nw[hcur] = nw;
-                grp_nb[hcur] = nb0 < 0 ? -1 : (int32_t)(nb0 + noff);
+                grp_nw[eb + hcur] = nw;
+                grp_nb[eb + hcur] = nb0 < 0 ? -1 : (int32_t)(nb0 + noff);
                 noff += F.nodes[x].ct_cnt + nw;
             }
         }
     }
     __syncthreads();
-    for (int p = t; p < m; p += T) win_tok[p] = (int32_t)s_tok[plan_pad(p)];
+    for (int p = t; p < m; p += T) win_tok[eb + p] = (int32_t)s_tok[plan_pad(p)];
 }
 
 // Step 3 (one thread per group head): records and label tokens of the new
@@ -1205,7 +1204,7 @@ __global__ void add_alloc_kernel(DevForest F, const unsigned long long *keys, in
 // the entries: a winner's leaf, holding the rest of its sequence, goes to its
 // token's slot among the parent's children.
 // pofs: nullptr after the multi-launch steps (spans from poff and grp_pb),
-// else the one-workgroup plan's spans per insert from ctr->add_pool_base.
+// else the plan kernel's spans per insert.
 // The grid is fixed, so it follows neither the forest's records nor a count
 // that only the device knows.
 __global__ __launch_bounds__(64 *kMergeWavesPerBlock) void add_build_kernel(
@@ -1216,8 +1215,7 @@ __global__ __launch_bounds__(64 *kMergeWavesPerBlock) void add_build_kernel(
     const int lane = (int)(threadIdx.x & 63);
     const int64_t waves = (int64_t)gridDim.x * kMergeWavesPerBlock;
     const int32_t cnt = (int32_t)add_count(n_add, ctr);
-    const int64_t nchunks = cnt > 0 ? (int64_t)ctr->move_chunks : 0;
-    const int64_t pool_base = (int64_t)ctr->add_pool_base;
+    const int64_t nchunks = n_add >= 0 ? (int64_t)ctr->move_chunks : (int64_t)(uint32_t)ctr->plan_alloc;
     uint32_t seen = 0;
     for (int64_t q = m_wave_index(); q < nchunks + cnt; q += waves) {
         if (q < nchunks) {
@@ -1249,7 +1247,7 @@ __global__ __launch_bounds__(64 *kMergeWavesPerBlock) void add_build_kernel(
         const int32_t d = st[i].d, t = st[i].t;
         const int64_t rest = len - d;  // >= 1: an ADD insert has a next token
         const int64_t dst = nb + (widx[e] - widx[k]) + wave_lower_count(F.ntok + nx.ct_beg, nx.ct_cnt, t, lane);
-        const int64_t pb = pofs ? pool_base + pofs[i] : grp_pb[k] + (poff[e] - poff[k]);
+        const int64_t pb = pofs ? pofs[i] : grp_pb[k] + (poff[e] - poff[k]);
         const int32_t p = batch_peer(B, i);
         copy_tokens_narrow(F, N, pb, s + d, rest, lane, seen);
         leaf_mext(F, dst, p, lane);

@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "forest_layout.h"
+#include "lcp.h"
 
 #ifndef PR_ROUTE_WAVES_PER_BLOCK
 #define PR_ROUTE_WAVES_PER_BLOCK 1
@@ -17,7 +18,6 @@
 
 namespace pr {
 
-constexpr int kWave = 64;
 constexpr int kRouteWavesPerBlock = PR_ROUTE_WAVES_PER_BLOCK;
 constexpr int kWinVectors = PR_WIN_VECTORS;  // 64-token vectors of the first-level window
 constexpr int kWideWinVectors = 4;           // ... of the wide one

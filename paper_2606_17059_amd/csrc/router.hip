@@ -72,7 +72,8 @@ struct MergeScratch {
     int32_t *grp_nw = nullptr, *grp_nb = nullptr, *win_tok = nullptr, *win_ins = nullptr;
     // add rounds: per sorted entry (cap + 1 entries)
     int32_t *win = nullptr, *widx = nullptr, *headv = nullptr, *hd = nullptr, *nch = nullptr, *cstart = nullptr;
-    int32_t *arest = nullptr;  // per insert: label tokens of an ADD insert, else -1
+    int32_t *addx = nullptr;   // per insert: parent of an ADD insert, else -1
+    int32_t *arest = nullptr;  // per insert: tokens past the walk's end
     int64_t *rest = nullptr, *poff = nullptr, *grp_pool = nullptr, *grp_pb = nullptr;
     int64_t cap = 0;
     void *sort_tmp = nullptr;
@@ -154,8 +155,8 @@ namespace {
 #define PR_ROUTE_LONGEST_FIRST 1
 #endif
 // Narrow (16- or 17-bit) label copies for routes; 0 keeps every forest on int32 labels.
-// Rounds of at most pr::kPlanMax ADD inserts plan their add phase in one
-// workgroup (0: always the multi-launch path, for comparisons).
+// Batches of at most pr::kPlanMaxBatch inserts plan their add phase in one
+// launch (0: always the multi-launch path, for comparisons).
 #ifndef PR_MERGE_PLAN
 #define PR_MERGE_PLAN 1
 #endif
@@ -418,6 +419,7 @@ void free_add_scratch(pr_forest *f) {
     dfree(f, &m.grp_pool, c);
     dfree(f, &m.grp_pb, c);
     dfree(f, &m.arest, c);
+    dfree(f, &m.addx, c);
 }
 
 void free_scratch(pr_forest *f) {
@@ -823,7 +825,7 @@ pr_status ensure_merge_scratch(pr_forest *f, int64_t n, hipStream_t s) {
             !dalloc(f, &m.win, c1) || !dalloc(f, &m.widx, c1) || !dalloc(f, &m.headv, c1) ||
             !dalloc(f, &m.hd, c1) || !dalloc(f, &m.nch, c1) || !dalloc(f, &m.cstart, c1) ||
             !dalloc(f, &m.rest, c1) || !dalloc(f, &m.poff, c1) || !dalloc(f, &m.grp_pool, c1) ||
-            !dalloc(f, &m.grp_pb, c1) || !dalloc(f, &m.arest, c1)) {
+            !dalloc(f, &m.grp_pb, c1) || !dalloc(f, &m.arest, c1) || !dalloc(f, &m.addx, c1)) {
             m.cap = cap;  // so that free_scratch releases the add arrays by their size
             free_scratch(f);
             return fail(PR_ENOMEM, "hipMalloc failed for merge scratch");
@@ -870,7 +872,7 @@ __global__ void reset_round_kernel(pr::MergeCounters *c) {
     c->pool_need = 0;
     c->node_need = 0;
     c->move_chunks = 0;
-    c->plan_n = 0;
+    c->plan_alloc = 0;
     c->plan_fallback = 0;
 }
 
@@ -1030,6 +1032,7 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
     if ((r = ensure_merge_scratch(f, n, s))) return r;
     MergeScratch &m = f->ms;
     const int bs = 256, wb = 64 * pr::kMergeWavesPerBlock;
+    const unsigned plan_grid = (unsigned)pr::plan_blocks(n);
     const unsigned build_blocks = (unsigned)std::min<int64_t>(pr::kMoveBlocks, std::max<int64_t>(256, n / 4));
     int first = 1;  // the next walk is the first to look at the batch
     bool done = false;
@@ -1052,11 +1055,11 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
         const pr::NarrowDst N = narrow_dst(f);
         for (int round = 0; round < kDeviceRounds; round++, first = 0) {
             const long long stamp = ++f->stamp;
-            hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_waves(n)), dim3(wb), 0, s, F, B, m.st, m.arest,
-                               f->d_ctr, first);
+            hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_waves(n)), dim3(wb), 0, s, F, B, m.st, m.addx,
+                               m.arest, f->d_ctr, first);
             if (!B.touch) {  // touches add nothing
-                hipLaunchKernelGGL(pr::add_plan_kernel, dim3(1), dim3(pr::kPlanThreads), 0, s, F, B, m.st, m.arest,
-                                   (int64_t)-1, m.keys_out, m.vals_out, m.win, m.widx, m.hd, m.cstart, m.grp_nw,
+                hipLaunchKernelGGL(pr::add_plan_kernel, dim3(plan_grid), dim3(pr::kPlanThreads), 0, s, F, B, m.st,
+                                   m.addx, m.arest, m.keys_out, m.vals_out, m.win, m.widx, m.hd, m.cstart, m.grp_nw,
                                    m.grp_nb, m.win_tok, m.rest, f->d_ctr);
                 hipLaunchKernelGGL(pr::add_build_kernel, dim3(build_blocks), dim3(wb), 0, s, F, B, N, m.keys_out,
                                    m.vals_out, (int64_t)-1, m.st, m.win, m.widx, m.poff, m.hd, m.cstart, m.grp_nw,
@@ -1083,8 +1086,8 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
     const bool host_rounds = !done;
     for (; !done && round < max_rounds; round++, first = 0) {
         hipLaunchKernelGGL(reset_round_kernel, dim3(1), dim3(1), 0, s, f->d_ctr);
-        hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_waves(n)), dim3(wb), 0, s, dev_view(f), B, m.st, m.arest,
-                           f->d_ctr, first);
+        hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_waves(n)), dim3(wb), 0, s, dev_view(f), B, m.st, m.addx,
+                           m.arest, f->d_ctr, first);
         hipLaunchKernelGGL(pr::merge_tally_kernel,
                            dim3((unsigned)std::min<int64_t>(256, (n + pr::kTallyThreads - 1) / pr::kTallyThreads)),
                            dim3(pr::kTallyThreads), 0, s, B, m.st, f->d_ctr);
@@ -1112,13 +1115,13 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
         const pr::DevForest F = dev_view(f);
         const pr::NarrowDst N = narrow_dst(f);
         long long add_stamp = 0;
+        const bool plan = PR_MERGE_PLAN && n_add > 0 && n_add <= pr::kPlanMax && n <= pr::kPlanMaxBatch;
         if (n_add > 0) {
-            const bool plan = PR_MERGE_PLAN && n_add <= pr::kPlanMax && n <= pr::kPlanMaxBatch;
             if (plan) {
-                // sort, marks, scans and groups in one workgroup
-                hipLaunchKernelGGL(pr::add_plan_kernel, dim3(1), dim3(pr::kPlanThreads), 0, s, F, B, m.st, m.arest,
-                                   n_add, m.keys_out, m.vals_out, m.win, m.widx, m.hd, m.cstart, m.grp_nw, m.grp_nb,
-                                   m.win_tok, m.rest, f->d_ctr);
+                // sort, marks, scans and groups in one launch
+                hipLaunchKernelGGL(pr::add_plan_kernel, dim3(plan_grid), dim3(pr::kPlanThreads), 0, s, F, B, m.st,
+                                   m.addx, m.arest, m.keys_out, m.vals_out, m.win, m.widx, m.hd, m.cstart, m.grp_nw,
+                                   m.grp_nb, m.win_tok, m.rest, f->d_ctr);
             } else {
                 hipLaunchKernelGGL(pr::add_keys_kernel, dim3(grid_threads(n, bs)), dim3(bs), 0, s, B, m.st, m.keys_in,
                                    m.vals_in);
@@ -1153,12 +1156,12 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
                                    n_add, m.grp_nw, m.grp_pool, m.grp_nb, m.grp_pb, f->d_ctr);
             }
             add_stamp = ++f->stamp;
-            hipLaunchKernelGGL(pr::add_build_kernel, dim3(std::max<unsigned>(pr::kMoveBlocks, grid_waves(n_add))), dim3(wb), 0, s,
-                               F, B, N, m.keys_out, m.vals_out, n_add, m.st, m.win, m.widx, m.poff, m.hd, m.cstart,
+            hipLaunchKernelGGL(pr::add_build_kernel, dim3(std::max<unsigned>(pr::kMoveBlocks, grid_waves(n_add))),
+                               dim3(wb), 0, s, F, B, N, m.keys_out, m.vals_out, plan ? -1 : n_add, m.st, m.win, m.widx, m.poff, m.hd, m.cstart,
                                m.grp_nw, m.grp_nb, m.grp_pb, plan ? m.rest : nullptr, m.win_tok, f->d_ctr, add_stamp);
         }
         hipLaunchKernelGGL(pr::add_finish_kernel, dim3(grid_threads(n, bs)), dim3(bs), 0, s, F, B, m.st, m.keys_out,
-                           n_add, m.grp_nw, m.grp_nb, add_stamp, f->d_ctr);
+                           plan ? -1 : n_add, m.grp_nw, m.grp_nb, add_stamp, f->d_ctr);
         if (n_split > 0)
             hipLaunchKernelGGL(pr::split_apply_kernel, dim3(grid_split(n)), dim3(64 * pr::kSplitWaves), 0, s, F, B, N,
                                m.st, f->d_ctr, add_stamp);
