@@ -146,9 +146,24 @@ def pr_load_snapshot(f: int, peer: int, tokens: np.ndarray, offsets: np.ndarray)
                                   o.shape[0] - 1))
 
 
+_torch = None
+_raw_stream = None
+
+
+def _load_torch():
+    """torch, imported on first use; a later call costs a comparison."""
+    global _torch, _raw_stream
+    if _torch is None:
+        import torch
+        # the current stream's handle without a Stream object around it
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _torch = torch
+    return _torch
+
+
 def _dev(t, dtype, name):
-    import torch
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    torch = _torch or _load_torch()
+    if not isinstance(t, torch.Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a CUDA (HIP) torch tensor")
     if t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}")
@@ -158,7 +173,9 @@ def _dev(t, dtype, name):
 
 
 def _stream_ptr(stream, device) -> int:
-    import torch
+    torch = _torch or _load_torch()
+    if stream is None and _raw_stream is not None and device.index is not None:
+        return _raw_stream(device.index)
     s = stream if stream is not None else torch.cuda.current_stream(device)
     return int(s.cuda_stream)
 
@@ -244,35 +261,35 @@ def pr_merge(f: int, peer_of, tokens, offsets, stream=None) -> None:
                           offsets.data_ptr(), n, _stream_ptr(stream, offsets.device)))
 
 
-def pr_route(f: int, q_tokens, q_offsets, match_len, chosen, num_peers: int, stream=None) -> None:
-    import torch
-    _dev(q_tokens, torch.int32, "q_tokens")
+def _route_args(q_tokens, q_offsets, match_len, chosen, num_peers: int) -> int:
+    """Check a route's tensors; the number of queries."""
+    torch = _torch or _load_torch()
+    i32 = torch.int32
+    _dev(q_tokens, i32, "q_tokens")
     _dev(q_offsets, torch.int64, "q_offsets")
-    _dev(match_len, torch.int32, "match_len")
-    _dev(chosen, torch.int32, "chosen")
+    _dev(match_len, i32, "match_len")
+    _dev(chosen, i32, "chosen")
     nq = q_offsets.numel() - 1
     if nq < 0:
         raise ValueError("q_offsets must have at least one entry")
     if match_len.numel() != nq * num_peers or chosen.numel() != nq:
         raise ValueError("match_len must hold [num_queries][num_peers] and chosen [num_queries]")
-    _check(lib().pr_route(f, q_tokens.data_ptr() or None, q_tokens.numel(), q_offsets.data_ptr(), nq,
-                          match_len.data_ptr() or None, chosen.data_ptr() or None,
-                          _stream_ptr(stream, q_offsets.device)))
+    return nq
+
+
+def pr_route(f: int, q_tokens, q_offsets, match_len, chosen, num_peers: int, stream=None) -> None:
+    nq = _route_args(q_tokens, q_offsets, match_len, chosen, num_peers)
+    st = (_lib_handle or lib()).pr_route(f, q_tokens.data_ptr() or None, q_tokens.numel(), q_offsets.data_ptr(), nq,
+                                         match_len.data_ptr() or None, chosen.data_ptr() or None,
+                                         _stream_ptr(stream, q_offsets.device))
+    if st != PR_OK:
+        _check(st)
 
 
 def pr_route_noalloc(f: int, q_tokens, q_offsets, match_len, chosen, num_peers: int, stream=None) -> None:
     """pr_route without allocation (at most PR_NOALLOC_MAX_QUERIES queries;
     the forest must be on the device already)."""
-    import torch
-    _dev(q_tokens, torch.int32, "q_tokens")
-    _dev(q_offsets, torch.int64, "q_offsets")
-    _dev(match_len, torch.int32, "match_len")
-    _dev(chosen, torch.int32, "chosen")
-    nq = q_offsets.numel() - 1
-    if nq < 0:
-        raise ValueError("q_offsets must have at least one entry")
-    if match_len.numel() != nq * num_peers or chosen.numel() != nq:
-        raise ValueError("match_len must hold [num_queries][num_peers] and chosen [num_queries]")
+    nq = _route_args(q_tokens, q_offsets, match_len, chosen, num_peers)
     _check(lib().pr_route_noalloc(f, q_tokens.data_ptr() or None, q_tokens.numel(), q_offsets.data_ptr(), nq,
                                   match_len.data_ptr() or None, chosen.data_ptr() or None,
                                   _stream_ptr(stream, q_offsets.device)))
@@ -282,7 +299,7 @@ def pr_route_select(f: int, q_tokens, q_offsets, eligible, local_peer: int, flag
                     num_peers: int, stream=None) -> None:
     """eligible: CUDA uint64 tensor of ceil(num_peers / 64) words (torch.int64
     holding the bits) or None; match_len and second may be None."""
-    import torch
+    torch = _torch or _load_torch()
     _dev(q_tokens, torch.int32, "q_tokens")
     _dev(q_offsets, torch.int64, "q_offsets")
     _dev(best, torch.int32, "best")
@@ -303,11 +320,13 @@ def pr_route_select(f: int, q_tokens, q_offsets, eligible, local_peer: int, flag
         _dev(eligible, torch.int64, "eligible")
         if eligible.numel() != (num_peers + 63) // 64:
             raise ValueError("eligible must hold ceil(num_peers / 64) words")
-    _check(lib().pr_route_select(f, q_tokens.data_ptr() or None, q_tokens.numel(), q_offsets.data_ptr(), nq,
-                                 eligible.data_ptr() if eligible is not None else None, int(local_peer),
-                                 int(flags), match_len.data_ptr() if match_len is not None else None,
-                                 best.data_ptr() or None, second.data_ptr() if second is not None else None,
-                                 _stream_ptr(stream, q_offsets.device)))
+    st = (_lib_handle or lib()).pr_route_select(
+        f, q_tokens.data_ptr() or None, q_tokens.numel(), q_offsets.data_ptr(), nq,
+        eligible.data_ptr() if eligible is not None else None, int(local_peer), int(flags),
+        match_len.data_ptr() if match_len is not None else None, best.data_ptr() or None,
+        second.data_ptr() if second is not None else None, _stream_ptr(stream, q_offsets.device))
+    if st != PR_OK:
+        _check(st)
 
 
 def eligible_words(flags) -> np.ndarray:
@@ -419,13 +438,14 @@ class Forest:
         return pr_evict_lru(self.handle, max_tokens, stream)
 
     def route(self, q_tokens, q_offsets, match_len=None, chosen=None, stream=None) -> Tuple:
-        import torch
-        nq = q_offsets.numel() - 1
-        dev = q_offsets.device
-        if match_len is None:
-            match_len = torch.empty((nq, self.num_peers), dtype=torch.int32, device=dev)
-        if chosen is None:
-            chosen = torch.empty(nq, dtype=torch.int32, device=dev)
+        if match_len is None or chosen is None:
+            torch = _load_torch()
+            nq = q_offsets.numel() - 1
+            dev = q_offsets.device
+            if match_len is None:
+                match_len = torch.empty((nq, self.num_peers), dtype=torch.int32, device=dev)
+            if chosen is None:
+                chosen = torch.empty(nq, dtype=torch.int32, device=dev)
         pr_route(self.handle, q_tokens, q_offsets, match_len, chosen, self.num_peers, stream)
         return match_len, chosen
 
@@ -438,16 +458,7 @@ class Forest:
         """Check the buffers once and return a callable that launches pr_route on
         them with no per-call checks or conversions (tight launch loops).  The
         callable keeps the tensors alive; it raises RouterError on a failed call."""
-        import torch
-        _dev(q_tokens, torch.int32, "q_tokens")
-        _dev(q_offsets, torch.int64, "q_offsets")
-        _dev(match_len, torch.int32, "match_len")
-        _dev(chosen, torch.int32, "chosen")
-        nq = q_offsets.numel() - 1
-        if nq < 0:
-            raise ValueError("q_offsets must have at least one entry")
-        if match_len.numel() != nq * self.num_peers or chosen.numel() != nq:
-            raise ValueError("match_len must hold [num_queries][num_peers] and chosen [num_queries]")
+        nq = _route_args(q_tokens, q_offsets, match_len, chosen, self.num_peers)
         fn = lib().pr_route
         args = (ctypes.c_void_p(self.handle), ctypes.c_void_p(q_tokens.data_ptr() or None),
                 ctypes.c_int64(q_tokens.numel()), ctypes.c_void_p(q_offsets.data_ptr()), ctypes.c_int64(nq),
@@ -471,7 +482,7 @@ class Forest:
                      want_second: bool = True, stream=None) -> Tuple:
         """Best and second-best eligible peer (pr_route_select).  eligible: a
         CUDA int64 tensor of packed words (see eligible_words) or None."""
-        import torch
+        torch = _torch or _load_torch()
         nq = q_offsets.numel() - 1
         dev = q_offsets.device
         if match_len is None and want_match_len:
