@@ -1,6 +1,7 @@
 // route.hip -- launches of the route kernels (a translation unit of its own:
 // its 60 kernel instances compile beside the rest of the library).
 #include "route_kernels.h"
+#include "route_order.h"
 
 #include <algorithm>
 
@@ -41,9 +42,36 @@ void launch_w(const RouteForest &F, const RouteBatch &B, const Select &sel, hipS
         launch_l<W, true>(F, B, sel, s);
 }
 
+// Waves for each query (a power of two).  A small batch of long queries takes
+// as long as its longest query's chain of compare steps, so a team shares them,
+// a wave for every 512 tokens of the mean query: 48 queries of 20,000 tokens
+// 34.4 -> 8.4 us, one 33.2 -> 8.0, 512 of 5,300 10.9 -> 7.1.  Past 8,192 waves
+// (the chip's slots) or half as many queries as tokens a query, teams read as
+// much more as they wait less (us with 1, 2, 4, 8, 16 waves):
+//   20,700 tokens   512 queries  48.1  32.2  21.3  16.7  17.2
+//                 2,048          56.0  51.4  48.5  48.4  53.5
+//                 4,096          78.9  86.9  81.0  85.6  97.4
+//    5,300 tokens 2,048          13.4  13.5  13.3  16.0  24.7
+//    2,500 tokens 1,024           7.9   7.8   7.5  10.0  16.5
+//                 2,048           8.8   9.6  10.5  16.9  29.2
+//    1,400 tokens   512           5.6   5.3   5.6   6.2   8.4
+//                 1,024           5.4   5.6   6.4   9.0  14.2
+int team_waves(int64_t n, int64_t tokens) {
+    if (n <= 0 || n > 2048) return 1;
+    const int64_t mean = tokens / n;
+    if (2 * n > mean) return 1;
+    int waves = 1;
+    while (waves < kTeamMax && 1024 * waves <= mean && 2 * waves * n <= 8192) waves *= 2;
+    return waves;
+}
+
 }  // namespace
 
 hipError_t launch_route(const RouteForest &F, const RouteBatch &B, const Select &sel, hipStream_t s) {
+    if (const int waves = team_waves(B.n, B.num_tokens); waves > 1) {
+        launch_route_team(F, B, sel, waves, s);
+        return hipGetLastError();
+    }
     switch (F.W) {
         case 1: launch_w<1>(F, B, sel, s); break;
         case 2: launch_w<2>(F, B, sel, s); break;

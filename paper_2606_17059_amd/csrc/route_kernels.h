@@ -29,7 +29,7 @@
 // compares its label against a window of the query's first 128 tokens, or 256
 // when the host chose the wide window for a long shared prefix.  Batches of long
 // queries can be served in an order computed on the device (longest first,
-// route_order_count_kernel and route_order_scatter_kernel below).
+// route_order.h).
 // Labels are read from the int32 pool, or, while every label token lies in
 // [0, 65535], from a 16-bit copy of it (half the label bytes and requests; a
 // query token outside that range equals no label token either way), or,
@@ -278,13 +278,51 @@ __device__ __forceinline__ int32_t select_peers(const int32_t (&m)[W], int32_t P
     return select_decode(k1, sel);
 }
 
+// A team's compare of a long label: its waves take a share each of up to 64 *
+// kLcpVectors tokens, all in flight together, and meet at a barrier with the
+// first mismatch each has found.  Every wave returns the same value, so the
+// waves of a team walk in step; the two rows of `first` alternate, so that a
+// wave that is ahead does not overwrite what another still reads.
+// What bounds a batch that leaves most of the chip idle is the chain of round
+// trips of its longest query, about 1 us for every 1,024 tokens of a label.
+struct Team {
+    int32_t *first;  // LDS, [2][kTeamMax]
+    int wv, waves, row;
+};
+
+template <typename LT, bool HB>
+__device__ __forceinline__ int64_t team_lcp(const LabelSrc<LT, HB> &lab, const int32_t *__restrict__ b, int64_t n,
+                                            int lane, Team &team) {
+    constexpr int64_t kMost = (int64_t)kWave * kLcpVectors;
+    for (int64_t base = 0; base < n;) {
+        // an equal share of what is left, in whole lines
+        const int64_t each = min(((n - base + team.waves - 1) / team.waves + 31) & ~(int64_t)31, kMost);
+        const int64_t from = base + team.wv * each, to = min(from + each, n);
+        int32_t at = INT32_MAX;
+        if (from < to) {
+            const int64_t r = wave_lcp<LT, HB>(lab, b, to, from, kMost, lane);
+            if (r < to) at = (int32_t)r;
+        }
+        int32_t *row = team.first + team.row * kTeamMax;
+        team.row ^= 1;
+        if (lane == 0) row[team.wv] = at;
+        __syncthreads();
+        const int32_t f = lane < team.waves ? row[lane] : INT32_MAX;
+        const uint64_t bal = __ballot(f != INT32_MAX);
+        if (bal) return __builtin_amdgcn_readlane(f, (int)(__ffsll((unsigned long long)bal) - 1));
+        base += each * team.waves;
+    }
+    return n;
+}
+
 // SEL = false: plain routing (every peer eligible, ties to the lowest id, no
 // second pick); the selection options are compiled out.  LT: the label
 // pool's token type (int32_t, or uint16_t for the 16-bit copy); HB (with
 // uint16_t): bit 16 of every label token comes from the bit plane hib
-// (17-bit labels).  WV: vectors of the first-level window.
-template <int W, bool SEL, typename LT, bool HB = false, int WV = kWinVectors>
-__global__ __launch_bounds__(kWave *kRouteWavesPerBlock)
+// (17-bit labels).  WV: vectors of the first-level window.  TEAM: a workgroup
+// of up to kTeamMax waves serves one query (team_lcp).
+template <int W, bool SEL, typename LT, bool HB = false, int WV = kWinVectors, bool TEAM = false>
+__global__ __launch_bounds__(TEAM ? kWave * kTeamMax : kWave * kRouteWavesPerBlock)
 __attribute__((amdgpu_waves_per_eu(PR_ROUTE_WAVES_PER_EU))) void route_kernel(
     const Node *__restrict__ nodes, const int32_t *__restrict__ ntok, const int32_t *__restrict__ nsep,
     const uint64_t *__restrict__ mext, const LT *__restrict__ pool, const uint32_t *__restrict__ hib,
@@ -293,8 +331,14 @@ __attribute__((amdgpu_waves_per_eu(PR_ROUTE_WAVES_PER_EU))) void route_kernel(
     int32_t *__restrict__ chosen, const int32_t *__restrict__ order) {
     const Select sel = SEL ? sel_in : Select{nullptr, -1, 0, nullptr};
     const int lane = (int)(threadIdx.x & (kWave - 1));
-    const int64_t slot = (int64_t)blockIdx.x * kRouteWavesPerBlock + uniform((int32_t)(threadIdx.x / kWave));
+    const int wv = uniform((int32_t)(threadIdx.x / kWave));
+    const int64_t slot = TEAM ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * kRouteWavesPerBlock + wv;
     if (slot >= nq) return;
+    Team team{nullptr, wv, TEAM ? (int)(blockDim.x / kWave) : 1, 0};
+    if constexpr (TEAM) {
+        __shared__ int32_t s_first[2][kTeamMax];
+        team.first = &s_first[0][0];
+    }
     // order (optional) is a permutation of the queries: the dispatcher starts
     // slots in index order, so slot i serves query order[i]
     const int64_t q = order ? (int64_t)order[slot] : slot;
@@ -375,7 +419,9 @@ __attribute__((amdgpu_waves_per_eu(PR_ROUTE_WAVES_PER_EU))) void route_kernel(
         const int64_t n = min((int64_t)c.lab_len, qlen - d);
         const LabelSrc<LT, HB> lab{pool + (uint32_t)c.lab_off, hib, (uint32_t)c.lab_off};
         int64_t l;
-        if constexpr (FIRST)
+        if (TEAM && n > kTeamSplit)
+            l = team_lcp<LT, HB>(lab, qs + d, n, lane, team);
+        else if constexpr (FIRST)
             l = wave_lcp_first<LT, HB, WV>(lab, qs, n, win, lane);
         else
             l = wave_lcp<LT, HB>(lab, qs + d, n, 0, (int64_t)kWave * kLcpFirstVectors, lane);
@@ -409,6 +455,7 @@ __attribute__((amdgpu_waves_per_eu(PR_ROUTE_WAVES_PER_EU))) void route_kernel(
 #endif
     while (more) more = level(std::false_type{}, NoWindow{}, std::false_type{});
 
+    if (TEAM && wv != 0) return;  // every wave of a team has the same result
     if (bad) {
         if (match_len)
             for (int p = lane; p < P; p += kWave) row[p] = -1;
@@ -429,130 +476,6 @@ __attribute__((amdgpu_waves_per_eu(PR_ROUTE_WAVES_PER_EU))) void route_kernel(
     if (lane == 0) {
         chosen[q] = best;  // 4 bytes a query: plain stores, which the L2 merges into whole lines
         if (sel.second) sel.second[q] = second;
-    }
-}
-
-// Longest-first order of a batch, a counting sort in two launches of a few
-// workgroups: every query gets a length bucket (unit tokens wide, the last
-// one open-ended), and order lists the queries by bucket, longest bucket
-// first.  Within a bucket the order is fixed by the layout below, so it is
-// deterministic.  Offsets are not checked here (a bad pair lands in some
-// bucket); the route kernel checks every query's offsets itself.
-
-// Query i of thread t in workgroup b: base + i * kOrderThreads + t.
-__device__ __forceinline__ int32_t order_query(int b, int i, int t) {
-    return b * kOrderChunk + i * kOrderThreads + t;
-}
-
-// Launch 1: each query's bucket, and each workgroup's bucket counts.
-__global__ __launch_bounds__(kOrderThreads) void route_order_count_kernel(const int64_t *__restrict__ qoff,
-                                                                          int32_t nq, uint32_t unit,
-                                                                          uint8_t *__restrict__ bkt,
-                                                                          int32_t *__restrict__ blockcnt) {
-    __shared__ int32_t cnt[kOrderWaves][kOrderBuckets];
-    const int t = (int)threadIdx.x, lane = t & (kWave - 1), wv = t / kWave, b = (int)blockIdx.x;
-    int64_t lo[kOrderPerThread], hi[kOrderPerThread];
-#pragma unroll
-    for (int i = 0; i < kOrderPerThread; i++) {
-        const int32_t q = min(order_query(b, i, t), nq - 1);
-        lo[i] = qoff[q];
-        hi[i] = qoff[q + 1];
-    }
-    int32_t c[kOrderBuckets];
-#pragma unroll
-    for (int k = 0; k < kOrderBuckets; k++) c[k] = 0;
-#pragma unroll
-    for (int i = 0; i < kOrderPerThread; i++) {
-        const int32_t q = order_query(b, i, t);
-        int bk = -1;
-        if (q < nq) {
-            const int64_t len = hi[i] - lo[i];
-            const uint32_t l32 = len <= 0 ? 0u : (len > (int64_t)INT32_MAX ? (uint32_t)INT32_MAX : (uint32_t)len);
-            const uint32_t x = l32 / unit;
-            bk = (int)(x < kOrderBuckets - 1 ? x : kOrderBuckets - 1);
-            bkt[q] = (uint8_t)bk;
-        }
-#pragma unroll
-        for (int k = 0; k < kOrderBuckets; k++) c[k] += __popcll(__ballot(bk == k));
-    }
-    if (lane == 0)
-#pragma unroll
-        for (int k = 0; k < kOrderBuckets; k++) cnt[wv][k] = c[k];
-    __syncthreads();
-    if (t < kOrderBuckets) {
-        int32_t sum = 0;
-        for (int w = 0; w < kOrderWaves; w++) sum += cnt[w][t];
-        blockcnt[b * kOrderBuckets + t] = sum;
-    }
-}
-
-// Launch 2: position of every query.  Bucket k of workgroup b starts after
-// every longer bucket and after bucket k of the earlier workgroups; inside
-// the workgroup, wave by wave, each wave in query order i then lane.
-__global__ __launch_bounds__(kOrderThreads) void route_order_scatter_kernel(const uint8_t *__restrict__ bkt,
-                                                                            int32_t nq,
-                                                                            const int32_t *__restrict__ blockcnt,
-                                                                            int32_t *__restrict__ order) {
-    __shared__ int32_t cnt[kOrderWaves][kOrderBuckets];
-    __shared__ int32_t bc[kOrderMaxBlocks * kOrderBuckets];
-    const int t = (int)threadIdx.x, lane = t & (kWave - 1), wv = t / kWave, b = (int)blockIdx.x;
-    const int nb = (int)gridDim.x;
-    if (t < nb * kOrderBuckets) bc[t] = blockcnt[t];  // every workgroup's counts, one load per thread
-    int bk[kOrderPerThread];
-#pragma unroll
-    for (int i = 0; i < kOrderPerThread; i++) {
-        const int32_t q = order_query(b, i, t);
-        bk[i] = q < nq ? (int)bkt[q] : -1;
-    }
-    int32_t c[kOrderBuckets];
-#pragma unroll
-    for (int k = 0; k < kOrderBuckets; k++) c[k] = 0;
-#pragma unroll
-    for (int i = 0; i < kOrderPerThread; i++)
-#pragma unroll
-        for (int k = 0; k < kOrderBuckets; k++) c[k] += __popcll(__ballot(bk[i] == k));
-    if (lane == 0)
-#pragma unroll
-        for (int k = 0; k < kOrderBuckets; k++) cnt[wv][k] = c[k];
-    __syncthreads();
-    // bucket totals over all workgroups, and bucket t's count in earlier ones
-    __shared__ int32_t tot[kOrderBuckets], pre[kOrderBuckets];
-    if (t < kOrderBuckets) {
-        int32_t all = 0, earlier = 0;
-        for (int j = 0; j < nb; j++) {
-            const int32_t v = bc[j * kOrderBuckets + t];
-            all += v;
-            earlier += j < b ? v : 0;
-        }
-        tot[t] = all;
-        pre[t] = earlier;
-    }
-    __syncthreads();
-    if (t < kOrderBuckets) {
-        // this workgroup's start in bucket t, then the waves' starts inside it
-        int32_t before = pre[t];
-        for (int k = t + 1; k < kOrderBuckets; k++) before += tot[k];  // longer buckets come first
-        int32_t run = before;
-        for (int w = 0; w < kOrderWaves; w++) {
-            const int32_t v = cnt[w][t];
-            cnt[w][t] = run;
-            run += v;
-        }
-    }
-    __syncthreads();
-    int32_t start[kOrderBuckets];
-#pragma unroll
-    for (int k = 0; k < kOrderBuckets; k++) start[k] = cnt[wv][k];
-    const uint64_t below = (1ull << lane) - 1ull;
-#pragma unroll
-    for (int i = 0; i < kOrderPerThread; i++) {
-        const int32_t q = order_query(b, i, t);
-#pragma unroll
-        for (int k = 0; k < kOrderBuckets; k++) {
-            const uint64_t m = __ballot(bk[i] == k);
-            if (bk[i] == k) order[start[k] + __popcll(m & below)] = q;
-            start[k] += __popcll(m);
-        }
     }
 }
 

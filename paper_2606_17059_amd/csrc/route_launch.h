@@ -21,6 +21,8 @@ namespace pr {
 constexpr int kRouteWavesPerBlock = PR_ROUTE_WAVES_PER_BLOCK;
 constexpr int kWinVectors = PR_WIN_VECTORS;  // 64-token vectors of the first-level window
 constexpr int kWideWinVectors = 4;           // ... of the wide one
+constexpr int kTeamMax = 16;                 // waves of a query's team at most
+constexpr int64_t kTeamSplit = 256;          // labels beyond this many tokens are split over the team
 static_assert(kWinVectors >= 2 && kWinVectors <= 16, "window of 2 to 16 vectors");
 
 // Peer selection (the argmax of Algorithm 1, with the push-back and failover
@@ -69,6 +71,9 @@ struct RouteBatch {
 
 // Enqueue the route kernel: plain routing, or selection when sel asks for it.
 hipError_t launch_route(const RouteForest &F, const RouteBatch &B, const Select &sel, hipStream_t s);
+
+// The launch of a batch with a team of `waves` waves for every query (route_team.hip).
+void launch_route_team(const RouteForest &F, const RouteBatch &B, const Select &sel, int waves, hipStream_t s);
 
 // Enqueue the two order launches; bkt, blockcnt and order as in route.hip.
 hipError_t launch_route_order(const int64_t *q_offsets, int64_t nq, int64_t ntok, hipStream_t s, uint8_t *bkt,
