@@ -196,11 +196,12 @@ __global__ void lru_level_nodes_kernel(DevForest F, const int32_t *__restrict__ 
 // v both cover the cut depth, so neither is an ancestor of the other: climb
 // to the two children of their lowest common ancestor and compare their first
 // tokens (siblings' first tokens differ).
+template <typename D>
 __device__ __forceinline__ bool lru_path_before(const int32_t *__restrict__ ntok, const int32_t *__restrict__ parent,
-                                                const int64_t *__restrict__ depth, int32_t u, int32_t v) {
+                                                const D *__restrict__ depth, int32_t u, int32_t v) {
     while (parent[u] != parent[v]) {
         const int32_t pu = parent[u], pv = parent[v];
-        const int64_t du = pu == 0 ? 0 : depth[pu], dv = pv == 0 ? 0 : depth[pv];
+        const D du = pu == 0 ? 0 : depth[pu], dv = pv == 0 ? 0 : depth[pv];
         if (du >= dv) u = pu;
         if (dv >= du) v = pv;
     }

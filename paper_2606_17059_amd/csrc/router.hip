@@ -126,6 +126,7 @@ struct pr_forest {
     uint32_t *d_stage = nullptr;  // h_stage as the device addresses it (nullptr: readbacks by DMA)
     unsigned long long *d_skipped = nullptr;  // inputs skipped by device calls
     pr::WalkStatus *d_walk = nullptr;         // what the last one-launch tree walk found
+    pr::SizeState *d_size = nullptr;          // a tree size's sum over workgroups, zero between calls
     pr::CompactState *d_compact = nullptr;    // a compaction's ranges and totals
     DevImage spare;               // the arrays the last compaction replaced, for the next one (see retire_image)
     MergeScratch ms;
@@ -134,6 +135,8 @@ struct pr_forest {
     long long stamp = 0;          // add-round counter (stamps of moved records)
     int64_t round_nodes = 0;      // records recent merges added at most (spare capacity kept for the next)
     int64_t round_pool = 0;       // pool tokens, likewise (0: no merge yet)
+    bool holes = false;           // a refused allocation left records below n_nodes unwritten (until the
+                                  // next compaction): no pass over all records
     int64_t refusals = 0;         // merge rounds repeated after running out of capacity
     int32_t local = -1;           // peer whose tree keeps access times (-1: none)
     int64_t now = 0;              // current time, set by the caller, never decreasing
@@ -605,8 +608,9 @@ pr_status commit(pr_forest *f) {
     if (s) return s;
     if (!f->d_skipped) {
         if (!dalloc(f, &f->d_walk, 1) || !dalloc(f, &f->d_compact, 1) || !dalloc(f, &f->d_ctr, 1) ||
-            !dalloc(f, &f->d_skipped, 1)) {
+            !dalloc(f, &f->d_size, 1) || !dalloc(f, &f->d_skipped, 1)) {
             dfree(f, &f->d_walk, 1);
+            dfree(f, &f->d_size, 1);
             dfree(f, &f->d_compact, 1);
             dfree(f, &f->d_ctr, 1);
             return fail(PR_ENOMEM, "hipMalloc failed");
@@ -620,7 +624,8 @@ pr_status commit(pr_forest *f) {
             f->d_stage = static_cast<uint32_t *>(dp);
         else
             (void)hipGetLastError();  // readbacks fall back to DMA copies
-        if (hipMemset(f->d_skipped, 0, sizeof(unsigned long long)) != hipSuccess)
+        if (hipMemset(f->d_skipped, 0, sizeof(unsigned long long)) != hipSuccess ||
+            hipMemset(f->d_size, 0, sizeof(pr::SizeState)) != hipSuccess)
             return fail(PR_EDEVICE, "hipMemset failed");
     }
     // earlier launches may still read the old image
@@ -695,6 +700,7 @@ pr_status commit(pr_forest *f) {
     f->has_dev = true;
     f->dirty = false;
     f->merged = false;
+    f->holes = false;
     f->layout_epoch++;
     if (f->local >= 0) {
         pr_status r = init_local_times(f, f->local_load_time);
@@ -1006,6 +1012,7 @@ pr_status run_small_merge(pr_forest *f, const pr::Batch &B, const pr::InsState *
 // to what the round asked for before the round is repeated.
 pr_status refused_round(pr_forest *f, int64_t want_nodes, int64_t want_pool, int64_t pool_need, hipStream_t s) {
     f->refusals++;
+    f->holes = true;
     f->dev.n_nodes = std::min<int64_t>(want_nodes, f->dev.cap_nodes);
     f->dev.n_pool = std::min<int64_t>(want_pool, f->dev.cap_pool);
     hipLaunchKernelGGL(set_used_kernel, dim3(1), dim3(1), 0, s, f->d_ctr, (unsigned long long)f->dev.n_nodes,
@@ -1422,6 +1429,7 @@ void pr_forest_destroy(pr_forest *f) {
         dfree(f, &f->d_skipped, 1);
         dfree(f, &f->d_ctr, 1);
         dfree(f, &f->d_walk, 1);
+        dfree(f, &f->d_size, 1);
         dfree(f, &f->d_compact, 1);
         if (f->h_stage) (void)hipHostFree(f->h_stage);
         free_route_buffers(f);
@@ -1632,6 +1640,7 @@ pr_status pr_forest_compact(pr_forest *f, int64_t *nodes_before, int64_t *nodes_
     nw.n_nodes = S.hi;
     nw.n_pool = S.n_pool;
     f->dev = nw;
+    f->holes = false;
     f->layout_epoch++;
     f->stamp = 0;  // no record carries a move stamp
     f->narrow = narrow && nw.pool16;
@@ -1655,6 +1664,15 @@ pr_status pr_tree_tokens(pr_forest *f, int32_t peer, int64_t *tokens, void *hip_
     pr_status r = commit(f);
     if (r) return r;
     hipStream_t s = (hipStream_t)hip_stream;
+    if (f->d_stage && !f->holes) {
+        const unsigned blocks = std::min(pr::kSizeBlocks, grid_threads(f->dev.n_nodes, pr::kSizeThreads * pr::kSizePer));
+        hipLaunchKernelGGL(pr::tree_size_kernel, dim3(std::max(1u, blocks)), dim3(pr::kSizeThreads), 0, s, dev_view(f),
+                           f->dev.n_nodes, peer, f->d_size, reinterpret_cast<unsigned long long *>(f->d_stage));
+        if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
+            return fail(PR_EDEVICE, "tree size failed");
+        std::memcpy(tokens, f->h_stage, sizeof(*tokens));
+        return ok();
+    }
     if (f->d_stage) {
         if (!enqueue_walk(f, peer, pr::WalkOut{}, s) || hipStreamSynchronize(s) != hipSuccess)
             return fail(PR_EDEVICE, "tree walk failed");
@@ -1753,30 +1771,37 @@ pr_status pr_evict_lru(pr_forest *f, int64_t max_tokens, int64_t *evicted, void 
     hipStream_t s = (hipStream_t)hip_stream;
     ExportScratch &W = f->xs;
     if (f->d_stage) {
-        // a tree of at most pr::kEvictNodes nodes: walk and eviction in two
-        // launches and one wait
+        // among few records one launch finds the tree and evicts; a tree of at
+        // most pr::kEvictNodes nodes takes a walk and a launch; one wait each
         if ((r = ensure_export_scratch(f, f->dev.n_nodes))) return r;
-        pr::WalkOut O{};
-        O.depth = W.depth;
-        O.parent = W.parent;
-        O.all = W.all;
         pr::EvictStatus *out = reinterpret_cast<pr::EvictStatus *>(f->d_stage + kEvictStage / 4);
-        if (!enqueue_walk(f, f->local, O, s)) return fail(PR_EDEVICE, "tree walk launch failed");
-        hipLaunchKernelGGL(pr::evict_kernel, dim3(1), dim3(pr::kWalkThreads), 0, s, dev_view(f), f->d_walk, W.all,
-                           W.depth, W.parent, max_tokens, f->d_ctr, out);
-        if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
-            f->broken = true;
-            return fail(PR_EDEVICE, "eviction failed");
-        }
-        pr::EvictStatus st;
-        std::memcpy(&st, static_cast<const char *>(f->h_stage) + kEvictStage, sizeof(st));
-        if (st.done) {
-            f->dev.n_nodes = (int64_t)st.n_nodes;
-            if (st.evicted == 0) return ok();
-            f->merged = true;
-            f->sets[(size_t)f->local] = pr::PeerSeqs();  // the host copy no longer describes the local peer
-            *evicted = (int64_t)st.evicted;
-            return ok();
+        for (int scan = !f->holes && f->dev.n_nodes <= pr::kEvictScan; scan >= 0; scan--) {
+            if (scan) {
+                hipLaunchKernelGGL((pr::evict_kernel<true>), dim3(1), dim3(pr::kWalkThreads), 0, s, dev_view(f),
+                                   f->d_walk, W.all, W.depth, W.parent, max_tokens, f->d_ctr, out);
+            } else {
+                pr::WalkOut O{};
+                O.depth = W.depth;
+                O.parent = W.parent;
+                O.all = W.all;
+                if (!enqueue_walk(f, f->local, O, s)) return fail(PR_EDEVICE, "tree walk launch failed");
+                hipLaunchKernelGGL((pr::evict_kernel<false>), dim3(1), dim3(pr::kWalkThreads), 0, s, dev_view(f),
+                                   f->d_walk, W.all, W.depth, W.parent, max_tokens, f->d_ctr, out);
+            }
+            if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
+                f->broken = true;
+                return fail(PR_EDEVICE, "eviction failed");
+            }
+            pr::EvictStatus st;
+            std::memcpy(&st, static_cast<const char *>(f->h_stage) + kEvictStage, sizeof(st));
+            if (st.done) {
+                f->dev.n_nodes = (int64_t)st.n_nodes;
+                if (st.evicted == 0) return ok();
+                f->merged = true;
+                f->sets[(size_t)f->local] = pr::PeerSeqs();  // the host copy no longer describes the local peer
+                *evicted = (int64_t)st.evicted;
+                return ok();
+            }
         }
     }
     int32_t counts[3];

@@ -8,9 +8,9 @@
 // that have children) lives in LDS, a scan of the child counts spreads the
 // level's children over the threads, four of a thread's children in flight, so
 // a level of up to 4,096 children costs about one load's latency.  Measured,
-// calls included: the size of the 15-level tree 320 -> 46 us, evicting from it
-// 500 -> 67 us; the size of a tree of 4,000 prompts (16,000 children looked at)
-// 186 -> 37 us, its export 410 -> 127 us.
+// calls included: the export of a tree of 4,000 prompts (16,000 children looked
+// at) 410 -> 127 us.  Sizes, and evictions among few records, need no walk
+// (below).
 //
 // A walk whose frontier, level or leaf list is too large ends without having
 // changed anything, and the level-by-level kernels (export_kernels.h,
@@ -281,16 +281,86 @@ __global__ __launch_bounds__(kWalkThreads) void tree_walk_kernel(DevForest F, in
                     dev, host);
 }
 
+// ---- the size of a tree ------------------------------------------------------
+// Records hold everything a tree's size needs: a record in use has not moved
+// (moved is 0) and peers hold all of a path or none of it, so the size is the
+// sum of the labels of the records that have the peer's bit and have not moved,
+// in one pass over the records without a level waiting for another.  What it
+// moves is 40 bytes a record; a forest whose records are not all written
+// (pr_forest::holes) is walked instead.  A tree of 15
+// levels among 1,500 records 33 -> 2.9 us, one of 4,000 prompts in a forest of
+// 65,000 records 33 -> 6.3 us (the walk's kernel -> this one).
+constexpr int kSizeThreads = 256;
+constexpr int kSizePer = 4;  // records a thread has in flight
+constexpr unsigned kSizeBlocks = 1024;
+
+// Zero between calls: the last workgroup to finish clears it.
+struct SizeState {
+    unsigned long long tokens;
+    uint32_t blocks, pad;
+};
+
+__global__ __launch_bounds__(kSizeThreads) void tree_size_kernel(DevForest F, int64_t n_nodes, int32_t p, SizeState *acc,
+                                                                 unsigned long long *host) {
+    __shared__ unsigned long long s_sum[kSizeThreads / 64];
+    const int32_t w = p >> 6;
+    const int64_t step = (int64_t)gridDim.x * kSizeThreads;
+    unsigned long long sum = 0;
+    for (int64_t i0 = (int64_t)blockIdx.x * kSizeThreads + threadIdx.x; i0 < n_nodes; i0 += step * kSizePer) {
+        uint64_t word[kSizePer];
+        int32_t len[kSizePer];
+        long long mv[kSizePer];
+#pragma unroll
+        for (int k = 0; k < kSizePer; k++) {
+            const int64_t i = i0 + k * step;
+            word[k] = 0;
+            len[k] = 0;
+            mv[k] = 0;
+            if (i < n_nodes) {
+                word[k] = w == 0 ? F.nodes[i].mask0 : F.mext[i * (F.W - 1) + (w - 1)];
+                len[k] = F.nodes[i].lab_len;
+                mv[k] = F.moved[i];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kSizePer; k++)
+            if (((word[k] >> (p & 63)) & 1ull) && mv[k] == 0) sum += (unsigned long long)len[k];
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
+    if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = sum;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    sum = 0;
+    for (int k = 0; k < kSizeThreads / 64; k++) sum += s_sum[k];
+    if (gridDim.x > 1) {
+        atomicAdd(&acc->tokens, sum);
+        __threadfence();
+        if (atomicAdd(&acc->blocks, 1u) + 1 < gridDim.x) return;
+        __threadfence();
+        sum = atomicAdd(&acc->tokens, 0ull);
+        acc->tokens = 0;
+        acc->blocks = 0;
+    }
+    __hip_atomic_store(reinterpret_cast<uint64_t *>(host), (uint64_t)sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // ---- eviction ----------------------------------------------------------------
-// The eviction of lru_kernels.h for a tree of at most kEvictNodes nodes, in one
-// launch after the walk (the walk's status on the device says whether it is
-// whole): a thread holds four nodes in registers; the time class where the
+// The eviction of lru_kernels.h in one workgroup, a thread with several nodes
+// in registers.  SCAN: among at most kEvictScan records the nodes are found as
+// for the tree's size; each writes its place to its children's parent words in
+// LDS, and depths are sums along the parents by pointer jumping (four rounds
+// for 15 levels, where a walk waits for memory level by level), and the class's
+// tokens above a depth by two scans over depths in place of a bisection: walk
+// and eviction of such a tree took 33 + 20 us, this launch takes 20.
+// Otherwise the kernel comes after a walk (whose status on the device says
+// whether it is whole) and takes at most kEvictNodes nodes.  The time class where the
 // budget runs out is found by a radix selection over the times' bytes that
 // differ, weighted by label tokens; the cut depth by bisection over sums; the
 // order of the paths at the cut depth by comparing pairs.  Nothing is changed
 // before the cuts are known to fit the node capacity.
-constexpr int kEvictPer = 4;
-constexpr int kEvictNodes = kWalkThreads * kEvictPer;
+constexpr int kEvictNodes = 4 * kWalkThreads;
+constexpr int kEvictScan = 8 * kWalkThreads;
 constexpr int kEvictLevel = 512;  // nodes at the cut depth
 
 struct EvictStatus {
@@ -299,11 +369,14 @@ struct EvictStatus {
     unsigned long long evicted, n_nodes;
 };
 
+// walk, all, depth, parent: of the walk (SCAN: not used).
+template <bool SCAN>
 __global__ __launch_bounds__(kWalkThreads) void evict_kernel(DevForest F, const WalkStatus *walk,
                                                             const int32_t *__restrict__ all,
                                                             const int64_t *__restrict__ depth,
                                                             const int32_t *__restrict__ parent, int64_t max_tokens,
                                                             MergeCounters *ctr, EvictStatus *out) {
+    constexpr int kEvictPer = SCAN ? kEvictScan / kWalkThreads : kEvictNodes / kWalkThreads;
     __shared__ unsigned long long s_hist[256];
     __shared__ int32_t s_level[kEvictLevel], s_rank[kEvictLevel];
     __shared__ long long s_sum[kPlanWaves];
@@ -319,30 +392,127 @@ __global__ __launch_bounds__(kWalkThreads) void evict_kernel(DevForest F, const 
             __hip_atomic_store(reinterpret_cast<uint64_t *>(out) + k, w[k], __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_SYSTEM);
     };
-    const int V = (int)walk->nodes;
-    if (!walk->done || V > kEvictNodes) {
-        report(false, 0, n0);
-        return;
-    }
-    const long long total = (long long)walk->tokens;
     int32_t id[kEvictPer], e[kEvictPer], len[kEvictPer];
     unsigned long long time[kEvictPer];
+    long long total = 0;
+    // SCAN: per record its parent, its depth, and the ancestor its depth counts
+    // from so far (later the class's tokens per depth)
+    constexpr int kLds = SCAN ? kEvictScan : 1;
+    __shared__ int32_t s_par[kLds], s_dep[kLds], s_anc[kLds];
+    if constexpr (SCAN) {
+        if (n0 > (unsigned long long)kEvictScan) {
+            report(false, 0, n0);
+            return;
+        }
+        const int n = (int)n0, lane = t & 63, w = F.local >> 6;
+        for (int q = t; q < n; q += kWalkThreads) s_anc[q] = -1;
+        int32_t beg[kEvictPer], cnt[kEvictPer];
+#pragma unroll
+        for (int k = 0; k < kEvictPer; k++) {
+            const int i = t + k * kWalkThreads;
+            id[k] = -1;
+            e[k] = len[k] = beg[k] = cnt[k] = 0;
+            time[k] = 0;
+            if (i < n) {
+                const Node r = F.nodes[i];
+                const uint64_t word = w == 0 ? r.mask0 : F.mext[(int64_t)i * (F.W - 1) + (w - 1)];
+                const bool held = i > 0 && ((word >> (F.local & 63)) & 1ull) && F.moved[i] == 0;
+                time[k] = F.ltime[i];
+                if (held) {
+                    id[k] = i;
+                    len[k] = r.lab_len;
+                }
+                if (held || i == 0) {
+                    beg[k] = r.ct_beg;
+                    cnt[k] = r.ct_cnt;
+                }
+            }
+        }
+        __syncthreads();
+        // every record is in one block of children; blocks past a few children
+        // are written by the whole wave
+#pragma unroll
+        for (int k = 0; k < kEvictPer; k++) {
+            const int i = t + k * kWalkThreads;
+            if (cnt[k] <= 8)
+                for (int j = 0; j < cnt[k]; j++)
+                    if ((uint32_t)(beg[k] + j) < (uint32_t)n) s_anc[beg[k] + j] = i;
+            for (uint64_t m = __ballot(cnt[k] > 8); m; m &= m - 1) {
+                const int l = __ffsll((unsigned long long)m) - 1;
+                const int32_t b = __builtin_amdgcn_readlane(beg[k], l), c = __builtin_amdgcn_readlane(cnt[k], l);
+                for (int j = lane; j < c; j += 64)
+                    if ((uint32_t)(b + j) < (uint32_t)n) s_anc[b + j] = i - lane + l;
+            }
+        }
+        __syncthreads();
+        int lost = 0;
+        if (t == 0) s_anc[0] = s_dep[0] = 0;
+#pragma unroll
+        for (int k = 0; k < kEvictPer; k++) {
+            if (id[k] < 0) continue;
+            s_dep[id[k]] = len[k];
+            lost |= s_anc[id[k]] < 0;
+            s_par[id[k]] = s_anc[id[k]];
+        }
+        if (__syncthreads_or(lost)) {
+            report(false, 0, n0);
+            return;
+        }
+        for (int round = 0; round < 16; round++) {  // 13 for a chain of 8,192
+            int32_t add[kEvictPer], up[kEvictPer];
+            int more = 0;
+#pragma unroll
+            for (int k = 0; k < kEvictPer; k++) {
+                const int32_t a = id[k] >= 0 ? s_anc[id[k]] : 0;
+                add[k] = a > 0 ? s_dep[a] : 0;
+                up[k] = a > 0 ? s_anc[a] : 0;
+                more |= up[k] > 0;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < kEvictPer; k++)
+                if (id[k] >= 0) {
+                    s_dep[id[k]] += add[k];
+                    s_anc[id[k]] = up[k];
+                }
+            if (!__syncthreads_or(more)) break;
+        }
+        long long mine = 0;
+#pragma unroll
+        for (int k = 0; k < kEvictPer; k++)
+            if (id[k] >= 0) {
+                e[k] = s_dep[id[k]];
+                mine += len[k];
+            }
+        total = walk_block_sum(mine, s_sum);
+    } else {
+        const int V = (int)walk->nodes;
+        if (!walk->done || V > kEvictNodes) {
+            report(false, 0, n0);
+            return;
+        }
+        total = (long long)walk->tokens;
+#pragma unroll
+        for (int k = 0; k < kEvictPer; k++) {
+            const int i = t + k * kWalkThreads;
+            id[k] = -1;
+            e[k] = len[k] = 0;
+            time[k] = 0;
+            if (i < V) {
+                id[k] = all[i];
+                e[k] = (int32_t)depth[id[k]];
+                len[k] = F.nodes[id[k]].lab_len;
+                time[k] = F.ltime[id[k]];
+            }
+        }
+    }
     unsigned long long lo = ~0ull, hi = 0;
 #pragma unroll
-    for (int k = 0; k < kEvictPer; k++) {
-        const int i = t + k * kWalkThreads;
-        id[k] = -1;
-        e[k] = len[k] = 0;
-        time[k] = 0;
-        if (i < V) {
-            id[k] = all[i];
-            e[k] = (int32_t)depth[id[k]];
-            len[k] = F.nodes[id[k]].lab_len;
-            time[k] = F.ltime[id[k]];
+    for (int k = 0; k < kEvictPer; k++)
+        if (id[k] >= 0) {
             lo = min(lo, time[k]);
             hi = max(hi, time[k]);
         }
-    }
     if (max_tokens >= total) {  // everything goes
 #pragma unroll
         for (int k = 0; k < kEvictPer; k++)
@@ -425,16 +595,52 @@ __global__ __launch_bounds__(kWalkThreads) void evict_kernel(DevForest F, const 
         __syncthreads();
         if ((t & 63) == 0) atomicMax(&s_n, maxd);
         __syncthreads();
-        long long a = 1, b = s_n;  // the deepest x whose tokens and the deeper ones' reach rem
-        while (a < b) {
-            const long long mid = (a + b + 1) / 2;
-            if (deeper(mid) >= (long long)rem)
-                a = mid;
-            else
-                b = mid - 1;
+        const int deepest = s_n;
+        // the deepest D whose tokens and the deeper ones' reach rem
+        if (SCAN && deepest + 2 <= kEvictScan) {
+            // class tokens per depth: a node's first and the one past its last
+            // token step the count, summed over depths, then the tokens above
+            constexpr int kPer = kLds / kWalkThreads > 0 ? kLds / kWalkThreads : 1;
+            for (int q = t; q < kLds; q += kWalkThreads) s_anc[q] = 0;
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < kEvictPer; k++)
+                if (id[k] >= 0 && time[k] == prefix) {
+                    atomicAdd(&s_anc[e[k] - len[k] + 1], 1);
+                    atomicAdd(&s_anc[e[k] + 1], -1);
+                }
+            __syncthreads();
+            const auto plus = [](long long x, long long y) { return x + y; };
+            long long c[kPer], step = 0, all_c, above = 0;
+#pragma unroll
+            for (int k = 0; k < kPer; k++) step += c[k] = s_anc[t * kPer + k];
+            long long at = plan_block_excl<long long>(step, 0, plus, s_sum, &all_c);
+#pragma unroll
+            for (int k = 0; k < kPer; k++) above += c[k] = at += c[k];
+            long long left = (long long)cls - plan_block_excl<long long>(above, 0, plus, s_sum, &all_c);
+#pragma unroll
+            for (int k = 0; k < kPer; k++) {
+                if (left >= (long long)rem && left - c[k] < (long long)rem) {  // one depth of all
+                    s_prefix = (unsigned long long)(t * kPer + k);
+                    s_rem = rem - (unsigned long long)(left - c[k]);
+                }
+                left -= c[k];
+            }
+            __syncthreads();
+            D = (long long)s_prefix;
+            r_at = (long long)s_rem;
+        } else {
+            long long a = 1, b = deepest;
+            while (a < b) {
+                const long long mid = (a + b + 1) / 2;
+                if (deeper(mid) >= (long long)rem)
+                    a = mid;
+                else
+                    b = mid - 1;
+            }
+            D = a;
+            r_at = (long long)rem - deeper(D + 1);
         }
-        D = a;
-        r_at = (long long)rem - deeper(D + 1);
         if (t == 0) s_n = 0;
         __syncthreads();
 #pragma unroll
@@ -455,8 +661,14 @@ __global__ __launch_bounds__(kWalkThreads) void evict_kernel(DevForest F, const 
         if (r_at < c)
             for (int q = t; q < c * c; q += kWalkThreads) {
                 const int i = q / c, j = q % c;
-                if (i < j)
-                    atomicAdd(&s_rank[lru_path_before(F.ntok, parent, depth, s_level[j], s_level[i]) ? i : j], 1);
+                if (i < j) {
+                    bool first;
+                    if constexpr (SCAN)
+                        first = lru_path_before(F.ntok, s_par, s_dep, s_level[j], s_level[i]);
+                    else
+                        first = lru_path_before(F.ntok, parent, depth, s_level[j], s_level[i]);
+                    atomicAdd(&s_rank[first ? i : j], 1);
+                }
             }
         __syncthreads();
     }

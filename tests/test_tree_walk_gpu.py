@@ -137,3 +137,56 @@ def test_times_that_differ_in_any_byte():
     for k, n in enumerate((4, 1, 20, 9, 2, 30, 10 ** 9)):
         p.evict(n, f"times, eviction {k}")
     p.close()
+
+
+@pytest.mark.parametrize("records", [8191, 8192, 8193])
+@pytest.mark.parametrize("P, local", [(2, 0), (67, 66)])
+def test_eviction_around_the_record_limit(records, P, local):
+    """Sizes and evictions over the records of a loaded forest (the root and a
+    record a sequence), with child blocks of 8, 9, 64 and 65 among them; cuts
+    and merges then add records and move others."""
+    p = Pair(P, local)
+    inner = [[5, k, 6, i] for k, c in enumerate((8, 9, 64, 65)) for i in range(c)]
+    seqs = inner + [[100 + i, 1, i % 3, 4] for i in range(records - 2 - 4 - len(inner))]
+    for q in (p.f, p.o):
+        q.set_time(3)
+        q.load_snapshot(local, *pins._csr(seqs)) if q is p.f else q.load(local, *pins._csr(seqs))
+    p.export(local, "loaded")
+    assert p.f.info()["num_nodes"] == records
+    for k, n in enumerate((5, 3000, 40)):
+        p.evict(n, f"{records} records, eviction {k}")
+    p.merge(local, inner[:70] + [[5, 1, 9], [7] * 9], t=8)
+    p.merge(1 - local if P == 2 else 1, [[5, 1, 6, 2, 2], [7, 7]])
+    p.evict(len(seqs), "after moves")
+    p.export(1, "another peer")
+    p.close()
+
+
+def test_eviction_from_a_deep_chain():
+    p = Pair(2, 0)
+    p.merge(0, _chain(1500), t=1)
+    p.merge(1, _chain(40)[:3])
+    for n in (1, 300, 7):
+        p.evict(n, f"chain, {n}")
+    p.close()
+
+
+def test_size_and_eviction_past_unwritten_records():
+    """A merge whose rebuilt block does not fit leaves records that nothing wrote
+    until the next compaction."""
+    p = Pair(3, 1)
+    seqs = [[7, 2 * i, 1, 2] for i in range(5000)]
+    p.f.set_time(2)
+    p.o.set_time(2)
+    p.f.load_snapshot(1, *pins._csr(seqs))
+    p.o.load(1, *pins._csr(seqs))
+    p.export(1, "loaded")
+    p.f.compact()
+    p.merge(0, [[7, 4, 1, 2, 2], [9, 9], [7, 5, 5]])
+    assert p.f.info()["merge_refusals"] >= 1, p.f.info()
+    for k, n in enumerate((3, 500)):
+        p.evict(n, f"past unwritten records, {k}")
+    p.export(0, "the inserts")
+    p.f.compact()
+    p.evict(77, "after a compaction")
+    p.close()
