@@ -205,6 +205,7 @@ constexpr int kDeviceRounds = 2;     // merge rounds queued before the first rea
 
 unsigned grid_threads(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 unsigned grid_waves(int64_t n) { return (unsigned)((n + pr::kMergeWavesPerBlock - 1) / pr::kMergeWavesPerBlock); }
+unsigned grid_walk(int64_t n) { return (unsigned)((n + pr::kMergeWalkWaves - 1) / pr::kMergeWalkWaves); }
 unsigned grid_split(int64_t n) { return (unsigned)((n + pr::kSplitWaves - 1) / pr::kSplitWaves); }
 
 bool drop_spare(pr_forest *f);
@@ -1062,7 +1063,7 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
         const pr::NarrowDst N = narrow_dst(f);
         for (int round = 0; round < kDeviceRounds; round++, first = 0) {
             const long long stamp = ++f->stamp;
-            hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_waves(n)), dim3(wb), 0, s, F, B, m.st, m.addx,
+            hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_walk(n)), dim3(64 * pr::kMergeWalkWaves), 0, s, F, B, m.st, m.addx,
                                m.arest, f->d_ctr, first);
             if (!B.touch) {  // touches add nothing
                 hipLaunchKernelGGL(pr::add_plan_kernel, dim3(plan_grid), dim3(pr::kPlanThreads), 0, s, F, B, m.st,
@@ -1093,7 +1094,7 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
     const bool host_rounds = !done;
     for (; !done && round < max_rounds; round++, first = 0) {
         hipLaunchKernelGGL(reset_round_kernel, dim3(1), dim3(1), 0, s, f->d_ctr);
-        hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_waves(n)), dim3(wb), 0, s, dev_view(f), B, m.st, m.addx,
+        hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_walk(n)), dim3(64 * pr::kMergeWalkWaves), 0, s, dev_view(f), B, m.st, m.addx,
                            m.arest, f->d_ctr, first);
         hipLaunchKernelGGL(pr::merge_tally_kernel,
                            dim3((unsigned)std::min<int64_t>(256, (n + pr::kTallyThreads - 1) / pr::kTallyThreads)),
