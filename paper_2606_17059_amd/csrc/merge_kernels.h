@@ -125,6 +125,12 @@ __device__ __forceinline__ unsigned long long wave_atomic_add(unsigned long long
     return (unsigned long long)readlane64((uint64_t)r, 0);
 }
 
+// Reads past the CU's first-level cache, whose lines atomics of the same launch
+// do not update.
+__device__ __forceinline__ uint64_t fresh_u64(const void *p) {
+    return __hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Marks the waves of a workgroup have made, a few last ones: two waves that
 // make the same one need one atomic.
 constexpr int kMarkSlots = 64;
@@ -373,12 +379,6 @@ __device__ __forceinline__ int32_t current_pos(const DevForest &F, int32_t c, lo
     if (stamp <= 0) return c;
     const long long mv = F.moved[c];
     return (mv >> 32) == stamp ? (int32_t)(uint32_t)mv : c;
-}
-
-// Reads past the CU's first-level cache, whose lines atomics of the same launch
-// do not update.
-__device__ __forceinline__ uint64_t fresh_u64(const void *p) {
-    return __hip_atomic_load((const uint64_t *)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __device__ __forceinline__ Node fresh_node(const Node *p) {
@@ -709,7 +709,9 @@ __global__ void add_group_kernel(DevForest F, const unsigned long long *keys, co
 // The outputs keep the multi-launch path's layout (keys hold the parent's node
 // id), so the build and finish steps serve both paths.  10,000 entries in 512
 // parents, a fifth of them in the hottest: 82-107 us in one workgroup, 69 us
-// in 64.
+// in 64.  500 entries of one parent: 17.7 us, 14.2 with entries ranked by
+// counting up to 512 (several threads each), four scans on one pair of barriers
+// and the three allocations in flight together.
 constexpr int kPlanThreads = 1024;
 constexpr int kPlanItems = 10;                              // sorted entries per thread
 constexpr int kPlanMax = kPlanThreads * kPlanItems;         // ADD entries per workgroup
@@ -718,7 +720,7 @@ constexpr int64_t kPlanMaxBatch = (int64_t)kPlanThreads * kPlanBatchItems;  // i
 constexpr int kPlanWaves = kPlanThreads / 64;
 constexpr int kPlanSlots = 2048;                            // parent hash table
 constexpr int kPlanMaxParents = kPlanSlots / 2;
-constexpr int kPlanSmall = 256;                             // entries ranked by counting instead
+constexpr int kPlanSmall = 512;                             // entries ranked by counting instead
 constexpr int kPlanMaxBlocks = 64;
 
 // Workgroups of a plan for n inserts: about 128 each, so that most rank by
@@ -834,7 +836,7 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
     __shared__ uint32_t s_wt[kPlanWaves * 8];                // per wave: packed digit totals, then prefixes
     __shared__ uint32_t s_dt[8];                             // packed digit totals of the workgroup
     __shared__ long long s_tmp[kPlanWaves];
-    __shared__ int s_tmp32[kPlanWaves];
+    __shared__ long long s_scan[3][kPlanWaves];              // the waves' totals of the scans
     __shared__ int s_misc[4];                                // distinct parents, table full, ADD entries
     __shared__ unsigned long long s_place;                   // first entry << 32 | first chunk
     constexpr int T = kPlanThreads;
@@ -931,22 +933,31 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
     __syncthreads();
 
     if (small) {
-        // rank of entry t: the entries with a smaller key, or an equal key
-        // earlier in the batch (every lane of a wave reads the same key: an
-        // LDS broadcast)
+        // rank of an entry: the entries with a smaller key, or an equal key
+        // earlier in the batch.  A wave ranks 64 entries against every parts-th
+        // key (its lanes read the same one: an LDS broadcast), so the count
+        // takes at most m / parts steps, 256 at the most.
+        const int waves = (m + 63) >> 6, parts = kPlanWaves / waves;
+        const int at = (wv % waves) * 64 + lane, part = wv / waves;
+        const bool mine = at < m && part < parts;
         unsigned long long mk = 0;
-        int mv = 0, rank = 0;
-        if (t < m) {
-            mk = s_key[plan_pad(t)];
-            mv = s_val[plan_pad(t)];
+        int mv = 0;
+        for (int j = t; j < m; j += T) s_cnt[j] = 0u;
+        __syncthreads();
+        if (mine) {
+            mk = s_key[plan_pad(at)];
+            mv = s_val[plan_pad(at)];
+            uint32_t rank = 0;
 #pragma unroll 8
-            for (int j = 0; j < m; j++) {
+            for (int j = part; j < m; j += parts) {
                 const unsigned long long kj = s_key[plan_pad(j)];
-                rank += (int)((kj < mk) | ((kj == mk) & (j < t)));
+                rank += (uint32_t)((kj < mk) | ((kj == mk) & (j < at)));
             }
+            atomicAdd(&s_cnt[at], rank);
         }
         __syncthreads();
-        if (t < m) {
+        if (mine && part == 0) {
+            const int rank = (int)s_cnt[at];
             s_key[plan_pad(rank)] = mk;
             s_val[plan_pad(rank)] = (uint16_t)mv;
         }
@@ -1066,7 +1077,9 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
     const unsigned long long before = (nv > 0 && e0 > 0) ? s_key[plan_pad(e0 - 1)] : 0ull;
     const unsigned long long after = (nv > 0 && e0 + nv < m) ? s_key[plan_pad(e0 + nv)] : 0ull;
     uint32_t wbits = 0, hbits = 0, lbits = 0;
-    int sw = 0, sc = 0, lh = -1;
+    int32_t ct[kPlanItems];  // children of the entry's parent (heads and ends of groups)
+    int sw = 0, lh = -1;
+    long long sct = 0;  // of heads: children << 32 | their chunks
 #pragma unroll
     for (int j = 0; j < kPlanItems; j++) {
         if (j < nv) {
@@ -1080,29 +1093,68 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
             hbits |= (uint32_t)h << j;
             lbits |= (uint32_t)l << j;
             sw += w;
-            if (h) {
+            ct[j] = 0;
+            if (h || l) {
                 const int32_t x = slotted ? s_tab[(int)(k[j] >> 32)] : (int32_t)(k[j] >> 32);
-                sc += (F.nodes[x].ct_cnt + 63) / 64;
-                lh = e;
+                ct[j] = F.nodes[x].ct_cnt;
             }
+            if (h) lh = e;
         }
     }
     // label tokens of the winners
-    long long srest = 0, pool_total;
+    long long srest = 0, pool_total = 0;
     int32_t rest[kPlanItems];
 #pragma unroll
     for (int j = 0; j < kPlanItems; j++) {
         rest[j] = j < nv && ((wbits >> j) & 1u) ? arest[v[j]] : 0;
         srest += rest[j];
     }
-    long long prest = plan_block_excl<long long>(srest, 0, plus64, s_tmp, &pool_total);
-    int tw, tc, th;
-    int pw = plan_block_excl<int>(sw, 0, plus, s_tmp32, &tw);
-    int pc = plan_block_excl<int>(sc, 0, plus, s_tmp32, &tc);
-    int ph = plan_block_excl<int>(lh, -1, [](int x, int y) { return x > y ? x : y; }, s_tmp32, &th);
-    // places of the workgroup's entries and of its chunks: both from one atomic,
-    // so that cstart ascends over all workgroups' entries
-    if (t == 0) s_place = atomicAdd(&ctr->plan_alloc, ((unsigned long long)m << 32) | (unsigned)tc);
+#pragma unroll
+    for (int j = 0; j < kPlanItems; j++)
+        if (j < nv && ((hbits >> j) & 1u)) sct += ((long long)ct[j] << 32) | (long long)((ct[j] + 63) / 64);
+    // the four scans share their barriers: label tokens, children and chunks,
+    // winners, group heads
+    const auto most = [](int x, int y) { return x > y ? x : y; };
+    const long long irest = plan_wave_incl(srest, plus64), ict = plan_wave_incl(sct, plus64);
+    const int iw = plan_wave_incl(sw, plus), ih = plan_wave_incl(lh, most);
+    if (lane == 63) {
+        s_scan[0][wv] = irest;
+        s_scan[1][wv] = ict;
+        s_scan[2][wv] = ((long long)iw << 32) | (uint32_t)ih;
+    }
+    __syncthreads();
+    long long prest = irest - srest, pct = ict - sct, all_ct = 0;
+    pool_total = 0;
+    int pw = iw - sw, tw = 0, ph = __shfl_up(ih, 1);
+    if (lane == 0) ph = -1;
+#pragma unroll
+    for (int w = 0; w < kPlanWaves; w++) {
+        const long long a = s_scan[0][w], b = s_scan[1][w], c = s_scan[2][w];
+        if (w < wv) {
+            prest += a;
+            pct += b;
+            pw += (int)(c >> 32);
+            ph = most(ph, (int)(uint32_t)c);
+        }
+        pool_total += a;
+        all_ct += b;
+        tw += (int)(c >> 32);
+    }
+    // places of the workgroup's entries and of its chunks, both from one atomic,
+    // so that cstart ascends over all workgroups' entries; records of its rebuilt
+    // blocks (old children and winners); label tokens: three atomics in flight
+    // together
+    const int tc = (int)(uint32_t)all_ct;
+    const long long need_all = (all_ct >> 32) + tw;
+    if (t == 0) {
+        s_place = atomicAdd(&ctr->plan_alloc, ((unsigned long long)m << 32) | (unsigned)tc);
+        const long long nb = (long long)atomicAdd(&ctr->n_nodes, (unsigned long long)need_all);
+        const long long pb = (long long)atomicAdd(&ctr->n_pool, (unsigned long long)pool_total);
+        const bool ok = nb + need_all <= F.cap_nodes && pb + pool_total <= F.cap_pool;
+        if (!ok) atomicAdd(&ctr->overflow, 1ull);
+        s_tmp[0] = ok ? nb : -1;
+        s_tmp[1] = pb;
+    }
     __syncthreads();
     const int eb = (int)(s_place >> 32), cb = (int)(uint32_t)s_place;
     for (int p = t; p < m; p += T) {
@@ -1114,6 +1166,7 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
     __syncthreads();  // s_key and s_val are staged over below
     // 4. per entry: widx, hd and cstart, staged in LDS and written out coalesced; widx stays in s_val for the group ends
     const int ph0 = ph;
+    int pc = (int)(uint32_t)pct;
 #pragma unroll
     for (int j = 0; j < kPlanItems; j++) {
         if (j < nv) {
@@ -1123,10 +1176,7 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
             s_val[plan_pad(e)] = (uint16_t)pw;
             s_key[plan_pad(e)] = ((unsigned long long)(uint32_t)pc << 32) | (uint32_t)ph;
             pw += (wbits >> j) & 1u;
-            if (h) {
-                const int32_t x = slotted ? s_tab[(int)(k[j] >> 32)] : (int32_t)(k[j] >> 32);
-                pc += (F.nodes[x].ct_cnt + 63) / 64;
-            }
+            if (h) pc += (ct[j] + 63) / 64;
         }
     }
     __syncthreads();
@@ -1139,33 +1189,8 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
         hd[eb + p] = eb + (int32_t)(uint32_t)sk;
         cstart[eb + p] = cb + (int32_t)(sk >> 32);
     }
-    // 5. records per rebuilt block (old children + winners), scanned over the
-    // groups in order; one allocation for all of them and one for the pool
-    int hcur = ph0;
-    int need = 0;
-#pragma unroll
-    for (int j = 0; j < kPlanItems; j++) {
-        if (j < nv) {
-            const int e = e0 + j;
-            if ((hbits >> j) & 1u) hcur = e;
-            if ((lbits >> j) & 1u) {
-                const int32_t x = slotted ? s_tab[(int)(k[j] >> 32)] : (int32_t)(k[j] >> 32);
-                const int nw = (int)s_val[plan_pad(e)] + (int)((wbits >> j) & 1u) - (int)s_val[plan_pad(hcur)];
-                need += F.nodes[x].ct_cnt + nw;
-            }
-        }
-    }
-    int need_all;
-    int noff = plan_block_excl<int>(need, 0, plus, s_tmp32, &need_all);
-    if (t == 0) {
-        const long long nb = (long long)atomicAdd(&ctr->n_nodes, (unsigned long long)need_all);
-        const long long pb = (long long)atomicAdd(&ctr->n_pool, (unsigned long long)pool_total);
-        const bool ok = nb + need_all <= F.cap_nodes && pb + pool_total <= F.cap_pool;
-        if (!ok) atomicAdd(&ctr->overflow, 1ull);
-        s_tmp[0] = ok ? nb : -1;
-        s_tmp[1] = pb;
-    }
-    __syncthreads();
+    __syncthreads();  // the staged outputs are read, s_tok below takes their place
+    // 5. a rebuilt block starts after the earlier groups' children and winners
     prest += s_tmp[1];
 #pragma unroll
     for (int j = 0; j < kPlanItems; j++)
@@ -1176,22 +1201,23 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
     // winners' tokens go to LDS at their place in win_tok (head + ordinal) and
     // out coalesced; entries past a group's winners hold no token
     const long long nb0 = s_tmp[0];
-    uint32_t *s_tok = reinterpret_cast<uint32_t *>(s_key);  // the staged outputs were read above
-    hcur = ph0;
+    uint32_t *s_tok = reinterpret_cast<uint32_t *>(s_key);
+    int hcur = ph0;
+    int32_t before_ct = (int32_t)(pct >> 32);  // children of the groups up to the entry's
 #pragma unroll
     for (int j = 0; j < kPlanItems; j++) {
         if (j < nv) {
             const int e = e0 + j;
             const bool w = (wbits >> j) & 1u;
-            if ((hbits >> j) & 1u) hcur = e;
+            if ((hbits >> j) & 1u) {
+                hcur = e;
+                before_ct += ct[j];
+            }
             const int wk = (int)s_val[plan_pad(hcur)];
             if (w) s_tok[plan_pad(hcur + ((int)s_val[plan_pad(e)] - wk))] = (uint32_t)k[j] ^ 0x80000000u;
             if ((lbits >> j) & 1u) {
-                const int32_t x = slotted ? s_tab[(int)(k[j] >> 32)] : (int32_t)(k[j] >> 32);
-                const int nw = (int)s_val[plan_pad(e)] + (int)w - wk;
-                grp_nw[eb + hcur] = nw;
-                grp_nb[eb + hcur] = nb0 < 0 ? -1 : (int32_t)(nb0 + noff);
-                noff += F.nodes[x].ct_cnt + nw;
+                grp_nw[eb + hcur] = (int)s_val[plan_pad(e)] + (int)w - wk;
+                grp_nb[eb + hcur] = nb0 < 0 ? -1 : (int32_t)(nb0 + (before_ct - ct[j]) + wk);
             }
         }
     }
