@@ -72,6 +72,7 @@ struct MergeCounters {
     unsigned long long wide_tokens;  // nonzero: an appended label token lies outside [0, 131071] (no narrow copy)
     unsigned long long hi_tokens;    // nonzero: an appended label token lies in [65536, 131071] (17-bit labels)
     unsigned long long plan_alloc;     // the round's planned ADD entries << 32 | chunks that move for them
+    unsigned long long rounds;         // the call's last round in which an insert walked (1: the first)
     unsigned long long plan_fallback;  // nonzero: a round had a plan bucket too large for its workgroup
 };
 
@@ -286,13 +287,13 @@ __device__ __forceinline__ InsState m_walk(const DevForest &F, const int32_t *s,
     return r;
 }
 
-// Walk every unfinished insert.  first: nothing has looked at the batch yet;
-// invalid entries are skipped and counted (touches ignore them).  addx[i] gets
+// Walk every unfinished insert.  round: 1 if nothing has looked at the batch yet;
+// invalid entries are then skipped and counted (touches ignore them).  addx[i] gets
 // the parent of an ADD insert, else -1, arest[i] the label tokens it needs.
 constexpr int kMergeWalkWaves = 16;  // a workgroup: marks are shared in it
 __global__ __launch_bounds__(64 *kMergeWalkWaves) void merge_walk_kernel(DevForest F, Batch B, InsState *st,
                                                                         int32_t *addx, int32_t *arest,
-                                                                        MergeCounters *ctr, int first) {
+                                                                        MergeCounters *ctr, int round) {
     __shared__ MarkTable s_marks;
     const int lane = (int)(threadIdx.x & 63);
     const int64_t i = (int64_t)blockIdx.x * kMergeWalkWaves + uniform((int32_t)(threadIdx.x / 64));
@@ -303,7 +304,7 @@ __global__ __launch_bounds__(64 *kMergeWalkWaves) void merge_walk_kernel(DevFore
     const int64_t b = B.offsets[i], e = B.offsets[i + 1];
     const int32_t p = batch_peer(B, i);
     bool walk;
-    if (first) {
+    if (round == 1) {
         walk = p >= 0 && p < B.P && b >= 0 && e >= b && e <= B.num_tokens && e - b <= (int64_t)INT32_MAX;
         if (!walk && lane == 0) {
             st[i].kind = kInsSkip;
@@ -323,6 +324,8 @@ __global__ __launch_bounds__(64 *kMergeWalkWaves) void merge_walk_kernel(DevFore
         st[i] = r;
         addx[i] = r.kind == kInsAdd ? r.x : -1;
         arest[i] = (int32_t)(e - b - r.d);
+        if (fresh_u64(&ctr->rounds) < (uint64_t)round)
+            __hip_atomic_store(&ctr->rounds, (unsigned long long)round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 

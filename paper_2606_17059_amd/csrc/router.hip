@@ -135,6 +135,7 @@ struct pr_forest {
     long long stamp = 0;          // add-round counter (stamps of moved records)
     int64_t round_nodes = 0;      // records recent merges added at most (spare capacity kept for the next)
     int64_t round_pool = 0;       // pool tokens, likewise (0: no merge yet)
+    int rounds[2] = {2, 2};       // rounds the last batch took (a merge's, a snapshot's), kMostRounds at most
     bool holes = false;           // a refused allocation left records below n_nodes unwritten (until the
                                   // next compaction): no pass over all records
     int64_t refusals = 0;         // merge rounds repeated after running out of capacity
@@ -201,7 +202,8 @@ constexpr size_t kStageBytes = 256;  // pinned readback staging per forest
 constexpr size_t kEvictStage = 128;  // where in it an eviction's status goes (a walk's is at its start)
 constexpr unsigned kExportBlocks = 2048;  // workgroups of an export's write when only the device knows its size
 constexpr int kCompactLevels = 6;    // levels a compaction enqueues before it reads anything back
-constexpr int kDeviceRounds = 2;     // merge rounds queued before the first readback
+constexpr int kDeviceRounds = 2;     // merge rounds queued before each readback but the first
+constexpr int kMostRounds = 4;       // ... before the first at most
 
 unsigned grid_threads(int64_t n, int bs) { return (unsigned)((n + bs - 1) / bs); }
 unsigned grid_waves(int64_t n) { return (unsigned)((n + pr::kMergeWavesPerBlock - 1) / pr::kMergeWavesPerBlock); }
@@ -1044,27 +1046,32 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
     const unsigned build_blocks = (unsigned)std::min<int64_t>(pr::kMoveBlocks, std::max<int64_t>(256, n / 4));
     int first = 1;  // the next walk is the first to look at the batch
     bool done = false;
-    // Rounds the device drives: kDeviceRounds full rounds, each sized on the
-    // device (the add phase planned in one workgroup, the later steps striding
-    // over what it planned), then one workgroup, which finishes up to
-    // pr::kSmallMax inserts that are left, and one readback.  Most batches end
-    // there: the first round places every insert but the losers of a slot or an
-    // edge, the second those, but for the losers among them.  With more left, as
-    // when many sequences share a prefix the forest does not have (a slot, then
-    // an edge, then the slots below it), two more rounds run.  Anything else (a
-    // round too large for the one-workgroup plan, a refused allocation)
-    // continues in the host-driven rounds below, which read the counters back
-    // after every walk.
+    // Rounds the device drives: full rounds, each sized on the device (the add
+    // phase planned there, the later steps striding over what it planned), then
+    // one workgroup, which finishes up to pr::kSmallMax inserts that are left, and
+    // one readback.  Most batches end there: the first round places every insert
+    // but the losers of a slot or an edge, the second those, but for the losers
+    // among them.  With more left, as when many sequences share a prefix the
+    // forest does not have (a slot, then an edge, then the slots below it), more
+    // rounds run.  As many are queued first as the last batch of the kind took (a
+    // readback and its wait cost 25 us, a round with nothing to do 16): one for a
+    // peer's next snapshot, most of which the forest still has, four for the first
+    // ones of a cold start, three for 10,000 requests.  Anything else (a round too
+    // large for the plan, a refused allocation) continues in the host-driven
+    // rounds below, which read the counters back after every walk.
+    int &taken = f->rounds[B.peer_of ? 0 : 1];
+    int queued = 0;
     for (int k = 0; PR_MERGE_PLAN && !done && f->d_stage && n <= pr::kPlanMaxBatch && k < 4; k++) {
         if ((r = ensure_capacity(f, f->dev.n_nodes + std::max<int64_t>(f->round_nodes, n),
                                  f->dev.n_pool + f->round_pool, s)))
             return r;
         const pr::DevForest F = dev_view(f);
         const pr::NarrowDst N = narrow_dst(f);
-        for (int round = 0; round < kDeviceRounds; round++, first = 0) {
+        for (int left = k == 0 ? taken : kDeviceRounds; left > 0; left--, first = 0) {
+            queued++;
             const long long stamp = ++f->stamp;
             hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_walk(n)), dim3(64 * pr::kMergeWalkWaves), 0, s, F, B, m.st, m.addx,
-                               m.arest, f->d_ctr, first);
+                               m.arest, f->d_ctr, queued);
             if (!B.touch) {  // touches add nothing
                 hipLaunchKernelGGL(pr::add_plan_kernel, dim3(plan_grid), dim3(pr::kPlanThreads), 0, s, F, B, m.st,
                                    m.addx, m.arest, m.keys_out, m.vals_out, m.win, m.widx, m.hd, m.cstart, m.grp_nw,
@@ -1081,6 +1088,8 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
         if (hipGetLastError() != hipSuccess) return fail(PR_EDEVICE, "merge launch failed");
         if ((r = run_small_merge(f, B, m.st, s, &ss))) return r;
         done = ss.done != 0;
+        // one more where the last workgroup had several inserts for a wave
+        taken = std::min(std::max((int)ss.rounds + (ss.left > (uint32_t)pr::kSmallWaves), 1), kMostRounds);
         if (ss.bad)
             return fail(PR_EDEVICE, "merge invariant broken; destroy the forest");
         if (ss.overflow && (r = refused_round(f, (int64_t)ss.n_nodes, (int64_t)ss.n_pool, 1, s))) return r;
@@ -1095,7 +1104,7 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
     for (; !done && round < max_rounds; round++, first = 0) {
         hipLaunchKernelGGL(reset_round_kernel, dim3(1), dim3(1), 0, s, f->d_ctr);
         hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_walk(n)), dim3(64 * pr::kMergeWalkWaves), 0, s, dev_view(f), B, m.st, m.addx,
-                           m.arest, f->d_ctr, first);
+                           m.arest, f->d_ctr, first ? 1 : 2);
         hipLaunchKernelGGL(pr::merge_tally_kernel,
                            dim3((unsigned)std::min<int64_t>(256, (n + pr::kTallyThreads - 1) / pr::kTallyThreads)),
                            dim3(pr::kTallyThreads), 0, s, B, m.st, f->d_ctr);

@@ -51,6 +51,7 @@ struct SmallStatus {
     uint32_t hi, wide;  // an appended token is in [65536, 131071], past 131071 (or negative)
     uint32_t stamps;    // stamps taken
     uint32_t left;      // unfinished inserts found at the start
+    uint32_t rounds;    // the last round in which one walked
     uint32_t overflow, fallback, bad;  // the counters' of the rounds before
     unsigned long long n_nodes, n_pool;
 };
@@ -304,6 +305,7 @@ __global__ __launch_bounds__(64 *kSmallWaves) void small_merge_kernel(DevForest 
         r.wide = (s_seen & 2u) || ctr->wide_tokens;
         r.stamps = (uint32_t)(stamp - stamp0);
         r.left = (uint32_t)left;
+        r.rounds = (uint32_t)ctr->rounds;
         r.overflow = ctr->overflow != 0;
         r.fallback = ctr->plan_fallback != 0;
         r.bad = ctr->bad_path != 0;
