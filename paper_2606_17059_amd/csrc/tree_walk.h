@@ -32,7 +32,8 @@ constexpr int kWalkThreads = 1024;
 constexpr int kWalkFront = 4096;       // frontier nodes in LDS
 constexpr int kWalkUnroll = 4;         // children a thread has in flight
 constexpr int kWalkChildren = 1 << 17; // children of one level: more are worth a chip-wide launch
-constexpr int kWalkLeaves = 8192;      // leaves sorted in LDS (exports)
+constexpr int kWalkLeaves = 8192;      // leaves ordered in LDS (exports)
+constexpr int kWalkBits = 1 << 18;     // records up to which a bitmap orders them
 
 // Device and host copies of what a walk found.
 struct WalkStatus {
@@ -234,26 +235,44 @@ __global__ __launch_bounds__(kWalkThreads) void tree_walk_kernel(DevForest F, in
     bool fits = O.offsets && (int64_t)n + 1 <= O.seqs_cap && all_leaf <= O.tokens_cap;
     if (O.offsets && n > kWalkLeaves) done = false;
     if (done && fits) {
-        // leaves by node id: a bitonic sort in LDS (the frontier's, which is
-        // free), then the offsets of their depths
+        // leaves by node id, then the offsets of their depths.  Ids differ, so
+        // up to kWalkBits records a bit each in LDS (the frontier's, which is
+        // free) and a scan of the words' counts put them in order; a bitonic sort
+        // in LDS beyond.
         int32_t *key = &s_id[0][0];
-        static_assert(2 * kWalkFront >= kWalkLeaves, "the leaves fit the frontier's LDS");
-        int np = 1;
-        while (np < n) np <<= 1;
-        for (int i = t; i < np; i += kWalkThreads) key[i] = i < n ? O.leaves[i] : INT32_MAX;
-        __syncthreads();
-        for (int k = 2; k <= np; k <<= 1)
-            for (int j = k >> 1; j > 0; j >>= 1) {
-                for (int q = t; q < np / 2; q += kWalkThreads) {
-                    const int a = ((q & ~(j - 1)) << 1) | (q & (j - 1)), b = a + j;
-                    const int32_t x = key[a], y = key[b];
-                    if ((x > y) == ((a & k) == 0)) {
-                        key[a] = y;
-                        key[b] = x;
+        static_assert(2 * kWalkFront >= kWalkLeaves && kWalkBits <= 32 * 2 * kWalkFront, "they fit the frontier's LDS");
+        if (n_nodes <= kWalkBits) {
+            uint32_t *bits = reinterpret_cast<uint32_t *>(&s_beg[0][0]);
+            const int words = (int)((n_nodes + 31) >> 5), each = (words + kWalkThreads - 1) / kWalkThreads;
+            for (int i = t; i < words; i += kWalkThreads) bits[i] = 0;
+            __syncthreads();
+            for (int i = t; i < n; i += kWalkThreads) atomicOr(&bits[O.leaves[i] >> 5], 1u << (O.leaves[i] & 31));
+            __syncthreads();
+            const int w0 = min(t * each, words), w1 = min(w0 + each, words);
+            int c = 0, total;
+            for (int i = w0; i < w1; i++) c += __popc(bits[i]);
+            int r = plan_block_excl<int>(c, 0, plus, s_tmp, &total);
+            for (int i = w0; i < w1; i++)
+                for (uint32_t v = bits[i]; v; v &= v - 1) key[r++] = 32 * i + __ffs((int)v) - 1;
+            __syncthreads();
+        } else {
+            int np = 1;
+            while (np < n) np <<= 1;
+            for (int i = t; i < np; i += kWalkThreads) key[i] = i < n ? O.leaves[i] : INT32_MAX;
+            __syncthreads();
+            for (int k = 2; k <= np; k <<= 1)
+                for (int j = k >> 1; j > 0; j >>= 1) {
+                    for (int q = t; q < np / 2; q += kWalkThreads) {
+                        const int a = ((q & ~(j - 1)) << 1) | (q & (j - 1)), b = a + j;
+                        const int32_t x = key[a], y = key[b];
+                        if ((x > y) == ((a & k) == 0)) {
+                            key[a] = y;
+                            key[b] = x;
+                        }
                     }
+                    __syncthreads();
                 }
-                __syncthreads();
-            }
+        }
         constexpr int kPer = kWalkLeaves / kWalkThreads;
         long long d[kPer], sum = 0;
 #pragma unroll

@@ -190,3 +190,22 @@ def test_size_and_eviction_past_unwritten_records():
     p.f.compact()
     p.evict(77, "after a compaction")
     p.close()
+
+
+@pytest.mark.parametrize("records", [1 << 18, (1 << 18) + 1])
+def test_export_order_around_the_bitmap_limit(records):
+    """Leaves put in order by a bitmap over the records, and by a sort past it."""
+    from paper_2606_17059_amd import Forest
+    rng = np.random.default_rng(3)
+    pairs = [[a, b] for a in range(512) for b in range(512)][:records - 513]
+    mine = [pairs[i] for i in rng.choice(len(pairs), 700, replace=False)]
+    f = Forest(2)
+    for p, seqs in ((1, pairs), (0, mine)):
+        f.load_snapshot(p, *pins._csr(seqs))
+    announce(f"export among {records} records")
+    t, o = f.export_snapshot(0)
+    assert f.info()["num_nodes"] == records
+    got = pins.csr_to_list(t.cpu().numpy(), o.cpu().numpy())
+    assert sorted(map(tuple, got)) == sorted(map(tuple, mine))
+    assert f.tree_tokens(0) == len({tuple(s[:k]) for s in mine for k in (1, 2)})
+    f.close()
