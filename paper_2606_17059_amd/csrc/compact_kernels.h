@@ -296,11 +296,13 @@ __global__ __launch_bounds__(kCompactThreads) void compact_lab_scan_kernel(Compa
 // Step 4c (a workgroup per kCompactSeg tokens of the new pool): labels, their
 // narrow copy, and for the nodes whose labels start there the new label offset
 // and a wide block's separators.  The segment's nodes are found by a search over
-// the label offsets and listed in LDS, where every token then finds its own:
-// short labels cost no more than long ones, every store is a full line, segments
-// are alike however the lengths are spread, and the bit plane is written in
-// whole words.  (A wave per node, most of which have one or two 64-token chunks,
-// took 160 us for 23 M tokens; this takes LABELS_US.)
+// the label offsets and listed in LDS with a bit per token that starts a label;
+// every token finds its own by counting the bits before it.  Short labels cost
+// no more than long ones, every store is a full line, segments are alike however
+// the lengths are spread, and the bit plane is written in whole words.  230 MB
+// for 23 M tokens: 160 us with a wave per node (most have one or two 64-token
+// chunks), 104 us with a search per token, four loads in flight and 32 KB of LDS
+// (five workgroups a CU), 58 us with all sixteen loads in flight and 17 KB.
 // blk nullptr: off holds whole offsets.
 constexpr int kCompactSeg = 4096;
 constexpr int kCompactSegThreads = 256;
@@ -309,10 +311,11 @@ __global__ __launch_bounds__(kCompactSegThreads) void compact_labels_kernel(DevF
                                                                            CompactState *S,
                                                                            const int64_t *__restrict__ off,
                                                                            const int64_t *__restrict__ blk) {
-    constexpr int T = kCompactSegThreads, kUnroll = 4;
-    __shared__ int32_t s_off[kCompactSeg + 1];   // label start, from the segment's
-    __shared__ uint32_t s_src[kCompactSeg + 1];  // of its source in the old pool
-    __shared__ int s_m;
+    constexpr int T = kCompactSegThreads, kUnroll = kCompactSeg / T, kWords = kCompactSeg / 64;
+    __shared__ uint32_t s_delta[kCompactSeg];        // per label in order: its source in the old pool less its start
+    __shared__ unsigned long long s_start[kWords];   // a bit per token that starts a label
+    __shared__ int s_before[kWords];                 // label starts in the words before
+    static_assert(kWords == 64, "a lane per word");
     const int t = (int)threadIdx.x, lane = t & 63;
     const int64_t n = S->hi, base = (int64_t)blockIdx.x * kCompactSeg;
     const int64_t end = min<int64_t>(S->n_pool, base + kCompactSeg);
@@ -332,20 +335,19 @@ __global__ __launch_bounds__(kCompactSegThreads) void compact_labels_kernel(DevF
         if (c >= kSep2Min) sep2_write(N.nsep + b, N.ntok + b, c, lane);
     };
     if (base == 0 && t < 64) separators(N.nodes[0].ct_beg, N.nodes[0].ct_cnt);  // the root has no label to list it by
-    if (t == 0) s_m = 0;
+    if (t < kWords) s_start[t] = 0;
     __syncthreads();
     for (int64_t i0 = lo;; i0 += T) {
         const int64_t i = i0 + t;
         const int64_t o = i < n ? at(i) : end;
         int32_t beg = 0, cnt = 0;
         if (o < end) {
-            const int k = (int)(i - lo);
             // the source is the old record's; a label that starts before the
             // segment is listed from the segment's start on
             const int32_t skip = (int32_t)max<int64_t>(base - o, 0);
-            s_off[k] = (int32_t)(o + skip - base);
-            s_src[k] = O.nodes[old_of[i]].lab_off + (uint32_t)skip;
-            atomicMax(&s_m, k + 1);
+            const uint32_t k = (uint32_t)(o + skip - base);
+            s_delta[i - lo] = O.nodes[old_of[i]].lab_off + (uint32_t)skip - k;
+            atomicOr(&s_start[k >> 6], 1ull << (k & 63u));
             if (o >= base) {
                 N.nodes[i].lab_off = (uint32_t)o;
                 beg = N.nodes[i].ct_beg;
@@ -358,38 +360,35 @@ __global__ __launch_bounds__(kCompactSegThreads) void compact_labels_kernel(DevF
         }
         if (__syncthreads_or(o >= end)) break;  // offsets ascend: the rest start past the segment
     }
-    const int m = s_m, len = (int)(end - base);
-    uint32_t all = 0;
-    for (int q0 = 0; q0 < len; q0 += T * kUnroll) {
-        uint32_t v[kUnroll];
+    if (t < kWords) {
+        const uint32_t c = (uint32_t)__popcll(s_start[t]);
+        s_before[t] = (int)(wave_incl_add_u32(c) - c);
+    }
+    __syncthreads();
+    // a wave takes 64 tokens of the new pool at a time, all of its loads in flight
+    const int len = (int)(end - base);
+    uint32_t all = 0, v[kUnroll];
 #pragma unroll
-        for (int u = 0; u < kUnroll; u++) {
-            const int k = q0 + u * T + t;
-            v[u] = 0;
-            if (k < len) {
-                int a = 0, b = m;  // the last node with s_off <= k
-                while (b - a > 1) {
-                    const int mid = (a + b) >> 1;
-                    if (s_off[mid] <= k)
-                        a = mid;
-                    else
-                        b = mid;
-                }
-                v[u] = (uint32_t)O.pool[(int64_t)s_src[a] + (k - s_off[a])];
-            }
+    for (int u = 0; u < kUnroll; u++) {
+        const int k = u * T + t;
+        v[u] = 0;
+        if (k < len) {
+            // the last label that starts at or before k
+            const int a = s_before[k >> 6] + (int)__popcll(s_start[k >> 6] & (~0ull >> (63 - lane))) - 1;
+            v[u] = (uint32_t)O.pool[s_delta[a] + (uint32_t)k];
         }
+    }
 #pragma unroll
-        for (int u = 0; u < kUnroll; u++) {
-            const int k = q0 + u * T + t;
-            if (k < len) {
-                N.pool[base + k] = (int32_t)v[u];
-                if (D.p16) D.p16[base + k] = (uint16_t)v[u];
-                all |= v[u];
-            }
-            const uint64_t bits = __ballot((v[u] >> 16) & 1u);
-            if (D.p16 && lane < 2 && k - lane + 32 * lane < len)
-                D.hib[(base + k - lane + 32 * lane) >> 5] = (uint32_t)(bits >> (32 * lane));
+    for (int u = 0; u < kUnroll; u++) {
+        const int k = u * T + t;
+        if (k < len) {
+            N.pool[base + k] = (int32_t)v[u];
+            if (D.p16) D.p16[base + k] = (uint16_t)v[u];
+            all |= v[u];
         }
+        const uint64_t bits = __ballot((v[u] >> 16) & 1u);
+        if (D.p16 && lane < 2 && k - lane + 32 * lane < len)
+            D.hib[(base + k - lane + 32 * lane) >> 5] = (uint32_t)(bits >> (32 * lane));
     }
     // (a wider token may raise the 17-bit flag too; it drops the narrow copy)
     if (__ballot((all >> 16) & 1u) && lane == 0 && !fresh_u64(&S->hi_tokens)) atomicOr(&S->hi_tokens, 1ull);

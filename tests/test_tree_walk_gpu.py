@@ -197,7 +197,7 @@ def test_export_order_around_the_bitmap_limit(records):
     """Leaves put in order by a bitmap over the records, and by a sort past it."""
     from paper_2606_17059_amd import Forest
     rng = np.random.default_rng(3)
-    pairs = [[a, b] for a in range(512) for b in range(512)][:records - 513]
+    pairs = [[a, b] for a in range(512) for b in range(512)][:records - 512]
     mine = [pairs[i] for i in rng.choice(len(pairs), 700, replace=False)]
     f = Forest(2)
     for p, seqs in ((1, pairs), (0, mine)):
