@@ -288,8 +288,12 @@ __device__ __forceinline__ InsState m_walk(const DevForest &F, const int32_t *s,
 }
 
 // Walk every unfinished insert.  round: 1 if nothing has looked at the batch yet;
-// invalid entries are then skipped and counted (touches ignore them).  addx[i] gets
-// the parent of an ADD insert, else -1, arest[i] the label tokens it needs.
+// invalid entries are then skipped and counted (touches ignore them).  Past 1 it
+// numbers the rounds queued without a look at the counters: one queued behind a
+// refused allocation parks its inserts, since they would ask for the same once
+// more and advance the counters by it.  0: a later round whose predecessors the
+// host has looked at.  addx[i] gets the parent of an ADD insert, else -1, arest[i]
+// the label tokens it needs.
 constexpr int kMergeWalkWaves = 16;  // a workgroup: marks are shared in it
 __global__ __launch_bounds__(64 *kMergeWalkWaves) void merge_walk_kernel(DevForest F, Batch B, InsState *st,
                                                                         int32_t *addx, int32_t *arest,
@@ -303,6 +307,7 @@ __global__ __launch_bounds__(64 *kMergeWalkWaves) void merge_walk_kernel(DevFore
     if (i >= B.n) return;
     const int64_t b = B.offsets[i], e = B.offsets[i + 1];
     const int32_t p = batch_peer(B, i);
+    const unsigned long long refused = ctr->overflow;  // nothing allocates beside a walk
     bool walk;
     if (round == 1) {
         walk = p >= 0 && p < B.P && b >= 0 && e >= b && e <= B.num_tokens && e - b <= (int64_t)INT32_MAX;
@@ -313,6 +318,10 @@ __global__ __launch_bounds__(64 *kMergeWalkWaves) void merge_walk_kernel(DevFore
     } else {
         const int32_t kind = st[i].kind;
         walk = kind != kInsSkip && kind != kInsDone;
+        if (walk && refused && round > 1) {
+            if (lane == 0) st[i].kind = kInsActive;
+            walk = false;
+        }
     }
     if (!walk) {
         if (lane == 0) addx[i] = -1;

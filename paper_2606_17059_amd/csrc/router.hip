@@ -1010,18 +1010,20 @@ pr_status run_small_merge(pr_forest *f, const pr::Batch &B, const pr::InsState *
 
 // A round ran out of capacity.  Every refused allocation wrote nothing and left
 // its inserts to walk again, but the refused requests still advanced the
-// counters: records and tokens past the last allocation that fit were never
-// written, so the counters are clipped to the capacities, and the forest grows
-// to what the round asked for before the round is repeated.
-pr_status refused_round(pr_forest *f, int64_t want_nodes, int64_t want_pool, int64_t pool_need, hipStream_t s) {
+// counters (to asked_nodes and asked_pool): records and tokens past the last
+// allocation that fit were never written, so the counters are clipped to the
+// capacities, and the forest grows before the round is repeated: to the records
+// it asked for, to want_pool tokens, and to pool_need past the clipped ones.
+pr_status refused_round(pr_forest *f, int64_t asked_nodes, int64_t asked_pool, int64_t want_pool, int64_t pool_need,
+                        hipStream_t s) {
     f->refusals++;
     f->holes = true;
-    f->dev.n_nodes = std::min<int64_t>(want_nodes, f->dev.cap_nodes);
-    f->dev.n_pool = std::min<int64_t>(want_pool, f->dev.cap_pool);
+    f->dev.n_nodes = std::min<int64_t>(asked_nodes, f->dev.cap_nodes);
+    f->dev.n_pool = std::min<int64_t>(asked_pool, f->dev.cap_pool);
     hipLaunchKernelGGL(set_used_kernel, dim3(1), dim3(1), 0, s, f->d_ctr, (unsigned long long)f->dev.n_nodes,
                        (unsigned long long)f->dev.n_pool);
     if (hipGetLastError() != hipSuccess) return fail(PR_EDEVICE, "merge launch failed");
-    return ensure_capacity(f, std::max<int64_t>(want_nodes, f->dev.n_nodes + 1),
+    return ensure_capacity(f, std::max<int64_t>(asked_nodes, f->dev.n_nodes + 1),
                            std::max<int64_t>(want_pool, f->dev.n_pool + pool_need), s);
 }
 
@@ -1092,7 +1094,8 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
         taken = std::min(std::max((int)ss.rounds + (ss.left > (uint32_t)pr::kSmallWaves), 1), kMostRounds);
         if (ss.bad)
             return fail(PR_EDEVICE, "merge invariant broken; destroy the forest");
-        if (ss.overflow && (r = refused_round(f, (int64_t)ss.n_nodes, (int64_t)ss.n_pool, 1, s))) return r;
+        // (the next round's walk is tallied, which says what tokens are needed)
+        if (ss.overflow && (r = refused_round(f, (int64_t)ss.n_nodes, (int64_t)ss.n_pool, 0, 0, s))) return r;
         if (ss.overflow || ss.fallback) break;
     }
     pr::MergeCounters c;
@@ -1104,14 +1107,16 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
     for (; !done && round < max_rounds; round++, first = 0) {
         hipLaunchKernelGGL(reset_round_kernel, dim3(1), dim3(1), 0, s, f->d_ctr);
         hipLaunchKernelGGL(pr::merge_walk_kernel, dim3(grid_walk(n)), dim3(64 * pr::kMergeWalkWaves), 0, s, dev_view(f), B, m.st, m.addx,
-                           m.arest, f->d_ctr, first ? 1 : 2);
+                           m.arest, f->d_ctr, first ? 1 : 0);
         hipLaunchKernelGGL(pr::merge_tally_kernel,
                            dim3((unsigned)std::min<int64_t>(256, (n + pr::kTallyThreads - 1) / pr::kTallyThreads)),
                            dim3(pr::kTallyThreads), 0, s, B, m.st, f->d_ctr);
         if ((r = read_counters_raw(f, &c, s))) return r;
         if (c.overflow) {
             if (++refusals > 4) break;  // reported below
-            if ((r = refused_round(f, (int64_t)c.n_nodes, (int64_t)c.n_pool, (int64_t)c.pool_need, s))) return r;
+            if ((r = refused_round(f, (int64_t)c.n_nodes, (int64_t)c.n_pool, (int64_t)c.n_pool, (int64_t)c.pool_need,
+                                   s)))
+                return r;
             continue;
         }
         f->dev.n_nodes = (int64_t)c.n_nodes;
