@@ -64,3 +64,32 @@ def test_rounds_queued_behind_a_refusal_ask_for_nothing():
     f.check()
     f.close()
     o.close()
+
+
+@pytest.mark.parametrize("n,L", [(100, 20000), (500, 1200)])
+@pytest.mark.parametrize("load", [True, False])
+def test_first_batch_past_the_pool_is_sized_before_it_runs(n, L, load):
+    """A cold forest's first snapshot or merge does not fit the pool it starts
+    with (262,144 tokens): the pool grows to what the walk finds missing, nothing
+    is refused, and the records hold the batch without gaps."""
+    import oracle
+    import torch
+    from paper_2606_17059_amd import Forest
+    rng = np.random.default_rng(n)
+    f, o = Forest(2), oracle.RadixOracle(2)
+    heads = rng.integers(0, 30000, (8, L // 2))
+    seqs = [heads[i % 8].tolist() + rng.integers(0, 30000, L - L // 2).tolist() for i in range(n)]
+    t, off = pins._csr(seqs)
+    if load:
+        announce(f"cold load {n} x {L}")
+        f.load_snapshot_device(1, *[torch.from_numpy(x).to(device()) for x in (t, off)])
+        o.merge(np.ones(n, np.int32), t, off)
+    else:
+        _merge(f, o, np.ones(n), seqs, f"cold merge {n} x {L}")
+    info = f.info()
+    assert info["merge_refusals"] == 0
+    assert info["pool_tokens"] <= n * L
+    assert info["device_bytes"] <= _capacity_bytes(info, n * L + 64, 0) + (8 << 20), info
+    _check(f, o, [s[:L - i] for i, s in enumerate(seqs[:64])] + [s[:L // 2] + [-1] for s in seqs[::9]], "cold")
+    f.close()
+    o.close()
