@@ -571,6 +571,14 @@ pr_status ensure_capacity(pr_forest *f, int64_t need_nodes, int64_t need_pool, h
     return PR_OK;
 }
 
+// Room for the given totals where the ids and the memory allow it: what a merge
+// may come to need.  What it does need is a refused round's request.
+pr_status reserve_capacity(pr_forest *f, int64_t nodes, int64_t pool, hipStream_t s) {
+    const pr_status r = ensure_capacity(f, std::min<int64_t>(nodes, (int64_t)INT32_MAX),
+                                        std::min<int64_t>(pool, (int64_t)UINT32_MAX), s);
+    return r == PR_ENOMEM ? PR_OK : r;
+}
+
 pr::DevForest dev_view(const pr_forest *f);
 
 // The narrow label copy.  While every label token lies in [0, 131071], routes
@@ -1013,7 +1021,8 @@ pr_status run_small_merge(pr_forest *f, const pr::Batch &B, const pr::InsState *
 // counters (to asked_nodes and asked_pool): records and tokens past the last
 // allocation that fit were never written, so the counters are clipped to the
 // capacities, and the forest grows before the round is repeated: to the records
-// it asked for, to want_pool tokens, and to pool_need past the clipped ones.
+// it asked for and to want_pool tokens, and, if there is room, to pool_need past
+// the clipped ones.
 pr_status refused_round(pr_forest *f, int64_t asked_nodes, int64_t asked_pool, int64_t want_pool, int64_t pool_need,
                         hipStream_t s) {
     f->refusals++;
@@ -1023,8 +1032,9 @@ pr_status refused_round(pr_forest *f, int64_t asked_nodes, int64_t asked_pool, i
     hipLaunchKernelGGL(set_used_kernel, dim3(1), dim3(1), 0, s, f->d_ctr, (unsigned long long)f->dev.n_nodes,
                        (unsigned long long)f->dev.n_pool);
     if (hipGetLastError() != hipSuccess) return fail(PR_EDEVICE, "merge launch failed");
-    return ensure_capacity(f, std::max<int64_t>(asked_nodes, f->dev.n_nodes + 1),
-                           std::max<int64_t>(want_pool, f->dev.n_pool + pool_need), s);
+    asked_nodes = std::max<int64_t>(asked_nodes, f->dev.n_nodes + 1);
+    const pr_status r = reserve_capacity(f, asked_nodes, std::max<int64_t>(want_pool, f->dev.n_pool + pool_need), s);
+    return r ? r : ensure_capacity(f, asked_nodes, want_pool, s);
 }
 
 // Insert a device batch into the device forest (see merge_kernels.h), or touch
@@ -1083,15 +1093,15 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
     bool walked = false;
     if (device_rounds && f->round_pool == 0 && !B.touch && B.num_tokens > f->dev.cap_pool - f->dev.n_pool) {
         if ((r = walk_and_tally(1)) ||
-            (r = ensure_capacity(f, f->dev.n_nodes + n, f->dev.n_pool + (int64_t)c.pool_need, s)))
+            (r = reserve_capacity(f, f->dev.n_nodes + n, f->dev.n_pool + (int64_t)c.pool_need, s)))
             return r;
         walked = true;
         first = 0;
         queued = 1;
     }
     for (int k = 0; device_rounds && !done && k < 4; k++) {
-        if ((r = ensure_capacity(f, f->dev.n_nodes + std::max<int64_t>(f->round_nodes, n),
-                                 f->dev.n_pool + f->round_pool, s)))
+        if ((r = reserve_capacity(f, f->dev.n_nodes + std::max<int64_t>(f->round_nodes, n),
+                                  f->dev.n_pool + (B.touch ? 0 : f->round_pool), s)))
             return r;
         const pr::DevForest F = dev_view(f);
         const pr::NarrowDst N = narrow_dst(f);
@@ -1150,8 +1160,8 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
         // between the phases.  A forest whose spare capacity is short of what the
         // last merges added grows first (the walk's tally bounds the pool tokens).
         const int64_t n_split = (int64_t)c.n_split, n_add = (int64_t)c.n_add;
-        if ((r = ensure_capacity(f, f->dev.n_nodes + std::max<int64_t>(f->round_nodes, n),
-                                 f->dev.n_pool + (int64_t)c.pool_need, s)))
+        if ((r = reserve_capacity(f, f->dev.n_nodes + std::max<int64_t>(f->round_nodes, n),
+                                  f->dev.n_pool + (int64_t)c.pool_need, s)))
             return r;
         const pr::DevForest F = dev_view(f);
         const pr::NarrowDst N = narrow_dst(f);
