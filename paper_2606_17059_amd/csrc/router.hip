@@ -135,7 +135,8 @@ struct pr_forest {
     long long stamp = 0;          // add-round counter (stamps of moved records)
     int64_t round_nodes = 0;      // records recent merges added at most (spare capacity kept for the next)
     int64_t round_pool = 0;       // pool tokens, likewise (0: no merge yet)
-    int rounds[2] = {2, 2};       // rounds the last batch took (a merge's, a snapshot's), kMostRounds at most
+    int rounds[3] = {2, 2, 2};    // rounds the last batch took (a merge's, a snapshot's, a touch's), kMostRounds at
+                                  // most
     bool holes = false;           // a refused allocation left records below n_nodes unwritten (until the
                                   // next compaction): no pass over all records
     int64_t refusals = 0;         // merge rounds repeated after running out of capacity
@@ -1071,7 +1072,7 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
     // ones of a cold start, three for 10,000 requests.  Anything else (a round too
     // large for the plan, a refused allocation) continues in the host-driven
     // rounds below, which read the counters back after every walk.
-    int &taken = f->rounds[B.peer_of ? 0 : 1];
+    int &taken = f->rounds[B.touch ? 2 : B.peer_of ? 0 : 1];
     int queued = 0;
     pr::MergeCounters c;
     std::memset(&c, 0, sizeof(c));
@@ -1127,13 +1128,13 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
         if (hipGetLastError() != hipSuccess) return fail(PR_EDEVICE, "merge launch failed");
         if ((r = run_small_merge(f, B, m.st, s, &ss))) return r;
         done = ss.done != 0;
-        // one more where the last workgroup had several inserts for a wave
-        taken = std::min(std::max((int)ss.rounds + (ss.left > (uint32_t)pr::kSmallWaves), 1), kMostRounds);
         if (ss.bad)
             return fail(PR_EDEVICE, "merge invariant broken; destroy the forest");
         // (the next round's walk is tallied, which says what tokens are needed)
         if (ss.overflow && (r = refused_round(f, (int64_t)ss.n_nodes, (int64_t)ss.n_pool, 0, 0, s))) return r;
         if (ss.overflow || ss.fallback) break;
+        // one more where the last workgroup had several inserts for a wave
+        taken = std::min(std::max((int)ss.rounds + (ss.left > (uint32_t)pr::kSmallWaves), 1), kMostRounds);
     }
     const int max_rounds = 100000;
     int round = 0;

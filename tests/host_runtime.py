@@ -181,6 +181,11 @@ class Forest:
         t, o = np.zeros(max(n * tokens, 1), np.int32), np.arange(n + 1, dtype=np.int64) * tokens
         return self.L.pr_merge(self.h, pe.ctypes.data, t.ctypes.data, n * tokens, o.ctypes.data, n, None)
 
+    def load_device(self, p, n, tokens=1):
+        """A snapshot of n sequences that is on the device."""
+        t, o = np.zeros(max(n * tokens, 1), np.int32), np.arange(n + 1, dtype=np.int64) * tokens
+        return self.L.pr_load_snapshot_device(self.h, p, t.ctypes.data, n * tokens, o.ctypes.data, n, None)
+
     def touch(self, n, tokens=1):
         t, o = np.zeros(max(n * tokens, 1), np.int32), np.arange(n + 1, dtype=np.int64) * tokens
         return self.L.pr_touch(self.h, t.ctypes.data, n * tokens, o.ctypes.data, n, None)

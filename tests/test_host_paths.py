@@ -3,7 +3,6 @@ chooses, and what it does when memory or ids run out (tests/host_runtime.py)."""
 import pytest
 
 import host_runtime
-from host_runtime import Counters
 
 
 @pytest.fixture(scope="module")
@@ -69,4 +68,30 @@ def test_a_refusal_the_memory_cannot_meet_is_an_error(rt):
     assert f.merge(65) == rt.R.PR_ENOMEM
     assert f.merge(65) == rt.R.PR_ESTATE
     rt.limit(None)
+    f.close()
+
+
+def _rounds(rt, call):
+    rt.clear()
+    assert call() == 0
+    return rt.launched("merge_walk_kernel")
+
+
+def test_rounds_queued_follow_the_batches_of_their_kind(rt):
+    """As many rounds as the last batch of the kind took: merges, snapshots and
+    touches each have their own count, and a refused batch says nothing."""
+    f = rt.forest(2, [[[1, 2, 3]]])
+    assert f.merge(65) == 0 and f.L.pr_set_local_peer(f.h, 0) == 0
+    rt.on["small_merge_kernel"] = rt.small_merge(rounds=3)
+    assert f.merge(65) == 0
+    rt.on["small_merge_kernel"] = rt.small_merge(rounds=1)
+    assert _rounds(rt, lambda: f.touch(65)) == 2  # none seen so far
+    assert _rounds(rt, lambda: f.touch(65)) == 1
+    load = lambda: f.load_device(1, 65)  # noqa: E731
+    assert _rounds(rt, load) == 2
+    assert _rounds(rt, load) == 1
+    # refused at its first of three queued rounds; the host-driven ones find all done
+    rt.on["small_merge_kernel"] = rt.small_merge(dict(done=0, overflow=1, rounds=1, add_nodes=10), rounds=3)
+    assert _rounds(rt, lambda: f.merge(65)) == 3 + 1
+    assert _rounds(rt, lambda: f.merge(65)) == 3
     f.close()
