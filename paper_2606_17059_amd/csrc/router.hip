@@ -213,17 +213,22 @@ unsigned grid_split(int64_t n) { return (unsigned)((n + pr::kSplitWaves - 1) / p
 
 bool drop_spare(pr_forest *f);
 
-// Device memory for the forest; when there is none left, what the forest keeps
-// for its next compaction is given back first.
-bool dev_malloc(pr_forest *f, void **p, size_t n) {
-    if (hipMalloc(p, n) != hipSuccess) {
+// Device memory; when there is none left, what the forest keeps for its next
+// compaction is given back first.  Every allocation of the library comes here.
+bool malloc_or_drop(pr_forest *f, void **p, size_t n) {
+    if (hipMalloc(p, n) == hipSuccess) return true;
+    (void)hipGetLastError();
+    if (drop_spare(f)) {
+        if (hipMalloc(p, n) == hipSuccess) return true;
         (void)hipGetLastError();
-        if (!drop_spare(f) || hipMalloc(p, n) != hipSuccess) {
-            (void)hipGetLastError();
-            *p = nullptr;
-            return false;
-        }
     }
+    *p = nullptr;
+    return false;
+}
+
+// Device memory the forest keeps.
+bool dev_malloc(pr_forest *f, void **p, size_t n) {
+    if (!malloc_or_drop(f, p, n)) return false;
     f->device_bytes += (int64_t)n;
     return true;
 }
@@ -336,9 +341,11 @@ int64_t slack_cap(int64_t n) {
     return (n + g - 1) / g * g;
 }
 
-// Node arrays (and access times, if wanted) for at least need records in nw:
-// the spare's, unless they are too small or far too large.
-bool new_node_arrays(pr_forest *f, DevImage &nw, int64_t need, bool times) {
+// Node arrays (and access times, if wanted) for at least need records in nw, and
+// extra if there is room: the spare's, unless they are too small or far too large.
+bool new_node_arrays(pr_forest *f, DevImage &nw, int64_t need, int64_t extra, bool times) {
+    const int64_t least = need;
+    need += extra;
     DevImage &sp = f->spare;
     if (sp.node_block && sp.cap_nodes >= need && sp.cap_nodes <= 8 * need) {
         nw.node_block = sp.node_block;
@@ -356,7 +363,7 @@ bool new_node_arrays(pr_forest *f, DevImage &nw, int64_t need, bool times) {
     } else {
         free_node_arrays(f, sp);
         dfree(f, &sp.ltime, sp.cap_nodes);
-        if (!alloc_node_arrays(f, nw, slack_cap(need))) return false;
+        if (!alloc_node_arrays(f, nw, slack_cap(need)) && !alloc_node_arrays(f, nw, least)) return false;
     }
     if (times) return nw.ltime || dalloc(f, &nw.ltime, nw.cap_nodes);
     dfree(f, &nw.ltime, nw.cap_nodes);
@@ -364,8 +371,10 @@ bool new_node_arrays(pr_forest *f, DevImage &nw, int64_t need, bool times) {
 }
 
 // The label pool (and its narrow copy, if wanted and there is memory for it)
-// for at least need tokens in nw, in the same way.
-bool new_pool(pr_forest *f, DevImage &nw, int64_t need, bool narrow) {
+// for at least need tokens in nw, and extra if there is room, in the same way.
+bool new_pool(pr_forest *f, DevImage &nw, int64_t need, int64_t extra, bool narrow) {
+    const int64_t least = need;
+    need += extra;
     DevImage &sp = f->spare;
     if (sp.pool && sp.cap_pool >= need && sp.cap_pool <= 8 * need) {
         nw.pool = sp.pool;
@@ -383,7 +392,10 @@ bool new_pool(pr_forest *f, DevImage &nw, int64_t need, bool narrow) {
     } else {
         free_arrays(f, sp);
         nw.cap_pool = std::min<int64_t>(slack_cap(need), (int64_t)UINT32_MAX);
-        if (!dalloc(f, &nw.pool, nw.cap_pool)) return false;
+        if (!dalloc(f, &nw.pool, nw.cap_pool)) {
+            nw.cap_pool = std::min<int64_t>(least, (int64_t)UINT32_MAX);
+            if (!dalloc(f, &nw.pool, nw.cap_pool)) return false;
+        }
     }
     if (narrow && !nw.pool16) {
         nw.cap_pool16 = nw.cap_pool;
@@ -874,12 +886,8 @@ pr_status ensure_merge_scratch(pr_forest *f, int64_t n, hipStream_t s) {
         f->device_bytes -= (int64_t)m.sort_tmp_bytes;
         m.sort_tmp_bytes = 0;
         m.sort_tmp = nullptr;
-        if (hipMalloc(&m.sort_tmp, need) != hipSuccess) {
-            (void)hipGetLastError();
-            return fail(PR_ENOMEM, "hipMalloc failed for sort scratch");
-        }
+        if (!dev_malloc(f, &m.sort_tmp, need)) return fail(PR_ENOMEM, "hipMalloc failed for sort scratch");
         m.sort_tmp_bytes = need;
-        f->device_bytes += (int64_t)need;
     }
     return PR_OK;
 }
@@ -1377,12 +1385,8 @@ pr_status export_impl(pr_forest *f, int32_t peer, int32_t *tokens, int64_t token
             f->device_bytes -= (int64_t)X.tmp_bytes;
             X.tmp = nullptr;
             X.tmp_bytes = 0;
-            if (hipMalloc(&X.tmp, need) != hipSuccess) {
-                (void)hipGetLastError();
-                return fail(PR_ENOMEM, "hipMalloc failed for the export");
-            }
+            if (!dev_malloc(f, &X.tmp, need)) return fail(PR_ENOMEM, "hipMalloc failed for the export");
             X.tmp_bytes = need;
-            f->device_bytes += (int64_t)need;
         }
         size_t t1 = need;
         if (rocprim::radix_sort_keys(X.tmp, t1, X.leaves, X.sorted, (size_t)n_leaves, 0, 32, s) != hipSuccess)
@@ -1420,15 +1424,12 @@ pr_status export_impl(pr_forest *f, int32_t peer, int32_t *tokens, int64_t token
 
 // Device buffers of one touch or eviction call, released on every return path.
 struct CallScratch {
+    pr_forest *f;
     std::vector<void *> bufs;
+    explicit CallScratch(pr_forest *f) : f(f) {}
     template <typename T>
     bool get(T **p, int64_t count) {
-        *p = nullptr;
-        if (hipMalloc((void **)p, (size_t)std::max<int64_t>(count, 1) * sizeof(T)) != hipSuccess) {
-            (void)hipGetLastError();
-            *p = nullptr;
-            return false;
-        }
+        if (!malloc_or_drop(f, (void **)p, (size_t)std::max<int64_t>(count, 1) * sizeof(T))) return false;
         bufs.push_back((void *)*p);
         return true;
     }
@@ -1611,7 +1612,7 @@ pr_status pr_forest_compact(pr_forest *f, int64_t *nodes_before, int64_t *nodes_
         free_arrays(f, nw);
         return fail(st, m);
     };
-    if (!new_node_arrays(f, nw, std::max<int64_t>(n_old + n_old / 8, 1024) + 2 * f->round_nodes, d.ltime != nullptr))
+    if (!new_node_arrays(f, nw, std::max<int64_t>(n_old + n_old / 8, 1024), 2 * f->round_nodes, d.ltime != nullptr))
         return fail_new(PR_ENOMEM, "hipMalloc failed for the compacted forest");
     const pr::DevForest O = dev_view(f);
     pr::DevForest N = O;
@@ -1624,7 +1625,7 @@ pr_status pr_forest_compact(pr_forest *f, int64_t *nodes_before, int64_t *nodes_
     N.pool = nullptr;
     N.cap_nodes = nw.cap_nodes;
     const bool narrow = f->narrow && d.pool16 && d.hib;
-    auto pool_need = [&](int64_t n) { return std::max<int64_t>(n + n / 8, 4096) + 2 * f->round_pool; };
+    auto pool_need = [&](int64_t n) { return std::max<int64_t>(n + n / 8, 4096); };
     int32_t *old_of = X.front, *start = X.next;
     int64_t *off = X.len1, *blk = X.offs;
     pr::CompactState S;
@@ -1662,7 +1663,7 @@ pr_status pr_forest_compact(pr_forest *f, int64_t *nodes_before, int64_t *nodes_
         if (S.n_pool > (int64_t)UINT32_MAX) return fail_new(PR_EDEVICE, "compacted label pool exceeds 2^32 tokens");
     }
     const int64_t pool_from = one_wait ? 0 : S.n_pool;  // tokens past the used ones are zero
-    if (!new_pool(f, nw, pool_need(one_wait ? d.n_pool : S.n_pool), narrow))
+    if (!new_pool(f, nw, pool_need(one_wait ? d.n_pool : S.n_pool), 2 * f->round_pool, narrow))
         return fail_new(PR_ENOMEM, "hipMalloc failed for the compacted label pool");
     N.pool = nw.pool;
     N.cap_pool = nw.cap_pool;
@@ -1731,7 +1732,7 @@ pr_status pr_tree_tokens(pr_forest *f, int32_t peer, int64_t *tokens, void *hip_
     int32_t counts[3];
     if ((r = walk_peer(f, peer, true, s, counts))) return r;
     if (counts[2] == 0) return ok();
-    CallScratch X;
+    CallScratch X(f);
     unsigned long long *d = nullptr;
     if (!X.get(&d, 1)) return fail(PR_ENOMEM, "hipMalloc failed");
     unsigned long long h = 0;
@@ -1853,7 +1854,7 @@ pr_status pr_evict_lru(pr_forest *f, int64_t max_tokens, int64_t *evicted, void 
     if ((r = walk_peer(f, f->local, true, s, counts))) return r;
     const int64_t V = counts[2];
     if (V == 0) return ok();
-    CallScratch X;
+    CallScratch X(f);
     unsigned long long *keys = nullptr, *keys_s = nullptr;
     int32_t *vals = nullptr, *vals_s = nullptr;
     int64_t *cnt1 = nullptr, *cum = nullptr;

@@ -107,12 +107,22 @@ hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned) {
     *d = h;
     return hipSuccess;
 }
+// Whether [p, p + n) lies in one allocation, or in none (host memory).
+static bool inside(const void *p, size_t n) {
+    auto it = g_allocs.upper_bound(const_cast<void *>(p));
+    if (it == g_allocs.begin()) return true;
+    --it;
+    const char *end = (const char *)it->first + it->second;
+    return (const char *)p >= end || (const char *)p + n <= end;
+}
 hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) {
+    if (!inside(d, n) || !inside(s, n)) return hipErrorInvalidValue;
     if (n <= kMoved) std::memmove(d, s, n);
     return hipSuccess;
 }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hipStream_t) { return hipMemcpy(d, s, n, k); }
 hipError_t hipMemset(void *d, int v, size_t n) {
+    if (!inside(d, n)) return hipErrorInvalidValue;
     if (n <= kMoved) std::memset(d, v, n);
     return hipSuccess;
 }

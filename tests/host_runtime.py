@@ -71,7 +71,7 @@ class HostRuntime:
         self.launches = []
         self.errors = []
         self.on = {"stage_copy_kernel": self._stage, "set_used_kernel": self._set_used,
-                   "small_merge_kernel": self.small_merge()}
+                   "small_merge_kernel": self.small_merge(), "compact_counters_kernel": self._compact_counters}
         hook = ctypes.CFUNCTYPE(None, ctypes.c_char_p, ctypes.POINTER(_vp), ctypes.c_uint, ctypes.c_uint)(self._hook)
         self._keep = hook
         self.L.host_runtime_hook(hook)
@@ -119,6 +119,32 @@ class HostRuntime:
         c = self.at(args, 0, Counters)
         c.n_nodes, c.n_pool, c.overflow = self.arg(args, 1, _u64), self.arg(args, 2, _u64), 0
 
+    def _compact_counters(self, args):
+        c, S = self.at(args, 0, Counters), self.at(args, 1, Compact)
+        c.n_nodes, c.n_pool = S.hi, S.n_pool
+
+    def compacts_to(self, nodes, pool):
+        """Compactions find that many live records and label tokens."""
+        def play(index):
+            def f(args):
+                S = self.at(args, index, Compact)
+                ctypes.memset(ctypes.addressof(S), 0, ctypes.sizeof(S))
+                S.lo = S.hi = nodes
+                S.n_pool = pool
+            return f
+        self.on["compact_small_kernel"] = play(5)
+        self.on["compact_lab_scan_kernel"] = play(0)
+
+    def walk_finds(self, nodes, leaves=0):
+        """The level-by-level walk finds that many nodes and leaves at its first level;
+        the one-launch walk and eviction report that the tree is too large for them."""
+        def level(args):
+            c = (_i32 * 3).from_address(self.arg(args, 9))
+            c[0], c[1], c[2] = 0, leaves, nodes
+        self.on["export_level_kernel"] = level
+        self.on["tree_walk_kernel"] = lambda args: ctypes.memset(self.arg(args, 5), 0, ctypes.sizeof(Walk))
+        self.on["evict_kernel"] = lambda args: ctypes.memset(self.arg(args, 7), 0, ctypes.sizeof(Evict))
+
     def small_merge(self, *replies, **fields):
         """A player of the one-workgroup merge: every launch reports `fields` (by
         default that all is done in one round), the first ones with the given replies
@@ -142,6 +168,22 @@ class HostRuntime:
         for p, seqs in enumerate(snapshots):
             f.load(p, seqs)
         return f
+
+    def large_merge(self, f, nodes, pool):
+        """A merge of 65 sequences that adds that many records and label tokens: the
+        forest grows to them (a refused request, a walk's tally), then uses them."""
+        tallies = [(1, pool), (0, 0)]
+
+        def tally(args):
+            c = self.at(args, 2, Counters)
+            c.n_split, c.pool_need = tallies.pop(0) if tallies else (0, 0)
+        self.on["merge_tally_kernel"] = tally
+        self.on["small_merge_kernel"] = self.small_merge(dict(done=0, overflow=1, add_nodes=nodes))
+        assert f.merge(65) == 0
+        i = f.info()
+        self.on["small_merge_kernel"] = self.small_merge(dict(add_nodes=nodes - i.num_nodes, add_pool=pool))
+        assert f.merge(65) == 0
+        assert f.info().num_nodes == nodes
 
 
 class Forest:

@@ -26,8 +26,7 @@ def test_forest_on_the_host_runtime(rt):
 def _after_a_large_merge(rt, added):
     """A forest whose last merge of 65 sequences added that many label tokens."""
     f = rt.forest(2, [[[1, 2, 3]]])
-    rt.on["small_merge_kernel"] = rt.small_merge(dict(add_nodes=65, add_pool=added))
-    assert f.merge(65) == 0
+    rt.large_merge(f, 5000, added)
     return f
 
 
@@ -36,8 +35,6 @@ def test_room_for_a_merge_like_the_last_one_is_not_a_condition(rt, what):
     """A merge wants as much spare room as the last ones took.  Where the ids or
     the memory do not allow that, it runs in the room there is."""
     for added, free in ((3 << 30, None), (1 << 20, 1 << 16)):
-        f = rt.forest(2)
-        f.close()
         f = _after_a_large_merge(rt, added)
         if what == "touch":
             assert f.L.pr_set_local_peer(f.h, 0) == 0
@@ -95,3 +92,50 @@ def test_rounds_queued_follow_the_batches_of_their_kind(rt):
     assert _rounds(rt, lambda: f.merge(65)) == 3 + 1
     assert _rounds(rt, lambda: f.merge(65)) == 3
     f.close()
+
+
+def _with_spare(rt, records=20000, pool=1 << 18):
+    """A forest whose last compaction kept the arrays it replaced, with merge scratch
+    for 3,000 sequences and a sort's for 1,600."""
+    f = rt.forest(2, [[[1, 2, 3]]])
+    rt.large_merge(f, records, pool)
+    assert [f.merge(n) for n in (1500, 1600)] == [0, 0]
+    rt.compacts_to(records, pool)
+    assert f.L.pr_set_local_peer(f.h, 0) == 0
+    rt.walk_finds(nodes=10, leaves=10)
+    assert f.compact() == 0 and f.export(1)[0] == 0
+    return f
+
+
+@pytest.mark.parametrize("what", ["eviction", "merge", "export"])
+def test_what_a_compaction_kept_is_given_back_when_memory_runs_out(rt, what):
+    """The arrays a compaction keeps for the next one make room for any later
+    call's scratch: it succeeds as it would have without them."""
+    f = _with_spare(rt)
+    kept = f.info().device_bytes
+    rt.walk_finds(nodes=10000, leaves=10000)
+    rt.limit(rt.used() + (1 << 10))
+    call = {"eviction": lambda: f.evict(5)[0], "merge": lambda: f.merge(3000), "export": lambda: f.export(1)[0]}[what]
+    refused, status = rt.refused(), call()
+    gone, after = rt.refused() - refused, f.info().device_bytes
+    rt.limit(None)
+    f.close()
+    assert status == 0 and gone == 1 and after < kept  # refused once, beside the kept arrays
+    assert rt.used() == 0
+
+
+def test_room_for_later_merges_is_not_a_condition_of_a_compaction(rt):
+    """A compaction leaves room for merges like the recent ones where there is
+    memory for it; else it takes what the forest needs."""
+    f = rt.forest(2, [[[1, 2, 3]]])
+    n = 1 << 20
+    rt.large_merge(f, n, 1 << 22)
+    rt.walk_finds(nodes=1)
+    assert f.export(1)[0] == 0  # its scratch is a compaction's
+    rt.compacts_to(n, 1 << 22)
+    # the forest once more, with an eighth to spare (48 bytes a record, six a token), not with two such merges on top
+    rt.limit(rt.used() + (n * 48 + (1 << 22) * 6) * 10 // 8)
+    status = f.compact()
+    rt.limit(None)
+    f.close()
+    assert status == 0
