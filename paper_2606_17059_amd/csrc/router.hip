@@ -319,18 +319,32 @@ int64_t image_bytes(const DevImage &d) {
            (d.pool16 ? d.cap_pool16 * 2 + hib_words(d.cap_pool16) * 4 : 0);
 }
 
-// The image a compaction replaced.  Its arrays are kept for the next
-// compaction, which then allocates nothing (hipMalloc and hipFree of arrays of
-// tens of MB take 0.3 to 0.6 ms each, more than the rebuild itself), as long as
-// they are small beside the GPU's memory; at most one such set per forest.
+// Bytes of the records and label tokens an image has in use.
+int64_t used_bytes(const pr_forest *f, const DevImage &d) {
+    return d.n_nodes * (int64_t)(sizeof(Node) + 2 * sizeof(int32_t) + 8 * f->W) + d.n_pool * (d.pool16 ? 6 : 4);
+}
+
+// The image a compaction replaces, nw the one that takes its place.  The old
+// arrays are kept for the next compaction, which then allocates nothing (hipMalloc
+// and hipFree of arrays of tens of MB take 0.3 to 0.6 ms each, more than the
+// rebuild itself), as long as they are small beside the GPU's memory and the
+// forest is one that merges fill and compactions empty in turn: the new arrays
+// are about as large (within a third) and at least half of what they held is
+// still there.  A compaction that shrinks its forest by more gives them back, but
+// for a few MB.  At most one set is kept per forest.
 constexpr int64_t kSpareBytes = 1ll << 30;
-void retire_image(pr_forest *f) {
+constexpr int64_t kSmallSpare = 8 << 20;
+bool retire_image(pr_forest *f, const DevImage &nw) {
     free_arrays(f, f->spare);
-    if (image_bytes(f->dev) <= kSpareBytes)
+    const int64_t bytes = image_bytes(f->dev);
+    const bool keep = bytes <= kSmallSpare || (bytes <= kSpareBytes && 2 * bytes <= 3 * image_bytes(nw) &&
+                                               used_bytes(f, f->dev) <= 2 * used_bytes(f, nw));
+    if (keep)
         f->spare = f->dev;
     else
         free_arrays(f, f->dev);
     f->dev = DevImage();
+    return keep;
 }
 
 // A capacity of at least n with 1/16 to 1/8 slack, so that needs that vary a
@@ -372,11 +386,12 @@ bool new_node_arrays(pr_forest *f, DevImage &nw, int64_t need, int64_t extra, bo
 
 // The label pool (and its narrow copy, if wanted and there is memory for it)
 // for at least need tokens in nw, and extra if there is room, in the same way.
+constexpr int64_t kSmallPool = 1 << 20;  // tokens a pool may have however few are needed
 bool new_pool(pr_forest *f, DevImage &nw, int64_t need, int64_t extra, bool narrow) {
     const int64_t least = need;
     need += extra;
     DevImage &sp = f->spare;
-    if (sp.pool && sp.cap_pool >= need && sp.cap_pool <= 8 * need) {
+    if (sp.pool && sp.cap_pool >= need && sp.cap_pool <= std::max<int64_t>(2 * need, kSmallPool)) {
         nw.pool = sp.pool;
         nw.cap_pool = sp.cap_pool;
         sp.pool = nullptr;
@@ -1682,9 +1697,9 @@ pr_status pr_forest_compact(pr_forest *f, int64_t *nodes_before, int64_t *nodes_
     if (S.bad) return fail_new(PR_EDEVICE, "compaction found more live nodes than exist");
     // install the new image once no launch on another stream still reads the old one
     if (hipDeviceSynchronize() != hipSuccess) return fail_new(PR_EDEVICE, "hipDeviceSynchronize failed");
-    retire_image(f);
     nw.n_nodes = S.hi;
     nw.n_pool = S.n_pool;
+    const bool kept = retire_image(f, nw);
     f->dev = nw;
     f->holes = false;
     f->layout_epoch++;
@@ -1694,7 +1709,7 @@ pr_status pr_forest_compact(pr_forest *f, int64_t *nodes_before, int64_t *nodes_
     if (f->narrow && S.wide_tokens) drop_pool16(f);
     f->host_img_valid = false;  // the host image no longer mirrors the device layout
     // scratch sized for far more records than are left goes back
-    if (X.cap > 4 * nw.n_nodes + (1 << 16)) free_export_scratch(f);
+    if (X.cap > (kept ? 4 : 2) * nw.n_nodes + (1 << 16)) free_export_scratch(f);
     if (nodes_after) *nodes_after = nw.n_nodes;
     return ok();
 }

@@ -139,3 +139,36 @@ def test_room_for_later_merges_is_not_a_condition_of_a_compaction(rt):
     rt.limit(None)
     f.close()
     assert status == 0
+
+
+@pytest.mark.parametrize("left", [1.0, 0.6, 0.4, 0.1])
+def test_a_compaction_gives_back_what_it_freed(rt, left):
+    """A compaction that leaves more than half of the forest keeps the replaced
+    arrays, and the next one allocates nothing; one that leaves less gives them
+    back, and the image is sized to what is left."""
+    f = rt.forest(2, [[[1, 2, 3]]])
+    nodes, pool = 1 << 17, 1 << 22
+    rt.large_merge(f, nodes, pool)
+    for _ in range(100):  # merges since then were small ones
+        assert f.merge(65) == 0
+    rt.walk_finds(nodes=1)
+    assert f.export(1)[0] == 0
+    rt.compacts_to(nodes, pool)
+    assert f.compact() == 0 and f.compact() == 0
+    full = f.info().device_bytes
+    rt.compacts_to(int(nodes * left), int(pool * left))
+    assert f.compact() == 0
+    info = f.info()
+    assert info.num_nodes == int(nodes * left)
+    if left > 0.5:
+        rt.limit(rt.used())
+        refused, status = rt.refused(), f.compact()
+        rt.limit(None)
+        assert status == 0 and rt.refused() == refused
+    else:
+        # records once more sized by the old forest's, tokens by what is left; room for the recent merges
+        assert info.device_bytes <= full / 2
+        image = 48 * nodes * 5 / 4 + 6.2 * pool * left * 5 / 4
+        assert info.device_bytes <= image + 2 * 6.2 * pool / 16 + 2 * 48 * nodes / 16 + (12 << 20)
+    f.close()
+    assert rt.used() == 0
