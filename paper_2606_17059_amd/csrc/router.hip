@@ -1070,7 +1070,8 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
     pr_status r;
     pr::SmallStatus ss;
     // one workgroup serves a batch up to a lane per sequence in about the time
-    // of five launches (65 and more take the rounds below, eleven launches)
+    // of five launches, unless its sequences are long (the rounds below take
+    // eleven launches)
     if (n <= pr::kSmallMax && f->d_stage) {
         if ((r = run_small_merge(f, B, nullptr, s, &ss))) return r;
         if (ss.done) return PR_OK;

@@ -18,7 +18,8 @@
 // the narrow copy as they are written to the pool.  What does not fit (the
 // capacity, or rebuilt parents with more than kSmallChunks chunks, which more
 // than one workgroup should move) ends the launch between two rounds with the
-// forest consistent, and the caller goes on with the other kernels.
+// forest consistent, and the caller goes on with the other kernels; batches of
+// long sequences (kSmallWork) are left to them from the start.
 //
 // One insert into the 57-topic trees of the request-at-a-time simulation, call
 // included: 106 us with the rounds' launches, 33 us here; touching one request 157 us
@@ -44,6 +45,17 @@ constexpr int kSmallMax = 64;      // inserts: one lane each
 constexpr int kSmallChunks = 256;  // chunks of 64 old children one round moves
 constexpr int kSmallGather = 16;   // inserts a thread looks at for the unfinished ones of a larger batch
 constexpr int64_t kSmallBatch = 64 * kSmallWaves * kSmallGather;
+// Inserts past a wave each are worked off one after the other, on one CU; launches
+// give each a wave and spread their labels over the chip, for 17 us more, since
+// this one then ends at once.  Sequences times their tokens up to which one
+// workgroup is the faster (us here / in launches, a merge of new sequences, call
+// included):
+//   24 of  5,000 tokens  89 /  98    10,000 tokens  148 / 137
+//   32 of  5,000         98 / 123    10,000         201 / 171
+//   48 of  1,200         73 /  87     5,000         133 / 111
+//   64 of  1,200         89 /  87     2,500         121 / 101    20,000 tokens 587 / 271
+// and up to a wave each at any length (16 of 20,000: 142 / 154).
+constexpr int64_t kSmallWork = 5500000;
 
 // Written to pinned host memory when the launch ends.
 struct SmallStatus {
@@ -136,8 +148,11 @@ __global__ __launch_bounds__(64 *kSmallWaves) void small_merge_kernel(DevForest 
             s_st[lane].kind = ok ? kInsActive : kInsSkip;
         }
         const uint32_t skip = (uint32_t)__popcll(__ballot(bad));
+        int64_t tokens;
+        (void)lane_excl(ok ? s_len[lane] : 0, lane, &tokens);
+        const bool large = !B.touch && n > kSmallWaves && tokens > kSmallWork / n;
         if (lane == 0) {
-            s_state = left > kSmallMax || broken ? 2 : 0;
+            s_state = left > kSmallMax || broken || large ? 2 : 0;
             s_seen = 0;
             s_skip = st ? (uint32_t)ctr->skipped : skip;
         }

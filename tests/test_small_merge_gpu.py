@@ -167,3 +167,81 @@ def test_touches_then_evictions(n):
         _check(f, o, base + qs, f"touch n={n} step={step}")
     f.close()
     o.close()
+
+
+def _long_heads(rng, n, L):
+    """n sequences of L tokens: half of them grow from the other half's middles."""
+    own = rng.integers(0, 60000, (n, L))
+    own[:, 0] = np.arange(n) * 5 + 10
+    for i in range(1, n, 2):
+        own[i, :L // (1 + i % 3)] = own[i - 1, :L // (1 + i % 3)]
+    return own.tolist()
+
+
+@pytest.mark.parametrize("n,L,launches", [(16, 20000, False), (17, 19000, False), (17, 21000, True), (64, 1300, False),
+                                          (64, 1400, True), (64, 8000, True)])
+def test_long_sequences_are_left_to_the_launches(n, L, launches):
+    """Past 16 sequences, batches whose sequences times valid tokens pass 5.5 million go to
+    the rounds of launches, which take scratch; the forest has room for either.  A bad
+    entry is counted once.  Touches stay in one launch."""
+    import oracle
+    from paper_2606_17059_amd import Forest, RouterError
+    rng = np.random.default_rng(n + L)
+    f, o = Forest(3), oracle.RadixOracle(3)
+    room = [[1, 2, 3]] + [[9, i] + rng.integers(0, 100, 40000).tolist() for i in range(90)]
+    t, off = pins._csr(room)
+    f.load_snapshot(2, t, off)
+    o.load(2, t, off)
+    queries = [[1, 2, 3, 4]]
+    _check(f, o, queries, "upload")
+    before = f.info()["device_bytes"]
+    seqs = _long_heads(rng, n, L)
+    peers = rng.integers(0, 3, n)
+    bad = np.array(peers)
+    bad[n // 2] = 3
+    announce(f"{n} sequences of {L} tokens")
+    f.merge(*_dev(bad, seqs))
+    assert (f.info()["device_bytes"] > before) == launches, (before, f.info())
+    with pytest.raises(RouterError, match="1 device inputs were skipped"):
+        f.check()
+    keep = [i for i in range(n) if i != n // 2]
+    t, off = pins._csr([seqs[i] for i in keep])
+    o.merge(peers[keep].astype(np.int32), t, off)
+    queries += seqs + [s[:L // 2] + [-5] for s in seqs]
+    _check(f, o, queries, f"{n} of {L}")
+    f.set_local_peer(1)
+    held = f.info()["device_bytes"]
+    t, off = pins._csr([s[:L - 3] for s in seqs])
+    import torch
+    announce(f"touch of {n} sequences of {L} tokens")
+    f.touch(*[torch.from_numpy(x).to(device()) for x in (t, off)])
+    assert f.info()["device_bytes"] == held
+    _check(f, o, queries, f"{n} of {L}, touched")
+    f.check()
+    f.close()
+    o.close()
+
+
+def test_small_batch_outgrows_the_pool_between_rounds():
+    """Twelve sequences that part from each other one after the other, their tails
+    more than the pool has left: the first rounds' tails fit, a later round's do not,
+    and the launches take over with some of the batch in."""
+    import oracle
+    from paper_2606_17059_amd import Forest
+    rng = np.random.default_rng(12)
+    f, o = Forest(2), oracle.RadixOracle(2)
+    f.merge(*_dev([0], [[5, 5]]))
+    o.merge(np.zeros(1, np.int32), *pins._csr([[5, 5]]))
+    path = rng.integers(0, 50, 40).tolist()
+    order = rng.permutation(12)
+    seqs = [path[:3 * k + 2] + [100 + k] + rng.integers(0, 30000, 40000).tolist() for k in order]
+    peers = np.arange(12) % 2
+    announce("12 tails of 40,000 tokens into a pool of 262,144")
+    f.merge(*_dev(peers, seqs))
+    o.merge(peers.astype(np.int32), *pins._csr(seqs))
+    queries = seqs + [s[:500] for s in seqs] + [path[:k] for k in range(40)] + [[5, 5, 5]]
+    _check(f, o, queries, "outgrown")
+    assert f.info()["pool_tokens"] <= 262144 + sum(map(len, seqs))
+    f.check()
+    f.close()
+    o.close()
