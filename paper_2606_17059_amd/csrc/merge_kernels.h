@@ -67,7 +67,6 @@ struct MergeCounters {
     unsigned long long node_need; // add round: exact node records the next round adds
     unsigned long long overflow;  // allocations refused for lack of capacity
     unsigned long long skipped;   // inserts with invalid peer or offsets
-    unsigned long long bad_path;  // an invariant of the round broke (the merge fails)
     unsigned long long move_chunks;  // add round: 64-child chunks of the old blocks that move
     unsigned long long wide_tokens;  // nonzero: an appended label token lies outside [0, 131071] (no narrow copy)
     unsigned long long hi_tokens;    // nonzero: an appended label token lies in [65536, 131071] (17-bit labels)
@@ -105,12 +104,14 @@ struct Batch {
     int64_t num_tokens;
     int64_t n;
     int32_t P;
-    int32_t stamp;  // 1: inserts into the local peer stamp their path with F.now
     int32_t peer;
     int32_t touch;  // 1: not inserts but touches of `peer`: a walk ends where its tree does, nothing is added
 };
 
 __device__ __forceinline__ int32_t batch_peer(const Batch &B, int64_t i) { return B.peer_of ? B.peer_of[i] : B.peer; }
+
+// Inserts into the local peer (and touches of it) stamp their path with F.now.
+__device__ __forceinline__ bool stamps_path(const DevForest &F, int32_t p) { return F.ltime && p == F.local; }
 
 constexpr int kMergeWavesPerBlock = 4;
 constexpr int kMoveBlocks = 1024;  // workgroups of the grid-stride move kernel
@@ -328,7 +329,7 @@ __global__ __launch_bounds__(64 *kMergeWalkWaves) void merge_walk_kernel(DevFore
         return;
     }
     const InsState r =
-        m_walk(F, B.tokens + b, e - b, p, B.touch, F.ltime && B.stamp && p == F.local, lane, s_marks);
+        m_walk(F, B.tokens + b, e - b, p, B.touch, stamps_path(F, p), lane, s_marks);
     if (lane == 0) {
         st[i] = r;
         addx[i] = r.kind == kInsAdd ? r.x : -1;
@@ -600,8 +601,7 @@ __global__ __launch_bounds__(64 *kSplitWaves) void split_apply_kernel(DevForest 
     }
     const int32_t p = batch_peer(B, i);
     uint32_t seen = 0;
-    cut_edge(F, N, F.nodes[r.c], r.c, r.l, s + r.d + r.l, rest, p, F.ltime && B.stamp && p == F.local, nb, pb, lane,
-             seen);
+    cut_edge(F, N, F.nodes[r.c], r.c, r.l, s + r.d + r.l, rest, p, stamps_path(F, p), nb, pb, lane, seen);
     narrow_flags(ctr, seen, lane);
     if (lane == 0) st[i].kind = kInsDone;  // the sequence ends at the leaf, or at the upper part (rest 0)
 }
@@ -1314,7 +1314,7 @@ __global__ __launch_bounds__(64 *kMergeWavesPerBlock) void add_build_kernel(
             const Node leaf{t, (uint32_t)pb, (int32_t)rest, 0, 0, 0, (p >> 6) == 0 ? 1ull << (p & 63) : 0ull};
             F.nodes[dst] = leaf;
             F.ntok[dst] = t;
-            if (F.ltime) F.ltime[dst] = (B.stamp && p == F.local) ? F.now : 0ull;
+            if (F.ltime) F.ltime[dst] = stamps_path(F, p) ? F.now : 0ull;
             st[i].kind = kInsDone;  // the winner's sequence ends at its new leaf
         }
     }

@@ -1000,7 +1000,7 @@ pr::DevForest dev_view(const pr_forest *f) {
 // or into one peer's (peer_of nullptr), or touches of one peer's.
 pr::Batch batch_of(const pr_forest *f, const int32_t *peer_of, int32_t peer, const int32_t *tokens,
                    int64_t num_tokens, const int64_t *offsets, int64_t n) {
-    return pr::Batch{peer_of, tokens, offsets, num_tokens, n, f->P, 1, peer, 0};
+    return pr::Batch{peer_of, tokens, offsets, num_tokens, n, f->P, peer, 0};
 }
 
 // What a merge's appended labels mean for the narrow copy: hi, wide count (or
@@ -1152,8 +1152,6 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
         if (hipGetLastError() != hipSuccess) return fail(PR_EDEVICE, "merge launch failed");
         if ((r = run_small_merge(f, B, m.st, s, &ss))) return r;
         done = ss.done != 0;
-        if (ss.bad)
-            return fail(PR_EDEVICE, "merge invariant broken; destroy the forest");
         // (the next round's walk is tallied, which says what tokens are needed)
         if (ss.overflow && (r = refused_round(f, (int64_t)ss.n_nodes, (int64_t)ss.n_pool, 0, 0, s))) return r;
         if (ss.overflow || ss.fallback) break;
@@ -1257,9 +1255,8 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
     hipLaunchKernelGGL(add_skipped_kernel, dim3(1), dim3(1), 0, s, f->d_skipped, f->d_ctr);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess)
         return fail(PR_EDEVICE, "merge failed");
-    if (c.overflow || c.bad_path)
-        return fail(PR_EDEVICE, "merge invariant broken (overflow " + std::to_string(c.overflow) + ", bad paths " +
-                                    std::to_string(c.bad_path) + "); destroy the forest");
+    if (c.overflow)
+        return fail(PR_EDEVICE, "merge invariant broken (overflow " + std::to_string(c.overflow) + "); destroy the forest");
     narrow_seen(f, c.hi_tokens != 0, c.wide_tokens != 0);
     f->merged = true;
     return PR_OK;

@@ -45,6 +45,7 @@ constexpr int kSmallMax = 64;      // inserts: one lane each
 constexpr int kSmallChunks = 256;  // chunks of 64 old children one round moves
 constexpr int kSmallGather = 16;   // inserts a thread looks at for the unfinished ones of a larger batch
 constexpr int64_t kSmallBatch = 64 * kSmallWaves * kSmallGather;
+static_assert(kPlanMaxBatch <= kSmallBatch, "the rounds' batches are looked at whole for what they left");
 // Inserts past a wave each are worked off one after the other, on one CU; launches
 // give each a wave and spread their labels over the chip, for 17 us more, since
 // this one then ends at once.  Sequences times their tokens up to which one
@@ -64,7 +65,7 @@ struct SmallStatus {
     uint32_t stamps;    // stamps taken
     uint32_t left;      // unfinished inserts found at the start
     uint32_t rounds;    // the last round in which one walked
-    uint32_t overflow, fallback, bad;  // the counters' of the rounds before
+    uint32_t overflow, fallback;  // the counters' of the rounds before
     unsigned long long n_nodes, n_pool;
 };
 
@@ -115,7 +116,7 @@ __global__ __launch_bounds__(64 *kSmallWaves) void small_merge_kernel(DevForest 
     uint32_t seen = 0;
     long long stamp = stamp0;
 
-    const bool broken = st && (ctr->overflow || ctr->plan_fallback || ctr->bad_path);
+    const bool broken = st && (ctr->overflow || ctr->plan_fallback);
     if (st) {
         // the unfinished inserts, in batch order
         int c = 0, at[kSmallGather];
@@ -166,8 +167,7 @@ __global__ __launch_bounds__(64 *kSmallWaves) void small_merge_kernel(DevForest 
             const int32_t kind = s_st[i].kind;
             if (kind == kInsSkip || kind == kInsDone) continue;
             const int32_t p = s_peer[i];
-            const InsState r = m_walk(F, B.tokens + s_off[i], s_len[i], p, B.touch, F.ltime && B.stamp && p == F.local,
-                                      lane);
+            const InsState r = m_walk(F, B.tokens + s_off[i], s_len[i], p, B.touch, stamps_path(F, p), lane);
             if (lane == 0) s_st[i] = r;
         }
         small_sync();
@@ -278,7 +278,7 @@ __global__ __launch_bounds__(64 *kSmallWaves) void small_merge_kernel(DevForest 
                 const Node leaf{s[0], (uint32_t)s_pb[i], (int32_t)rest, 0, 0, 0, p < 64 ? 1ull << p : 0ull};
                 F.nodes[dst] = leaf;
                 F.ntok[dst] = leaf.tok;
-                if (F.ltime) F.ltime[dst] = (B.stamp && p == F.local) ? F.now : 0ull;
+                if (F.ltime) F.ltime[dst] = stamps_path(F, p) ? F.now : 0ull;
                 s_st[i].kind = kInsDone;
             }
         }
@@ -303,7 +303,7 @@ __global__ __launch_bounds__(64 *kSmallWaves) void small_merge_kernel(DevForest 
             r.c = current_pos(F, r.c, stamp);
             const int64_t rest = B.touch ? 0 : s_len[i] - (int64_t)r.d - r.l;
             cut_edge(F, N, fresh_node(&F.nodes[r.c]), r.c, r.l, B.tokens + s_off[i] + r.d + r.l, rest, s_peer[i],
-                     F.ltime && B.stamp && s_peer[i] == F.local, s_nb[i], s_pb[i], lane, seen);
+                     stamps_path(F, s_peer[i]), s_nb[i], s_pb[i], lane, seen);
             if (lane == 0) s_st[i].kind = kInsDone;
         }
         if (s_chunks) stamp++;
@@ -323,7 +323,6 @@ __global__ __launch_bounds__(64 *kSmallWaves) void small_merge_kernel(DevForest 
         r.rounds = (uint32_t)ctr->rounds;
         r.overflow = ctr->overflow != 0;
         r.fallback = ctr->plan_fallback != 0;
-        r.bad = ctr->bad_path != 0;
         r.n_nodes = n_nodes;
         r.n_pool = n_pool;
         // the rounds after these do not look at the entries they skip again
