@@ -42,7 +42,10 @@ void launch_w(const RouteForest &F, const RouteBatch &B, const Select &sel, hipS
         launch_l<W, true>(F, B, sel, s);
 }
 
-// Waves for each query (a power of two).  A small batch of long queries takes
+// Waves launched for each query (a power of two); a query shorter than the mean
+// that tokens gives, as where they are a buffer that the batch only starts, ends
+// the ones it does not pay for (512 queries of 300 tokens in a buffer of 32 M: 3.6
+// us with a wave each, 6.2 with sixteen, 4.1 with fifteen that end).  A small batch of long queries takes
 // as long as its longest query's chain of compare steps, so a team shares them,
 // a wave for every 512 tokens of the mean query: 48 queries of 20,000 tokens
 // 34.4 -> 8.4 us, one 33.2 -> 8.0, 512 of 5,300 10.9 -> 7.1.  Past 8,192 waves
@@ -56,19 +59,19 @@ void launch_w(const RouteForest &F, const RouteBatch &B, const Select &sel, hipS
 //                 2,048           8.8   9.6  10.5  16.9  29.2
 //    1,400 tokens   512           5.6   5.3   5.6   6.2   8.4
 //                 1,024           5.4   5.6   6.4   9.0  14.2
-int team_waves(int64_t n, int64_t tokens) {
+int team_waves(int64_t n, int64_t tokens, int W) {
     if (n <= 0 || n > 2048) return 1;
     const int64_t mean = tokens / n;
-    if (2 * n > mean) return 1;
+    if (2 * n > mean || mean < team_least(W) || (W >= 16 && n > 256 && mean < 8192)) return 1;
     int waves = 1;
-    while (waves < kTeamMax && 1024 * waves <= mean && 2 * waves * n <= 8192) waves *= 2;
+    while (waves < kTeamMax && 2 * kTeamTokens * waves <= mean && 2 * waves * n <= 8192) waves *= 2;
     return waves;
 }
 
 }  // namespace
 
 hipError_t launch_route(const RouteForest &F, const RouteBatch &B, const Select &sel, hipStream_t s) {
-    if (const int waves = team_waves(B.n, B.num_tokens); waves > 1) {
+    if (const int waves = team_waves(B.n, B.num_tokens, F.W); waves > 1) {
         launch_route_team(F, B, sel, waves, s);
         return hipGetLastError();
     }

@@ -287,7 +287,7 @@ __device__ __forceinline__ int32_t select_peers(const int32_t (&m)[W], int32_t P
 // trips of its longest query, about 1 us for every 1,024 tokens of a label.
 struct Team {
     int32_t *first;  // LDS, [2][kTeamMax]
-    int wv, waves, row;
+    int wv, lg, row;  // 1 << lg waves
 };
 
 template <typename LT, bool HB>
@@ -296,7 +296,7 @@ __device__ __forceinline__ int64_t team_lcp(const LabelSrc<LT, HB> &lab, const i
     constexpr int64_t kMost = (int64_t)kWave * kLcpVectors;
     for (int64_t base = 0; base < n;) {
         // an equal share of what is left, in whole lines
-        const int64_t each = min(((n - base + team.waves - 1) / team.waves + 31) & ~(int64_t)31, kMost);
+        const int64_t each = min(((((n - base - 1) >> team.lg) + 1) + 31) & ~(int64_t)31, kMost);
         const int64_t from = base + team.wv * each, to = min(from + each, n);
         int32_t at = INT32_MAX;
         if (from < to) {
@@ -307,10 +307,10 @@ __device__ __forceinline__ int64_t team_lcp(const LabelSrc<LT, HB> &lab, const i
         team.row ^= 1;
         if (lane == 0) row[team.wv] = at;
         __syncthreads();
-        const int32_t f = lane < team.waves ? row[lane] : INT32_MAX;
+        const int32_t f = (lane >> team.lg) == 0 ? row[lane] : INT32_MAX;
         const uint64_t bal = __ballot(f != INT32_MAX);
         if (bal) return __builtin_amdgcn_readlane(f, (int)(__ffsll((unsigned long long)bal) - 1));
-        base += each * team.waves;
+        base += each << team.lg;
     }
     return n;
 }
@@ -334,7 +334,7 @@ __attribute__((amdgpu_waves_per_eu(PR_ROUTE_WAVES_PER_EU))) void route_kernel(
     const int wv = uniform((int32_t)(threadIdx.x / kWave));
     const int64_t slot = TEAM ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * kRouteWavesPerBlock + wv;
     if (slot >= nq) return;
-    Team team{nullptr, wv, TEAM ? (int)(blockDim.x / kWave) : 1, 0};
+    Team team{nullptr, wv, TEAM ? 31 - __clz((int)(blockDim.x / kWave)) : 0, 0};
     if constexpr (TEAM) {
         __shared__ int32_t s_first[2][kTeamMax];
         team.first = &s_first[0][0];
@@ -419,7 +419,7 @@ __attribute__((amdgpu_waves_per_eu(PR_ROUTE_WAVES_PER_EU))) void route_kernel(
         const int64_t n = min((int64_t)c.lab_len, qlen - d);
         const LabelSrc<LT, HB> lab{pool + (uint32_t)c.lab_off, hib, (uint32_t)c.lab_off};
         int64_t l;
-        if (TEAM && n > kTeamSplit)
+        if (TEAM && n > kTeamSplit && team.lg > 0)
             l = team_lcp<LT, HB>(lab, qs + d, n, lane, team);
         else if constexpr (FIRST)
             l = wave_lcp_first<LT, HB, WV>(lab, qs, n, win, lane);
@@ -447,6 +447,16 @@ __attribute__((amdgpu_waves_per_eu(PR_ROUTE_WAVES_PER_EU))) void route_kernel(
 #if PR_FIRST_WINDOW
     int32_t win[WV];
     load_window<WV>(win, qs, (int32_t)min(qlen, (int64_t)kWave * WV), lane);
+    if constexpr (TEAM) {
+        // the host knows the batch's mean at most (its buffer may be larger than its
+        // queries): a query keeps the waves that its own length pays for, and the
+        // rest end here, past the loads that the walk waits for first (a barrier
+        // waits for the waves that are left)
+        if (qlen < team_least(W) || qlen < kTeamTokens << team.lg) {
+            team.lg = qlen < team_least(W) ? 0 : 31 - __clz((int32_t)qlen / (int32_t)kTeamTokens);
+            if ((wv >> team.lg) != 0) return;
+        }
+    }
     bool more = false;
     if (qlen > 0) more = single ? level(std::true_type{}, win, std::true_type{})
                                 : level(std::true_type{}, win, std::false_type{});

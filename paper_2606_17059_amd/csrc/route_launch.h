@@ -23,7 +23,20 @@ constexpr int kWinVectors = PR_WIN_VECTORS;  // 64-token vectors of the first-le
 constexpr int kWideWinVectors = 4;           // ... of the wide one
 constexpr int kTeamMax = 16;                 // waves of a query's team at most
 constexpr int64_t kTeamSplit = 256;          // labels beyond this many tokens are split over the team
+constexpr int64_t kTeamTokens = 512;         // ... and a query has a wave for every so many tokens at most
 static_assert(kWinVectors >= 2 && kWinVectors <= 16, "window of 2 to 16 vectors");
+
+// Tokens of the shortest query that a team serves.  Meeting at a barrier for each
+// label costs about 0.3 us of the 0.5 us that 1,000 tokens take a wave; with more
+// mask words a level has more to do in every wave, and sixteen spill in a team
+// (us with 1 / 4 waves, 8 past 4,000 tokens; 48 queries each):
+//   mask words    1,800 tokens  2,400          4,400          6,300
+//       2          4.28 / 4.60   5.41 /  4.56   6.96 /  4.91   8.24 /  5.46
+//       8          5.34 / 5.84   6.47 /  5.94   7.91 /  6.28   8.18 /  6.26
+//      16          6.57 / 7.81   7.62 /  8.11   9.39 /  8.61  10.74 /  8.94
+//      16, 512     8.00 / 10.3   9.03 / 10.10  10.98 / 13.17  12.94 / 13.53   queries
+// One mask word: 4.79 / 4.49 at 1,300 tokens, 4.34 / 4.44 at 1,100.
+constexpr int64_t team_least(int W) { return W == 1 ? 1024 : (W < 16 ? 2048 : 5120); }
 
 // Peer selection (the argmax of Algorithm 1, with the push-back and failover
 // rules of Sections "Hot specialist push-back" and "In-flight forwarded

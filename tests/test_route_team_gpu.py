@@ -97,3 +97,66 @@ def test_team_limits(n, mean):
     co = mo.argmax(axis=1).astype(np.int32)
     assert_rows_equal(m.cpu().numpy(), c.cpu().numpy(), mo, co, what="limits")
     f.close()
+
+
+@pytest.mark.parametrize("P", [3, 130, 1000])
+@pytest.mark.parametrize("n", [1, 48, 512, 2048])
+def test_batch_in_a_larger_buffer(n, P):
+    """Queries of 0 to 5,000 tokens at the start of a buffer of 4 M, as a server's
+    staging buffer: teams are launched by the buffer's size, and every query ends the
+    waves its own length does not pay for (at 1,023 and 1,024 tokens, 2,047 and 2,048
+    and so on), some of a batch all but one."""
+    import torch
+    from paper_2606_17059_amd import Forest
+    rng = np.random.default_rng(n + P)
+    f, o = Forest(P), oracle.RadixOracle(P)
+    stems = [rng.integers(0, 70000, 5200).tolist() for _ in range(4)]
+    for p in {0, P // 2, P - 1}:
+        seqs = [s[:int(rng.integers(400, 5200))] for s in stems] + [stems[p % 4][:700] + [p] * 300]
+        t, off = pins._csr(seqs)
+        f.load_snapshot(p, t, off)
+        o.load(p, t, off)
+    edges = [0, 1, 256, 257, 511, 512, 1023, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 5000]
+    qs = []
+    for i in range(n):
+        L = edges[(i + n) % len(edges)] if i % 2 == 0 else int(rng.integers(0, 5000))
+        q = stems[int(rng.integers(0, 4))][:L]
+        if q and rng.random() < 0.5:
+            at = int(rng.integers(0, L))
+            q = q[:at] + [q[at] + 1] + q[at + 1:]
+        qs.append(q)
+    t, off = pins._csr(qs)
+    buf = np.full(max(4 << 20, len(t) + 9), 7, np.int32)
+    buf[:len(t)] = t
+    announce(f"{n} queries of {P} peers in a larger buffer")
+    m, c = f.route(torch.from_numpy(buf).to(device()), torch.from_numpy(off).to(device()))
+    mo, co = o.route(t, off, 8)
+    assert_rows_equal(m.cpu().numpy(), c.cpu().numpy(), mo, co, what="larger buffer")
+    f.close()
+    o.close()
+
+
+@pytest.mark.parametrize("P", [64, 65, 512, 513])
+@pytest.mark.parametrize("n", [5, 256, 257])
+@pytest.mark.parametrize("mean", [1023, 1024, 2047, 2048, 5119, 5120, 8191, 8192])
+def test_team_limits_by_mask_words(P, n, mean):
+    """The shortest mean a team serves depends on the mask words of a record: 1,024
+    tokens with one, 2,048 with two to eight, 5,120 (8,192 past 256 queries) with sixteen."""
+    import torch
+    from paper_2606_17059_amd import Forest
+    rng = np.random.default_rng(P + n + mean)
+    stem = rng.integers(0, 50000, mean).astype(np.int32)
+    f = Forest(P)
+    for p, s in ((0, stem), (P - 1, stem[:mean // 2])):
+        f.load_snapshot(p, s, np.array([0, len(s)], np.int64))
+    q = np.tile(stem, (n, 1))
+    at = rng.integers(0, mean, n)
+    q[np.arange(n), at] += 1
+    announce(f"team limits P={P} n={n} mean={mean}")
+    m, c = f.route(torch.from_numpy(q.reshape(-1)).to(device()),
+                   torch.from_numpy(np.arange(n + 1, dtype=np.int64) * mean).to(device()))
+    mo = np.zeros((n, P), np.int32)
+    mo[:, 0] = at
+    mo[:, P - 1] = np.minimum(at, mean // 2)
+    assert_rows_equal(m.cpu().numpy(), c.cpu().numpy(), mo, mo.argmax(axis=1).astype(np.int32), what="limits")
+    f.close()
