@@ -386,6 +386,17 @@ __global__ __launch_bounds__(kTallyThreads) void merge_tally_kernel(Batch B, con
     }
 }
 
+// Records [nb, nb + n) of an allocation that was refused, as far as they lie below
+// the capacity: they stay in use (the counters are clipped, not wound back), so
+// they become records that no peer holds.  Thread t of T.
+__device__ __forceinline__ void void_records(const DevForest &F, int64_t nb, int64_t n, int t, int T) {
+    const int64_t end = min(nb + n, F.cap_nodes);
+    for (int64_t i = nb + t; i < end; i += T) {
+        F.nodes[i] = Node{};
+        for (int w = 0; w < F.W - 1; w++) F.mext[i * (F.W - 1) + w] = 0;
+    }
+}
+
 // Where node c's record lives now: an add phase earlier in the same round
 // (stamp > 0) may have moved it into its parent's rebuilt block.
 __device__ __forceinline__ int32_t current_pos(const DevForest &F, int32_t c, long long stamp) {
@@ -591,8 +602,9 @@ __global__ __launch_bounds__(64 *kSplitWaves) void split_apply_kernel(DevForest 
     }
     if (rest <= 0) pb = 0;  // no pool span
     if (nb + k > F.cap_nodes || pb + rest > F.cap_pool) {
-        // refused: nothing is written, the claim is withdrawn, and the insert
-        // walks again once the host has grown the forest
+        // refused: nothing is cut, the claim is withdrawn, and the insert walks
+        // again once the host has grown the forest
+        void_records(F, nb, k, lane, 64);
         if (lane == 0) {
             atomicAdd(&ctr->overflow, 1ull);
             F.nodes[r.c].aux = 0;
@@ -1166,8 +1178,10 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
         if (!ok) atomicAdd(&ctr->overflow, 1ull);
         s_tmp[0] = ok ? nb : -1;
         s_tmp[1] = pb;
+        s_tmp[2] = nb;
     }
     __syncthreads();
+    if (s_tmp[0] < 0) void_records(F, s_tmp[2], need_all, t, T);
     const int eb = (int)(s_place >> 32), cb = (int)(uint32_t)s_place;
     for (int p = t; p < m; p += T) {
         const unsigned long long kk = s_key[plan_pad(p)];
@@ -1238,8 +1252,8 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
 }
 
 // Step 3 (one thread per group head): records and label tokens of the new
-// block, or grp_nb = -1 (nothing is written; the parent keeps its old,
-// consistent block) when the capacity runs out.
+// block, or grp_nb = -1 (the parent keeps its old, consistent block) when the
+// capacity runs out.
 __global__ void add_alloc_kernel(DevForest F, const unsigned long long *keys, int64_t n_add, const int32_t *grp_nw,
                                  const int64_t *grp_pool, int32_t *grp_nb, int64_t *grp_pb, MergeCounters *ctr) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1249,6 +1263,7 @@ __global__ void add_alloc_kernel(DevForest F, const unsigned long long *keys, in
     const int64_t pb = (int64_t)atomicAdd(&ctr->n_pool, (unsigned long long)grp_pool[k]);
     if (nb + cnt > F.cap_nodes || pb + grp_pool[k] > F.cap_pool) {
         atomicAdd(&ctr->overflow, 1ull);
+        void_records(F, nb, cnt, 0, 1);
         grp_nb[k] = -1;
         return;
     }

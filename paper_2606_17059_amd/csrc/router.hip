@@ -137,8 +137,6 @@ struct pr_forest {
     int64_t round_pool = 0;       // pool tokens, likewise (0: no merge yet)
     int rounds[3] = {2, 2, 2};    // rounds the last batch took (a merge's, a snapshot's, a touch's), kMostRounds at
                                   // most
-    bool holes = false;           // a refused allocation left records below n_nodes unwritten (until the
-                                  // next compaction): no pass over all records
     int64_t refusals = 0;         // merge rounds repeated after running out of capacity
     int32_t local = -1;           // peer whose tree keeps access times (-1: none)
     int64_t now = 0;              // current time, set by the caller, never decreasing
@@ -739,7 +737,6 @@ pr_status commit(pr_forest *f) {
     f->has_dev = true;
     f->dirty = false;
     f->merged = false;
-    f->holes = false;
     f->layout_epoch++;
     if (f->local >= 0) {
         pr_status r = init_local_times(f, f->local_load_time);
@@ -1042,15 +1039,14 @@ pr_status run_small_merge(pr_forest *f, const pr::Batch &B, const pr::InsState *
 
 // A round ran out of capacity.  Every refused allocation wrote nothing and left
 // its inserts to walk again, but the refused requests still advanced the
-// counters (to asked_nodes and asked_pool): records and tokens past the last
-// allocation that fit were never written, so the counters are clipped to the
-// capacities, and the forest grows before the round is repeated: to the records
-// it asked for and to want_pool tokens, and, if there is room, to pool_need past
-// the clipped ones.
+// counters (to asked_nodes and asked_pool).  The counters are clipped to the
+// capacities (below them, what a refused request got is records that no peer
+// holds, and tokens that no label has), and the forest grows before the round is
+// repeated: to the records it asked for and to want_pool tokens, and, if there is
+// room, to pool_need past the clipped ones.
 pr_status refused_round(pr_forest *f, int64_t asked_nodes, int64_t asked_pool, int64_t want_pool, int64_t pool_need,
                         hipStream_t s) {
     f->refusals++;
-    f->holes = true;
     f->dev.n_nodes = std::min<int64_t>(asked_nodes, f->dev.cap_nodes);
     f->dev.n_pool = std::min<int64_t>(asked_pool, f->dev.cap_pool);
     hipLaunchKernelGGL(set_used_kernel, dim3(1), dim3(1), 0, s, f->d_ctr, (unsigned long long)f->dev.n_nodes,
@@ -1699,7 +1695,6 @@ pr_status pr_forest_compact(pr_forest *f, int64_t *nodes_before, int64_t *nodes_
     nw.n_pool = S.n_pool;
     const bool kept = retire_image(f, nw);
     f->dev = nw;
-    f->holes = false;
     f->layout_epoch++;
     f->stamp = 0;  // no record carries a move stamp
     f->narrow = narrow && nw.pool16;
@@ -1723,7 +1718,7 @@ pr_status pr_tree_tokens(pr_forest *f, int32_t peer, int64_t *tokens, void *hip_
     pr_status r = commit(f);
     if (r) return r;
     hipStream_t s = (hipStream_t)hip_stream;
-    if (f->d_stage && !f->holes) {
+    if (f->d_stage) {
         const unsigned blocks = std::min(pr::kSizeBlocks, grid_threads(f->dev.n_nodes, pr::kSizeThreads * pr::kSizePer));
         hipLaunchKernelGGL(pr::tree_size_kernel, dim3(std::max(1u, blocks)), dim3(pr::kSizeThreads), 0, s, dev_view(f),
                            f->dev.n_nodes, peer, f->d_size, reinterpret_cast<unsigned long long *>(f->d_stage));
@@ -1731,16 +1726,6 @@ pr_status pr_tree_tokens(pr_forest *f, int32_t peer, int64_t *tokens, void *hip_
             return fail(PR_EDEVICE, "tree size failed");
         std::memcpy(tokens, f->h_stage, sizeof(*tokens));
         return ok();
-    }
-    if (f->d_stage) {
-        if (!enqueue_walk(f, peer, pr::WalkOut{}, s) || hipStreamSynchronize(s) != hipSuccess)
-            return fail(PR_EDEVICE, "tree walk failed");
-        pr::WalkStatus st;
-        std::memcpy(&st, f->h_stage, sizeof(st));
-        if (st.done) {
-            *tokens = (int64_t)st.tokens;
-            return ok();
-        }
     }
     int32_t counts[3];
     if ((r = walk_peer(f, peer, true, s, counts))) return r;
@@ -1834,7 +1819,7 @@ pr_status pr_evict_lru(pr_forest *f, int64_t max_tokens, int64_t *evicted, void 
         // most pr::kEvictNodes nodes takes a walk and a launch; one wait each
         if ((r = ensure_export_scratch(f, f->dev.n_nodes))) return r;
         pr::EvictStatus *out = reinterpret_cast<pr::EvictStatus *>(f->d_stage + kEvictStage / 4);
-        for (int scan = !f->holes && f->dev.n_nodes <= pr::kEvictScan; scan >= 0; scan--) {
+        for (int scan = f->dev.n_nodes <= pr::kEvictScan; scan >= 0; scan--) {
             if (scan) {
                 hipLaunchKernelGGL((pr::evict_kernel<true>), dim3(1), dim3(pr::kWalkThreads), 0, s, dev_view(f),
                                    f->d_walk, W.all, W.depth, W.parent, max_tokens, f->d_ctr, out);

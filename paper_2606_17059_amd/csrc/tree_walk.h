@@ -304,9 +304,8 @@ __global__ __launch_bounds__(kWalkThreads) void tree_walk_kernel(DevForest F, in
 // Records hold everything a tree's size needs: a record in use has not moved
 // (moved is 0) and peers hold all of a path or none of it, so the size is the
 // sum of the labels of the records that have the peer's bit and have not moved,
-// in one pass over the records without a level waiting for another.  What it
-// moves is 40 bytes a record; a forest whose records are not all written
-// (pr_forest::holes) is walked instead.  A tree of 15
+// in one pass over the records without a level waiting for another (records of
+// refused allocations have no peers).  What it moves is 40 bytes a record.  A tree of 15
 // levels among 1,500 records 33 -> 2.9 us, one of 4,000 prompts in a forest of
 // 65,000 records 33 -> 6.3 us (the walk's kernel -> this one).
 constexpr int kSizeThreads = 256;

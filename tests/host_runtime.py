@@ -145,6 +145,19 @@ class HostRuntime:
         self.on["tree_walk_kernel"] = lambda args: ctypes.memset(self.arg(args, 5), 0, ctypes.sizeof(Walk))
         self.on["evict_kernel"] = lambda args: ctypes.memset(self.arg(args, 7), 0, ctypes.sizeof(Evict))
 
+    def evicts(self, tokens):
+        """A player of the one-workgroup evictions, which evict that many tokens."""
+        def play(args):
+            c, out = self.at(args, 6, Counters), self.at(args, 7, Evict)
+            out.done, out.evicted, out.n_nodes = 1, tokens, c.n_nodes
+        return play
+
+    def size_is(self, tokens):
+        """Tree sizes that the pass over the records finds."""
+        def size(args):
+            _u64.from_address(self.arg(args, 4)).value = tokens
+        self.on["tree_size_kernel"] = size
+
     def small_merge(self, *replies, **fields):
         """A player of the one-workgroup merge: every launch reports `fields` (by
         default that all is done in one round), the first ones with the given replies

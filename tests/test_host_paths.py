@@ -172,3 +172,19 @@ def test_a_compaction_gives_back_what_it_freed(rt, left):
         assert info.device_bytes <= image + 2 * 6.2 * pool / 16 + 2 * 48 * nodes / 16 + (12 << 20)
     f.close()
     assert rt.used() == 0
+
+
+def test_sizes_and_evictions_after_a_refusal(rt):
+    """A refused round leaves no record unwritten, so sizes and evictions go on
+    taking the passes over the records."""
+    f = rt.forest(2, [[[1, 2, 3]]])
+    assert f.merge(65) == 0 and f.L.pr_set_local_peer(f.h, 0) == 0
+    rt.on["small_merge_kernel"] = rt.small_merge(dict(done=0, overflow=1, add_nodes=500))
+    assert f.merge(65) == 0 and f.info().merge_refusals == 1
+    rt.size_is(42)
+    rt.clear()
+    assert f.tokens(0) == (0, 42)
+    rt.on["evict_kernel"] = rt.evicts(7)
+    assert f.evict(7) == (0, 7)
+    assert rt.launched("tree_walk_kernel") == 0 and rt.launched("evict_kernelILb1E") == 1, rt.launches
+    f.close()

@@ -93,3 +93,58 @@ def test_first_batch_past_the_pool_is_sized_before_it_runs(n, L, load):
     _check(f, o, [s[:L - i] for i, s in enumerate(seqs[:64])] + [s[:L // 2] + [-1] for s in seqs[::9]], "cold")
     f.close()
     o.close()
+
+
+@pytest.mark.parametrize("P,local", [(3, 1), (130, 66)])
+@pytest.mark.parametrize("kind", ["adds", "cuts", "host rounds"])
+def test_sizes_and_evictions_among_refused_records(P, local, kind):
+    """Rounds refused for want of label tokens leave records that nothing uses; the
+    passes over all records that sizes and evictions take see no peer in them."""
+    import oracle
+    import torch
+    from paper_2606_17059_amd import Forest
+    rng = np.random.default_rng(P)
+    # device memory that held other things: what a refused round leaves unwritten shows
+    junk = torch.full((64 << 20,), -1, dtype=torch.int32, device=device())
+    torch.cuda.synchronize()
+    del junk
+    torch.cuda.empty_cache()
+    f, o = Forest(P), oracle.Oracle(P)
+    f.set_local_peer(local)
+    o.set_local(local)
+    stored = []
+
+    def merge(seqs, what, mine):
+        peers = rng.integers(0, P, len(seqs))
+        peers[peers == local] = 0
+        peers[:mine] = local
+        _merge(f, o, peers, seqs, what)
+        stored.extend(seqs)
+
+    merge([[i % 7, i, 3, 4, 5, 6][:3 + i % 4] for i in range(90)], "a small first batch", 30)
+    tail = lambda: rng.integers(0, 9, 5000).tolist()  # noqa: E731
+    if kind == "adds":
+        merge([[100 + i] + tail() for i in range(70)], "adds past the pool", 2)
+    elif kind == "cuts":
+        merge([s[:2] + [50 + i] + tail() for i, s in enumerate(stored[:70])], "cuts past the pool", 2)
+    else:  # 16,385 inserts are the host's to drive
+        merge([[100 + i] + tail() for i in range(70)] + [[3]] * 16315, "host-driven adds past the pool", 2)
+    info = f.info()
+    assert info["num_nodes"] < 8192, info
+    if kind != "host rounds":  # those are sized by their walk's tally
+        assert info["merge_refusals"] == 1, info
+    for p in {0, local, P - 1}:
+        assert f.tree_tokens(p) == o.tree_tokens(p), p
+    f.set_time(1)
+    o.set_time(1)
+    merge([[3, i, 1] for i in range(70)], "newer paths", 40)
+    for k, n in enumerate((3, 60, 1)):
+        announce(f"eviction {k}")
+        assert f.evict_lru(n) == o.evict(n), k
+        assert f.tree_tokens(local) == o.tree_tokens(local), k
+        t, off = f.export_snapshot(local)
+        got = sorted(map(tuple, pins.csr_to_list(t.cpu().numpy(), off.cpu().numpy())))
+        assert got == sorted(map(tuple, pins.csr_to_list(*o.export(local)))), k
+    _check(f, o, [s[:30] for s in stored[:300]], "after evictions")
+    f.close()
+    o.close()
