@@ -1718,6 +1718,16 @@ pr_status pr_tree_tokens(pr_forest *f, int32_t peer, int64_t *tokens, void *hip_
     pr_status r = commit(f);
     if (r) return r;
     hipStream_t s = (hipStream_t)hip_stream;
+    if (f->d_stage && f->dev.n_nodes > pr::kSizeRecords) {
+        if (!enqueue_walk(f, peer, pr::WalkOut{}, s) || hipStreamSynchronize(s) != hipSuccess)
+            return fail(PR_EDEVICE, "tree walk failed");
+        pr::WalkStatus st;
+        std::memcpy(&st, f->h_stage, sizeof(st));
+        if (st.done) {
+            *tokens = (int64_t)st.tokens;
+            return ok();
+        }
+    }
     if (f->d_stage) {
         const unsigned blocks = std::min(pr::kSizeBlocks, grid_threads(f->dev.n_nodes, pr::kSizeThreads * pr::kSizePer));
         hipLaunchKernelGGL(pr::tree_size_kernel, dim3(std::max(1u, blocks)), dim3(pr::kSizeThreads), 0, s, dev_view(f),

@@ -305,12 +305,17 @@ __global__ __launch_bounds__(kWalkThreads) void tree_walk_kernel(DevForest F, in
 // (moved is 0) and peers hold all of a path or none of it, so the size is the
 // sum of the labels of the records that have the peer's bit and have not moved,
 // in one pass over the records without a level waiting for another (records of
-// refused allocations have no peers).  What it moves is 40 bytes a record.  A tree of 15
+// refused allocations have no peers).  What it moves is 40 bytes a record of the
+// forest, whosever it is, so past kSizeRecords records the walk is tried first: of
+// 20 M records, 196 us for any tree, where a walk finds one of 450 nodes in 53 us,
+// one of 4,200 in 175, and turns back from a larger one after 22 (at 8 M: 110, 41,
+// 84 and 20).  A tree of 15
 // levels among 1,500 records 33 -> 2.9 us, one of 4,000 prompts in a forest of
 // 65,000 records 33 -> 6.3 us (the walk's kernel -> this one).
 constexpr int kSizeThreads = 256;
 constexpr int kSizePer = 4;  // records a thread has in flight
 constexpr unsigned kSizeBlocks = 1024;
+constexpr int64_t kSizeRecords = 1 << 23;
 
 // Zero between calls: the last workgroup to finish clears it.
 struct SizeState {

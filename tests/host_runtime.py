@@ -135,6 +135,13 @@ class HostRuntime:
         self.on["compact_small_kernel"] = play(5)
         self.on["compact_lab_scan_kernel"] = play(0)
 
+    def walk_counts(self, tokens):
+        """The one-launch walk finds a tree of that many tokens."""
+        def play(args):
+            w = Walk.from_address(self.arg(args, 5))
+            w.done, w.tokens = 1, tokens
+        self.on["tree_walk_kernel"] = play
+
     def walk_finds(self, nodes, leaves=0):
         """The level-by-level walk finds that many nodes and leaves at its first level;
         the one-launch walk and eviction report that the tree is too large for them."""

@@ -188,3 +188,21 @@ def test_sizes_and_evictions_after_a_refusal(rt):
     assert f.evict(7) == (0, 7)
     assert rt.launched("tree_walk_kernel") == 0 and rt.launched("evict_kernelILb1E") == 1, rt.launches
     f.close()
+
+
+@pytest.mark.parametrize("records,walks", [(1 << 23, 0), ((1 << 23) + 1, 1)])
+def test_a_tree_among_very_many_records_is_walked(rt, records, walks):
+    """The pass over all records is not taken for a tree that a walk finds sooner;
+    trees too large for the walk take it all the same."""
+    f = rt.forest(2, [[[1, 2, 3]]])
+    rt.large_merge(f, records, 100)
+    rt.size_is(42)
+    rt.walk_counts(42)
+    rt.clear()
+    assert f.tokens(0) == (0, 42)
+    assert (rt.launched("tree_walk_kernel"), rt.launched("tree_size_kernel")) == (walks, 1 - walks)
+    rt.walk_finds(nodes=5)
+    rt.clear()
+    assert f.tokens(1) == (0, 42)
+    assert (rt.launched("tree_walk_kernel"), rt.launched("tree_size_kernel")) == (walks, 1)
+    f.close()
