@@ -158,3 +158,53 @@ def test_compact_stream_merges():
         assert got == sorted(tuple(x) for x in pins.csr_to_list(*o.export(p))), p
     f.close()
     o.close()
+
+
+def test_routes_in_flight_while_compactions_swap_two_images():
+    """Routes queued on a stream read the image they were launched with: compactions
+    on another stream wait for them before they give it up, and two compactions in
+    turn, which reuse each other's arrays, do not write one that a route still reads.
+    Each compaction begins while dozens of routes are queued; merges in between
+    (ordered after the routes) make every image another one."""
+    import torch
+    rng = np.random.default_rng(31)
+    heads = [rng.integers(0, 3000, 60).tolist() for _ in range(40)]
+    seqs = [heads[i % 40][:20 + i % 41] + rng.integers(0, 3000, 30).tolist() for i in range(6000)]
+    owners = [i % 5 for i in range(len(seqs))]
+    snap = W.from_lists(seqs, owners)
+    f = _forest(snap, 5)
+    o = oracle_for(snap, 5)
+    qs = W.from_lists([seqs[int(i)][:int(rng.integers(1, 51))] + [int(rng.integers(0, 3000))]
+                       for i in rng.integers(0, len(seqs), 3000)])
+    # the batch many times over, so that a launch takes a while
+    reps = 30
+    qt = torch.from_numpy(np.tile(qs.tokens, reps)).cuda()
+    lens = np.tile(np.diff(qs.offsets), reps)
+    qo = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)])).cuda()
+    n = reps * len(qs)
+    outs = [(torch.empty((n, 5), dtype=torch.int32, device="cuda"), torch.empty(n, dtype=torch.int32, device="cuda"))
+            for _ in range(40)]
+    side = torch.cuda.Stream()
+    for step in range(5):
+        m_or, c_or = o.route(qs.tokens, qs.offsets, nthreads())
+        for m, c in outs:
+            m.fill_(-7)
+            c.fill_(-7)
+        torch.cuda.synchronize()
+        announce(f"compaction {step} behind {len(outs)} routes on another stream")
+        for m, c in outs:
+            f.route(qt, qo, m, c, stream=side)
+        before, after = f.compact()
+        assert after <= before
+        with torch.cuda.stream(side):  # and again from the new image, while the next merge waits
+            m2, c2 = f.route(qt, qo)
+        torch.cuda.synchronize()
+        want = torch.from_numpy(m_or).cuda().repeat(reps, 1), torch.from_numpy(c_or).cuda().repeat(reps)
+        for k, (m, c) in enumerate(outs + [(m2, c2)]):
+            assert torch.equal(m, want[0]) and torch.equal(c, want[1]), (step, k)
+        more = W.from_lists([heads[i % 40][:20 + i % 41] + [3000 + step, i] for i in range(500)],
+                            [i % 5 for i in range(500)])
+        _merge(f, more, f"between compactions {step}")
+        o.merge(more.peer, more.tokens, more.offsets)
+    f.close()
+    o.close()
