@@ -397,6 +397,12 @@ __device__ __forceinline__ void void_records(const DevForest &F, int64_t nb, int
     }
 }
 
+// grp_nb of a group whose block at record nb was refused: below -1 it tells
+// add_finish_kernel where the block's records are.
+__device__ __forceinline__ int32_t refused_block(const DevForest &F, int64_t nb) {
+    return nb < F.cap_nodes ? (int32_t)(-2 - nb) : -1;
+}
+
 // Where node c's record lives now: an add phase earlier in the same round
 // (stamp > 0) may have moved it into its parent's rebuilt block.
 __device__ __forceinline__ int32_t current_pos(const DevForest &F, int32_t c, long long stamp) {
@@ -1176,12 +1182,10 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
         const long long pb = (long long)atomicAdd(&ctr->n_pool, (unsigned long long)pool_total);
         const bool ok = nb + need_all <= F.cap_nodes && pb + pool_total <= F.cap_pool;
         if (!ok) atomicAdd(&ctr->overflow, 1ull);
-        s_tmp[0] = ok ? nb : -1;
+        s_tmp[0] = ok ? nb : -2 - nb;
         s_tmp[1] = pb;
-        s_tmp[2] = nb;
     }
     __syncthreads();
-    if (s_tmp[0] < 0) void_records(F, s_tmp[2], need_all, t, T);
     const int eb = (int)(s_place >> 32), cb = (int)(uint32_t)s_place;
     for (int p = t; p < m; p += T) {
         const unsigned long long kk = s_key[plan_pad(p)];
@@ -1243,7 +1247,8 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
             if (w) s_tok[plan_pad(hcur + ((int)s_val[plan_pad(e)] - wk))] = (uint32_t)k[j] ^ 0x80000000u;
             if ((lbits >> j) & 1u) {
                 grp_nw[eb + hcur] = (int)s_val[plan_pad(e)] + (int)w - wk;
-                grp_nb[eb + hcur] = nb0 < 0 ? -1 : (int32_t)(nb0 + (before_ct - ct[j]) + wk);
+                const int32_t at = (before_ct - ct[j]) + wk;
+                grp_nb[eb + hcur] = nb0 < 0 ? refused_block(F, -2 - nb0 + at) : (int32_t)(nb0 + at);
             }
         }
     }
@@ -1252,8 +1257,8 @@ __global__ __launch_bounds__(kPlanThreads) void add_plan_kernel(DevForest F, Bat
 }
 
 // Step 3 (one thread per group head): records and label tokens of the new
-// block, or grp_nb = -1 (the parent keeps its old, consistent block) when the
-// capacity runs out.
+// block, or grp_nb < 0 (refused_block; the parent keeps its old, consistent block)
+// when the capacity runs out.
 __global__ void add_alloc_kernel(DevForest F, const unsigned long long *keys, int64_t n_add, const int32_t *grp_nw,
                                  const int64_t *grp_pool, int32_t *grp_nb, int64_t *grp_pb, MergeCounters *ctr) {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1263,8 +1268,7 @@ __global__ void add_alloc_kernel(DevForest F, const unsigned long long *keys, in
     const int64_t pb = (int64_t)atomicAdd(&ctr->n_pool, (unsigned long long)grp_pool[k]);
     if (nb + cnt > F.cap_nodes || pb + grp_pool[k] > F.cap_pool) {
         atomicAdd(&ctr->overflow, 1ull);
-        void_records(F, nb, cnt, 0, 1);
-        grp_nb[k] = -1;
+        grp_nb[k] = refused_block(F, nb);
         return;
     }
     grp_nb[k] = (int32_t)nb;
@@ -1338,8 +1342,9 @@ __global__ __launch_bounds__(64 *kMergeWavesPerBlock) void add_build_kernel(
 
 // Step 5 (a thread per insert, which is also entry e of the sorted ones): the
 // separators of every rebuilt wide block, and its parent, wherever the parent's
-// record lives now, pointed at it; and the first step of the split phase, which
-// depends on neither: per child c, the lowest batch index wins the claim.
+// record lives now, pointed at it; the records of refused blocks; and the first
+// step of the split phase, which depends on none of them: per child c, the lowest
+// batch index wins the claim.
 // stamp: that of the round's build, or 0 if nothing was added.
 __global__ __launch_bounds__(256) void add_finish_kernel(DevForest F, Batch B, const InsState *st,
                                                         const unsigned long long *keys, int64_t n_add,
@@ -1352,11 +1357,16 @@ __global__ __launch_bounds__(256) void add_finish_kernel(DevForest F, Batch B, c
     const int64_t cnt = add_count(n_add, ctr);
     int32_t nb = -1, nw = 0, x = 0, c = 0;
     if (i < cnt && add_is_head(keys, i)) {
-        nb = grp_nb[i];  // -1: the build of this group was refused
+        nb = grp_nb[i];  // below 0: the build of this group was refused
         nw = grp_nw[i];
         x = key_parent(keys[i]);
-        if (nb >= 0) c = F.nodes[x].ct_cnt + nw;
+        if (nb != -1) c = F.nodes[x].ct_cnt + nw;
     }
+    for (uint64_t lost = __ballot(nb < -1); lost; lost &= lost - 1) {
+        const int l = __ffsll((unsigned long long)lost) - 1;
+        void_records(F, -2 - (int64_t)__builtin_amdgcn_readlane(nb, l), __builtin_amdgcn_readlane(c, l), lane, 64);
+    }
+    if (nb < 0) c = 0;
     for (uint64_t wide = __ballot(c > kSepCount); wide; wide &= wide - 1) {
         const int l = __ffsll((unsigned long long)wide) - 1;
         const int32_t b = __builtin_amdgcn_readlane(nb, l), n = __builtin_amdgcn_readlane(c, l);

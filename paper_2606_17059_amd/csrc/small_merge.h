@@ -149,9 +149,12 @@ __global__ __launch_bounds__(64 *kSmallWaves) void small_merge_kernel(DevForest 
             s_st[lane].kind = ok ? kInsActive : kInsSkip;
         }
         const uint32_t skip = (uint32_t)__popcll(__ballot(bad));
-        int64_t tokens;
-        (void)lane_excl(ok ? s_len[lane] : 0, lane, &tokens);
-        const bool large = !B.touch && n > kSmallWaves && tokens > kSmallWork / n;
+        bool large = false;
+        if (n > kSmallWaves && !B.touch) {
+            int64_t tokens;
+            (void)lane_excl(ok ? s_len[lane] : 0, lane, &tokens);
+            large = tokens > kSmallWork / n;
+        }
         if (lane == 0) {
             s_state = left > kSmallMax || broken || large ? 2 : 0;
             s_seen = 0;
