@@ -1109,12 +1109,12 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
     const bool device_rounds = PR_MERGE_PLAN && f->d_stage && n <= pr::kPlanMaxBatch;
     // A forest whose merges have not shown what they add, and a batch that its
     // pool may not hold: the first round's walk is tallied, and the pool grows by
-    // that, where a refused allocation would take a second set of launches (first
-    // snapshot of 4,000 prompts of 2,000 tokens: 1,253 us refused, 594 us)
+    // that and, as at an upload, a quarter, where a refused allocation would take a second set of launches (first
+    // snapshot of 4,000 prompts of 2,000 tokens: 1,253 us refused, 531 us)
     bool walked = false;
     if (device_rounds && f->round_pool == 0 && !B.touch && B.num_tokens > f->dev.cap_pool - f->dev.n_pool) {
         if ((r = walk_and_tally(1)) ||
-            (r = reserve_capacity(f, f->dev.n_nodes + n, f->dev.n_pool + (int64_t)c.pool_need, s)))
+            (r = reserve_capacity(f, f->dev.n_nodes + n, f->dev.n_pool + (int64_t)(c.pool_need + c.pool_need / 4), s)))
             return r;
         walked = true;
         first = 0;
