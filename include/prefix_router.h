@@ -383,7 +383,7 @@ typedef struct {
                                   16-bit copy plus a plane of bit 16), else 32 */
     int64_t merge_refusals;    /* device update rounds that ran out of capacity and
                                   ran again after the forest grew (their refused
-                                  allocations wrote nothing) */
+                                  allocations changed no tree) */
     int64_t first_window_tokens; /* query tokens a route loads before its walk
                                     starts: 256 while, at the last upload of host
                                     snapshots, the root had a single child with a

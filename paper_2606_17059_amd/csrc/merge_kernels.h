@@ -547,16 +547,16 @@ __device__ __forceinline__ void cut_edge(const DevForest &F, const NarrowDst &N,
     }
 }
 
-// Cut child c's edge after l tokens; the winning insert's rest becomes a leaf,
-// and the winner is done.  An add phase earlier in the round may have moved
-// c's record (stamp, as for the claim); it also may have given c a new child
-// block, which the lower part of the edge takes along.
 // Waves per workgroup of split_apply_kernel: a workgroup takes one allocation
 // of records and one of pool tokens for all its winners (two atomics on the
 // merge's counters instead of two per winner, which serialise on their two
 // addresses when a batch cuts thousands of edges).
 constexpr int kSplitWaves = 16;
 
+// Cut child c's edge after l tokens; the winning insert's rest becomes a leaf,
+// and the winner is done.  An add phase earlier in the round may have moved
+// c's record (stamp, as for the claim); it also may have given c a new child
+// block, which the lower part of the edge takes along.
 __global__ __launch_bounds__(64 *kSplitWaves) void split_apply_kernel(DevForest F, Batch B, NarrowDst N,
                                                                      InsState *st, MergeCounters *ctr,
                                                                      long long stamp) {

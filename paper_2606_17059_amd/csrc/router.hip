@@ -157,13 +157,13 @@ namespace {
 #ifndef PR_ROUTE_LONGEST_FIRST
 #define PR_ROUTE_LONGEST_FIRST 1
 #endif
-// Narrow (16- or 17-bit) label copies for routes; 0 keeps every forest on int32 labels.
 // Batches of at most pr::kPlanMaxBatch inserts plan their add phase in one
 // launch (0: always the multi-launch path, for comparisons).
 #ifndef PR_MERGE_PLAN
 #define PR_MERGE_PLAN 1
 #endif
 
+// Narrow (16- or 17-bit) label copies for routes; 0 keeps every forest on int32 labels.
 #ifndef PR_NARROW_LABELS
 #define PR_NARROW_LABELS 1
 #endif
@@ -248,7 +248,7 @@ void dfree(pr_forest *f, T **p, int64_t count) {
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Words of the bit plane for a pool capacity of cap tokens: two per 64-token
-// chunk (the narrow copy kernel writes a chunk's two words together).
+// chunk (a wave writes a chunk's two words together).
 int64_t hib_words(int64_t cap) { return 2 * ((cap + 63) / 64) + 2; }
 
 // The per-node arrays of one capacity (records, first tokens, separators,
@@ -563,9 +563,9 @@ pr_status ensure_capacity(pr_forest *f, int64_t need_nodes, int64_t need_pool, h
         uint32_t *nhb = nullptr;
         const bool narrow = f->narrow && d.pool16 && d.hib;
         const bool keep16 = narrow && dalloc(f, &n16, cap) && dalloc(f, &nhb, hib_words(cap));
-        // the tail is zeroed: a merge round refused for lack of capacity can
-        // leave unwritten tokens below the used size, which the narrow copy
-        // then converts
+        // the tails are zeroed: the bit plane's, because words that two spans share
+        // are ORed into it, and the pool's, so that tokens of a refused round, which
+        // no label has, have a value
         if (hipMemcpyAsync(np, d.pool, d.n_pool * sizeof(int32_t), hipMemcpyDeviceToDevice, s) != hipSuccess ||
             hipMemsetAsync(np + d.n_pool, 0, (cap - d.n_pool) * sizeof(int32_t), s) != hipSuccess ||
             (keep16 &&

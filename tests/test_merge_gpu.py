@@ -184,12 +184,12 @@ def _merge_lists(f, o, items, label):
 
 
 def test_device_driven_rounds_hand_over_to_host_rounds():
-    """After a forest's first merge, a merge runs two rounds sized on the
-    device before it reads anything back; what they leave goes on in rounds
-    the host reads back after every walk.  Three batches force each hand-over:
-    a chain of inserts that share a new prefix and part from it one token
-    after another (a slot, then the same edge over and over: more rounds than
-    the device runs); more ADD entries in one round than the one-workgroup
+    """Batches of more than 64 inserts run rounds sized on the device before
+    anything is read back; what they leave goes on in rounds the host reads
+    back after every walk.  Three batches force a hand-over each (longer chains
+    for the rounds themselves: test_small_merge_gpu.py): a chain of inserts that
+    share a new prefix and part from it one token after another (a slot, then
+    the same edge over and over, in one launch); more ADD entries in one round than the one-workgroup
     plan takes (the multi-launch path); and label tokens far beyond the pool's
     spare room after compaction (the device round's allocation is refused,
     the host grows the forest and repeats it).  Every row against the oracle

@@ -245,3 +245,37 @@ def test_small_batch_outgrows_the_pool_between_rounds():
     f.check()
     f.close()
     o.close()
+
+
+@pytest.mark.parametrize("n", [64, 65, 75, 200])
+@pytest.mark.parametrize("order", ["shortest first", "longest first", "shuffled"])
+def test_chains_hand_over_from_launch_to_launch(n, order):
+    """A chain of inserts that part from one new path a token after another.  With the
+    shortest first a round places one of them, the next cut of what the last one hung:
+    up to 64 are done in one launch, 75 leave few enough for it after the queued
+    rounds, 200 pass to the host's rounds; the other orders take fewer."""
+    import oracle
+    from paper_2606_17059_amd import Forest
+    rng = np.random.default_rng(n)
+    f, o = Forest(3), oracle.RadixOracle(3)
+    stored = []
+    for k in range(2):  # the second chain with as many rounds queued as the first took
+        path = [500 + k] + rng.integers(0, 40, n).tolist()
+        seqs = [path[:i + 1] + [100 + i, 1, 2] for i in range(n)]
+        if order != "shortest first":
+            seqs = seqs[::-1] if order == "longest first" else [seqs[i] for i in rng.permutation(n)]
+        peers = rng.integers(0, 3, n)
+        announce(f"chain {k} of {n}, {order}")
+        f.merge(*_dev(peers, seqs))
+        o.merge(peers.astype(np.int32), *pins._csr(seqs))
+        stored += seqs
+        _check(f, o, stored + [s[:-2] + [9] for s in stored] + [path[:i] for i in range(0, n, 7)], f"chain {k}")
+    assert f.tree_tokens(1) == len({tuple(s[:i]) for p, s in _held(f, 1) for i in range(1, len(s) + 1)})
+    f.check()
+    f.close()
+    o.close()
+
+
+def _held(f, p):
+    t, o = f.export_snapshot(p)
+    return [(p, s) for s in pins.csr_to_list(t.cpu().numpy(), o.cpu().numpy())]

@@ -172,7 +172,7 @@ def test_eviction_from_a_deep_chain():
 
 
 def test_size_and_eviction_past_unwritten_records():
-    """A merge whose rebuilt block does not fit leaves records that nothing wrote
+    """A merge whose rebuilt block does not fit leaves records that no peer holds
     until the next compaction."""
     p = Pair(3, 1)
     seqs = [[7, 2 * i, 1, 2] for i in range(5000)]
