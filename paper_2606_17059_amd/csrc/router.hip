@@ -1107,12 +1107,17 @@ pr_status run_merge(pr_forest *f, const pr::Batch &B, hipStream_t s) {
         return read_counters_raw(f, &c, s);
     };
     const bool device_rounds = PR_MERGE_PLAN && f->d_stage && n <= pr::kPlanMaxBatch;
-    // A forest whose merges have not shown what they add, and a batch that its
-    // pool may not hold: the first round's walk is tallied, and the pool grows by
-    // that and, as at an upload, a quarter, where a refused allocation would take a second set of launches (first
-    // snapshot of 4,000 prompts of 2,000 tokens: 1,253 us refused, 531 us)
+    // A forest whose merges have not shown what they add, and a batch of more than
+    // four times what its pool has left (prompts share most of their tokens): the
+    // first round's walk is tallied, and the pool grows by that and, as at an
+    // upload, a quarter, where a refused allocation would take a second set of
+    // launches (first snapshot of 4,000 prompts of 2,000 tokens: 687 to 1,253 us
+    // refused, 510 to 531 us).  Up to there the tally costs about what the
+    // refusals do that it spares (500 prompts of 1,200 tokens, which do not fit:
+    // 451 us with it, 473 without; 16 snapshots of 500, of which the first fits,
+    // 2,864 with it, 2,812 without).
     bool walked = false;
-    if (device_rounds && f->round_pool == 0 && !B.touch && B.num_tokens > f->dev.cap_pool - f->dev.n_pool) {
+    if (device_rounds && f->round_pool == 0 && !B.touch && B.num_tokens / 4 > f->dev.cap_pool - f->dev.n_pool) {
         if ((r = walk_and_tally(1)) ||
             (r = reserve_capacity(f, f->dev.n_nodes + n, f->dev.n_pool + (int64_t)(c.pool_need + c.pool_need / 4), s)))
             return r;

@@ -66,12 +66,12 @@ def test_rounds_queued_behind_a_refusal_ask_for_nothing():
     o.close()
 
 
-@pytest.mark.parametrize("n,L", [(100, 20000), (500, 1200)])
+@pytest.mark.parametrize("n,L", [(100, 20000), (900, 1200)])
 @pytest.mark.parametrize("load", [True, False])
 def test_first_batch_past_the_pool_is_sized_before_it_runs(n, L, load):
-    """A cold forest's first snapshot or merge does not fit the pool it starts
-    with (262,144 tokens): the pool grows to what the walk finds missing, nothing
-    is refused, and the records hold the batch without gaps."""
+    """A cold forest's first snapshot or merge has more than four times the tokens
+    of the pool it starts with (262,144): the pool grows to what the walk finds
+    missing, nothing is refused, and the records hold the batch without gaps."""
     import oracle
     import torch
     from paper_2606_17059_amd import Forest
