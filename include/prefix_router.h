@@ -257,10 +257,10 @@ pr_status pr_tree_tokens(pr_forest *f, int32_t peer, int64_t *tokens, void *hip_
  * use).  Host-synchronous; waits for the whole device before it frees the old
  * image, so no launch on any stream may still read it.  Holds the old and new
  * image at once while it runs.  Where the forest keeps its size, to a half, or
- * is one of a few MB, it also keeps the old one's arrays, up to 1 GiB, for the
- * next compaction (given back when memory runs out, when a compaction shrinks
- * the forest by more, when host snapshots are uploaded and with the forest;
- * counted in pr_forest_info's device_bytes).
+ * is one of up to 64 MB, it also keeps the old one's arrays, up to 1 GiB, for
+ * the next compaction (given back when memory runs out, when a compaction
+ * shrinks a larger forest by more, when host snapshots are uploaded and with the
+ * forest; counted in pr_forest_info's device_bytes).
  * Errors: PR_EINVAL (f NULL), PR_ESTATE, PR_ENOMEM, PR_EDEVICE.  After an
  * error before the install the old image stays in use; a failed install
  * leaves the forest broken (PR_ESTATE from then on).

@@ -325,17 +325,17 @@ int64_t used_bytes(const pr_forest *f, const DevImage &d) {
 // The image a compaction replaces, nw the one that takes its place.  The old
 // arrays are kept for the next compaction, which then allocates nothing (hipMalloc
 // and hipFree of arrays of tens of MB take 0.3 to 0.6 ms each, more than the
-// rebuild itself), as long as they are small beside the GPU's memory and the
-// forest is one that merges fill and compactions empty in turn: the new arrays
-// are about as large (within a third) and at least half of what they held is
-// still there.  A compaction that shrinks its forest by more gives them back, but
-// for a few MB.  At most one set is kept per forest.
+// rebuild itself): up to 64 MB in any case, more as long as they are small beside
+// the GPU's memory and the forest is one that merges fill and compactions empty in
+// turn: at least half of what they held is still there, and the new arrays are at
+// least a quarter as large (spare capacity grows fourfold).  A compaction that
+// shrinks its forest by more gives them back.  At most one set is kept per forest.
 constexpr int64_t kSpareBytes = 1ll << 30;
-constexpr int64_t kSmallSpare = 8 << 20;
+constexpr int64_t kSmallSpare = 64 << 20;
 bool retire_image(pr_forest *f, const DevImage &nw) {
     free_arrays(f, f->spare);
     const int64_t bytes = image_bytes(f->dev);
-    const bool keep = bytes <= kSmallSpare || (bytes <= kSpareBytes && 2 * bytes <= 3 * image_bytes(nw) &&
+    const bool keep = bytes <= kSmallSpare || (bytes <= kSpareBytes && bytes <= 4 * image_bytes(nw) &&
                                                used_bytes(f, f->dev) <= 2 * used_bytes(f, nw));
     if (keep)
         f->spare = f->dev;
@@ -384,7 +384,7 @@ bool new_node_arrays(pr_forest *f, DevImage &nw, int64_t need, int64_t extra, bo
 
 // The label pool (and its narrow copy, if wanted and there is memory for it)
 // for at least need tokens in nw, and extra if there is room, in the same way.
-constexpr int64_t kSmallPool = 1 << 20;  // tokens a pool may have however few are needed
+constexpr int64_t kSmallPool = 8 << 20;  // tokens a pool may have however few are needed
 bool new_pool(pr_forest *f, DevImage &nw, int64_t need, int64_t extra, bool narrow) {
     const int64_t least = need;
     need += extra;

@@ -141,13 +141,14 @@ def test_room_for_later_merges_is_not_a_condition_of_a_compaction(rt):
     assert status == 0
 
 
+@pytest.mark.parametrize("size", [1, 16])
 @pytest.mark.parametrize("left", [1.0, 0.6, 0.4, 0.1])
-def test_a_compaction_gives_back_what_it_freed(rt, left):
+def test_a_compaction_gives_back_what_it_freed(rt, left, size):
     """A compaction that leaves more than half of the forest keeps the replaced
-    arrays, and the next one allocates nothing; one that leaves less gives them
-    back, and the image is sized to what is left."""
+    arrays, and the next one allocates nothing; one that leaves less of a forest of
+    more than 64 MB gives them back, and the image is sized to what is left."""
     f = rt.forest(2, [[[1, 2, 3]]])
-    nodes, pool = 1 << 17, 1 << 22
+    nodes, pool = size << 16, size << 21  # 16 MB, 256 MB
     rt.large_merge(f, nodes, pool)
     for _ in range(100):  # merges since then were small ones
         assert f.merge(65) == 0
@@ -160,7 +161,7 @@ def test_a_compaction_gives_back_what_it_freed(rt, left):
     assert f.compact() == 0
     info = f.info()
     assert info.num_nodes == int(nodes * left)
-    if left > 0.5:
+    if left > 0.5 or size == 1:
         rt.limit(rt.used())
         refused, status = rt.refused(), f.compact()
         rt.limit(None)
