@@ -503,10 +503,12 @@ pr_status ensure_capacity(pr_forest *f, int64_t need_nodes, int64_t need_pool, h
     if (need_nodes > d.cap_nodes) {
         // rebuilt child blocks append records with every add round, so node
         // arrays grow fourfold: each growth (allocate, copy, wait for the
-        // device, free) costs milliseconds of host time
+        // device, free) costs milliseconds of host time; where memory for that is
+        // short, to what is needed
         const int64_t cap = std::min<int64_t>(std::max<int64_t>(need_nodes, 4 * d.cap_nodes), (int64_t)INT32_MAX);
         DevImage nd;
-        if (!alloc_node_arrays(f, nd, cap)) return fail(PR_ENOMEM, "hipMalloc failed while growing the forest");
+        if (!alloc_node_arrays(f, nd, cap) && !alloc_node_arrays(f, nd, need_nodes))
+            return fail(PR_ENOMEM, "hipMalloc failed while growing the forest");
         const int64_t n = d.n_nodes;
         if (hipMemcpyAsync(nd.nodes, d.nodes, n * sizeof(Node), hipMemcpyDeviceToDevice, s) != hipSuccess ||
             hipMemcpyAsync(nd.ntok, d.ntok, n * sizeof(int32_t), hipMemcpyDeviceToDevice, s) != hipSuccess ||
@@ -554,9 +556,12 @@ pr_status ensure_capacity(pr_forest *f, int64_t need_nodes, int64_t need_pool, h
     if (need_pool > d.cap_pool) {
         // like the node arrays, a pool that is still small grows fourfold
         const int64_t more = d.cap_pool < (16 << 20) ? 4 * d.cap_pool : d.cap_pool + d.cap_pool / 2;
-        const int64_t cap = std::min<int64_t>(std::max<int64_t>(need_pool, more), (int64_t)UINT32_MAX);
+        int64_t cap = std::min<int64_t>(std::max<int64_t>(need_pool, more), (int64_t)UINT32_MAX);
         int32_t *np = nullptr;
-        if (!dalloc(f, &np, cap)) return fail(PR_ENOMEM, "hipMalloc failed while growing the label pool");
+        if (!dalloc(f, &np, cap)) {
+            cap = need_pool;
+            if (!dalloc(f, &np, cap)) return fail(PR_ENOMEM, "hipMalloc failed while growing the label pool");
+        }
         // the narrow copy grows with the pool, under the same wait (without
         // the memory, routes fall back to the int32 pool)
         uint16_t *n16 = nullptr;

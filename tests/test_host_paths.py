@@ -55,6 +55,18 @@ def test_a_touch_reserves_no_label_tokens(rt):
     f.close()
 
 
+def test_a_refusal_is_met_exactly_where_memory_is_short(rt):
+    """Growth is fourfold where there is memory for it, else to what is needed."""
+    f = rt.forest(2, [[[1, 2, 3]]])
+    rt.large_merge(f, 1 << 18, 100)
+    rt.on["small_merge_kernel"] = rt.small_merge(dict(done=0, overflow=1, add_nodes=(1 << 18) + (1 << 17)))
+    rt.limit(rt.used() + 49_000_000)  # for the records asked for, not for four times those there are
+    status, error = f.merge(65), f.error()
+    rt.limit(None)
+    f.close()
+    assert status == 0, error
+
+
 def test_a_refusal_the_memory_cannot_meet_is_an_error(rt):
     """A refused round's records are a condition: without memory for them the
     merge fails and the forest refuses what follows."""
